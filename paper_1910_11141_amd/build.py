@@ -4,6 +4,8 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -44,10 +46,16 @@ def build(force: bool = True, verbose: bool = False) -> str:
     if not force and not is_stale() and os.path.exists(UBENCH_LIB) and \
             os.path.getmtime(UBENCH_LIB) >= os.path.getmtime(UBENCH_SRC):
         return LIB_PATH
-    for cmd in ([HIPCC] + FLAGS + sources() + ["-o", LIB_PATH], [HIPCC] + FLAGS + [UBENCH_SRC, "-o", UBENCH_LIB]):
-        if verbose:
+    with tempfile.TemporaryDirectory() as tmp:
+        objects = [os.path.join(tmp, os.path.basename(s) + ".o") for s in sources()]
+        compile_flags = [f for f in FLAGS if f != "-shared"]
+        cmds = [[HIPCC] + compile_flags + ["-c", s, "-o", o] for s, o in zip(sources(), objects)]
+        cmds.append([HIPCC] + FLAGS + [UBENCH_SRC, "-o", UBENCH_LIB])
+        for cmd in cmds if verbose else []:
             print(" ".join(cmd), file=sys.stderr)
-        subprocess.run(cmd, check=True)
+        with ThreadPoolExecutor(max_workers=min(len(cmds), os.cpu_count() or 1)) as pool:  # one compiler per source
+            list(pool.map(lambda cmd: subprocess.run(cmd, check=True), cmds))
+        subprocess.run([HIPCC] + FLAGS + objects + ["-o", LIB_PATH], check=True)
     return LIB_PATH
 
 

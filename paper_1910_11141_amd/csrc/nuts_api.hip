@@ -22,6 +22,7 @@
 #include "nuts_quad.h"
 #include "nuts_tile.h"
 #include "nuts_wave.h"
+#include "nuts_wide.h"
 
 namespace {
 
@@ -83,7 +84,7 @@ struct nuts_target {
     void* dX = nullptr;
     void* dXT = nullptr;
     void* dY = nullptr;
-    nuts::TileData tile;  // operand-order copies of X for the tile kernel (binary64 logistic regression)
+    nuts::TileData tile;  // operand-order copies of X for the tile and wide kernels (logistic regression)
     nuts::GridData grid;  // operand-order copy of X for the grid kernels (binary32 logistic regression)
     nuts::QuadData quad;  // operand-order copy of P for the quad kernel (binary64 dense Gaussian, dim <= 128)
     // per-call scratch, grown on demand and kept
@@ -117,6 +118,11 @@ int upload(const std::vector<T>& host, void** dev)
     HIP_TRY(hipMemcpy(*dev, host.data(), host.size() * sizeof(T), hipMemcpyHostToDevice), NUTS_E_DEVICE);
     return NUTS_OK;
 }
+
+// Binary32 logistic regression: the grid kernels pay two launches per round; measured against the wave kernel they win
+// from a few thousand multiply-adds per gradient upwards (N d = 800: 2-5 times slower; 25 000: 3-7 times faster, at 8 to
+// 1024 chains).
+bool grid_pays(int64_t n, int64_t d) { return n * d >= (1 << 14); }
 
 template <typename T>
 int build_device_data(nuts_target* t, const nuts_target_desc* desc)
@@ -179,10 +185,16 @@ int build_device_data(nuts_target* t, const nuts_target_desc* desc)
         if (rc) return rc;
         rc = upload(yh, &t->dY);
         if (rc) return rc;
-        if (sizeof(T) == sizeof(double) && nuts::tile_supports_shape(d, n)) {
+        if (sizeof(T) == sizeof(double) ? nuts::tile_supports_shape(d, n) || nuts::wide_supports_shape(d, n)
+                                        : nuts::wide_supports_shape(d, n) && !grid_pays(n, d)) {
             std::vector<double> op, colsum, ftab;
-            nuts::tile_pack_operands(reinterpret_cast<const double*>(X), reinterpret_cast<const double*>(y), n, d,
-                                     &t->tile, &op, &colsum);
+            if (sizeof(T) == sizeof(double)) {
+                nuts::tile_pack_operands(reinterpret_cast<const double*>(X), reinterpret_cast<const double*>(y), n, d,
+                                         &t->tile, &op, &colsum);
+            } else {
+                const std::vector<double> Xd(X, X + (size_t)n * d), yd(y, y + n);
+                nuts::tile_pack_operands(Xd.data(), yd.data(), n, d, &t->tile, &op, &colsum);
+            }
             nuts::build_softplus_table(&ftab);
             {
                 std::vector<double> logtab;
@@ -677,8 +689,47 @@ int launch_grid(nuts_target* t, nuts::DevSample sa)
     return NUTS_OK;
 }
 
+bool tile_eligible(const nuts_target* t, int max_depth)
+{
+    return t->kind == NUTS_TARGET_LOGISTIC_REGRESSION && t->dtype == NUTS_F64 && t->tile.base != nullptr &&
+           t->dim <= nuts::kTileMaxDim && max_depth <= nuts::kTileMaxDepth;
+}
+
+// The lock-step kernel of nuts_wide.h: more features, binary32 targets with few rows, or four chains per workgroup.
+bool wide_eligible(const nuts_target* t, int max_depth)
+{
+    return t->kind == NUTS_TARGET_LOGISTIC_REGRESSION && t->tile.base != nullptr && t->dim <= nuts::kWideMaxDim &&
+           t->n <= 1000000 && max_depth <= nuts::kTileMaxDepth;
+}
+
+int launch_wide(nuts_target* t, nuts::DevSample sa, int nc, int cus)
+{
+    const size_t block = nuts::wide_block_bytes((int)t->dim, t->dtype == NUTS_F64 ? 8 : 4, nc, sa.max_depth);
+    long blocks = (sa.n_chains + nc - 1) / nc;
+    if (blocks > cus) blocks = cus;  // one workgroup per compute unit; further chains wait in the queue
+    if (t->static_call) {  // the scratch array is what it is: fewer workgroups rather than a refusal
+        const long fit = (long)(((size_t)NUTS_STATIC_SCRATCH_BYTES - kStaticHeader) / block);
+        if (fit >= 1 && blocks > fit) blocks = fit;
+    }
+    int rc = ensure_workspace(t, block * (size_t)blocks);
+    if (rc) return rc;
+    sa.workspace = t->ws_cur;
+    sa.slot_bytes = block;
+    const nuts::WideArgs wa{nuts::tile_args(t->tile, 1.0 / (t->prior_scale * t->prior_scale)), t->tile.ks1};
+    (t->dtype == NUTS_F64 ? nuts::wide_launch_f64 : nuts::wide_launch_f32)(wa, sa, nc, (int)blocks, g_stream);
+    HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
+    t->last_variant = NUTS_VARIANT_TILE;
+    t->last_grid = (int)blocks;
+    t->last_slots = 0;
+    return NUTS_OK;
+}
+
 int launch_tile(nuts_target* t, nuts::DevSample sa)
 {
+    int cus = 0;
+    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device), NUTS_E_DEVICE);
+    const int nc = nuts::wide_chains_per_block(sa.n_chains, cus);
+    if (!tile_eligible(t, sa.max_depth) || nc == 4) return launch_wide(t, sa, nc, cus);
     nuts::TileLaunch tl;
     nuts::tile_plan(t->tile, sa.n_chains, sa.max_depth, &tl);
     int rc = ensure_workspace(t, tl.workspace_bytes);
@@ -691,12 +742,6 @@ int launch_tile(nuts_target* t, nuts::DevSample sa)
     t->last_grid = tl.blocks;
     t->last_slots = 0;
     return NUTS_OK;
-}
-
-bool tile_eligible(const nuts_target* t, int max_depth)
-{
-    return t->kind == NUTS_TARGET_LOGISTIC_REGRESSION && t->dtype == NUTS_F64 && t->tile.base != nullptr &&
-           max_depth <= nuts::kTileMaxDepth;
 }
 
 }  // namespace
@@ -831,12 +876,11 @@ int sample_impl(const nuts_target* target, int64_t n_chains, int64_t n_iters, do
         return fail(NUTS_E_UNSUPPORTED, "the dense-Gaussian register kernel needs a dense Gaussian target with dim <= %d",
                     nuts::kDenseMaxDim);
 
-    const bool use_tile = opt.variant == NUTS_VARIANT_TILE || (opt.variant == NUTS_VARIANT_AUTO && tile_eligible(t, max_tree_depth));
     const bool use_elem = opt.variant == NUTS_VARIANT_ELEM || (opt.variant == NUTS_VARIANT_AUTO && elem_eligible(t));
-    // the grid kernels pay two launches per round; measured against the wave kernel they win from a few thousand
-    // multiply-adds per gradient upwards (N d = 800: 2-5 times slower; 25 000: 3-7 times faster, at 8 to 1024 chains)
     const bool use_grid = opt.variant == NUTS_VARIANT_GRID ||
-                          (opt.variant == NUTS_VARIANT_AUTO && grid_eligible(t) && t->n * t->dim >= (1 << 14));
+                          (opt.variant == NUTS_VARIANT_AUTO && grid_eligible(t) && grid_pays(t->n, t->dim));
+    const bool use_tile = opt.variant == NUTS_VARIANT_TILE ||
+                          (opt.variant == NUTS_VARIANT_AUTO && !use_grid && wide_eligible(t, max_tree_depth));
     // A precision matrix that is not banded goes to the matrix cores, four chains per wavefront, once there are
     // enough chains to give every compute unit several (below that the one-chain-per-wavefront kernel spreads
     // them over more SIMDs; measured crossover, see the profile summary of the quad kernel)

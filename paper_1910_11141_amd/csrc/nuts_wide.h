@@ -1,0 +1,761 @@
+// Wide tile kernel: logistic regression in either dtype with up to 128 features, NC = 16 or 4 chains per
+// workgroup in lock step, their gradients together on the matrix cores.
+//
+// The round is that of the tile kernel (nuts_tile.h): 8 wavefronts; every chain has its program counter, return
+// stack and tree state in the registers of 32 lanes, of which each owns up to 4 components of every state vector;
+// control sweep, batched gradient  Z = X~ Theta, s = sign(Z) F'(|Z|), G = X~' s  on 16-row tiles of the same packed
+// operand stream, completion.  What differs:
+//   * any d <= 128 (MT = ceil(d / 16) feature tiles), binary64 arithmetic in the contraction for both dtypes: binary32
+//     targets (state, momentum and gradient rounded to binary32 after every update) keep the sums of the general
+//     wave kernel, whose place this kernel takes;
+//   * NC = 4 runs the two GEMMs on v_mfma_f64_4x4x4_4b: its four blocks are the four groups of 4 rows (first GEMM) or
+//     of 4 features (second GEMM) of the 16x16x4 instruction's operands in the same lanes, and an element of the result
+//     is accumulated in the same order, so a chain's gradient has the same bits whichever form computed it.
+// The number of chains decides between the two forms (wide_chains_per_block below).
+//
+// What bounds it: with 16 chains the matrix instructions (1000 rows x 120 features: 63.5 k of the gradient phase's 78 k ticks,
+// its logistic functions another 5 k); with 4 chains the operand stream, which every compute unit reads from L2 at about
+// 50 bytes per tick (1000 x 60: 1 MB in 19 k ticks, where the instructions would take 11 k).  Measured against the wave
+// kernel, which read X twice per chain and gradient with the vector ALUs: binary64, 512 chains, 5000 x 60: 1.1e5 -> 7e6
+// gradient evaluations per second; binary32, 250 chains, 700 x 17: 3.6e6 -> 3.6e7.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include "nuts_dev.h"
+#include "nuts_fastmath.h"
+#include "nuts_rng.h"
+#include "nuts_tile_common.h"
+
+namespace nuts {
+
+constexpr int kWideLds = 160 * 1024;
+
+// Shape-dependent constants of one instantiation.
+template <typename T, int MT, int NC>
+struct WideShape {
+    static constexpr int kCpl = (16 * MT + 31) / 32;     // components per lane
+    static constexpr int kVec = kTileLanes * kCpl;       // elements of a stored vector
+    static constexpr int kPitch = 16 * MT + 1;           // doubles per chain in the LDS tiles (odd: see nuts_tile.h)
+    // partial gradients: one slot per wave, or, where eight do not fit beside the tables, one per pair of waves
+    static constexpr int kSlots = (NC == 16 && MT > 2) ? 4 : kTileWaves;
+    // With more than two feature tiles the waves' partial sums are added in pairs (w, w + 4) first, in both forms.
+    static constexpr bool kPairs = MT > 2;
+    static constexpr int kFixed = (NC * kPitch + kSlots * NC * kPitch + kTileWaves * NC + 16 * MT +
+                                   kFtabDoubles + kLogTabDoubles) * 8 + 256;
+    static constexpr int kEntry = NC * 2 * kVec * (int)sizeof(T);  // one pool buffer or first-leaf slot of every chain
+    static constexpr int kRoom = (kWideLds - kFixed) / kEntry;
+    // The vectors that only the start and the end of a doubling or of an iteration touch (the other end of the trajectory,
+    // the proposal, the momentum drawn ahead) are in registers when a lane owns one component; with more they would crowd
+    // the gradient loop out of the register file, and are kept in LDS or, if they do not fit, in global memory.
+    static constexpr bool kHeld = kCpl == 1;
+    static constexpr bool kRestLds = !kHeld && kRoom >= 5;
+    static constexpr int kEntries = kRoom - (kRestLds ? 3 : 0);
+    static constexpr int kLdsPool = kEntries >= 9 ? 5 : (kEntries + 1) / 2;   // shallow tree levels that live in LDS
+    static constexpr int kLdsFirst = kEntries >= 9 ? 4 : kEntries / 2;
+    static constexpr bool kHoldTheta = MT <= 2;          // positions as operands in registers across a round's tiles
+    // operands of a whole tile are requested one tile ahead, or (many features: not enough registers, and half a tile
+    // of that many instructions covers the latency) half a tile ahead
+    static constexpr bool kFullAhead = MT <= (NC == 4 ? 4 : 2);
+};
+
+struct WideArgs {
+    TileArgs ta;
+    int ks1;  // k-steps of the first GEMM, 4 MT - 4 < ks1 <= 4 MT (with a constant column possibly 4 MT - 4)
+};
+
+// Vectors of a chain that are kept outside the registers when !kHeld (after the level-indexed ones in the workspace).
+enum : int { kRestOtherTh = 0, kRestOtherR = 1, kRestOtherG = 2, kRestTop = 3, kRestTopG = 4, kRestNext = 5, kRestCount = 6 };
+__host__ __device__ inline int wide_num_vectors(int max_depth) { return tile_num_vectors(max_depth) + kRestCount; }
+
+// State of one chain: as TileChain (nuts_tile.h), with kCpl components per lane.
+template <typename T, int kCpl, bool kHeld>
+struct WideChain {
+    int pc, level, j, v, m, nleap, iter, cur_s, cur_idx, frame_idx, sub;
+    uint64_t ret;
+    uint32_t gchain, free_mask;  // gchain: global id of the chain
+    double H0, w_tree, cur_w, log_unit_w, edge_logp, top_logp;
+    double frame_w, pool_logp, u_sub;  // lane-distributed, see TileChain
+    T tha[kCpl], ra[kCpl], ga[kCpl];                 // the end of the trajectory that the current doubling extends
+    T rest[kHeld ? kRestCount : 1][kHeld ? kCpl : 1];  // kHeld: the vectors kRest*
+    double kin_n;
+    int ahead_iter, u_sub_leaf;
+    uint32_t dirbits, dirbits_n;
+};
+
+// Quad s of every row of 16 lanes, in all four quads of the row.
+template <int s>
+__device__ __forceinline__ double spread_quad(double x)
+{
+    constexpr int kPattern = (s << 7) | 0x13;  // source lane = (lane & 0x13) | 4 s
+    const int lo = __builtin_amdgcn_ds_swizzle(__double2loint(x), kPattern);
+    const int hi = __builtin_amdgcn_ds_swizzle(__double2hiint(x), kPattern);
+    return __hiloint2double(hi, lo);
+}
+
+template <typename T, int MT, int NC>
+__global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, DevSample sa)
+{
+    typedef WideShape<T, MT, NC> S;
+    constexpr int kCpl = S::kCpl, kVec = S::kVec, kLP = S::kLdsPool, kLF = S::kLdsFirst;
+    const TileArgs& ta = wa.ta;
+    __shared__ double sTheta[NC][S::kPitch];
+    __shared__ double sG[S::kSlots][NC][S::kPitch];
+    __shared__ double sLL[kTileWaves][NC];
+    __shared__ double sHalfCol[16 * MT];  // column sums of X~, halved
+    __shared__ int sHalted;
+    __shared__ __align__(16) double sFtab[kFtabDoubles + kLogTabDoubles];
+    __shared__ T sPool[NC][kLP > 0 ? kLP : 1][2][kLP > 0 ? kVec : 1];
+    __shared__ T sFirst[NC][kLF > 0 ? kLF : 1][2][kLF > 0 ? kVec : 1];
+    __shared__ T sRest[NC][kRestCount][S::kRestLds ? kVec : 1];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1), wave = uni(tid >> 6);
+    // 16 chains: two per wave; 4 chains: one in the lower half of each of the first four waves (one per SIMD)
+    const bool owns = NC == 16 || (wave < 4 && lane < kTileLanes);
+    const int grp = NC == 16 ? tid / kTileLanes : (wave & 3);
+    const int k = tid & (kTileLanes - 1);
+    const int d = ta.d, D = sa.max_depth;
+    const DrawKey key{sa.key0, sa.key1};
+    const bool slice = sa.sampler == kSamplerSlice;
+    const uint32_t all_bufs = (1u << (D + 1)) - 1u;
+    // component e of this lane: pairs (2i, 2i + 1) that share a Box-Muller draw as far as they go, then single ones
+    auto comp = [&](int e) __attribute__((always_inline)) -> int {
+        return e < kCpl / 2 * 2 ? 64 * (e / 2) + 2 * k + (e & 1) : 64 * (kCpl / 2) + k;
+    };
+
+    T* const wsc = reinterpret_cast<T*>(sa.workspace + (size_t)blockIdx.x * sa.slot_bytes) +
+                   (size_t)grp * wide_num_vectors(D) * kVec + k;
+    // level-indexed tree storage: shallow levels in LDS, the others in global memory (a lane reads what it wrote itself)
+    auto pool_load = [&](int b, int c, T (&v)[kCpl]) __attribute__((always_inline)) {
+        if (b < kLP) {
+#pragma unroll
+            for (int e = 0; e < kCpl; ++e) v[e] = sPool[grp][b < kLP ? b : 0][c][e * kTileLanes + k];
+        } else {
+#pragma unroll
+            for (int e = 0; e < kCpl; ++e) v[e] = wsc[(size_t)(2 * b + c) * kVec + e * kTileLanes];
+        }
+    };
+    auto pool_store = [&](int b, int c, const T (&v)[kCpl]) __attribute__((always_inline)) {
+        if (b < kLP) {
+#pragma unroll
+            for (int e = 0; e < kCpl; ++e) sPool[grp][b < kLP ? b : 0][c][e * kTileLanes + k] = v[e];
+        } else {
+#pragma unroll
+            for (int e = 0; e < kCpl; ++e) wsc[(size_t)(2 * b + c) * kVec + e * kTileLanes] = v[e];
+        }
+    };
+    auto first_load = [&](int s, int c, T (&v)[kCpl]) __attribute__((always_inline)) {
+        if (s <= kLF) {
+#pragma unroll
+            for (int e = 0; e < kCpl; ++e) v[e] = sFirst[grp][s <= kLF ? s - 1 : 0][c][e * kTileLanes + k];
+        } else {
+#pragma unroll
+            for (int e = 0; e < kCpl; ++e) v[e] = wsc[(size_t)(2 * (D + 1) + 2 * s + c) * kVec + e * kTileLanes];
+        }
+    };
+    auto first_store = [&](int s, int c, const T (&v)[kCpl]) __attribute__((always_inline)) {
+        if (s <= kLF) {
+#pragma unroll
+            for (int e = 0; e < kCpl; ++e) sFirst[grp][s <= kLF ? s - 1 : 0][c][e * kTileLanes + k] = v[e];
+        } else {
+#pragma unroll
+            for (int e = 0; e < kCpl; ++e) wsc[(size_t)(2 * (D + 1) + 2 * s + c) * kVec + e * kTileLanes] = v[e];
+        }
+    };
+
+    for (int i = tid; i < kFtabDoubles + kLogTabDoubles; i += kTileThreads) sFtab[i] = ta.ftab[i];
+    for (int i = tid; i < NC * S::kPitch; i += kTileThreads) (&sTheta[0][0])[i] = 0.0;
+    for (int i = tid; i < 16 * MT; i += kTileThreads) sHalfCol[i] = 0.5 * ta.colsum[i];
+    if (tid == 0) sHalted = 0;
+    __syncthreads();
+
+    // where component i goes in the first GEMM's contraction (see feat1 in tile_pack_operands)
+    auto slot_of = [&](int i) __attribute__((always_inline)) -> int {
+        return ta.z0_col < 0 ? i : (i == ta.z0_col ? d - 1 : (i == d - 1 ? ta.z0_col : i));
+    };
+    const __amdgpu_buffer_rsrc_t ops_rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(ta.ops), 0, (int)ta.ops_bytes, 0x00020000);
+
+    WideChain<T, kCpl, S::kHeld> c{};
+    c.pc = owns ? kPcFetch : kPcHalt;
+    c.cur_idx = -1;
+    auto rest_load = [&](int x, T (&v)[kCpl]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < kCpl; ++e)
+            v[e] = S::kHeld ? c.rest[S::kHeld ? x : 0][S::kHeld ? e : 0]
+                            : (S::kRestLds ? sRest[grp][x][S::kRestLds ? e * kTileLanes + k : 0]
+                                           : wsc[(size_t)(tile_num_vectors(D) + x) * kVec + e * kTileLanes]);
+    };
+    auto rest_store = [&](int x, const T (&v)[kCpl]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < kCpl; ++e) {
+            if (S::kHeld) c.rest[S::kHeld ? x : 0][S::kHeld ? e : 0] = v[e];
+            else if (S::kRestLds) sRest[grp][x][S::kRestLds ? e * kTileLanes + k : 0] = v[e];
+            else wsc[(size_t)(tile_num_vectors(D) + x) * kVec + e * kTileLanes] = v[e];
+        }
+    };
+    unsigned long long n_leaf = 0, n_rounds = 0;
+    unsigned n_extra = 0;
+    long long cyc_control = 0, cyc_grad = 0, cyc_post = 0;
+
+    // standard normals for this lane's components, in the dtype of the state
+    auto draw_normals = [&](uint32_t tag, uint32_t it, T (&out)[kCpl]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < kCpl; ++e) {
+            const int i = comp(e);
+            if (e < kCpl / 2 * 2 && (e & 1)) continue;  // made with its neighbour
+            double z0 = 0.0, z1 = 0.0;
+            if (i < d) {
+                const Words4 w = draw(key, (uint32_t)(i >> 1), tag, 0, it, c.gchain);
+                const double rho = sqrt(-2.0 * log_unit(uniform52(w.w0, w.w1), sFtab + kFtabDoubles));
+                const double phi = 6.283185307179586476925286766559 * uniform52(w.w2, w.w3);
+                if (e < kCpl / 2 * 2) {
+                    z0 = rho * circle_point(phi, false);
+                    z1 = i + 1 < d ? rho * circle_point(phi, true) : 0.0;
+                } else {
+                    z0 = rho * circle_point(phi, i & 1);
+                }
+            }
+            out[e] = (T)z0;
+            if (e < kCpl / 2 * 2) out[e + 1 < kCpl ? e + 1 : e] = (T)z1;
+        }
+    };
+    auto push_ret = [&](unsigned code) __attribute__((always_inline)) { c.ret = (c.ret << 2) | code; };
+    auto do_return = [&]() __attribute__((always_inline)) {
+        c.pc = ret_to_pc((unsigned)(c.ret & 3u));
+        c.ret >>= 2;
+        c.level += 1;
+    };
+    auto descend_to_leaf = [&]() __attribute__((always_inline)) {
+        c.ret <<= 2 * c.level;  // one kRetAfterLeft (= 0) per level
+        c.level = 0;
+        c.pc = kPcLeaf;
+    };
+    auto materialise_cur = [&]() __attribute__((always_inline)) {
+        if (c.cur_idx >= 0) return;
+        const int b = __ffs(c.free_mask) - 1;
+        c.free_mask &= ~(1u << b);
+        pool_store(b, 0, c.tha);
+        pool_store(b, 1, c.ga);
+        if (k == b) c.pool_logp = c.edge_logp;
+        c.cur_idx = b;
+    };
+    // (theta+ - theta-) . r at both ends of the span between the extended end and (t, r); going backwards the span is the
+    // negative of their difference, exactly, so the signs of the sums are turned by the direction
+    auto no_uturn = [&](const T (&t)[kCpl], const T (&r)[kCpl]) __attribute__((always_inline)) -> bool {
+        double a = 0.0, b = 0.0;
+#pragma unroll
+        for (int e = 0; e < kCpl; ++e) {
+            const T span = c.v > 0 ? c.tha[e] - t[e] : t[e] - c.tha[e];
+            a = fma((double)span, (double)r[e], a);
+            b = fma((double)span, (double)c.ra[e], b);
+        }
+        return group_both_nonnegative(a, b, lane);
+    };
+
+    // ---- blocks of the chain program; each runs for the lanes whose chain waits at it (see nuts_tile.h) ----
+    auto block_after_right = [&]() __attribute__((always_inline)) {
+        if (c.cur_s) {
+            const int f = c.m - (1 << c.level) + 1;  // first leaf of this subtree, 1-based
+            const int s = (f == 1) ? c.j : min(__ffs(f - 1) - 1, c.j);
+            T tf[kCpl], rf[kCpl];
+            first_load(s, 0, tf);
+            first_load(s, 1, rf);
+            const double l_w = __shfl(c.frame_w, c.level, kTileLanes);
+            const int l_idx = __shfl(c.frame_idx, c.level, kTileLanes);
+            const double u = __shfl(c.u_sub, c.level + (c.u_sub_leaf != c.nleap ? 16 : 0), kTileLanes);
+            const double w_new = l_w + c.cur_w;
+            if (u * w_new < c.cur_w) {  // right with probability w_R / (w_L + w_R)
+                c.free_mask |= (1u << l_idx);
+            } else {
+                if (c.cur_idx >= 0) c.free_mask |= (1u << c.cur_idx);
+                c.cur_idx = l_idx;
+            }
+            c.cur_w = w_new;
+            c.cur_s = no_uturn(tf, rf);
+        }
+        do_return();
+    };
+    auto block_after_left = [&]() __attribute__((always_inline)) {
+        if (!c.cur_s) {  // the right half is never built
+            do_return();
+            return;
+        }
+        materialise_cur();
+        if (k == c.level) {
+            c.frame_w = c.cur_w;
+            c.frame_idx = c.cur_idx;
+        }
+        c.level -= 1;
+        push_ret(kRetAfterRight);
+        descend_to_leaf();
+    };
+    auto block_double_end = [&]() __attribute__((always_inline)) {
+        bool go_on = false;
+        if (c.cur_s) {
+            const double u = __shfl(c.pool_logp, 16 + c.j, kTileLanes);
+            if (u * c.w_tree < c.cur_w) {  // accept the new half with probability min(1, w_new / w_tree)
+                if (c.cur_idx < 0) {
+                    rest_store(kRestTop, c.tha);
+                    rest_store(kRestTopG, c.ga);
+                    c.top_logp = c.edge_logp;
+                } else {
+                    T t[kCpl], g[kCpl];
+                    pool_load(c.cur_idx, 0, t);
+                    pool_load(c.cur_idx, 1, g);
+                    rest_store(kRestTop, t);
+                    rest_store(kRestTopG, g);
+                    c.top_logp = __shfl(c.pool_logp, c.cur_idx, kTileLanes);
+                }
+            }
+            c.w_tree += c.cur_w;
+            T to[kCpl], ro[kCpl];
+            rest_load(kRestOtherTh, to);
+            rest_load(kRestOtherR, ro);
+            go_on = no_uturn(to, ro);
+        }
+        c.j += 1;
+        c.free_mask = all_bufs;  // nothing of the finished doubling stays in the pool
+        c.pc = (go_on && c.j < D) ? kPcDoubleBegin : kPcIterEnd;
+    };
+    auto block_iter_end = [&]() __attribute__((always_inline)) {
+        const size_t row = (size_t)c.iter * (size_t)sa.n_chains + (size_t)(c.gchain - (uint32_t)sa.first_chain);
+        if (sa.out_states) {
+            T* dst = static_cast<T*>(sa.out_states) + row * d;
+            T t[kCpl];
+            rest_load(kRestTop, t);
+#pragma unroll
+            for (int e = 0; e < kCpl; ++e)
+                if (comp(e) < d) dst[comp(e)] = t[e];
+        }
+        if (k == 0) {
+            if (sa.out_depths) sa.out_depths[row] = c.j;
+            if (sa.out_nleap) sa.out_nleap[row] = c.nleap;
+        }
+        c.iter += 1;
+        c.pc = (c.iter < sa.iter_end) ? kPcIterBegin : kPcFetch;
+    };
+    auto block_fetch = [&]() __attribute__((always_inline)) {
+        unsigned long long q = 0;
+        if (k == 0) q = atomicAdd(&sa.counters[kCtrQueue], 1ull);
+        q = __shfl(q, 0, kTileLanes);
+        T t[kCpl];
+#pragma unroll
+        for (int e = 0; e < kCpl; ++e) t[e] = (T)0;
+        if ((long)q >= sa.n_chains) {
+            c.pc = kPcHalt;
+            if (k == 0) atomicAdd(&sHalted, 1);
+            return;
+        }
+        c.gchain = (uint32_t)(sa.first_chain + (long)q);
+        c.iter = sa.iter_begin;
+        c.ahead_iter = -1;
+        c.u_sub_leaf = kNoLeaf;
+        c.free_mask = all_bufs;
+        if (sa.init_states) {
+            const T* src = static_cast<const T*>(sa.init_states) + (size_t)q * d;
+#pragma unroll
+            for (int e = 0; e < kCpl; ++e)
+                if (comp(e) < d) t[e] = src[comp(e)];
+        } else {
+            draw_normals(kDrawInit, 0, t);
+        }
+        rest_store(kRestTop, t);
+        c.pc = kPcInitEval;
+    };
+    // every random number of an iteration that does not depend on where the trajectory goes
+    auto draw_iteration = [&](int it) __attribute__((always_inline)) {
+        T r[kCpl];
+        draw_normals(kDrawMomentum, (uint32_t)it, r);
+        rest_store(kRestNext, r);
+        double kin = 0.0;
+#pragma unroll
+        for (int e = 0; e < kCpl; ++e) kin = fma((double)r[e], (double)r[e], kin);
+        c.kin_n = group_sum(kin);
+        const bool slice_lane = slice && k == kTileLanes - 1;
+        const Words4 w = draw(key, slice_lane ? 0u : (uint32_t)(k & 15),
+                              k < 16 ? kDrawDirection : (slice_lane ? kDrawSlice : kDrawTop), 0, (uint32_t)it, c.gchain);
+        const unsigned long long votes = __ballot((k < 16) && (w.w0 >> 31));
+        c.dirbits_n = (uint32_t)(votes >> (lane & 32)) & 0xffffu;
+        if (k >= 16) c.frame_w = uniform52(w.w0, w.w1);
+        if (slice_lane) c.frame_w = log(c.frame_w);
+        c.ahead_iter = it;
+    };
+    auto block_iter_begin = [&]() __attribute__((always_inline)) {
+        if (c.ahead_iter != c.iter) draw_iteration(c.iter);
+        c.dirbits = c.dirbits_n;
+        if (k >= 16) c.pool_logp = c.frame_w;
+        rest_load(kRestTop, c.tha);
+        rest_load(kRestTopG, c.ga);
+        rest_load(kRestNext, c.ra);
+        rest_store(kRestOtherTh, c.tha);
+        rest_store(kRestOtherG, c.ga);
+        rest_store(kRestOtherR, c.ra);
+        c.H0 = -c.top_logp + 0.5 * c.kin_n;
+        c.w_tree = 1.0;
+        c.log_unit_w = 0.0;
+        c.j = 0;
+        c.nleap = 0;
+        c.u_sub_leaf = kNoLeaf;
+        c.pc = kPcDoubleBegin;
+    };
+    auto block_double_begin = [&]() __attribute__((always_inline)) {
+        const int v = ((c.dirbits >> c.j) & 1u) ? 1 : -1;
+        if (v != c.v) {  // the doubling turns round: the two ends change places
+            T t[kCpl], r[kCpl], g[kCpl];
+            rest_load(kRestOtherTh, t);
+            rest_load(kRestOtherR, r);
+            rest_load(kRestOtherG, g);
+            rest_store(kRestOtherTh, c.tha);
+            rest_store(kRestOtherR, c.ra);
+            rest_store(kRestOtherG, c.ga);
+#pragma unroll
+            for (int e = 0; e < kCpl; ++e) {
+                c.tha[e] = t[e];
+                c.ra[e] = r[e];
+                c.ga[e] = g[e];
+            }
+        }
+        c.v = v;
+        c.m = 0;
+        c.level = c.j;
+        push_ret(kRetDoubleEnd);
+        descend_to_leaf();
+    };
+
+    const int pairs1 = (wa.ks1 + 1) / 2;                // operand pairs of the first GEMM that the stream holds
+    const int tile_bytes = (pairs1 + 2 * MT) * 64 * 16;  // bytes of a tile in the stream
+    auto load_at = [&](int byte_off) __attribute__((always_inline)) -> double2 {
+        return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(ops_rsrc, lane * 16, byte_off, 0));
+    };
+
+    for (;;) {
+        const long long t0 = clock64();
+        // ---- 1. control ----
+        if (c.pc == kPcAfterRight && c.cur_s && c.u_sub_leaf != c.nleap && c.u_sub_leaf + 2 * sa.leaf_steps != c.nleap) {
+            const Words4 w = draw(key, (uint32_t)(c.nleap + (k >= 16 ? 2 * sa.leaf_steps : 0)), kDrawSubtree, (uint32_t)(k & 15),
+                                  (uint32_t)c.iter, c.gchain);
+            c.u_sub = uniform52(w.w0, w.w1);
+            c.u_sub_leaf = c.nleap;
+        }
+        for (;;) {
+            const int pa = __builtin_amdgcn_readlane(c.pc, 0), pb = __builtin_amdgcn_readlane(c.pc, kTileLanes);
+            const bool any_right = pa == kPcAfterRight || pb == kPcAfterRight;
+            const bool any_left = pa == kPcAfterLeft || pb == kPcAfterLeft;
+            if (!any_right && !any_left) break;
+            if (any_right && c.pc == kPcAfterRight) block_after_right();
+            if (c.pc == kPcAfterLeft) block_after_left();
+        }
+        const bool wave_busy = __any(c.pc == kPcDoubleEnd);
+        if (c.pc == kPcDoubleEnd) block_double_end();
+        if (c.pc == kPcIterEnd) block_iter_end();
+        if (c.pc == kPcFetch) block_fetch();
+        if (c.pc == kPcIterBegin) block_iter_begin();
+        if (c.pc == kPcDoubleBegin) block_double_begin();
+        if (!wave_busy && c.pc == kPcLeaf && c.ahead_iter != c.iter + 1 && c.nleap >= 1 && c.iter + 1 < sa.iter_end)
+            draw_iteration(c.iter + 1);
+
+        // ---- 2. batched gradient ----
+        const bool at_leaf = c.pc == kPcLeaf, at_init = c.pc == kPcInitEval;
+        const T half = (T)(0.5 * (c.v * sa.eps)), full = (T)(c.v * sa.eps);
+        if (owns) {
+            if (at_init) rest_load(kRestTop, c.tha);  // (the ends of the trajectory are set when the iteration begins)
+#pragma unroll
+            for (int e = 0; e < kCpl; ++e) {
+                if (at_leaf) {  // first half-kick and drift, in place
+                    c.ra[e] = c.ra[e] + half * c.ga[e];
+                    c.tha[e] = c.tha[e] + full * c.ra[e];
+                }
+                if (comp(e) < 16 * MT) sTheta[grp][slot_of(comp(e))] = (at_leaf || at_init) ? (double)c.tha[e] : 0.0;
+            }
+        }
+        double2 a1[2 * MT], a2[S::kFullAhead ? 2 * MT : 1];
+        {
+            const int base = wave * tile_bytes;
+#pragma unroll
+            for (int i = 0; i < 2 * MT; ++i)
+                if (i < 2 * MT - 2 || i < pairs1) a1[i] = load_at(base + i * 1024);
+            if (S::kFullAhead) {
+#pragma unroll
+                for (int i = 0; i < 2 * MT; ++i) a2[i] = load_at(base + (pairs1 + i) * 1024);
+            }
+        }
+        tile_lds_barrier();
+        if (*const_cast<volatile int*>(&sHalted) == NC) break;  // every chain of the workgroup has halted
+        n_rounds += 1;
+        const long long t1 = clock64();
+        {
+            typedef __attribute__((ext_vector_type(4))) double acc16;
+            acc16 G16[NC == 16 ? MT : 1];
+            double G4[NC == 4 ? MT : 1];
+#pragma unroll
+            for (int u = 0; u < MT; ++u) {
+                if (NC == 16) G16[NC == 16 ? u : 0] = acc16{0.0, 0.0, 0.0, 0.0};
+                else G4[NC == 4 ? u : 0] = 0.0;
+            }
+            double sum_abs = 0.0, prod = 1.0, log_prod = 0.0;
+            // B operand of the first GEMM: component 4 s + lane/16 of the position of chain lane % NC
+            const double* const b_src = &sTheta[lane & (NC - 1)][lane >> 4];
+            double b1[S::kHoldTheta ? 4 * MT : 1];
+            if (S::kHoldTheta) {
+#pragma unroll
+                for (int s = 0; s < 4 * MT; ++s) b1[s] = b_src[4 * s];
+            }
+            const double z0 = ta.z0_col >= 0 ? ta.z0_val * sTheta[lane & (NC - 1)][d - 1] : 0.0;
+            auto row_tile = [&](const int t, const bool ragged, const bool more) __attribute__((always_inline)) {
+                const int here = t * tile_bytes, next = (t + kTileWaves) * tile_bytes;
+                // (the positions are read from LDS again for every tile: kept across tiles they would fill 8 MT registers)
+                if (!S::kHoldTheta) asm volatile("" ::: "memory");
+                acc16 z;
+                double z4;
+                if (NC == 16) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) z[q] = (!ragged || 4 * q + (lane >> 4) < ta.rem_rows) ? z0 : 0.0;
+                } else {
+                    z4 = (!ragged || 4 * ((lane >> 2) & 3) + (lane >> 4) < ta.rem_rows) ? z0 : 0.0;
+                }
+#pragma unroll
+                for (int s = 0; s < 4 * MT; ++s) {
+                    if (s < 4 * MT - 4 || s < wa.ks1) {
+                        const double a = (s & 1) ? a1[s >> 1].y : a1[s >> 1].x;
+                        const double b = S::kHoldTheta ? b1[S::kHoldTheta ? s : 0] : b_src[4 * s];
+                        if (NC == 16) z = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, z, 0, 0, 0);
+                        else z4 = __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, z4, 0, 0, 0);
+                    }
+                    // the second GEMM's operand takes the register pair that has just been used up
+                    if (!S::kFullAhead && (s & 1)) a1[s >> 1] = load_at(here + (pairs1 + (s >> 1)) * 1024);
+                }
+                if (S::kFullAhead && more) {
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int i = 0; i < 2 * MT; ++i)
+                        if (i < 2 * MT - 2 || i < pairs1) a1[i] = load_at(next + i * 1024);
+                }
+                double sg[4];
+                if (NC == 16) {
+                    const double zq[4] = {z[0], z[1], z[2], z[3]};
+                    double slope[4];
+                    if (MT <= 2) {
+                        logistic_slopes<4>(zq, sFtab, slope);
+                    } else {  // (two at a time: fewer table coefficients in registers at once)
+                        const double za[2] = {zq[0], zq[1]}, zb[2] = {zq[2], zq[3]};
+                        double ra[2], rb[2];
+                        logistic_slopes<2>(za, sFtab, ra);
+                        __builtin_amdgcn_sched_barrier(0);
+                        logistic_slopes<2>(zb, sFtab, rb);
+                        slope[0] = ra[0], slope[1] = ra[1], slope[2] = rb[0], slope[3] = rb[1];
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        sg[q] = __builtin_copysign(slope[q], zq[q]);
+                        asm("v_add_f64 %0, %0, |%1|" : "+v"(sum_abs) : "v"(zq[q]));
+                    }
+                    prod *= ((fabs(sg[0]) + 0.5) * (fabs(sg[1]) + 0.5)) * ((fabs(sg[2]) + 0.5) * (fabs(sg[3]) + 0.5));
+                } else {
+                    const double slope = logistic_slope(z4, sFtab);
+                    const double x = __builtin_copysign(slope, z4);
+                    asm("v_add_f64 %0, %0, |%1|" : "+v"(sum_abs) : "v"(z4));
+                    prod *= fabs(x) + 0.5;
+                    // rows 4s + k of the tile sit in quad s: every block of the second GEMM wants them
+                    sg[0] = spread_quad<0>(x);
+                    sg[1] = spread_quad<1>(x);
+                    sg[2] = spread_quad<2>(x);
+                    sg[3] = spread_quad<3>(x);
+                }
+#pragma unroll
+                for (int u = 0; u < MT; ++u)
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) {
+                        const int p = u * 2 + (s >> 1);
+                        const double2 pr = S::kFullAhead ? a2[S::kFullAhead ? p : 0] : a1[p];
+                        const double a = (s & 1) ? pr.y : pr.x;
+                        if (NC == 16) G16[NC == 16 ? u : 0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, sg[s], G16[NC == 16 ? u : 0], 0, 0, 0);
+                        else G4[NC == 4 ? u : 0] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, sg[s], G4[NC == 4 ? u : 0], 0, 0, 0);
+                        // (past the end of the stream the buffer's bounds check answers with zeros)
+                        if (!S::kFullAhead && (s & 1)) a1[p] = load_at(next + p * 1024);
+                    }
+                if (S::kFullAhead && more) {
+#pragma unroll
+                    for (int i = 0; i < 2 * MT; ++i) a2[i] = load_at(next + (pairs1 + i) * 1024);
+                }
+            };
+            // (z0: a last tile that is not full is run after the loop, by the wave whose turn it is)
+            const int n_loop = ta.rem_rows != 0 ? ta.n_tiles - 1 : ta.n_tiles;
+            for (int t_chunk = wave; t_chunk < n_loop; t_chunk += 64 * kTileWaves) {
+                const int t_stop = min(n_loop, t_chunk + 64 * kTileWaves);
+                for (int t = t_chunk; t < t_stop; t += kTileWaves) row_tile(t, false, t + kTileWaves < ta.n_tiles);
+                if (t_chunk + 64 * kTileWaves < n_loop) {  // more follow: fold the product of sigmas
+                    log_prod += log_unit(prod, sFtab + kFtabDoubles);
+                    prod = 1.0;
+                }
+            }
+            if (ta.rem_rows != 0 && wave == ((ta.n_tiles - 1) & (kTileWaves - 1))) row_tile(ta.n_tiles - 1, true, false);
+            log_prod += log_unit(prod, sFtab + kFtabDoubles);
+            double ll = log_prod - 0.5 * sum_abs;
+            if (NC == 4) {  // the chain's 16 lanes: four quads of every row, then the rows
+                ll += dpp_rotate<0x128>(ll);
+                ll += dpp_rotate<0x124>(ll);
+            }
+            ll = add_other_row(ll);
+            ll = add_other_half(ll);
+            if (lane < NC) sLL[wave][lane] = ll;
+            // partial gradients to LDS: element (u, q) of the accumulators is feature 16u + 4q + lane/16 (16 chains) or
+            // 16u + 4((lane/4) % 4) + lane/16 (4 chains) of chain lane % NC
+            auto put = [&](double* dst, bool add) __attribute__((always_inline)) {
+#pragma unroll
+                for (int u = 0; u < MT; ++u) {
+                    if (NC == 16) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const double g = G16[NC == 16 ? u : 0][q];
+                            dst[16 * u + 4 * q] = add ? dst[16 * u + 4 * q] + g : g;
+                        }
+                    } else {
+                        dst[16 * u] = G4[NC == 4 ? u : 0];
+                    }
+                }
+            };
+            const int off = NC == 16 ? (lane >> 4) : 4 * ((lane >> 2) & 3) + (lane >> 4);
+            if (S::kSlots == kTileWaves) {
+                put(&sG[wave & (S::kSlots - 1)][lane & (NC - 1)][off], false);
+            } else {  // two waves share a slot, one after the other
+                if (wave < 4) put(&sG[wave & 3][lane & (NC - 1)][off], false);
+                tile_lds_barrier();
+                if (wave >= 4) put(&sG[wave & 3][lane & (NC - 1)][off], true);
+            }
+        }
+        tile_lds_barrier();
+        const long long t2 = clock64();
+
+        // ---- 3. every chain collects its gradient and finishes its step ----
+        if (at_leaf || at_init) {
+            const double ll_part = (k < kTileWaves) ? sLL[k & (kTileWaves - 1)][grp] : 0.0;
+            double sq = ll_part, kin = 0.0;
+#pragma unroll
+            for (int e = 0; e < kCpl; ++e) {
+                const int i = comp(e);
+                double gsum = 0.0;
+                if (i < 16 * MT) {
+                    if (S::kSlots == 4) {
+#pragma unroll
+                        for (int w = 0; w < 4; ++w) gsum += sG[w][grp][i];
+                    } else if (S::kPairs) {
+#pragma unroll
+                        for (int w = 0; w < 4; ++w) gsum += sG[w][grp][i] + sG[(w + 4) & (S::kSlots - 1)][grp][i];
+                    } else {
+#pragma unroll
+                        for (int w = 0; w < kTileWaves; ++w) gsum += sG[w & (S::kSlots - 1)][grp][i];
+                    }
+                }
+                const double th = (double)c.tha[e];
+                const double hc = i < 16 * MT ? sHalfCol[i] : 0.0;
+                const T g = i < d ? (T)((hc - gsum) - th * ta.prior_prec) : (T)0;
+                // |theta|^2 for the prior, (1/2) colsum . theta = (1/2) sum z~ for the likelihood
+                sq += fma(th, th * (-0.5 * ta.prior_prec), hc * th);
+                if (at_leaf) {
+                    const T r_new = c.ra[e] + half * g;
+                    c.ra[e] = r_new;
+                    kin = fma((double)r_new, (double)r_new, kin);
+                }
+                c.ga[e] = g;
+            }
+            if (at_leaf) {
+                c.nleap += 1;
+                n_leaf += 1;
+                c.sub += 1;
+                if (c.sub >= sa.leaf_steps) {  // otherwise the leaf is not finished: the chain stays at LEAF
+                    c.sub = 0;
+                    group_sum2(sq, kin);
+                    const double logp = ta.n_pad * 0.6931471805599453 + sq;
+                    c.edge_logp = logp;
+                    c.m += 1;
+                    double delta = (-logp + 0.5 * kin) - c.H0;
+                    if (!(fabs(delta) < INFINITY)) delta = INFINITY;
+                    if (slice) {
+                        const double log_slice = __shfl(c.pool_logp, kTileLanes - 1, kTileLanes);
+                        c.cur_w = (log_slice <= -delta) ? 1.0 : 0.0;
+                        c.cur_s = (log_slice < kDeltaMax - delta);
+                    } else {
+                        double e = c.log_unit_w - delta;  // logarithm of the leaf's weight in the current unit
+                        if (e > 600.0) {  // the energy has fallen far: this leaf becomes the unit
+                            const double shrink = exp_bounded(-e);
+                            c.w_tree *= shrink;
+                            if (k < 16) c.frame_w *= shrink;
+                            c.log_unit_w = delta;
+                            e = 0.0;
+                        }
+                        c.cur_w = exp_bounded(e);
+                        c.cur_s = (delta <= kDeltaMax);
+                    }
+                    c.cur_idx = -1;  // the proposal of a one-leaf subtree is the edge itself
+                    if ((c.m & 1) && c.j >= 1) {
+                        const int s = (c.m == 1) ? c.j : min(__ffs(c.m - 1) - 1, c.j);
+                        first_store(s, 0, c.tha);
+                        first_store(s, 1, c.ra);
+                    }
+                    do_return();
+                }
+            } else {
+                rest_store(kRestTopG, c.ga);
+                c.top_logp = ta.n_pad * 0.6931471805599453 + group_sum(sq);
+                n_extra += 1;
+                c.pc = kPcIterBegin;
+            }
+        }
+        cyc_control += t1 - t0;
+        cyc_grad += t2 - t1;
+        cyc_post += clock64() - t2;
+    }
+
+    if (owns && k == 0) {
+        atomicAdd(&sa.counters[kCtrUseful], n_leaf);
+        atomicAdd(&sa.counters[kCtrExtra], (unsigned long long)n_extra);
+    }
+    if (tid == 0) {
+        atomicAdd(&sa.counters[kCtrIssued], n_rounds * NC);
+        atomicAdd(&sa.counters[kCtrRounds], n_rounds);
+        atomicAdd(&sa.counters[kCtrCycControl], (unsigned long long)cyc_control);
+        atomicAdd(&sa.counters[kCtrCycGrad], (unsigned long long)cyc_grad);
+        atomicAdd(&sa.counters[kCtrCycPost], (unsigned long long)cyc_post);
+    }
+}
+
+// Chains per workgroup for a run of n_chains on a chip of `cus` compute units (one workgroup each).  A round of 4 chains
+// takes a little less than half as long as one of 16 (1000 x 25: 14.5 k ticks against 27.7 k; 1000 x 60: 25 k against 52 k),
+// so up to 8 chains per compute unit - two rounds of 4 after one another - the small form wins (1792 chains: 2.0 ms
+// against 2.3; 1000 x 60: 3.4 against 4.2) and beyond it loses.
+inline int wide_chains_per_block(long n_chains, int cus) { return n_chains <= 8L * cus ? 4 : 16; }
+
+inline size_t wide_block_bytes(int d, int dtype_bytes, int nc, int max_depth)
+{
+    const int cpl = ((d + 15) / 16 * 16 + 31) / 32;
+    return (size_t)nc * wide_num_vectors(max_depth) * kTileLanes * cpl * dtype_bytes;
+}
+
+// One instantiation per feature-tile count and form (each dtype in a translation unit of its own).
+template <typename T, int MT>
+inline void wide_launch_mt(const WideArgs& wa, const DevSample& sa, int nc, int blocks, hipStream_t stream)
+{
+    if (nc == 4)
+        hipLaunchKernelGGL((nuts_wide_kernel<T, MT, 4>), dim3((unsigned)blocks), dim3(kTileThreads), 0, stream, wa, sa);
+    else
+        hipLaunchKernelGGL((nuts_wide_kernel<T, MT, 16>), dim3((unsigned)blocks), dim3(kTileThreads), 0, stream, wa, sa);
+}
+template <typename T>
+inline void wide_launch(const WideArgs& wa, const DevSample& sa, int nc, int blocks, hipStream_t stream)
+{
+    switch ((wa.ta.d + 15) / 16) {
+    case 1: wide_launch_mt<T, 1>(wa, sa, nc, blocks, stream); break;
+    case 2: wide_launch_mt<T, 2>(wa, sa, nc, blocks, stream); break;
+    case 3: wide_launch_mt<T, 3>(wa, sa, nc, blocks, stream); break;
+    case 4: wide_launch_mt<T, 4>(wa, sa, nc, blocks, stream); break;
+    case 5: wide_launch_mt<T, 5>(wa, sa, nc, blocks, stream); break;
+    case 6: wide_launch_mt<T, 6>(wa, sa, nc, blocks, stream); break;
+    case 7: wide_launch_mt<T, 7>(wa, sa, nc, blocks, stream); break;
+    default: wide_launch_mt<T, 8>(wa, sa, nc, blocks, stream); break;
+    }
+}
+void wide_launch_f64(const WideArgs& wa, const DevSample& sa, int nc, int blocks, hipStream_t stream);
+void wide_launch_f32(const WideArgs& wa, const DevSample& sa, int nc, int blocks, hipStream_t stream);
+
+}  // namespace nuts

@@ -1175,3 +1175,60 @@ def test_dense_register_kernel_banded_f32_and_options():
     for kw in (dict(leaf_steps=4), dict(sampler=SLICE), dict(sampler=SLICE, leaf_steps=2)):
         assert_parity(gpu_run(w, variant=DENSE, **kw), ref_run(w, **kw), F64_TOL, label=f"banded {kw}")
     both_schedules(w, DENSE)
+
+
+# ------------------------------------------------------------------ wide tile kernel (up to 128 features, both dtypes, 16 or 4 chains in lock step)
+
+def wide_workload(n_data, dim, dtype, n_chains):
+    w = W.small_logreg(n_data, dim, seed=900 + n_data + dim, dtype=dtype)
+    w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = n_chains, 6, 0.15 / np.sqrt(max(n_data, 1) / 10), 6
+    return w
+
+
+# feature counts at the edges of the tiles of 16, of the k-steps of 4 (also with the constant column outside the first
+# GEMM: d = 1 mod 4) and of the components per lane; row counts below, at and beyond a tile and a round of 8 tiles
+@pytest.mark.parametrize("n_data,dim", [(1, 33), (15, 48), (16, 49), (129, 63), (128, 64), (300, 65), (77, 80), (145, 81), (40, 96),
+                                        (131, 97), (64, 112), (17, 113), (129, 128), (9000, 34)])
+def test_wide_kernel_f64_both_forms_match_the_oracle_and_each_other(n_data, dim):
+    B = N()
+    w = wide_workload(n_data, dim, np.float64, 9 if n_data < 9000 else 3)
+    tgt = gpu_target(w)
+    few = gpu_run(w, tgt=tgt)                              # four chains per workgroup
+    assert few[3]["variant"] == B.NUTS_VARIANT_TILE and few[3]["leaf_slots_useful"] == few[2].sum()
+    assert_parity(few, ref_run(w), F64_TOL, label=w.name)
+    many = gpu_run(w, tgt=tgt, n_chains=2100, n_iters=2)    # sixteen
+    for k in range(3):                                      # the same bits whichever form computes a chain
+        assert np.array_equal(many[k][:, :w.n_chains], few[k][:2])
+
+
+@pytest.mark.parametrize("n_data,dim", [(1, 1), (50, 5), (700, 17), (131, 32), (200, 33), (129, 100), (120, 128)])
+def test_wide_kernel_f32_small_data_sets_keep_the_sums_of_the_wave_kernel(n_data, dim):
+    B = N()
+    w = wide_workload(n_data, dim, np.float32, 13)
+    tgt = gpu_target(w)
+    g = gpu_run(w, tgt=tgt)
+    assert g[3]["variant"] == B.NUTS_VARIANT_TILE
+    f32_parity(g, ref_run(w))
+    slice4 = gpu_run(w, tgt=tgt, sampler=1, leaf_steps=4, schedule=1)
+    f32_parity(slice4, ref_run(w, sampler=1, leaf_steps=4))
+    many = gpu_run(w, tgt=tgt, n_chains=2100, n_iters=2)
+    for k in range(3):
+        assert np.array_equal(many[k][:, :13], g[k][:2])
+
+
+@pytest.mark.parametrize("n_chains", [1, 5, 1023])
+def test_tile_kernel_four_chain_form_deep_trees_divergences_and_options(n_chains):
+    """Up to 8 chains per compute unit the tile variant steps 4 chains per workgroup: the same bits as 16 per workgroup."""
+    w = W.small_logreg(50, 5, seed=6)
+    w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = n_chains, 8, 0.5, 7
+    init = np.random.default_rng(1).standard_normal((n_chains, 5)) * 8
+    tgt = gpu_target(w)
+    r = ref_run(w, init=init)
+    g = gpu_run(w, tgt=tgt, init=init)
+    assert_parity(g, r, F64_TOL, label="four chains per workgroup")
+    assert_parity(gpu_run(w, tgt=tgt, init=init, sampler=1, leaf_steps=3, schedule=1), ref_run(w, init=init, sampler=1, leaf_steps=3),
+                  F64_TOL, label="four chains per workgroup, slice")
+    wide = gpu_run(w, tgt=tgt, n_chains=2100, n_iters=3)
+    few = gpu_run(w, tgt=tgt, n_iters=3)
+    for k in range(3):
+        assert np.array_equal(wide[k][:, :n_chains], few[k])
