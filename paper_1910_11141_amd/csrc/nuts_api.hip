@@ -45,6 +45,9 @@ int fail(int code, const char* fmt, ...)
     } while (0)
 
 size_t elem_size(int dtype) { return dtype == NUTS_F64 ? sizeof(double) : sizeof(float); }
+constexpr int kLdsBytes = 160 * 1024;  // of a compute unit,
+constexpr int kLdsGranule = 1280;      // handed out in pieces of this size
+
 
 // Scratch memory of nuts_sample_static: one array per GPU, part of the loaded code object, never
 // allocated or freed.  The first kStaticHeader bytes hold the call's counters, the rest its workspace.
@@ -470,12 +473,11 @@ int launch_dense_inst(nuts_target* t, nuts::DevSample sa)
     using namespace nuts;
     DevTarget<T> tg = dev_target<T>(t);
     const int threads = kDenseWaves * kWave;
-    size_t lds_bytes = ((size_t)(kBanded ? 0 : t->dim) * kDensePitch +
-                        (size_t)kDenseWaves * (kDensePitch + 2 * kBandHalf)) * sizeof(T);
+    size_t lds_bytes = dense_base_elems(kBanded ? 0 : (int)t->dim) * sizeof(T);
     lds_bytes = (lds_bytes + 15) & ~(size_t)15;
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(nuts_dense_kernel<T, kBanded>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes), NUTS_E_DEVICE);
-    size_t slot = (size_t)dense_num_vectors(sa.max_depth) * kDensePitch * sizeof(T);
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes), NUTS_E_DEVICE);
+    size_t slot = (size_t)row_num_vectors(sa.max_depth) * kDensePitch * sizeof(T);
     slot = (slot + 255) & ~(size_t)255;
     int per_cu = 0, cus = 0;
     HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (nuts_dense_kernel<T, kBanded>), threads, lds_bytes), NUTS_E_DEVICE);
@@ -488,13 +490,18 @@ int launch_dense_inst(nuts_target* t, nuts::DevSample sa)
     if (rc) return rc;
     sa.workspace = t->ws_cur;
     sa.slot_bytes = slot;
-    hipLaunchKernelGGL((nuts_dense_kernel<T, kBanded>), dim3((unsigned)blocks), dim3(threads), lds_bytes, g_stream, tg, sa);
+    hipLaunchKernelGGL((nuts_dense_kernel<T, kBanded>), dim3((unsigned)blocks), dim3(threads), lds_bytes, g_stream, tg, sa, rl);
     HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
     t->last_variant = NUTS_VARIANT_DENSE;
     t->last_grid = (int)blocks;
     t->last_slots = blocks * kDenseWaves < sa.n_chains ? blocks * kDenseWaves : sa.n_chains;
     return NUTS_OK;
 }
+    // what the workgroups of a compute unit leave of its LDS holds the shallow levels of the trees
+    const long share = (blocks + cus - 1) / cus;
+    const size_t budget = (size_t)(kLdsBytes / share) / kLdsGranule * kLdsGranule;
+    const RowLds rl = row_lds_split(budget > lds_bytes ? (budget - lds_bytes) / kDenseWaves : 0, 1, sizeof(T), sa.max_depth);
+    lds_bytes += (size_t)kDenseWaves * (rl.n_first + rl.n_pool) * row_entry_bytes(1, sizeof(T));
 
 template <typename T>
 int launch_dense(nuts_target* t, const nuts::DevSample& sa)

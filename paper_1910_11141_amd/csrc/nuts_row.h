@@ -1,0 +1,467 @@
+// The chain program of the register-resident Gaussian kernels: one chain per wavefront, kC pairs of components per lane.
+//
+// The recursion over the trajectory's tree needs no return stack here.  Leaf m (1-based) of a doubling of 2^j leaves
+// completes the subtrees of levels 1 .. ctz(m), and unless it is the last leaf the subtree it leaves behind is the left
+// half of the one of level ctz(m) + 1: the pair (j, m) says where the program stands, and a leaf or a span that must not
+// be continued ends the whole doubling.  The lanes of a wave agree on it, so every branch is a scalar one.
+//
+// A step of one chain is a serial chain of instructions, and with few chains its latency is all that counts (d = 100
+// banded, 1024 chains, one wave per SIMD: leaf 1315 ticks, merge 1080, left half 480).  What is done about it here:
+//   * the lowest level of the tree stays in registers (an odd leaf is kept until its neighbour has been merged with it),
+//   * the first leaves of the next levels and the pool's first buffers are in LDS as far as it reaches (n_first, n_pool),
+//   * the other end of the trajectory and the proposal are in registers (kHeld),
+//   * the uniforms of the merges of four leaves come from one generator pass.
+// d = 100 banded, 1024 chains, 100 iterations: 15.3 ms (tree storage in global memory, a return stack) -> 10.6 ms.
+#pragma once
+#include "nuts_dev.h"
+#include "nuts_fastmath.h"
+#include "nuts_rng.h"
+
+namespace nuts {
+
+constexpr int kRowMaxDepth = 20;
+
+// Workspace vectors of one slot (128 kC elements each), D = max_tree_depth:
+//   2*b + c                 proposal pool, b <= D, c in {theta, grad}
+//   2*(D+1) + 2*s + c       first-leaf slots, s <= D, c in {theta, r}
+//   4*(D+1) + x             x < 5: the other end (theta, r, grad) and the proposal (theta, grad), unless kHeld
+enum : int { kRowOtherTh = 0, kRowOtherR = 1, kRowOtherG = 2, kRowTop = 3, kRowTopG = 4, kRowRest = 5 };
+__host__ __device__ inline int row_num_vectors(int max_depth) { return 4 * (max_depth + 1) + kRowRest; }
+
+template <typename T>
+struct RowVec;
+template <>
+struct RowVec<float> {
+    typedef float2 type;
+};
+template <>
+struct RowVec<double> {
+    typedef double2 type;
+};
+
+// How much of the tree's storage a slot has in LDS.
+struct RowLds {
+    int n_first;  // first-leaf slots 2 .. n_first + 1
+    int n_pool;   // pool buffers 0 .. n_pool - 1
+};
+inline size_t row_entry_bytes(int kc, size_t elem) { return (size_t)2 * 128 * kc * elem; }  // one slot or buffer
+// Of `bytes` of LDS per slot: the first leaves are read back by every merge, so they come first.
+inline RowLds row_lds_split(size_t bytes, int kc, size_t elem, int max_depth)
+{
+    const int n = (int)(bytes / row_entry_bytes(kc, elem)), most = max_depth > 1 ? max_depth - 1 : 0;
+    RowLds r;
+    r.n_first = n < most ? n : most;
+    r.n_pool = n - r.n_first < max_depth + 1 ? n - r.n_first : max_depth + 1;
+    return r;
+}
+
+template <typename T, int kC, bool kHeld>
+struct RowChain {
+    static constexpr int kVpl = 2 * kC, kPitch = 128 * kC;
+    typedef typename RowVec<T>::type Vec;
+
+    const DevSample& sa;
+    const int lane, d, D;
+    T* const ws;     // this slot's vectors in global memory
+    T* const lds;    // this slot's vectors in LDS: n_first pairs, then n_pool pairs
+    const RowLds rl;
+
+    T th[kVpl], r[kVpl], g[kVpl];        // the end of the trajectory that the current doubling extends
+    T pth[kVpl], pr[kVpl], pg[kVpl];     // the last odd leaf, until the leaf after it has been merged with it
+    T rest[kHeld ? kRowRest : 1][kHeld ? kVpl : 1];
+    static constexpr int kInEdge = -1, kInPrev = -2;  // cur_idx / frame_idx: the proposal is th, or pth
+
+    int j = 0, m = 0, v = 0, nleap = 0, iter = 0;  // v: direction of the end in th (0: both ends are the same point)
+    long chain = 0;
+    uint32_t gchain = 0, free_mask = 0;
+    // Weights of trajectory points are numbers, not logarithms: a leaf weighs exp(H0 - H) / unit (slice sampler: 1 or 0),
+    // a subtree the sum of its leaves, so a merge is an add and a selection one product and a comparison.  log_unit_w is
+    // the logarithm of the unit: 0 until a leaf's energy falls more than 600 below what the unit can represent; then
+    // that leaf becomes the unit and what the iteration holds is rescaled.
+    double H0 = 0, w_tree = 0, cur_w = 0, log_unit_w = 0, edge_logp = 0, prev_logp = 0, top_logp = 0, log_slice = 0;
+    // Random numbers that do not depend on where the trajectory goes, one generator pass for many: lane j < 32 votes the
+    // direction of doubling j into dirbits and lane 32 + j holds the TOP uniform of doubling j (once per iteration);
+    // lane 16 q + l holds the SUBTREE uniform of level u_sub_base + l for the leaf that ends q leaf pairs after leapfrog count
+    // u_sub_leaf: only every second leaf can complete a merge.
+    double u_top = 0, u_sub = 0;
+    uint32_t dirbits = 0;
+    int u_sub_leaf = 0, u_sub_base = 0;
+    int cur_s = 0, cur_idx = kInEdge;
+    double frame_w = 0, pool_logp = 0;  // lane k: level k / pool buffer k
+    int frame_idx = 0;
+    unsigned long long n_leaf = 0, n_extra = 0;
+
+    __device__ RowChain(const DevSample& sa_, int d_, int lane_, T* ws_, T* lds_, RowLds rl_)
+        : sa(sa_), lane(lane_), d(d_), D(sa_.max_depth), ws(ws_), lds(lds_), rl(rl_) {}
+
+    __device__ int elem(int q, int e) const { return (q * kWave + lane) * 2 + e; }  // component of register 2q + e
+    __device__ DrawKey key() const { return DrawKey{sa.key0, sa.key1}; }
+
+    __device__ __forceinline__ void load(const T* src, T (&dst)[kVpl]) const
+    {
+#pragma unroll
+        for (int q = 0; q < kC; ++q) {
+            const Vec x = *reinterpret_cast<const Vec*>(src + elem(q, 0));
+            dst[2 * q] = x.x;
+            dst[2 * q + 1] = x.y;
+        }
+    }
+    __device__ __forceinline__ void store(T* dst, const T (&src)[kVpl]) const
+    {
+#pragma unroll
+        for (int q = 0; q < kC; ++q) *reinterpret_cast<Vec*>(dst + elem(q, 0)) = Vec{src[2 * q], src[2 * q + 1]};
+    }
+    __device__ __forceinline__ void copy(T (&dst)[kVpl], const T (&src)[kVpl]) const
+    {
+#pragma unroll
+        for (int i = 0; i < kVpl; ++i) dst[i] = src[i];
+    }
+    // two vectors of a pool buffer or first-leaf slot (LDS and global memory are different instructions: no generic pointer)
+    __device__ __forceinline__ void pair_load(int in_lds, int lds_entry, int vec, T (&a)[kVpl], T (&b)[kVpl]) const
+    {
+        if (in_lds) {
+            load(lds + (size_t)(2 * lds_entry) * kPitch, a);
+            load(lds + (size_t)(2 * lds_entry + 1) * kPitch, b);
+        } else {
+            load(ws + (size_t)vec * kPitch, a);
+            load(ws + (size_t)(vec + 1) * kPitch, b);
+        }
+    }
+    __device__ __forceinline__ void pair_store(int in_lds, int lds_entry, int vec, const T (&a)[kVpl], const T (&b)[kVpl]) const
+    {
+        if (in_lds) {
+            store(lds + (size_t)(2 * lds_entry) * kPitch, a);
+            store(lds + (size_t)(2 * lds_entry + 1) * kPitch, b);
+        } else {
+            store(ws + (size_t)vec * kPitch, a);
+            store(ws + (size_t)(vec + 1) * kPitch, b);
+        }
+    }
+    __device__ __forceinline__ void first_load(int s, T (&a)[kVpl], T (&b)[kVpl]) const
+    {
+        pair_load(s - 2 < rl.n_first, s - 2, 2 * (D + 1) + 2 * s, a, b);
+    }
+    __device__ __forceinline__ void first_store(int s, const T (&a)[kVpl], const T (&b)[kVpl]) const
+    {
+        pair_store(s - 2 < rl.n_first, s - 2, 2 * (D + 1) + 2 * s, a, b);
+    }
+    __device__ __forceinline__ void pool_load(int b, T (&t)[kVpl], T (&gr)[kVpl]) const
+    {
+        pair_load(b < rl.n_pool, rl.n_first + b, 2 * b, t, gr);
+    }
+    __device__ __forceinline__ void pool_store(int b, const T (&t)[kVpl], const T (&gr)[kVpl]) const
+    {
+        pair_store(b < rl.n_pool, rl.n_first + b, 2 * b, t, gr);
+    }
+    __device__ __forceinline__ void rest_load(int x, T (&a)[kVpl]) const
+    {
+        if constexpr (kHeld)
+            copy(a, rest[x]);
+        else
+            load(ws + (size_t)(4 * (D + 1) + x) * kPitch, a);
+    }
+    __device__ __forceinline__ void rest_store(int x, const T (&a)[kVpl])
+    {
+        if constexpr (kHeld)
+            copy(rest[x], a);
+        else
+            store(ws + (size_t)(4 * (D + 1) + x) * kPitch, a);
+    }
+
+    // Standard normals for every component, zero beyond d (components 2k, 2k + 1 share draw k: they are in one lane).
+    __device__ __forceinline__ void draw_normals(uint32_t tag, uint32_t iteration, T (&out)[kVpl]) const
+    {
+#pragma unroll 1
+        for (int q = 0; q < kC; ++q) {  // rolled: once per iteration, must not cost registers
+            double z0 = 0.0, z1 = 0.0;
+            const int i = elem(q, 0);
+            if (i < d) {
+                normal_pair(draw(key(), (uint32_t)(i >> 1), tag, 0, iteration, gchain), z0, z1);
+                if (i + 1 >= d) z1 = 0.0;
+            }
+#pragma unroll
+            for (int p = 0; p < kC; ++p)
+                if (p == q) {
+                    out[2 * p] = (T)z0;
+                    out[2 * p + 1] = (T)z1;
+                }
+        }
+    }
+
+    __device__ uint32_t all_bufs() const { return (1u << (D + 1)) - 1u; }
+    // The current proposal gets a pool buffer, unless it has one.
+    __device__ __forceinline__ void materialise_cur()
+    {
+        if (cur_idx >= 0) return;
+        const int b = __ffs(free_mask) - 1;
+        free_mask &= ~(1u << b);
+        if (cur_idx == kInPrev) {
+            pool_store(b, pth, pg);
+            if (lane == b) pool_logp = prev_logp;
+        } else {
+            pool_store(b, th, g);
+            if (lane == b) pool_logp = edge_logp;
+        }
+        cur_idx = b;
+    }
+
+    // (theta+ - theta-) . r at both ends of the span between the extended end and (xt, xr)
+    __device__ __forceinline__ bool no_uturn(const T (&xt)[kVpl], const T (&xr)[kVpl]) const
+    {
+        double da = 0.0, db = 0.0;
+#pragma unroll
+        for (int i = 0; i < kVpl; ++i) {
+            const T delta = v > 0 ? th[i] - xt[i] : xt[i] - th[i];
+            da = fma((double)delta, (double)xr[i], da);
+            db = fma((double)delta, (double)r[i], db);
+        }
+        wave_sum2(da, db);
+        return (da >= 0.0) && (db >= 0.0);
+    }
+
+    // Takes the next chain from the queue; false if there is none.  Its starting point is in th, and the caller owes
+    // start_chain() that point's gradient.
+    __device__ bool fetch()
+    {
+        unsigned long long c = 0;
+        if (lane == 0) c = atomicAdd(&sa.counters[kCtrQueue], 1ull);
+        const unsigned lo = (unsigned)uni((int)(unsigned)c), hi = (unsigned)uni((int)(unsigned)(c >> 32));
+        c = ((unsigned long long)hi << 32) | lo;
+        if ((long)c >= sa.n_chains) return false;
+        chain = (long)c;
+        gchain = (uint32_t)(sa.first_chain + chain);
+        iter = sa.iter_begin;
+        if (sa.init_states) {
+            const T* src = (const T*)sa.init_states + (size_t)chain * d;
+#pragma unroll
+            for (int q = 0; q < kC; ++q)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) th[2 * q + e] = elem(q, e) < d ? src[elem(q, e)] : T(0);
+        } else {
+            draw_normals(kDrawInit, 0, th);
+        }
+        return true;
+    }
+    __device__ void start_chain(double lp)  // lp: this lane's share of theta . grad
+    {
+        rest_store(kRowTop, th);
+        rest_store(kRowTopG, g);
+        top_logp = 0.5 * wave_sum(lp);
+        n_extra += 1;
+    }
+
+    __device__ void iter_begin()
+    {
+        rest_load(kRowTop, th);
+        rest_load(kRowTopG, g);
+        draw_normals(kDrawMomentum, (uint32_t)iter, r);
+        double kin = 0.0;
+#pragma unroll
+        for (int i = 0; i < kVpl; ++i) kin = fma((double)r[i], (double)r[i], kin);
+        rest_store(kRowOtherTh, th);  // both ends of the trajectory start at the current point
+        rest_store(kRowOtherR, r);
+        rest_store(kRowOtherG, g);
+        v = 0;
+        H0 = -top_logp + 0.5 * wave_sum(kin);
+        w_tree = 1.0;  // the starting point: weight exp(0), or the first candidate
+        log_unit_w = 0.0;
+        if (sa.sampler == kSamplerSlice) {
+            const Words4 w = draw(key(), 0, kDrawSlice, 0, (uint32_t)iter, gchain);
+            log_slice = log(uniform52(w.w0, w.w1));
+        }
+        const Words4 wj = draw(key(), (uint32_t)(lane & 31), (lane & 32) ? kDrawTop : kDrawDirection, 0, (uint32_t)iter, gchain);
+        dirbits = (uint32_t)__ballot(wj.w0 >> 31);
+        u_top = uniform52(wj.w0, wj.w1);
+        u_sub_leaf = kNoLeaf;
+        j = 0;
+        nleap = 0;
+    }
+
+    __device__ void double_begin()
+    {
+        const int dir = ((dirbits >> j) & 1u) ? 1 : -1;
+        if (v == -dir) {  // the doubling turns round: the two ends change places
+            T xt[kVpl], xr[kVpl], xg[kVpl];
+            rest_load(kRowOtherTh, xt);
+            rest_load(kRowOtherR, xr);
+            rest_load(kRowOtherG, xg);
+            rest_store(kRowOtherTh, th);
+            rest_store(kRowOtherR, r);
+            rest_store(kRowOtherG, g);
+            copy(th, xt);
+            copy(r, xr);
+            copy(g, xg);
+        }
+        v = dir;
+        m = 0;
+        free_mask = all_bufs();  // nothing of the last doubling stays in the pool
+    }
+
+    // Half-kick and drift up to the position whose gradient is wanted, and the kick after it.
+    __device__ __forceinline__ void kick_drift()
+    {
+        const T half = (T)(0.5 * (v * sa.eps)), full = (T)(v * sa.eps);
+#pragma unroll
+        for (int i = 0; i < kVpl; ++i) {
+            r[i] = r[i] + half * g[i];
+            th[i] = th[i] + full * r[i];
+        }
+    }
+    __device__ __forceinline__ void kick()
+    {
+        const T half = (T)(0.5 * (v * sa.eps));
+#pragma unroll
+        for (int i = 0; i < kVpl; ++i) r[i] = r[i] + half * g[i];
+    }
+
+    // One subtree's halves become one: weights added, proposal selected, U-turn test over its span.
+    __device__ __forceinline__ void merge(int level)
+    {
+        T xt[kVpl], xr[kVpl];
+        if (level > 1) {
+            // the subtree's first leaf is asked for before anything else: the latency runs under the random draw
+            // and the weight arithmetic below
+            const int f = m - (1 << level) + 1;  // first leaf of this subtree, 1-based
+            first_load((f == 1) ? j : min(__ffs(f - 1) - 1, j), xt, xr);
+        }
+        const double l_w = read_lane(frame_w, level);
+        const int l_idx = __builtin_amdgcn_readlane(frame_idx, level);
+        const int gap = 2 * sa.leaf_steps;
+        int ahead = nleap - u_sub_leaf;
+        if ((ahead != 0 && ahead != gap && ahead != 2 * gap && ahead != 3 * gap) || (level & 16) != u_sub_base) {
+            u_sub_base = level & 16;
+            const Words4 w = draw(key(), (uint32_t)(nleap + (lane >> 4) * gap), kDrawSubtree, (uint32_t)(u_sub_base + (lane & 15)),
+                                  (uint32_t)iter, gchain);
+            u_sub = uniform52(w.w0, w.w1);
+            u_sub_leaf = nleap;
+            ahead = 0;
+        }
+        const int q = ahead == 0 ? 0 : (ahead == gap ? 1 : (ahead == 2 * gap ? 2 : 3));
+        const double u = read_lane(u_sub, uni((level & 15) + 16 * q));
+        // right with probability w_R / (w_L + w_R) (never when both are zero)
+        const double w_new = l_w + cur_w;
+        if (u * w_new < cur_w) {
+            if (l_idx >= 0) free_mask |= (1u << l_idx);
+        } else {
+            if (cur_idx >= 0) free_mask |= (1u << cur_idx);
+            cur_idx = l_idx;
+        }
+        cur_w = w_new;
+        cur_s = level > 1 ? no_uturn(xt, xr) : no_uturn(pth, pr);
+    }
+
+    // What follows a leaf's last leapfrog step (lp: this lane's share of theta . grad): its weight, then every merge it
+    // completes.  True if the doubling wants another leaf.
+    __device__ __forceinline__ bool finish_leaf(double lp)
+    {
+        double kin = 0.0;
+#pragma unroll
+        for (int i = 0; i < kVpl; ++i) kin = fma((double)r[i], (double)r[i], kin);
+        wave_sum2(lp, kin);
+        edge_logp = 0.5 * lp;
+        m += 1;
+        nleap += sa.leaf_steps;
+        n_leaf += sa.leaf_steps;
+        double delta = (-edge_logp + 0.5 * kin) - H0;
+        if (!(fabs(delta) < INFINITY)) delta = INFINITY;
+        if (sa.sampler == kSamplerSlice) {
+            cur_w = (log_slice <= -delta) ? 1.0 : 0.0;
+            cur_s = (log_slice < kDeltaMax - delta);
+        } else {
+            double e = log_unit_w - delta;  // logarithm of the leaf's weight in the current unit
+            if (e > 600.0) {  // the energy has fallen far: this leaf becomes the unit
+                const double shrink = exp_bounded(-e);
+                w_tree *= shrink;
+                frame_w *= shrink;
+                log_unit_w = delta;
+                e = 0.0;
+            }
+            cur_w = exp_bounded(e);
+            cur_s = (delta <= kDeltaMax);
+        }
+        cur_idx = kInEdge;
+        if (!cur_s) return false;
+        const int n_done = __ffs(m) - 1;  // levels that this leaf completes
+        if (n_done == 0) {
+            if (j == 0) return false;
+            // the left half of a two-leaf subtree stays in registers; larger subtrees that it opens share one copy
+            copy(pth, th);
+            copy(pr, r);
+            copy(pg, g);
+            prev_logp = edge_logp;
+            cur_idx = kInPrev;
+            const int s = (m == 1) ? j : min(__ffs(m - 1) - 1, j);
+            if (s >= 2) first_store(s, th, r);
+        } else {
+            for (int level = 1; level <= n_done; ++level) {
+                merge(uni(level));
+                if (!cur_s) return false;
+            }
+            if (n_done == j) return false;
+            materialise_cur();
+        }
+        if (lane == n_done + 1) {
+            frame_w = cur_w;
+            frame_idx = cur_idx;
+        }
+        return true;
+    }
+
+    // The end of a doubling; true if another one follows.
+    __device__ bool double_end()
+    {
+        bool go_on = false;
+        if (cur_s) {
+            const double u = read_lane(u_top, uni(32 + j));
+            if (u * w_tree < cur_w) {  // accept the new half with probability min(1, w_new / w_tree)
+                if (cur_idx == kInEdge) {
+                    rest_store(kRowTop, th);
+                    rest_store(kRowTopG, g);
+                    top_logp = edge_logp;
+                } else if (cur_idx == kInPrev) {
+                    rest_store(kRowTop, pth);
+                    rest_store(kRowTopG, pg);
+                    top_logp = prev_logp;
+                } else {
+                    T t[kVpl], gr[kVpl];
+                    pool_load(cur_idx, t, gr);
+                    rest_store(kRowTop, t);
+                    rest_store(kRowTopG, gr);
+                    top_logp = read_lane(pool_logp, uni(cur_idx));
+                }
+            }
+            w_tree += cur_w;
+            T xt[kVpl], xr[kVpl];
+            rest_load(kRowOtherTh, xt);
+            rest_load(kRowOtherR, xr);
+            go_on = no_uturn(xt, xr);
+        }
+        // (an invalid new half ends the iteration: the tree's weight is not needed any more)
+        j += 1;
+        return go_on && j < D;
+    }
+
+    // Emits the iteration's outputs; true if another iteration follows.
+    __device__ bool iter_end()
+    {
+        const size_t row = (size_t)iter * (size_t)sa.n_chains + (size_t)chain;
+        if (sa.out_states) {
+            T x[kVpl];
+            rest_load(kRowTop, x);
+            T* dst = (T*)sa.out_states + row * d;
+#pragma unroll
+            for (int q = 0; q < kC; ++q)
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+                    if (elem(q, e) < d) dst[elem(q, e)] = x[2 * q + e];
+        }
+        if (lane == 0) {
+            if (sa.out_depths) sa.out_depths[row] = j;
+            if (sa.out_nleap) sa.out_nleap[row] = nleap;
+        }
+        iter += 1;
+        return iter < sa.iter_end;
+    }
+};
+
+}  // namespace nuts
