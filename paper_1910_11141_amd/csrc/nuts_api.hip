@@ -82,7 +82,7 @@ struct nuts_target {
     // device copies
     void* dPT = nullptr;
     void* dFtab = nullptr;  // table of the logistic function for the weight merges of the register kernels
-    void* dBand = nullptr;  // banded precision matrices of dim <= kBandRows: the band, see DevTarget::band
+    void* dBand = nullptr;  // banded precision matrices: the band, see DevTarget::band
     void* dInvVar = nullptr;
     void* dX = nullptr;
     void* dXT = nullptr;
@@ -144,9 +144,9 @@ int build_device_data(nuts_target* t, const nuts_target_desc* desc)
         for (int64_t i = 0; i < d; ++i)
             for (int64_t k = 0; k < d; ++k)
                 if (P[(size_t)i * d + k] != (T)0 && std::llabs(i - k) > half) half = std::llabs(i - k);
-        if (half <= nuts::kBandHalf && d <= nuts::kBandRows) {
+        if (half <= nuts::kBandHalf) {
             const int w = 2 * nuts::kBandHalf + 1;
-            std::vector<T> band((size_t)nuts::kBandRows * w, (T)0);
+            std::vector<T> band((size_t)std::max<int64_t>(d, nuts::kBandRows) * w, (T)0);
             for (int64_t i = 0; i < d; ++i)
                 for (int64_t k = std::max<int64_t>(0, i - nuts::kBandHalf); k <= std::min<int64_t>(d - 1, i + nuts::kBandHalf); ++k)
                     band[(size_t)i * w + (size_t)(k - i + nuts::kBandHalf)] = P[(size_t)i * d + k];

@@ -23,7 +23,7 @@ struct DevTarget {
     long n;           // data rows
     const T* PT;      // dense Gaussian: transpose of the precision, [k][i]
     const T* band;    // dense Gaussian whose precision is banded (|i - k| <= kBandHalf): [row][k - i + kBandHalf],
-                      // kBandRows rows, zero outside the matrix; NULL otherwise
+                      // max(d, kBandRows) rows, zero outside the matrix; NULL otherwise
     const T* inv_var; // diagonal Gaussian: 1/sigma_i^2
     const T* X;       // logistic regression: [n][d]
     const T* XT;      // logistic regression: [d][n]
