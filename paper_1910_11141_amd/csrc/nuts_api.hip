@@ -16,6 +16,7 @@
 
 #include "../../include/nuts.h"
 #include "nuts_dev.h"
+#include "nuts_block.h"
 #include "nuts_dense.h"
 #include "nuts_elem.h"
 #include "nuts_grid.h"
@@ -44,10 +45,10 @@ int fail(int code, const char* fmt, ...)
         if (e_ != hipSuccess) return fail((code), "%s failed: %s", #expr, hipGetErrorString(e_)); \
     } while (0)
 
-size_t elem_size(int dtype) { return dtype == NUTS_F64 ? sizeof(double) : sizeof(float); }
 constexpr int kLdsBytes = 160 * 1024;  // of a compute unit,
 constexpr int kLdsGranule = 1280;      // handed out in pieces of this size
 
+size_t elem_size(int dtype) { return dtype == NUTS_F64 ? sizeof(double) : sizeof(float); }
 
 // Scratch memory of nuts_sample_static: one array per GPU, part of the loaded code object, never
 // allocated or freed.  The first kStaticHeader bytes hold the call's counters, the rest its workspace.
@@ -90,6 +91,7 @@ struct nuts_target {
     nuts::TileData tile;  // operand-order copies of X for the tile and wide kernels (logistic regression)
     nuts::GridData grid;  // operand-order copy of X for the grid kernels (binary32 logistic regression)
     nuts::QuadData quad;  // operand-order copy of P for the quad kernel (binary64 dense Gaussian, dim <= 128)
+    nuts::BlockData block;  // operand-order copy of P for the block kernel (dense Gaussian, 128 < dim <= 512, not banded)
     // per-call scratch, grown on demand and kept
     char* workspace = nullptr;
     size_t workspace_bytes = 0;
@@ -166,6 +168,14 @@ int build_device_data(nuts_target* t, const nuts_target_desc* desc)
             int rc = upload(op, &dev);
             if (rc) return rc;
             t->quad.ops = static_cast<double*>(dev);
+        }
+        if (d > nuts::kDenseMaxDim && d <= nuts::kBlockMaxDim && !t->dBand) {
+            std::vector<double> op;
+            nuts::block_pack_operands(P, d, &t->block, &op);
+            void* dev = nullptr;
+            int rc = upload(op, &dev);
+            if (rc) return rc;
+            t->block.ops = static_cast<double*>(dev);
         }
         return upload(PT, &t->dPT);
     }
@@ -268,6 +278,7 @@ void release(nuts_target* t)
         (void)hipFree(t->tile.base);
         (void)hipFree(t->grid.ops);
         (void)hipFree(t->quad.ops);
+        (void)hipFree(t->block.ops);
         (void)hipFree(t->tile.ftab);
         (void)hipFree(t->tile.colsum);
         (void)hipFree(t->workspace);
@@ -486,6 +497,11 @@ int launch_dense_inst(nuts_target* t, nuts::DevSample sa)
     long blocks = (sa.n_chains + kDenseWaves - 1) / kDenseWaves;
     const long resident = (long)per_cu * cus;
     if (blocks > resident) blocks = resident;
+    // what the workgroups of a compute unit leave of its LDS holds the shallow levels of the trees
+    const long share = (blocks + cus - 1) / cus;
+    const size_t budget = (size_t)(kLdsBytes / share) / kLdsGranule * kLdsGranule;
+    const RowLds rl = row_lds_split(budget > lds_bytes ? (budget - lds_bytes) / kDenseWaves : 0, 1, sizeof(T), sa.max_depth);
+    lds_bytes += (size_t)kDenseWaves * (rl.n_first + rl.n_pool) * row_entry_bytes(1, sizeof(T));
     int rc = ensure_workspace(t, slot * (size_t)blocks * kDenseWaves);
     if (rc) return rc;
     sa.workspace = t->ws_cur;
@@ -497,16 +513,38 @@ int launch_dense_inst(nuts_target* t, nuts::DevSample sa)
     t->last_slots = blocks * kDenseWaves < sa.n_chains ? blocks * kDenseWaves : sa.n_chains;
     return NUTS_OK;
 }
-    // what the workgroups of a compute unit leave of its LDS holds the shallow levels of the trees
-    const long share = (blocks + cus - 1) / cus;
-    const size_t budget = (size_t)(kLdsBytes / share) / kLdsGranule * kLdsGranule;
-    const RowLds rl = row_lds_split(budget > lds_bytes ? (budget - lds_bytes) / kDenseWaves : 0, 1, sizeof(T), sa.max_depth);
-    lds_bytes += (size_t)kDenseWaves * (rl.n_first + rl.n_pool) * row_entry_bytes(1, sizeof(T));
 
 template <typename T>
 int launch_dense(nuts_target* t, const nuts::DevSample& sa)
 {
     return t->dBand ? launch_dense_inst<T, true>(t, sa) : launch_dense_inst<T, false>(t, sa);
+}
+
+// Chosen automatically only; one wavefront per chain, so it is reported as the wave variant that it stands in for.
+bool block_eligible(const nuts_target* t) { return t->kind == NUTS_TARGET_GAUSS_DENSE_PRECISION && t->block.ops != nullptr; }
+
+template <typename T>
+int launch_block(nuts_target* t, nuts::DevSample sa)
+{
+    int cus = 0;
+    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device), NUTS_E_DEVICE);
+    nuts::BlockPlan bp;
+    const int nc = nuts::block_chains_per_group((int)t->dim, sa.n_chains, cus);
+    nuts::block_plan(t->block, sizeof(T), sa.n_chains, cus, sa.max_depth, nc, &bp);
+    const size_t group_bytes = bp.slot_bytes * (size_t)bp.nc;
+    if (t->static_call) {  // the scratch array is what it is: fewer workgroups rather than a refusal
+        const long fit = (long)(((size_t)NUTS_STATIC_SCRATCH_BYTES - kStaticHeader) / group_bytes);
+        if (fit >= 1 && bp.blocks > fit) bp.blocks = (int)fit;
+    }
+    int rc = ensure_workspace(t, group_bytes * (size_t)bp.blocks);
+    if (rc) return rc;
+    sa.workspace = t->ws_cur;
+    sa.slot_bytes = bp.slot_bytes;
+    HIP_TRY(nuts::block_launch<T>(t->block, sa, bp, g_stream), NUTS_E_DEVICE);
+    t->last_variant = NUTS_VARIANT_WAVE;
+    t->last_grid = bp.blocks;
+    t->last_slots = 0;
+    return NUTS_OK;
 }
 
 bool quad_eligible(const nuts_target* t, int max_depth)
@@ -896,6 +934,8 @@ int sample_impl(const nuts_target* target, int64_t n_chains, int64_t n_iters, do
                            n_chains >= nuts::kQuadAutoChains);
     const bool use_dense = !use_quad && (opt.variant == NUTS_VARIANT_DENSE || (opt.variant == NUTS_VARIANT_AUTO && dense_eligible(t)));
 
+    const bool use_block = opt.variant == NUTS_VARIANT_AUTO && block_eligible(t);
+
     int rc = NUTS_OK;
     if (use_static) {
         // nothing below may allocate: the target must already hold its device data, counters and events
@@ -943,6 +983,8 @@ int sample_impl(const nuts_target* target, int64_t n_chains, int64_t n_iters, do
             r = launch_quad(t, s);
         else if (use_dense)
             r = t->dtype == NUTS_F64 ? launch_dense<double>(t, s) : launch_dense<float>(t, s);
+        else if (use_block)
+            r = t->dtype == NUTS_F64 ? launch_block<double>(t, s) : launch_block<float>(t, s);
         else if (use_tile)
             r = launch_tile(t, s);
         else if (use_grid)

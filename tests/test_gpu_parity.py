@@ -1232,3 +1232,67 @@ def test_tile_kernel_four_chain_form_deep_trees_divergences_and_options(n_chains
     few = gpu_run(w, tgt=tgt, n_iters=3)
     for k in range(3):
         assert np.array_equal(wide[k][:, :n_chains], few[k])
+
+
+# ------------------------------------------------------------------ block kernel (dense Gaussian, 128 < d <= 512, matrix streamed from L2)
+
+# dimensions at the edges of the row groups of 16, of the quarters of 32 columns (odd and even counts of column pairs per
+# quarter) and of the components per lane; chain counts with idle slots and with more chains than a workgroup takes
+@pytest.mark.parametrize("dim,dtype,n_chains", [(129, np.float64, 1), (144, np.float64, 5), (159, np.float32, 9), (161, np.float64, 4),
+                                                (255, np.float64, 6), (256, np.float32, 3), (257, np.float64, 5), (320, np.float32, 5),
+                                                (384, np.float64, 3), (385, np.float64, 3), (512, np.float32, 2), (512, np.float64, 2)])
+def test_block_kernel_ragged_dimensions_and_chain_counts(dim, dtype, n_chains):
+    P = W.random_spd_precision(dim, 3).astype(dtype)
+    w = W.Workload(f"block_d{dim}", W.GAUSS_DENSE, dim, np.dtype(dtype), n_chains, 5, 0.2, 7, seed=6 + dim, precision=P)
+    tgt = gpu_target(w)
+    g, r = gpu_run(w, tgt=tgt), ref_run(w)
+    assert g[3]["leaf_slots_useful"] == g[2].sum() and g[3]["extra_grad_evals"] == n_chains
+    assert g[3]["rounds"] < g[3]["leaf_slots_useful"] or n_chains == 1         # chains share rounds
+    check = (lambda a, b, label: assert_parity(a, b, F64_TOL, label=label)) if dtype is np.float64 else (lambda a, b, label: f32_parity(a, b))
+    check(g, r, w.name)
+    kw = dict(sampler=SLICE, leaf_steps=3, schedule=1)
+    check(gpu_run(w, tgt=tgt, **kw), ref_run(w, sampler=SLICE, leaf_steps=3), f"{w.name} slice")
+
+
+@pytest.mark.parametrize("dim,dtype", [(130, np.float64), (250, np.float32), (300, np.float64)])
+def test_block_kernel_both_forms_give_the_same_bits_and_chains_are_independent(dim, dtype):
+    w = W.Workload(f"block_many_d{dim}", W.GAUSS_DENSE, dim, np.dtype(dtype), 2500, 2, 0.2, 6, seed=3,
+                   precision=W.random_spd_precision(dim, 5).astype(dtype))
+    tgt = gpu_target(w)
+    many = gpu_run(w, tgt=tgt)                                  # eight chains per workgroup, some from the queue
+    few = gpu_run(w, tgt=tgt, n_chains=9, first_chain=2045)      # four
+    again = gpu_run(w, tgt=tgt)
+    for k in range(3):
+        assert np.array_equal(many[k][:, 2045:2054], few[k]) and np.array_equal(many[k], again[k])
+
+
+def test_block_kernel_deep_trees_divergences_and_nonfinite_starts():
+    w = W.Workload("block_far", W.GAUSS_DENSE, 140, np.dtype(np.float64), 12, 6, 0.9, 6, seed=4,
+                   precision=W.random_spd_precision(140, 3))
+    init = np.random.default_rng(3).standard_normal((12, 140)) * 10
+    init[3] = 1e200
+    init[7] = np.inf
+    g, r = gpu_run(w, init=init), ref_run(w, init=init)
+    assert np.array_equal(np.isfinite(g[0]), np.isfinite(r[0]))
+    assert np.array_equal(g[1], r[1]) and np.array_equal(g[2], r[2])
+    fin = np.isfinite(r[0]).all(axis=(0, 2))
+    assert state_error(g[0][:, fin], r[0][:, fin]) < F64_TOL
+    w.step_size, w.max_tree_depth, w.n_iters, w.n_chains = 0.004, 10, 2, 3    # deep trees: levels beyond those in LDS
+    assert_parity(gpu_run(w), ref_run(w), F64_TOL, label="block kernel, deep trees")
+
+
+@pytest.mark.parametrize("dim,dtype", [(129, np.float64), (200, np.float32), (513, np.float64)])
+def test_banded_precision_beyond_the_register_kernel(dim, dtype):
+    """The wave kernel takes nine entries of each row of a banded matrix; one entry off the band and it takes them all."""
+    P = W.ar1_precision(dim, 0.8)
+    P[5, 1] = P[1, 5] = 0.05
+    w = W.Workload(f"band_d{dim}", W.GAUSS_DENSE, dim, np.dtype(dtype), 5, 3, 0.1, 6, seed=8, precision=P.astype(dtype))
+    off = P.copy()
+    off[9, 3] = off[3, 9] = 1e-300 if dtype is np.float64 else 1e-38
+    check = (lambda a, b: assert_parity(a, b, F64_TOL, label=w.name)) if dtype is np.float64 else f32_parity
+    g = gpu_run(w)
+    check(g, ref_run(w))
+    w.precision = off.astype(dtype)
+    full = gpu_run(w, variant=N().NUTS_VARIANT_WAVE)
+    for k in range(3):
+        assert np.array_equal(g[k], full[k])
