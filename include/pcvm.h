@@ -84,7 +84,7 @@ typedef struct {
 /* Run `batch` executions to completion (synchronous: returns when the outputs are written).
  *   inputs   DEVICE, int64 [n_inputs][batch]
  *   outputs  DEVICE, int64 [batch]
- *   stack_depth  entries per stack, 1 .. PCVM_MAX_DEPTH; the call allocates (n_vars * 8 + 4) * stack_depth
+ *   stack_depth  entries per stack, 1 .. PCVM_MAX_DEPTH; the call allocates up to (n_vars * 8 + 4) * stack_depth
  *            bytes per member of device memory and frees it before returning
  *   max_steps    per-group bound on scheduler steps (> 0): a program that does not halt ends with STEP_LIMIT
  *   trace    DEVICE int32 [2 * trace_capacity] or NULL: (block, number of active members) of the first

@@ -164,3 +164,54 @@ def test_queued_limits_are_reported_and_other_members_finish():
     assert e.value.code == pcvm.PCVM_E_STEP_LIMIT
     out, _, _ = gpu(P, [3, 4] * 100, 6, queued=True)
     assert list(out) == [3, 5] * 100
+
+
+# ------------------------------------------------------------------ programs on either side of 64 operations and blocks
+
+def long_program(n_ops, n_blocks):
+    """n_blocks blocks that share n_ops operations: every function, pushes and pops of two variables, a loop over n."""
+    b = PP._Builder("long", ["n", "x", "y", "c"], 1, "x")
+    body = [PP.update("x", PP.ADDI, "x", imm=7), PP.push("y", PP.MUL, "x", "n"), PP.update("y", PP.SUB, "y", "x"),
+            PP.push("x", PP.MOD, "y", "x"), PP.update("c", PP.LT, "x", "y"), PP.update("x", PP.ADD, "x", "c"),
+            PP.update("c", PP.COPY, "x"), PP.pop("x"), PP.update("x", PP.ANDI, "x", imm=(1 << 40) - 1), PP.update("y", PP.MULI, "y", imm=-3),
+            PP.update("c", PP.SHRI, "y", imm=3), PP.update("x", PP.ADD, "x", "c"), PP.pop("y"), PP.update("x", PP.ADD, "x", "n"), PP.update("c", PP.LE, "x", "y"),
+            PP.update("c", PP.EQ, "c", "n"), PP.update("y", PP.CONST, imm=-(1 << 35))]
+    ops = [body[i % len(body)] for i in range(n_ops - 2)]
+    per = [ops[i * len(ops) // (n_blocks - 2):(i + 1) * len(ops) // (n_blocks - 2)] for i in range(n_blocks - 2)]
+    for i, o in enumerate(per):
+        b.block(f"b{i}", i, o, (PP.JUMP, f"b{i + 1}" if i + 1 < len(per) else "test"))
+    b.block("test", 98, [PP.update("n", PP.ADDI, "n", imm=-1), PP.update("c", PP.LEI, "n", imm=0)], (PP.BRANCH, "c", "done", "b0"))
+    b.block("done", 99, [], (PP.RETURN,))
+    return b.build()
+
+
+@pytest.mark.parametrize("n_ops,n_blocks", [(18, 3), (64, 9), (65, 9), (50, 64), (50, 65), (130, 70)])
+def test_small_and_general_interpreters_match_the_oracle(n_ops, n_blocks):
+    P = long_program(n_ops, n_blocks)
+    assert len(P.ops) == n_ops and len(P.blocks) == n_blocks
+    ins = np.random.default_rng(n_ops).integers(1, 9, size=150)
+    want, st, trace = V.run(P, ins, 40, group=64)
+    out, stats, tr = gpu(P, ins, 40, trace_capacity=len(trace))
+    assert np.array_equal(out, want) and stats["steps"] == st["steps"]
+    assert [tuple(r) for r in tr] == trace
+    for policy in (0, 1):
+        assert np.array_equal(gpu(P, ins, 40, queued=True, policy=policy)[0], want)
+
+
+@pytest.mark.parametrize("depth", [1, 2, 3, 17, 64, 300])
+def test_stack_rings_spill_and_refill_at_any_depth(depth):
+    """Deep recursion through two pushed arguments: every ring length, entries that leave the ring and come back."""
+    P = PP.ackermann()
+    from paper_1910_11141_amd import pcvm
+    ins = np.array([[0, 1, 2, 2, 3] * 30, [3, 4, 3, 0, 3] * 30])
+    try:
+        want = V.run(P, ins, depth)[0]
+    except Exception:
+        with pytest.raises(pcvm.PcvmError) as e:
+            gpu(P, ins, depth)
+        assert e.value.code == pcvm.PCVM_E_STACK_OVERFLOW
+        with pytest.raises(pcvm.PcvmError):
+            gpu(P, ins, depth, queued=True, policy=1)
+        return
+    for kw in (dict(), dict(queued=True), dict(queued=True, policy=1)):
+        assert np.array_equal(gpu(P, ins, depth, **kw)[0], want)
