@@ -57,7 +57,8 @@ enum {
                                AUTO extends the family to dim <= 128 and to binary32 data sets that are too
                                small for the grid kernels, and reports it under this number                 */
     NUTS_VARIANT_ELEM = 3,  /* one wavefront per chain with the moving trajectory end held in registers
-                               (standard normal / diagonal Gaussian, dim <= 1024 binary32, <= 512 binary64) */
+                               (standard normal / diagonal Gaussian, dim <= 1024 binary32, <= 512 binary64;
+                               AUTO runs the same kernel up to dim = 2048 and reports it as WAVE there)     */
     NUTS_VARIANT_GRID = 4,  /* every gradient round is a chip-wide binary32 MFMA GEMM over the data rows
                                (logistic regression, binary32, dim <= 128; up to 1024 chains are resident
                                at a time, further chains wait in a queue); this variant returns only when

@@ -82,7 +82,7 @@ struct nuts_target {
     int device = -1;  // -1: no device data (standard normal before its first use)
     // device copies
     void* dPT = nullptr;
-    void* dFtab = nullptr;  // table of the logistic function for the weight merges of the register kernels
+    void* dFtab = nullptr;  // table of the logistic function for the weight merges of the grid kernels
     void* dBand = nullptr;  // banded precision matrices: the band, see DevTarget::band
     void* dInvVar = nullptr;
     void* dX = nullptr;
@@ -153,12 +153,6 @@ int build_device_data(nuts_target* t, const nuts_target_desc* desc)
                 for (int64_t k = std::max<int64_t>(0, i - nuts::kBandHalf); k <= std::min<int64_t>(d - 1, i + nuts::kBandHalf); ++k)
                     band[(size_t)i * w + (size_t)(k - i + nuts::kBandHalf)] = P[(size_t)i * d + k];
             int rc = upload(band, &t->dBand);
-            if (rc) return rc;
-        }
-        if (d <= nuts::kDenseMaxDim) {
-            std::vector<double> ftab;
-            nuts::build_softplus_table(&ftab);
-            int rc = upload(ftab, &t->dFtab);
             if (rc) return rc;
         }
         if (sizeof(T) == sizeof(double) && d <= nuts::kQuadMaxDim) {
@@ -339,8 +333,7 @@ int ensure_workspace(nuts_target* t, size_t bytes)
     return NUTS_OK;
 }
 
-// The logistic table of the weight merges (wave, element-wise, dense and grid kernels).  Built when the
-// target is created if a device is there, else at the first regular launch; never by nuts_sample_static.
+// The logistic table of the grid kernels' weight merges.  Built when the target is created; never by nuts_sample_static.
 int ensure_ftab(nuts_target* t)
 {
     if (t->dFtab) return NUTS_OK;
@@ -430,7 +423,9 @@ int launch_wave(nuts_target* t, nuts::DevSample sa)
     return NUTS_OK;
 }
 
-// Largest dimension the register-resident element-wise kernel takes, per dtype.
+// Largest dimension of the element-wise variant, per dtype.  The kernel itself goes on to kElemMaxDim: AUTO takes it there
+// in place of the wave kernel, as which it is reported (one wavefront per chain, too).
+constexpr int kElemMaxDim = 2048;
 int elem_max_dim(int dtype) { return dtype == NUTS_F64 ? 512 : 1024; }
 
 bool elem_eligible(const nuts_target* t)
@@ -438,39 +433,56 @@ bool elem_eligible(const nuts_target* t)
     return (t->kind == NUTS_TARGET_STD_NORMAL || t->kind == NUTS_TARGET_GAUSS_DIAG) && t->dim <= elem_max_dim(t->dtype);
 }
 
-template <typename T, int kVpl>
-int launch_elem_inst(nuts_target* t, nuts::DevSample sa)
+// LDS for the shallow levels of the trees of one-chain-per-wave workgroups of four: what the `blocks` workgroups leave
+// of each compute unit's LDS beyond `base` bytes each.
+nuts::RowLds row_lds(long blocks, int cus, size_t base, int kc, size_t elem, int max_depth, bool grad)
 {
-    nuts::DevTarget<T> tg = dev_target<T>(t);
-    const int waves_per_block = 4, threads = waves_per_block * nuts::kWave;
-    size_t slot = (size_t)nuts::elem_num_vectors(sa.max_depth) * tg.dstride * sizeof(T);
+    const long share = (blocks + cus - 1) / cus;
+    const size_t budget = (size_t)(kLdsBytes / share) / kLdsGranule * kLdsGranule;
+    return nuts::row_lds_split(budget > base ? (budget - base) / 4 : 0, kc, elem, max_depth, grad);
+}
+
+template <typename T, int kC>
+int launch_elem_inst(nuts_target* t, nuts::DevSample sa, int variant)
+{
+    const nuts::DevTarget<T> tg = dev_target<T>(t);
+    size_t slot = (size_t)nuts::row_num_vectors(sa.max_depth) * 128 * kC * sizeof(T);
     slot = (slot + 255) & ~(size_t)255;
+    const void* fn = reinterpret_cast<const void*>(nuts::nuts_elem_kernel<T, kC>);
+    HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes), NUTS_E_DEVICE);
+    size_t lds_bytes = nuts::elem_lane_bytes<T, kC>() <= 32 ? 0 : 128 * kC * sizeof(T);
     int per_cu = 0, cus = 0;
-    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, nuts::nuts_elem_kernel<T, kVpl>, threads, 0), NUTS_E_DEVICE);
+    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (nuts::nuts_elem_kernel<T, kC>), 256, lds_bytes), NUTS_E_DEVICE);
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device), NUTS_E_DEVICE);
     if (per_cu < 1) per_cu = 1;
-    long blocks = (sa.n_chains + waves_per_block - 1) / waves_per_block;
-    const long resident = (long)per_cu * cus;
-    if (blocks > resident) blocks = resident;
-    int rc = ensure_workspace(t, slot * (size_t)blocks * waves_per_block);
+    long blocks = (sa.n_chains + 3) / 4;
+    if (blocks > (long)per_cu * cus) blocks = (long)per_cu * cus;
+    if (t->static_call) {  // the scratch array is what it is: fewer workgroups rather than a refusal
+        const long fit = (long)(((size_t)NUTS_STATIC_SCRATCH_BYTES - kStaticHeader) / (4 * slot));
+        if (fit >= 1 && blocks > fit) blocks = fit;
+    }
+    const nuts::RowLds rl = row_lds(blocks, cus, lds_bytes, kC, sizeof(T), sa.max_depth, false);
+    lds_bytes += (size_t)4 * (rl.n_first + rl.n_pool) * nuts::row_entry_bytes(kC, sizeof(T));
+    int rc = ensure_workspace(t, slot * (size_t)blocks * 4);
     if (rc) return rc;
     sa.workspace = t->ws_cur;
     sa.slot_bytes = slot;
-    rc = ensure_ftab(t);
-    if (rc) return rc;
-    hipLaunchKernelGGL((nuts::nuts_elem_kernel<T, kVpl>), dim3((unsigned)blocks), dim3(threads), 0, g_stream, tg, sa,
-                       static_cast<const double*>(t->dFtab));
+    hipLaunchKernelGGL((nuts::nuts_elem_kernel<T, kC>), dim3((unsigned)blocks), dim3(256), lds_bytes, g_stream, tg, sa, rl);
     HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
-    t->last_variant = NUTS_VARIANT_ELEM;
+    t->last_variant = variant;
     t->last_grid = (int)blocks;
-    t->last_slots = blocks * waves_per_block < sa.n_chains ? blocks * waves_per_block : sa.n_chains;  // waves that get a chain
+    t->last_slots = blocks * 4 < sa.n_chains ? blocks * 4 : sa.n_chains;  // waves that get a chain
     return NUTS_OK;
 }
 
-int launch_elem(nuts_target* t, const nuts::DevSample& sa)
+template <typename T>
+int launch_elem(nuts_target* t, const nuts::DevSample& sa, int variant)
 {
-    if (t->dtype == NUTS_F64) return t->dim <= 128 ? launch_elem_inst<double, 2>(t, sa) : launch_elem_inst<double, 8>(t, sa);
-    return t->dim <= 256 ? launch_elem_inst<float, 4>(t, sa) : launch_elem_inst<float, 16>(t, sa);
+    if (t->dim <= 128) return launch_elem_inst<T, 1>(t, sa, variant);
+    if (t->dim <= 256) return launch_elem_inst<T, 2>(t, sa, variant);
+    if (t->dim <= 512) return launch_elem_inst<T, 4>(t, sa, variant);
+    if (t->dim <= 1024) return launch_elem_inst<T, 8>(t, sa, variant);
+    return launch_elem_inst<T, 16>(t, sa, variant);
 }
 
 bool dense_eligible(const nuts_target* t)
@@ -497,10 +509,7 @@ int launch_dense_inst(nuts_target* t, nuts::DevSample sa)
     long blocks = (sa.n_chains + kDenseWaves - 1) / kDenseWaves;
     const long resident = (long)per_cu * cus;
     if (blocks > resident) blocks = resident;
-    // what the workgroups of a compute unit leave of its LDS holds the shallow levels of the trees
-    const long share = (blocks + cus - 1) / cus;
-    const size_t budget = (size_t)(kLdsBytes / share) / kLdsGranule * kLdsGranule;
-    const RowLds rl = row_lds_split(budget > lds_bytes ? (budget - lds_bytes) / kDenseWaves : 0, 1, sizeof(T), sa.max_depth);
+    const RowLds rl = row_lds(blocks, cus, lds_bytes, 1, sizeof(T), sa.max_depth, true);
     lds_bytes += (size_t)kDenseWaves * (rl.n_first + rl.n_pool) * row_entry_bytes(1, sizeof(T));
     int rc = ensure_workspace(t, slot * (size_t)blocks * kDenseWaves);
     if (rc) return rc;
@@ -856,7 +865,7 @@ int nuts_create_target(const nuts_target_desc* desc, nuts_target** out)
     if (desc->kind != NUTS_TARGET_STD_NORMAL || have_device) {  // the standard normal has no data: it needs no device yet
         rc = ensure_device(t);
         if (!rc) rc = desc->dtype == NUTS_F64 ? build_device_data<double>(t, desc) : build_device_data<float>(t, desc);
-        if (!rc) rc = ensure_ftab(t);
+        if (!rc && t->grid.ops) rc = ensure_ftab(t);
         if (rc) {
             release(t);
             return rc;
@@ -921,7 +930,10 @@ int sample_impl(const nuts_target* target, int64_t n_chains, int64_t n_iters, do
         return fail(NUTS_E_UNSUPPORTED, "the dense-Gaussian register kernel needs a dense Gaussian target with dim <= %d",
                     nuts::kDenseMaxDim);
 
-    const bool use_elem = opt.variant == NUTS_VARIANT_ELEM || (opt.variant == NUTS_VARIANT_AUTO && elem_eligible(t));
+    const int elem_variant = elem_eligible(t) ? NUTS_VARIANT_ELEM : NUTS_VARIANT_WAVE;
+    const bool use_elem = opt.variant == NUTS_VARIANT_ELEM ||
+                          (opt.variant == NUTS_VARIANT_AUTO && t->dim <= kElemMaxDim &&
+                           (t->kind == NUTS_TARGET_STD_NORMAL || t->kind == NUTS_TARGET_GAUSS_DIAG));
     const bool use_grid = opt.variant == NUTS_VARIANT_GRID ||
                           (opt.variant == NUTS_VARIANT_AUTO && grid_eligible(t) && grid_pays(t->n, t->dim));
     const bool use_tile = opt.variant == NUTS_VARIANT_TILE ||
@@ -990,7 +1002,7 @@ int sample_impl(const nuts_target* target, int64_t n_chains, int64_t n_iters, do
         else if (use_grid)
             r = launch_grid(t, s);
         else if (use_elem)
-            r = launch_elem(t, s);
+            r = t->dtype == NUTS_F64 ? launch_elem<double>(t, s, elem_variant) : launch_elem<float>(t, s, elem_variant);
         else
             r = t->dtype == NUTS_F64 ? launch_wave<double>(t, s) : launch_wave<float>(t, s);
         if (r) return r;

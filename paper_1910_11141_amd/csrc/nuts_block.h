@@ -90,7 +90,7 @@ __global__ __launch_bounds__(kBlockThreads) void nuts_block_kernel(BlockArgs ba,
     };
     T* const tree = reinterpret_cast<T*>(smem + tree_off) + (size_t)grp * (rl.n_first + rl.n_pool) * 2 * 128 * kC;
     const size_t slot = (size_t)blockIdx.x * NC + grp;
-    RowChain<T, kC, (kC <= 2)> ch(sa, ba.d, lane, reinterpret_cast<T*>(sa.workspace + slot * sa.slot_bytes), tree, rl);
+    RowChain<T, kC, (kC <= 2), true> ch(sa, ba.d, lane, reinterpret_cast<T*>(sa.workspace + slot * sa.slot_bytes), tree, rl);
 
     enum { kInit, kLeaf, kDone };
     int state = kDone, sub = 0;
@@ -252,7 +252,7 @@ inline void block_plan(const BlockData& bd, size_t elem, long n_chains, int cus,
     if (blocks > cus) blocks = cus;  // one workgroup per compute unit; further chains wait in the queue
     bp->blocks = (int)blocks;
     const size_t base = block_base_bytes(nc, bd.pq), room = 158 * 1024 - base;  // (2 KB for the static variables)
-    bp->rl = row_lds_split(room / nc, kc, elem, max_depth);
+    bp->rl = row_lds_split(room / nc, kc, elem, max_depth, true);
     bp->tree_off = (int)base;
     bp->lds_bytes = base + (size_t)nc * (bp->rl.n_first + bp->rl.n_pool) * row_entry_bytes(kc, elem);
     bp->slot_bytes = ((size_t)row_num_vectors(max_depth) * 128 * kc * elem + 255) & ~(size_t)255;

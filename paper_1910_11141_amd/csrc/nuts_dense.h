@@ -120,7 +120,7 @@ __global__ __launch_bounds__(kDenseWaves* kWave, sizeof(T) == 8 && !kBanded ? 1 
     __syncthreads();
     const size_t slot = (size_t)blockIdx.x * kDenseWaves + wave;
     T* tree = mat + dense_base_elems(mat_rows) + (size_t)wave * (rl.n_first + rl.n_pool) * 2 * kDensePitch;
-    RowChain<T, 1, true> ch(sa, tg.d, lane, reinterpret_cast<T*>(sa.workspace + slot * sa.slot_bytes), tree, rl);
+    RowChain<T, 1, true, true> ch(sa, tg.d, lane, reinterpret_cast<T*>(sa.workspace + slot * sa.slot_bytes), tree, rl);
     const DenseGradient<T, kBanded> grad(tg, lane, mat, bcast);
     while (ch.fetch()) {
         ch.start_chain(grad(ch.th, ch.g));

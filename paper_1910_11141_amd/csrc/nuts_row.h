@@ -46,16 +46,18 @@ struct RowLds {
 };
 inline size_t row_entry_bytes(int kc, size_t elem) { return (size_t)2 * 128 * kc * elem; }  // one slot or buffer
 // Of `bytes` of LDS per slot: the first leaves are read back by every merge, so they come first.
-inline RowLds row_lds_split(size_t bytes, int kc, size_t elem, int max_depth)
+// (without gradients pool buffers are written and hardly ever read: they stay in memory)
+inline RowLds row_lds_split(size_t bytes, int kc, size_t elem, int max_depth, bool grad)
 {
     const int n = (int)(bytes / row_entry_bytes(kc, elem)), most = max_depth > 1 ? max_depth - 1 : 0;
     RowLds r;
     r.n_first = n < most ? n : most;
-    r.n_pool = n - r.n_first < max_depth + 1 ? n - r.n_first : max_depth + 1;
+    r.n_pool = !grad ? 0 : n - r.n_first < max_depth + 1 ? n - r.n_first : max_depth + 1;
     return r;
 }
 
-template <typename T, int kC, bool kHeld>
+// kGrad: the gradient belongs to the state (otherwise the kernel recomputes it from the position and g is not touched).
+template <typename T, int kC, bool kHeld, bool kGrad>
 struct RowChain {
     static constexpr int kVpl = 2 * kC, kPitch = 128 * kC;
     typedef typename RowVec<T>::type Vec;
@@ -66,8 +68,8 @@ struct RowChain {
     T* const lds;    // this slot's vectors in LDS: n_first pairs, then n_pool pairs
     const RowLds rl;
 
-    T th[kVpl], r[kVpl], g[kVpl];        // the end of the trajectory that the current doubling extends
-    T pth[kVpl], pr[kVpl], pg[kVpl];     // the last odd leaf, until the leaf after it has been merged with it
+    T th[kVpl], r[kVpl], g[kGrad ? kVpl : 1];     // the end of the trajectory that the current doubling extends
+    T pth[kVpl], pr[kVpl], pg[kGrad ? kVpl : 1];  // the last odd leaf, until the leaf after it has been merged with it
     T rest[kHeld ? kRowRest : 1][kHeld ? kVpl : 1];
     static constexpr int kInEdge = -1, kInPrev = -2;  // cur_idx / frame_idx: the proposal is th, or pth
 
@@ -145,13 +147,21 @@ struct RowChain {
     {
         pair_store(s - 2 < rl.n_first, s - 2, 2 * (D + 1) + 2 * s, a, b);
     }
-    __device__ __forceinline__ void pool_load(int b, T (&t)[kVpl], T (&gr)[kVpl]) const
+    template <int kG>
+    __device__ __forceinline__ void pool_load(int b, T (&t)[kVpl], T (&gr)[kG]) const
     {
-        pair_load(b < rl.n_pool, rl.n_first + b, 2 * b, t, gr);
+        if constexpr (kGrad)
+            pair_load(b < rl.n_pool, rl.n_first + b, 2 * b, t, gr);
+        else
+            load(ws + (size_t)(2 * b) * kPitch, t);
     }
-    __device__ __forceinline__ void pool_store(int b, const T (&t)[kVpl], const T (&gr)[kVpl]) const
+    template <int kG>
+    __device__ __forceinline__ void pool_store(int b, const T (&t)[kVpl], const T (&gr)[kG]) const
     {
-        pair_store(b < rl.n_pool, rl.n_first + b, 2 * b, t, gr);
+        if constexpr (kGrad)
+            pair_store(b < rl.n_pool, rl.n_first + b, 2 * b, t, gr);
+        else
+            store(ws + (size_t)(2 * b) * kPitch, t);
     }
     __device__ __forceinline__ void rest_load(int x, T (&a)[kVpl]) const
     {
@@ -245,7 +255,7 @@ struct RowChain {
     __device__ void start_chain(double lp)  // lp: this lane's share of theta . grad
     {
         rest_store(kRowTop, th);
-        rest_store(kRowTopG, g);
+        if constexpr (kGrad) rest_store(kRowTopG, g);
         top_logp = 0.5 * wave_sum(lp);
         n_extra += 1;
     }
@@ -253,14 +263,14 @@ struct RowChain {
     __device__ void iter_begin()
     {
         rest_load(kRowTop, th);
-        rest_load(kRowTopG, g);
+        if constexpr (kGrad) rest_load(kRowTopG, g);
         draw_normals(kDrawMomentum, (uint32_t)iter, r);
         double kin = 0.0;
 #pragma unroll
         for (int i = 0; i < kVpl; ++i) kin = fma((double)r[i], (double)r[i], kin);
         rest_store(kRowOtherTh, th);  // both ends of the trajectory start at the current point
         rest_store(kRowOtherR, r);
-        rest_store(kRowOtherG, g);
+        if constexpr (kGrad) rest_store(kRowOtherG, g);
         v = 0;
         H0 = -top_logp + 0.5 * wave_sum(kin);
         w_tree = 1.0;  // the starting point: weight exp(0), or the first candidate
@@ -281,16 +291,18 @@ struct RowChain {
     {
         const int dir = ((dirbits >> j) & 1u) ? 1 : -1;
         if (v == -dir) {  // the doubling turns round: the two ends change places
-            T xt[kVpl], xr[kVpl], xg[kVpl];
+            T xt[kVpl], xr[kVpl];
             rest_load(kRowOtherTh, xt);
             rest_load(kRowOtherR, xr);
-            rest_load(kRowOtherG, xg);
             rest_store(kRowOtherTh, th);
             rest_store(kRowOtherR, r);
-            rest_store(kRowOtherG, g);
             copy(th, xt);
             copy(r, xr);
-            copy(g, xg);
+            if constexpr (kGrad) {
+                rest_load(kRowOtherG, xt);
+                rest_store(kRowOtherG, g);
+                copy(g, xt);
+            }
         }
         v = dir;
         m = 0;
@@ -387,7 +399,7 @@ struct RowChain {
             // the left half of a two-leaf subtree stays in registers; larger subtrees that it opens share one copy
             copy(pth, th);
             copy(pr, r);
-            copy(pg, g);
+            if constexpr (kGrad) copy(pg, g);
             prev_logp = edge_logp;
             cur_idx = kInPrev;
             const int s = (m == 1) ? j : min(__ffs(m - 1) - 1, j);
@@ -416,17 +428,17 @@ struct RowChain {
             if (u * w_tree < cur_w) {  // accept the new half with probability min(1, w_new / w_tree)
                 if (cur_idx == kInEdge) {
                     rest_store(kRowTop, th);
-                    rest_store(kRowTopG, g);
+                    if constexpr (kGrad) rest_store(kRowTopG, g);
                     top_logp = edge_logp;
                 } else if (cur_idx == kInPrev) {
                     rest_store(kRowTop, pth);
-                    rest_store(kRowTopG, pg);
+                    if constexpr (kGrad) rest_store(kRowTopG, pg);
                     top_logp = prev_logp;
                 } else {
-                    T t[kVpl], gr[kVpl];
+                    T t[kVpl], gr[kGrad ? kVpl : 1];
                     pool_load(cur_idx, t, gr);
                     rest_store(kRowTop, t);
-                    rest_store(kRowTopG, gr);
+                    if constexpr (kGrad) rest_store(kRowTopG, gr);
                     top_logp = read_lane(pool_logp, uni(cur_idx));
                 }
             }

@@ -1296,3 +1296,25 @@ def test_banded_precision_beyond_the_register_kernel(dim, dtype):
     full = gpu_run(w, variant=N().NUTS_VARIANT_WAVE)
     for k in range(3):
         assert np.array_equal(g[k], full[k])
+
+
+# ------------------------------------------------------------------ element-wise targets over the register kernel's whole range
+
+@pytest.mark.parametrize("dim,dtype", [(129, np.float64), (256, np.float32), (513, np.float64), (1024, np.float64), (1025, np.float32),
+                                       (1025, np.float64), (2048, np.float64), (2049, np.float32)])
+def test_elementwise_targets_up_to_and_beyond_the_register_kernel(dim, dtype):
+    """AUTO against the oracle and, bit for bit in the states, against the general wave kernel."""
+    sig = (10.0 ** np.random.default_rng(dim).uniform(-1, 1, dim)).astype(dtype)
+    w = W.Workload(f"elem_d{dim}", W.GAUSS_DIAG, dim, np.dtype(dtype), 6, 3, 0.02, 8, seed=19, scales=sig)
+    g = gpu_run(w)
+    assert g[3]["leaf_slots_useful"] == g[2].sum() and g[2].max() > 32        # deep enough for tree levels outside LDS
+    if dtype is np.float64:
+        assert_parity(g, ref_run(w), F64_TOL, label=w.name)
+    else:
+        f32_parity(g, ref_run(w))
+    general = gpu_run(w, variant=N().NUTS_VARIANT_WAVE)
+    for k in range(3):
+        assert np.array_equal(g[k], general[k])
+    kw = dict(sampler=SLICE, leaf_steps=3, schedule=1)
+    for a, b in zip(gpu_run(w, **kw)[:3], gpu_run(w, variant=N().NUTS_VARIANT_WAVE, **kw)[:3]):
+        assert np.array_equal(a, b)

@@ -170,12 +170,12 @@ def test_queued_limits_are_reported_and_other_members_finish():
 
 def long_program(n_ops, n_blocks):
     """n_blocks blocks that share n_ops operations: every function, pushes and pops of two variables, a loop over n."""
-    b = PP._Builder("long", ["n", "x", "y", "c"], 1, "x")
-    body = [PP.update("x", PP.ADDI, "x", imm=7), PP.push("y", PP.MUL, "x", "n"), PP.update("y", PP.SUB, "y", "x"),
+    b = PP._Builder("long", ["n", "x", "y", "c", "s"], 1, "s")
+    body = [PP.update("x", PP.ADDI, "n", imm=7), PP.update("s", PP.ADD, "s", "x"), PP.push("y", PP.MUL, "x", "n"), PP.update("y", PP.SUB, "y", "x"),
             PP.push("x", PP.MOD, "y", "x"), PP.update("c", PP.LT, "x", "y"), PP.update("x", PP.ADD, "x", "c"),
             PP.update("c", PP.COPY, "x"), PP.pop("x"), PP.update("x", PP.ANDI, "x", imm=(1 << 40) - 1), PP.update("y", PP.MULI, "y", imm=-3),
-            PP.update("c", PP.SHRI, "y", imm=3), PP.update("x", PP.ADD, "x", "c"), PP.pop("y"), PP.update("x", PP.ADD, "x", "n"), PP.update("c", PP.LE, "x", "y"),
-            PP.update("c", PP.EQ, "c", "n"), PP.update("y", PP.CONST, imm=-(1 << 35))]
+            PP.update("c", PP.SHRI, "y", imm=3), PP.update("x", PP.ADD, "x", "c"), PP.pop("y"), PP.update("s", PP.ADD, "s", "c"), PP.update("c", PP.LE, "x", "y"),
+            PP.update("c", PP.EQ, "c", "n"), PP.update("y", PP.CONST, imm=-(1 << 35)), PP.update("s", PP.MULI, "s", imm=31), PP.update("s", PP.SUB, "s", "y")]
     ops = [body[i % len(body)] for i in range(n_ops - 2)]
     per = [ops[i * len(ops) // (n_blocks - 2):(i + 1) * len(ops) // (n_blocks - 2)] for i in range(n_blocks - 2)]
     for i, o in enumerate(per):
