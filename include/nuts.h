@@ -62,9 +62,10 @@ enum {
     NUTS_VARIANT_GRID = 4,  /* every gradient round is a chip-wide binary32 MFMA GEMM over the data rows
                                (logistic regression, binary32, dim <= 128; up to 1024 chains are resident
                                at a time, further chains wait in a queue); this variant returns only when
-                               sampling has finished; beyond 128 chains the resident ones are spread over
-                               up to four streams, the caller's and three that the target owns, forked
-                               from and joined to the caller's stream by events                            */
+                               sampling has finished; beyond 128 chains the resident ones are divided
+                               between two streams, the caller's and one that the target owns, forked
+                               from and joined to the caller's stream by events; chains that want a
+                               gradient are packed together, so idle ones cost nothing beyond 128 columns  */
     NUTS_VARIANT_DENSE = 5, /* one wavefront per chain, moving trajectory end in registers, precision matrix in LDS
                                (dense Gaussian, dim <= 128)                                                 */
     NUTS_VARIANT_QUAD = 6   /* four chains per wavefront, their precision-matrix products together as MFMA blocks

@@ -593,7 +593,7 @@ bool grid_eligible(const nuts_target* t)
 
 // Rounds of (control, gradient) launches, enqueued in batches; the host waits for each batch
 // and stops when every chain has halted, so this variant returns only when sampling is complete.
-// Slots beyond the first 128 form further sets whose rounds run on streams that the target owns.
+// Slots beyond the first 128 may run on a second stream, which the target owns.
 int launch_grid(nuts_target* t, nuts::DevSample sa)
 {
     using namespace nuts;
@@ -602,7 +602,7 @@ int launch_grid(nuts_target* t, nuts::DevSample sa)
     // at most 1024 chains are resident; a slot whose chain has finished takes the next one from the queue
     const int n_slots = sa.n_chains >= kGridMaxChains ? kGridMaxChains : (int)((sa.n_chains + 3) / 4 * 4);
     const int n_sets = (n_slots + kGridSetChains - 1) / kGridSetChains;
-    // consecutive sets share a stream: one control launch serves them all, one gradient launch each
+    // consecutive sets share a stream: one control launch and one gradient launch serve them all
     const int sets_per_stream = (n_sets + kGridMaxStreams - 1) / kGridMaxStreams;
     const int n_streams = (n_sets + sets_per_stream - 1) / sets_per_stream;
     int cus = 0;
@@ -638,7 +638,8 @@ int launch_grid(nuts_target* t, nuts::DevSample sa)
     const size_t o_theta = take((size_t)kGridFeatPad * ga.chain_stride * sizeof(float));
     const size_t o_gpart = take((size_t)ga.n_slices * ga.chain_stride * kGridFeatPad * sizeof(float));
     const size_t o_llpart = take((size_t)ga.n_slices * ga.chain_stride * sizeof(double));
-    const size_t o_active = take((size_t)kGridMaxSets * kGridBatch * sizeof(int));
+    const size_t o_active = take((size_t)kGridMaxStreams * kGridBatch * sizeof(int));
+    const size_t o_column = take((size_t)ga.chain_stride * sizeof(int));
     const size_t o_halted = take((size_t)ga.chain_stride * sizeof(int));
     const size_t o_saved = take((size_t)ga.chain_stride * sizeof(Chain::Saved));
     const size_t o_chain = take(chain_ws * ga.chain_stride);
@@ -649,6 +650,7 @@ int launch_grid(nuts_target* t, nuts::DevSample sa)
     ga.b.g_part = reinterpret_cast<float*>(w + o_gpart);
     ga.b.ll_part = reinterpret_cast<double*>(w + o_llpart);
     ga.b.active_all = reinterpret_cast<int*>(w + o_active);
+    ga.b.column = reinterpret_cast<int*>(w + o_column);
     ga.b.halted = reinterpret_cast<int*>(w + o_halted);
     ga.b.saved = w + o_saved;
     ga.b.chain_ws = w + o_chain;
@@ -659,6 +661,7 @@ int launch_grid(nuts_target* t, nuts::DevSample sa)
     hipStream_t stream[kGridMaxStreams] = {g_stream};
     for (int q = 0; q < n_streams; ++q) {
         span[q] = ga;
+        span[q].stream = q;
         span[q].slot_base = q * sets_per_stream * kGridSetChains;
         const int left = n_slots - span[q].slot_base, full = sets_per_stream * kGridSetChains;
         span[q].n_span_slots = left < full ? left : full;
@@ -693,7 +696,7 @@ int launch_grid(nuts_target* t, nuts::DevSample sa)
     auto enqueue_batch = [&](int b) -> int {
         for (int q = 0; q < n_streams; ++q)
             hipLaunchKernelGGL(nuts_grid_fill_kernel, dim3(1), dim3(64), 0, stream[q],
-                               ga.b.active_all + q * sets_per_stream * kGridBatch, sets_per_stream * kGridBatch, 0);
+                               ga.b.active_all + q * kGridBatch, kGridBatch, 0);
         for (int i = 0; i < kGridBatch; ++i) {
             for (int q = 0; q < n_streams; ++q) {
                 hipLaunchKernelGGL(nuts_grid_control_kernel, dim3((unsigned)span[q].n_span_slots), dim3(256), 0, stream[q], tg, sa,

@@ -1318,3 +1318,23 @@ def test_elementwise_targets_up_to_and_beyond_the_register_kernel(dim, dtype):
     kw = dict(sampler=SLICE, leaf_steps=3, schedule=1)
     for a, b in zip(gpu_run(w, **kw)[:3], gpu_run(w, variant=N().NUTS_VARIANT_WAVE, **kw)[:3]):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("n_chains", [128, 129, 256, 260, 700, 1100])
+def test_grid_kernels_pack_the_chains_that_want_a_gradient(n_chains):
+    """Columns are handed out round by round beyond 128 chains per stream: a chain's results have the same bits in any
+    company, on either schedule, whichever column its gradient was computed in."""
+    B = N()
+    w = W.small_logreg(3000, 9, seed=77, dtype=np.float32)
+    w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = n_chains, 4, 0.02, 7
+    tgt = gpu_target(w)
+    g = gpu_run(w, tgt=tgt, variant=B.NUTS_VARIANT_GRID)
+    assert g[3]["leaf_slots_issued"] >= g[3]["leaf_slots_useful"] + g[3]["extra_grad_evals"]
+    assert len(set(g[2].sum(axis=0))) > 3                       # trajectories of different lengths: idle slots in between
+    sync = gpu_run(w, tgt=tgt, variant=B.NUTS_VARIANT_GRID, schedule=1)
+    few = gpu_run(w, tgt=tgt, variant=B.NUTS_VARIANT_GRID, n_chains=6, first_chain=n_chains - 6)
+    for k in range(3):
+        assert np.array_equal(g[k], sync[k])
+        assert np.array_equal(g[k][:, n_chains - 6:], few[k])
+    pick = np.arange(4)
+    f32_parity([x[:, :4] for x in g[:3]], ref_run(w, chain_ids=pick))
