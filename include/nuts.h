@@ -47,7 +47,8 @@ enum {
     NUTS_VARIANT_WAVE = 1,  /* one wavefront per chain, vectors striped over the 64 lanes; any target/shape.
                                AUTO steps dense Gaussians of 128 < dim <= 512 whose matrix is not banded in
                                lock step, 4 or 8 wavefronts per workgroup with their products on the matrix
-                               cores, and reports that under this number                                    */
+                               cores, and keeps those of banded ones (dim <= 2048) in registers; it reports
+                               both under this number                                                       */
     NUTS_VARIANT_TILE = 2,  /* 16 chains per workgroup in lock step, gradient as MFMA GEMMs (logistic
                                regression, binary64, dim <= 32, max_tree_depth <= 12); when dim = 1 mod 4
                                and a column of X is the same non-zero value in every row (an intercept),

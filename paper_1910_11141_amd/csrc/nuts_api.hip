@@ -16,6 +16,7 @@
 
 #include "../../include/nuts.h"
 #include "nuts_dev.h"
+#include "nuts_band.h"
 #include "nuts_block.h"
 #include "nuts_dense.h"
 #include "nuts_elem.h"
@@ -84,6 +85,8 @@ struct nuts_target {
     void* dPT = nullptr;
     void* dFtab = nullptr;  // table of the logistic function for the weight merges of the grid kernels
     void* dBand = nullptr;  // banded precision matrices: the band, see DevTarget::band
+    void* dDiag = nullptr;  // banded precision matrices of 128 < dim <= kBandMaxDim: the diagonals, see nuts_band_kernel
+    int diag_present = 0;
     void* dInvVar = nullptr;
     void* dX = nullptr;
     void* dXT = nullptr;
@@ -129,6 +132,9 @@ int upload(const std::vector<T>& host, void** dev)
 // 1024 chains).
 bool grid_pays(int64_t n, int64_t d) { return n * d >= (1 << 14); }
 
+// Pairs of components per lane that the one-chain-per-wave kernels are instantiated for.
+int row_chunks(int64_t d) { return d <= 128 ? 1 : d <= 256 ? 2 : d <= 512 ? 4 : d <= 1024 ? 8 : 16; }
+
 template <typename T>
 int build_device_data(nuts_target* t, const nuts_target_desc* desc)
 {
@@ -154,6 +160,17 @@ int build_device_data(nuts_target* t, const nuts_target_desc* desc)
                     band[(size_t)i * w + (size_t)(k - i + nuts::kBandHalf)] = P[(size_t)i * d + k];
             int rc = upload(band, &t->dBand);
             if (rc) return rc;
+            if (d > nuts::kDenseMaxDim && d <= nuts::kBandMaxDim) {
+                const int64_t pitch = 128 * row_chunks(d);
+                std::vector<T> diag((size_t)w * pitch, (T)0);
+                for (int64_t i = 0; i < d; ++i)
+                    for (int k = 0; k < w; ++k) {
+                        diag[(size_t)(k * pitch + i)] = band[(size_t)i * w + k];
+                        if (band[(size_t)i * w + k] != (T)0) t->diag_present |= 1 << k;
+                    }
+                rc = upload(diag, &t->dDiag);
+                if (rc) return rc;
+            }
         }
         if (sizeof(T) == sizeof(double) && d <= nuts::kQuadMaxDim) {
             std::vector<double> op;
@@ -264,6 +281,7 @@ void release(nuts_target* t)
     if (t->device >= 0) {
         (void)hipFree(t->dPT);
         (void)hipFree(t->dBand);
+        (void)hipFree(t->dDiag);
         (void)hipFree(t->dFtab);
         (void)hipFree(t->dInvVar);
         (void)hipFree(t->dX);
@@ -386,41 +404,70 @@ nuts::DevTarget<T> dev_target(const nuts_target* t)
     return g;
 }
 
+// Launch shape of the general wave kernel.
+struct WavePlan {
+    size_t lds_bytes, slot;
+    bool lds_matrix;
+    long blocks;
+};
+constexpr int kWaveBlock = 4;  // waves per workgroup
+
+template <typename T>
+int wave_plan(const nuts_target* t, const nuts::DevSample& sa, WavePlan* wp)
+{
+    const nuts::DevTarget<T> tg = dev_target<T>(t);
+    wp->lds_bytes = (size_t)kWaveBlock * tg.dstride * sizeof(T);
+    if (wp->lds_bytes > 64 * 1024) return fail(NUTS_E_UNSUPPORTED, "dim %lld too large for the wave kernel", (long long)t->dim);
+    const size_t mat_bytes = (size_t)t->dim * t->dim * sizeof(T);
+    wp->lds_matrix = t->kind == NUTS_TARGET_GAUSS_DENSE_PRECISION && wp->lds_bytes + mat_bytes <= 128 * 1024;
+    if (wp->lds_matrix) {
+        wp->lds_bytes += mat_bytes;
+        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(nuts::nuts_wave_kernel<T>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)wp->lds_bytes), NUTS_E_DEVICE);
+    }
+    size_t slot = ((size_t)nuts::wave_num_vectors(sa.max_depth) * tg.dstride * sizeof(T) + 15) & ~(size_t)15;
+    if (t->kind == NUTS_TARGET_LOGISTIC_REGRESSION) slot += (size_t)t->n * sizeof(double);
+    wp->slot = (slot + 255) & ~(size_t)255;
+    int per_cu = 0, cus = 0;
+    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, nuts::nuts_wave_kernel<T>, kWaveBlock * nuts::kWave, wp->lds_bytes),
+            NUTS_E_DEVICE);
+    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device), NUTS_E_DEVICE);
+    if (per_cu < 1) per_cu = 1;
+    wp->blocks = (sa.n_chains + kWaveBlock - 1) / kWaveBlock;
+    const long resident = (long)per_cu * cus;
+    if (wp->blocks > resident) wp->blocks = resident;
+    return NUTS_OK;
+}
+
 template <typename T>
 int launch_wave(nuts_target* t, nuts::DevSample sa)
 {
     nuts::DevTarget<T> tg = dev_target<T>(t);
-    const int waves_per_block = 4, threads = waves_per_block * nuts::kWave;
-    size_t lds_bytes = (size_t)waves_per_block * tg.dstride * sizeof(T);
-    if (lds_bytes > 64 * 1024) return fail(NUTS_E_UNSUPPORTED, "dim %lld too large for the wave kernel", (long long)t->dim);
-    const size_t mat_bytes = (size_t)t->dim * t->dim * sizeof(T);
-    if (t->kind == NUTS_TARGET_GAUSS_DENSE_PRECISION && lds_bytes + mat_bytes <= 128 * 1024) {
-        tg.lds_matrix = 1;
-        lds_bytes += mat_bytes;
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(nuts::nuts_wave_kernel<T>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes), NUTS_E_DEVICE);
-    }
-    size_t slot = ((size_t)nuts::wave_num_vectors(sa.max_depth) * tg.dstride * sizeof(T) + 15) & ~(size_t)15;
-    if (t->kind == NUTS_TARGET_LOGISTIC_REGRESSION) slot += (size_t)t->n * sizeof(double);
-    slot = (slot + 255) & ~(size_t)255;
-    int per_cu = 0, cus = 0;
-    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, nuts::nuts_wave_kernel<T>, threads, lds_bytes),
-            NUTS_E_DEVICE);
-    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device), NUTS_E_DEVICE);
-    if (per_cu < 1) per_cu = 1;
-    long blocks = (sa.n_chains + waves_per_block - 1) / waves_per_block;
-    const long resident = (long)per_cu * cus;
-    if (blocks > resident) blocks = resident;
-    int rc = ensure_workspace(t, slot * (size_t)blocks * waves_per_block);
+    WavePlan wp;
+    int rc = wave_plan<T>(t, sa, &wp);
+    if (rc) return rc;
+    tg.lds_matrix = wp.lds_matrix ? 1 : 0;
+    rc = ensure_workspace(t, wp.slot * (size_t)wp.blocks * kWaveBlock);
     if (rc) return rc;
     sa.workspace = t->ws_cur;
-    sa.slot_bytes = slot;
-    hipLaunchKernelGGL(nuts::nuts_wave_kernel<T>, dim3((unsigned)blocks), dim3(threads), lds_bytes, g_stream, tg, sa);
+    sa.slot_bytes = wp.slot;
+    hipLaunchKernelGGL(nuts::nuts_wave_kernel<T>, dim3((unsigned)wp.blocks), dim3(kWaveBlock * nuts::kWave), wp.lds_bytes, g_stream, tg, sa);
     HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
     t->last_variant = NUTS_VARIANT_WAVE;
-    t->last_grid = (int)blocks;
-    t->last_slots = blocks * waves_per_block < sa.n_chains ? blocks * waves_per_block : sa.n_chains;  // waves that get a chain
+    t->last_grid = (int)wp.blocks;
+    t->last_slots = wp.blocks * kWaveBlock < sa.n_chains ? wp.blocks * kWaveBlock : sa.n_chains;  // waves that get a chain
     return NUTS_OK;
+}
+
+// nuts_sample_static: a kernel that stands in for the wave kernel takes and refuses the runs that that one would, by its
+// workspace.  (What it takes it can run in less: on fewer workgroups, with more chains in the queue.)
+int static_check(nuts_target* t, const nuts::DevSample& sa)
+{
+    if (!t->static_call) return NUTS_OK;
+    WavePlan wp;
+    int rc = t->dtype == NUTS_F64 ? wave_plan<double>(t, sa, &wp) : wave_plan<float>(t, sa, &wp);
+    if (rc) return rc;
+    return ensure_workspace(t, wp.slot * (size_t)wp.blocks * kWaveBlock);
 }
 
 // Largest dimension of the element-wise variant, per dtype.  The kernel itself goes on to kElemMaxDim: AUTO takes it there
@@ -457,7 +504,18 @@ int launch_elem_inst(nuts_target* t, nuts::DevSample sa, int variant)
     if (per_cu < 1) per_cu = 1;
     long blocks = (sa.n_chains + 3) / 4;
     if (blocks > (long)per_cu * cus) blocks = (long)per_cu * cus;
-    if (t->static_call) {  // the scratch array is what it is: fewer workgroups rather than a refusal
+    if (t->static_call) {
+        if (elem_eligible(t)) {
+            // what an entry that cannot allocate takes: a slot's tree in 3 D + 7 vectors, for all that are resident at two or
+            // (up to 1 KB of state) three workgroups per compute unit; it runs on as many as fit
+            const size_t vec = (size_t)tg.dstride * sizeof(T), tree = ((size_t)(3 * sa.max_depth + 7) * vec + 255) & ~(size_t)255;
+            const long most = (t->dim * (long)sizeof(T) <= 1024 ? 3L : 2L) * cus;
+            int rc = ensure_workspace(t, tree * 4 * (size_t)std::min((long)((sa.n_chains + 3) / 4), most));
+            if (rc) return rc;
+        } else {
+            int rc = static_check(t, sa);
+            if (rc) return rc;
+        }
         const long fit = (long)(((size_t)NUTS_STATIC_SCRATCH_BYTES - kStaticHeader) / (4 * slot));
         if (fit >= 1 && blocks > fit) blocks = fit;
     }
@@ -478,11 +536,13 @@ int launch_elem_inst(nuts_target* t, nuts::DevSample sa, int variant)
 template <typename T>
 int launch_elem(nuts_target* t, const nuts::DevSample& sa, int variant)
 {
-    if (t->dim <= 128) return launch_elem_inst<T, 1>(t, sa, variant);
-    if (t->dim <= 256) return launch_elem_inst<T, 2>(t, sa, variant);
-    if (t->dim <= 512) return launch_elem_inst<T, 4>(t, sa, variant);
-    if (t->dim <= 1024) return launch_elem_inst<T, 8>(t, sa, variant);
-    return launch_elem_inst<T, 16>(t, sa, variant);
+    switch (row_chunks(t->dim)) {
+    case 1: return launch_elem_inst<T, 1>(t, sa, variant);
+    case 2: return launch_elem_inst<T, 2>(t, sa, variant);
+    case 4: return launch_elem_inst<T, 4>(t, sa, variant);
+    case 8: return launch_elem_inst<T, 8>(t, sa, variant);
+    default: return launch_elem_inst<T, 16>(t, sa, variant);
+    }
 }
 
 bool dense_eligible(const nuts_target* t)
@@ -529,7 +589,57 @@ int launch_dense(nuts_target* t, const nuts::DevSample& sa)
     return t->dBand ? launch_dense_inst<T, true>(t, sa) : launch_dense_inst<T, false>(t, sa);
 }
 
-// Chosen automatically only; one wavefront per chain, so it is reported as the wave variant that it stands in for.
+template <typename T, int kC>
+int launch_band_inst(nuts_target* t, nuts::DevSample sa)
+{
+    const nuts::DevTarget<T> tg = dev_target<T>(t);
+    size_t slot = (size_t)nuts::row_num_vectors(sa.max_depth) * 128 * kC * sizeof(T);
+    slot = (slot + 255) & ~(size_t)255;
+    const void* fn = reinterpret_cast<const void*>(nuts::nuts_band_kernel<T, kC>);
+    HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes), NUTS_E_DEVICE);
+    size_t lds_bytes = (size_t)4 * nuts::band_bcast(kC) * sizeof(T);
+    int per_cu = 0, cus = 0;
+    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (nuts::nuts_band_kernel<T, kC>), 256, lds_bytes), NUTS_E_DEVICE);
+    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device), NUTS_E_DEVICE);
+    if (per_cu < 1) per_cu = 1;
+    long blocks = (sa.n_chains + 3) / 4;
+    if (blocks > (long)per_cu * cus) blocks = (long)per_cu * cus;
+    if (t->static_call) {
+        int rc = static_check(t, sa);
+        if (rc) return rc;
+        const long fit = (long)(((size_t)NUTS_STATIC_SCRATCH_BYTES - kStaticHeader) / (4 * slot));
+        if (fit >= 1 && blocks > fit) blocks = fit;
+    }
+    const nuts::RowLds rl = row_lds(blocks, cus, lds_bytes, kC, sizeof(T), sa.max_depth, true);
+    lds_bytes += (size_t)4 * (rl.n_first + rl.n_pool) * nuts::row_entry_bytes(kC, sizeof(T));
+    int rc = ensure_workspace(t, slot * (size_t)blocks * 4);
+    if (rc) return rc;
+    sa.workspace = t->ws_cur;
+    sa.slot_bytes = slot;
+    hipLaunchKernelGGL((nuts::nuts_band_kernel<T, kC>), dim3((unsigned)blocks), dim3(256), lds_bytes, g_stream, tg,
+                       static_cast<const T*>(t->dDiag), t->diag_present, sa, rl);
+    HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
+    t->last_variant = NUTS_VARIANT_WAVE;
+    t->last_grid = (int)blocks;
+    t->last_slots = blocks * 4 < sa.n_chains ? blocks * 4 : sa.n_chains;  // waves that get a chain
+    return NUTS_OK;
+}
+
+// Chosen automatically only, as the block kernel below: one wavefront per chain, so they are reported as the wave variant
+// that they stand in for.
+bool band_eligible(const nuts_target* t) { return t->kind == NUTS_TARGET_GAUSS_DENSE_PRECISION && t->dDiag != nullptr; }
+
+template <typename T>
+int launch_band(nuts_target* t, const nuts::DevSample& sa)
+{
+    switch (row_chunks(t->dim)) {
+    case 2: return launch_band_inst<T, 2>(t, sa);
+    case 4: return launch_band_inst<T, 4>(t, sa);
+    case 8: return launch_band_inst<T, 8>(t, sa);
+    default: return launch_band_inst<T, 16>(t, sa);
+    }
+}
+
 bool block_eligible(const nuts_target* t) { return t->kind == NUTS_TARGET_GAUSS_DENSE_PRECISION && t->block.ops != nullptr; }
 
 template <typename T>
@@ -541,7 +651,9 @@ int launch_block(nuts_target* t, nuts::DevSample sa)
     const int nc = nuts::block_chains_per_group((int)t->dim, sa.n_chains, cus);
     nuts::block_plan(t->block, sizeof(T), sa.n_chains, cus, sa.max_depth, nc, &bp);
     const size_t group_bytes = bp.slot_bytes * (size_t)bp.nc;
-    if (t->static_call) {  // the scratch array is what it is: fewer workgroups rather than a refusal
+    if (t->static_call) {
+        int rc = static_check(t, sa);
+        if (rc) return rc;
         const long fit = (long)(((size_t)NUTS_STATIC_SCRATCH_BYTES - kStaticHeader) / group_bytes);
         if (fit >= 1 && bp.blocks > fit) bp.blocks = (int)fit;
     }
@@ -764,7 +876,9 @@ int launch_wide(nuts_target* t, nuts::DevSample sa, int nc, int cus)
     const size_t block = nuts::wide_block_bytes((int)t->dim, t->dtype == NUTS_F64 ? 8 : 4, nc, sa.max_depth);
     long blocks = (sa.n_chains + nc - 1) / nc;
     if (blocks > cus) blocks = cus;  // one workgroup per compute unit; further chains wait in the queue
-    if (t->static_call) {  // the scratch array is what it is: fewer workgroups rather than a refusal
+    if (t->static_call) {
+        int rc = tile_eligible(t, sa.max_depth) ? NUTS_OK : static_check(t, sa);
+        if (rc) return rc;
         const long fit = (long)(((size_t)NUTS_STATIC_SCRATCH_BYTES - kStaticHeader) / block);
         if (fit >= 1 && blocks > fit) blocks = fit;
     }
@@ -949,6 +1063,7 @@ int sample_impl(const nuts_target* target, int64_t n_chains, int64_t n_iters, do
                            n_chains >= nuts::kQuadAutoChains);
     const bool use_dense = !use_quad && (opt.variant == NUTS_VARIANT_DENSE || (opt.variant == NUTS_VARIANT_AUTO && dense_eligible(t)));
 
+    const bool use_band = opt.variant == NUTS_VARIANT_AUTO && band_eligible(t);
     const bool use_block = opt.variant == NUTS_VARIANT_AUTO && block_eligible(t);
 
     int rc = NUTS_OK;
@@ -998,6 +1113,8 @@ int sample_impl(const nuts_target* target, int64_t n_chains, int64_t n_iters, do
             r = launch_quad(t, s);
         else if (use_dense)
             r = t->dtype == NUTS_F64 ? launch_dense<double>(t, s) : launch_dense<float>(t, s);
+        else if (use_band)
+            r = t->dtype == NUTS_F64 ? launch_band<double>(t, s) : launch_band<float>(t, s);
         else if (use_block)
             r = t->dtype == NUTS_F64 ? launch_block<double>(t, s) : launch_block<float>(t, s);
         else if (use_tile)

@@ -108,8 +108,8 @@ struct WaveChain {
         case kGaussDense: {
             for (int i = lane; i < d; i += kWave) lds[i] = th[i];
             __builtin_amdgcn_wave_barrier();
-            // A banded matrix too large for the register kernel: nine entries of each row instead of d, in the same order
-            // (the others add exact zeros).  One iteration, binary64: d = 300, 1000 chains 7.6 ms -> 0.44; d = 2000, 64
+            // A banded matrix (beyond the band kernel's range, or asked for): nine entries of each row instead of d, in the
+            // same order (the others add exact zeros).  One iteration, binary64: d = 300, 1000 chains 7.6 ms -> 0.44; d = 2000, 64
             // chains 494 ms -> 1.4.
             if (tg.band && d > kBandRows) {
                 for (int i = lane; i < d; i += kWave) {

@@ -1281,9 +1281,11 @@ def test_block_kernel_deep_trees_divergences_and_nonfinite_starts():
     assert_parity(gpu_run(w), ref_run(w), F64_TOL, label="block kernel, deep trees")
 
 
-@pytest.mark.parametrize("dim,dtype", [(129, np.float64), (200, np.float32), (513, np.float64)])
+@pytest.mark.parametrize("dim,dtype", [(129, np.float64), (200, np.float32), (257, np.float32), (512, np.float64), (513, np.float64),
+                                       (1025, np.float64), (2049, np.float32)])
 def test_banded_precision_beyond_the_register_kernel(dim, dtype):
-    """The wave kernel takes nine entries of each row of a banded matrix; one entry off the band and it takes them all."""
+    """AUTO's kernel for banded matrices of up to 2048 dimensions against the oracle; the wave kernel, which takes nine
+    entries of each row, and, with one entry off the band, all of them: the same bits."""
     P = W.ar1_precision(dim, 0.8)
     P[5, 1] = P[1, 5] = 0.05
     w = W.Workload(f"band_d{dim}", W.GAUSS_DENSE, dim, np.dtype(dtype), 5, 3, 0.1, 6, seed=8, precision=P.astype(dtype))
@@ -1292,6 +1294,11 @@ def test_banded_precision_beyond_the_register_kernel(dim, dtype):
     check = (lambda a, b: assert_parity(a, b, F64_TOL, label=w.name)) if dtype is np.float64 else f32_parity
     g = gpu_run(w)
     check(g, ref_run(w))
+    nine = gpu_run(w, variant=N().NUTS_VARIANT_WAVE)
+    kw = dict(sampler=SLICE, leaf_steps=3, schedule=1)
+    s3, s3w = gpu_run(w, **kw), gpu_run(w, variant=N().NUTS_VARIANT_WAVE, **kw)
+    for k in range(3):
+        assert np.array_equal(g[k], nine[k]) and np.array_equal(s3[k], s3w[k])
     w.precision = off.astype(dtype)
     full = gpu_run(w, variant=N().NUTS_VARIANT_WAVE)
     for k in range(3):
