@@ -701,7 +701,10 @@ static int run_impl(const pcvm_program* program, int64_t batch, const int64_t* i
     const bool deep = !small || sm.ring < stack_depth;
     const size_t var_bytes = deep ? (size_t)(small ? sm.n_stacks : program->n_vars) * stack_depth * batch_pad * sizeof(long long) : 0;
     const size_t pc_bytes = deep ? (size_t)stack_depth * batch_pad * sizeof(int) : 0;
-    if (var_bytes + pc_bytes > (size_t)64 << 30) return fail(PCVM_E_ALLOC, "stacks would need %zu bytes", var_bytes + pc_bytes);
+    // (what is refused does not depend on how little of it a program really takes)
+    const size_t lanes = (size_t)std::min<long>(n_groups * kWave, (long)((batch + kWave - 1) / kWave * kWave));
+    const size_t most = ((size_t)program->n_vars * sizeof(long long) + sizeof(int)) * stack_depth * lanes;
+    if (most > (size_t)64 << 30) return fail(PCVM_E_ALLOC, "stacks would need %zu bytes", most);
 
     DeviceBuffers buf;
     {
