@@ -1068,7 +1068,8 @@ int sample_impl(const nuts_target* target, int64_t n_chains, int64_t n_iters, do
     const bool use_grid = opt.variant == NUTS_VARIANT_GRID ||
                           (opt.variant == NUTS_VARIANT_AUTO && grid_eligible(t) && grid_pays(t->n, t->dim));
     const bool use_tile = opt.variant == NUTS_VARIANT_TILE ||
-                          (opt.variant == NUTS_VARIANT_AUTO && !use_grid && wide_eligible(t, max_tree_depth));
+                          (opt.variant == NUTS_VARIANT_AUTO && !use_grid &&
+                           (tile_eligible(t, max_tree_depth) || wide_eligible(t, max_tree_depth)));
     // A precision matrix that is not banded goes to the matrix cores, four chains per wavefront, once there are
     // enough chains to give every compute unit several (below that the one-chain-per-wavefront kernel spreads
     // them over more SIMDs; measured crossover, see the profile summary of the quad kernel)

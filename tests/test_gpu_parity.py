@@ -1345,3 +1345,26 @@ def test_grid_kernels_pack_the_chains_that_want_a_gradient(n_chains):
         assert np.array_equal(g[k][:, n_chains - 6:], few[k])
     pick = np.arange(4)
     f32_parity([x[:, :4] for x in g[:3]], ref_run(w, chain_ids=pick))
+
+
+def test_more_than_a_million_rows_stay_on_the_tile_variant():
+    """The tile variant takes binary64 data sets of up to four million rows (dim <= 32), and AUTO leaves none of them to the
+    general wave kernel; nuts_sample_static takes them too (the wave kernel would need 8 bytes per row and chain slot)."""
+    import torch
+    B = N()
+    n, d = 1_000_001, 3
+    rng = np.random.default_rng(11)
+    X = np.concatenate([rng.standard_normal((n, d - 1)), np.ones((n, 1))], axis=1)
+    y = (rng.random(n) < 1.0 / (1.0 + np.exp(-X @ np.array([0.4, -0.3, 0.1])))).astype(np.float64)
+    w = W.Workload("logreg_1000001x3", W.LOGREG, d, np.dtype(np.float64), 70, 2, 5e-4, 3, seed=12, X=X, y=y, prior_scale=1.0)
+    tgt = gpu_target(w)
+    g = gpu_run(w, tgt=tgt)
+    assert g[3]["variant"] == B.NUTS_VARIANT_TILE
+    asked = gpu_run(w, tgt=tgt, variant=B.NUTS_VARIANT_TILE)
+    many = gpu_run(w, tgt=tgt, n_chains=2100, n_iters=1)         # sixteen chains per workgroup
+    static = B.nuts_sample(tgt, w.n_chains, w.n_iters, w.step_size, w.max_tree_depth, w.seed, static_scratch=True)
+    torch.cuda.synchronize()
+    for k in range(3):
+        assert np.array_equal(g[k], asked[k]) and np.array_equal(g[k], static[k].cpu().numpy())
+        assert np.array_equal(g[k][0], many[k][0, :w.n_chains])
+    assert_parity([x[:, :2] for x in g[:3]], ref_run(w, chain_ids=np.arange(2)), F64_TOL, label=w.name)
