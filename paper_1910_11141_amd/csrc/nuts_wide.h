@@ -10,7 +10,8 @@
 //     wave kernel, whose place this kernel takes;
 //   * NC = 4 runs the two GEMMs on v_mfma_f64_4x4x4_4b: its four blocks are the four groups of 4 rows (first GEMM) or
 //     of 4 features (second GEMM) of the 16x16x4 instruction's operands in the same lanes, and an element of the result
-//     is accumulated in the same order, so a chain's gradient has the same bits whichever form computed it.
+//     is accumulated in the same order, as is the log-likelihood: a chain has the same bits whichever form stepped it
+//     (with up to 32 features and binary64 the 16-chain form is the kernel of nuts_tile.h).
 // The number of chains decides between the two forms (wide_chains_per_block below).
 //
 // What bounds it: with 16 chains the matrix instructions (1000 rows x 120 features: 63.5 k of the gradient phase's 78 k ticks,
@@ -90,6 +91,13 @@ __device__ __forceinline__ double spread_quad(double x)
     const int lo = __builtin_amdgcn_ds_swizzle(__double2loint(x), kPattern);
     const int hi = __builtin_amdgcn_ds_swizzle(__double2hiint(x), kPattern);
     return __hiloint2double(hi, lo);
+}
+
+// What the lane s quads further on in its row of 16 holds (cyclically).
+template <int s>
+__device__ __forceinline__ double quad_after(double x)
+{
+    return dpp_rotate<0x130 - 4 * s>(x);  // row_ror: 16 - 4 s
 }
 
 template <typename T, int MT, int NC>
@@ -554,13 +562,19 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
                 } else {
                     const double slope = logistic_slope(z4, sFtab);
                     const double x = __builtin_copysign(slope, z4);
-                    asm("v_add_f64 %0, %0, |%1|" : "+v"(sum_abs) : "v"(z4));
-                    prod *= fabs(x) + 0.5;
                     // rows 4s + k of the tile sit in quad s: every block of the second GEMM wants them
                     sg[0] = spread_quad<0>(x);
                     sg[1] = spread_quad<1>(x);
                     sg[2] = spread_quad<2>(x);
                     sg[3] = spread_quad<3>(x);
+                    // Sums and products in the order of the 16-chain form, where one lane holds the tile's rows k, 4 + k, 8 + k and
+                    // 12 + k: here quad 0 of every row of 16 lanes gets them so (what the other quads add up is not used).  They
+                    // run while the swizzles above are under way.  (1000 x 25, 512 chains, 20 iterations: 2.21 ms with a sum
+                    // per lane, 2.39 so.)
+                    const double a = fabs(z4), f = fabs(x) + 0.5, f2 = f * quad_after<1>(f);
+                    sum_abs = (((sum_abs + a) + quad_after<1>(a)) + quad_after<2>(a)) + quad_after<3>(a);
+                    prod *= f2 * quad_after<2>(f2);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
 #pragma unroll
                 for (int u = 0; u < MT; ++u)
@@ -592,10 +606,6 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
             if (ta.rem_rows != 0 && wave == ((ta.n_tiles - 1) & (kTileWaves - 1))) row_tile(ta.n_tiles - 1, true, false);
             log_prod += log_unit(prod, sFtab + kFtabDoubles);
             double ll = log_prod - 0.5 * sum_abs;
-            if (NC == 4) {  // the chain's 16 lanes: four quads of every row, then the rows
-                ll += dpp_rotate<0x128>(ll);
-                ll += dpp_rotate<0x124>(ll);
-            }
             ll = add_other_row(ll);
             ll = add_other_half(ll);
             if (lane < NC) sLL[wave][lane] = ll;

@@ -1368,3 +1368,23 @@ def test_more_than_a_million_rows_stay_on_the_tile_variant():
         assert np.array_equal(g[k], asked[k]) and np.array_equal(g[k], static[k].cpu().numpy())
         assert np.array_equal(g[k][0], many[k][0, :w.n_chains])
     assert_parity([x[:, :2] for x in g[:3]], ref_run(w, chain_ids=np.arange(2)), F64_TOL, label=w.name)
+
+
+# Rounding made visible: logits of 1e12 and a step size to match.  The likelihood is linear as far as a trajectory reaches,
+# so its energy is constant up to the rounding of sums of 1e14, which is of the order of 0.01 and decides selections in
+# some of the thousands of trees.  Any difference in how the forms add up a log-likelihood shows.
+@pytest.mark.parametrize("n_data,dim", [(300, 3), (131, 17), (300, 25), (1100, 32), (9000, 5), (300, 40), (145, 100)])
+def test_chains_have_the_same_bits_in_either_lock_step_form_where_rounding_decides(n_data, dim):
+    rng = np.random.default_rng(dim)
+    X = 1e12 * rng.standard_normal((n_data, dim))
+    if dim == 25:
+        X[:, 7] = 1e12                                            # a constant column that stays out of the first GEMM
+    y = (rng.random(n_data) < 0.5).astype(np.float64)
+    w = W.Workload("rounding", W.LOGREG, dim, np.dtype(np.float64), 1000, 6, 2e-13 * (300 / n_data) ** 0.5, 5, seed=4, X=X, y=y, prior_scale=1.0)
+    tgt = gpu_target(w)
+    few = gpu_run(w, tgt=tgt)                                     # four chains per workgroup
+    many = gpu_run(w, tgt=tgt, n_chains=4096)                     # sixteen
+    assert len(np.unique(few[2])) > 3
+    for k in range(3):
+        differ = (few[k] != many[k][:, :w.n_chains])
+        assert differ.sum() == 0, f"{differ.sum()} of {differ.size} values differ"
