@@ -236,10 +236,10 @@ int build_device_data(nuts_target* t, const nuts_target_desc* desc)
             std::vector<double> op, colsum;
             if (sizeof(T) == sizeof(double)) {
                 nuts::tile_pack_operands(reinterpret_cast<const double*>(X), reinterpret_cast<const double*>(y), n, d,
-                                         &t->tile, &op, &colsum);
+                                         nuts::wide_uses_residuals(d, sizeof(T)), &t->tile, &op, &colsum);
             } else {
                 const std::vector<double> Xd(X, X + (size_t)n * d), yd(y, y + n);
-                nuts::tile_pack_operands(Xd.data(), yd.data(), n, d, &t->tile, &op, &colsum);
+                nuts::tile_pack_operands(Xd.data(), yd.data(), n, d, nuts::wide_uses_residuals(d, sizeof(T)), &t->tile, &op, &colsum);
             }
             void* dev = nullptr;
             rc = upload(op, &dev);
@@ -942,7 +942,7 @@ int nuts_tile_pack(const double* X, const double* y, int64_t n, int64_t d, nuts_
     if (!nuts::tile_supports_shape(d, n)) return fail(NUTS_E_INVALID_ARG, "nuts_tile_pack: shape outside the tile variant's range");
     nuts::TileData td;
     std::vector<double> op, colsum;
-    nuts::tile_pack_operands(X, y, n, d, &td, &op, &colsum);
+    nuts::tile_pack_operands(X, y, n, d, false, &td, &op, &colsum);
     layout->ks1 = td.ks1;
     layout->mt = td.mt;
     layout->n_tiles = td.n_tiles;

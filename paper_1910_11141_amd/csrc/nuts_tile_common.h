@@ -35,6 +35,7 @@ struct TileData {
     long n_rows = 0, n_pad = 0;
     int z0_col = -1;         // the constant column that stays out of the first GEMM, or -1
     double z0_val = 0.0;     // its value
+    bool residual = false;   // laid out for the residual form of the wide kernel: no constant column, real tiles only
 };
 
 struct TileLaunch {
@@ -50,7 +51,7 @@ struct TileArgs {
     double prior_prec;
     double n_pad;  // zero rows appended to fill the last tiles
     unsigned ops_bytes;  // size of the operand stream
-    int rem_rows;        // kZ0 kernels: real rows of the last tile if that tile is not full, else 0
+    int rem_rows;        // kZ0 kernels and residual form: real rows of the last tile if that tile is not full, else 0
     int z0_col;          // the constant column that is the accumulators' initial value (kZ0 kernels), and its value
     double z0_val;
 };
@@ -68,9 +69,10 @@ inline bool wide_supports_shape(int64_t d, int64_t n) { return d >= 1 && d <= kW
 // 16-byte load per lane brings two of them.  Rows beyond n are zero, features
 // beyond d are zero.
 __host__ __device__ constexpr int tile_pairs_per_tile(int ks1, int mt) { return (ks1 + 1) / 2 + 2 * mt; }
-inline void tile_pack_operands(const double* X, const double* y, int64_t n, int64_t d, TileData* td,
+inline void tile_pack_operands(const double* X, const double* y, int64_t n, int64_t d, bool residual, TileData* td,
                                std::vector<double>* out, std::vector<double>* colsum)
 {
+    td->residual = residual;
     colsum->assign(kWideMaxDim, 0.0);
     for (int64_t f = 0; f < d; ++f) {
         double acc = 0.0;
@@ -82,7 +84,7 @@ inline void tile_pack_operands(const double* X, const double* y, int64_t n, int6
     td->mt = (int)((d + 15) / 16);
     td->z0_col = -1;
     td->z0_val = 0.0;
-    if (d % 4 == 1 && d > 1) {  // one feature less is one k-step less
+    if (!residual && d % 4 == 1 && d > 1) {  // one feature less is one k-step less
         for (int64_t f = 0; f < d && td->z0_col < 0; ++f) {
             bool same = X[f] != 0.0 && std::isfinite(X[f]);
             for (int64_t r = 1; r < n && same; ++r) same = X[r * d + f] == X[f];
@@ -99,8 +101,8 @@ inline void tile_pack_operands(const double* X, const double* y, int64_t n, int6
     td->n_alloc_tiles = (int)((tiles + kTileWaves - 1) / kTileWaves * kTileWaves);
     // Rows of zeros have logit 0, which is harmless (a known constant in the log-likelihood, nothing in the gradient),
     // unless the accumulators start from the constant column's share: then only real tiles are run, and the rows that
-    // fill the last one start from zero.
-    td->n_tiles = z0 ? (int)tiles : td->n_alloc_tiles;
+    // fill the last one start from zero.  The residual form runs the real ones only, too, and leaves the rows beyond them out.
+    td->n_tiles = z0 || residual ? (int)tiles : td->n_alloc_tiles;
     td->n_rows = (long)n;
     td->n_pad = (long)td->n_tiles * kTileRows - (long)n;
     const int pairs1 = (td->ks1 + 1) / 2;
@@ -134,7 +136,7 @@ inline TileArgs tile_args(const TileData& td, double prior_prec)
 {
     return TileArgs{td.base, td.ftab, td.colsum, td.d, td.n_tiles, prior_prec, (double)td.n_pad,
                     (unsigned)((size_t)td.n_alloc_tiles * 2 * tile_pairs_per_tile(td.ks1, td.mt) * 64 * sizeof(double)),
-                    td.z0_col >= 0 ? (int)(td.n_rows % kTileRows) : 0, td.z0_col, td.z0_val};
+                    td.z0_col >= 0 || td.residual ? (int)(td.n_rows % kTileRows) : 0, td.z0_col, td.z0_val};
 }
 
 // Global-memory vectors of one chain slot, 32 doubles each (wide kernel: 32 elements per component of a lane):

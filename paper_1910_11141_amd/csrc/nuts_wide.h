@@ -3,22 +3,29 @@
 //
 // The round is that of the tile kernel (nuts_tile.h): 8 wavefronts; every chain has its program counter, return
 // stack and tree state in the registers of 32 lanes, of which each owns up to 4 components of every state vector;
-// control sweep, batched gradient  Z = X~ Theta, s = sign(Z) F'(|Z|), G = X~' s  on 16-row tiles of the same packed
-// operand stream, completion.  What differs:
-//   * any d <= 128 (MT = ceil(d / 16) feature tiles), binary64 arithmetic in the contraction for both dtypes: binary32
-//     targets (state, momentum and gradient rounded to binary32 after every update) keep the sums of the general
-//     wave kernel, whose place this kernel takes;
+// control sweep, batched gradient  Z = X~ Theta, G = X~' s(Z)  on 16-row tiles of the same packed operand stream,
+// completion.  What differs:
+//   * any d <= 128 (MT = ceil(d / 16) feature tiles), binary64 arithmetic in the contraction for both dtypes (binary32
+//     targets: state, momentum and gradient rounded to binary32 after every update, as in the general wave kernel);
+//   * where it takes the general wave kernel's place (more than 32 features, or binary32), s is the residual sigma(-Z) as
+//     there, and the log-likelihood is sum log sigma(|z~|) - sum max(-z~, 0), a product per row of a tile and lane.  The tile
+//     kernel's s = sign(Z) F'(|Z|) with half the column sums added is cheaper, but a difference of large sums: 5000 x 60 at
+//     the posterior, against 113 bits, gradient off by 2.9e-12 (wave kernel 4.9e-13, residuals 1.5e-13) and log-density
+//     by 3.7e-12 (1.2e-13, 7.5e-14), other shapes alike;
 //   * NC = 4 runs the two GEMMs on v_mfma_f64_4x4x4_4b: its four blocks are the four groups of 4 rows (first GEMM) or
 //     of 4 features (second GEMM) of the 16x16x4 instruction's operands in the same lanes, and an element of the result
 //     is accumulated in the same order, as is the log-likelihood: a chain has the same bits whichever form stepped it
 //     (with up to 32 features and binary64 the 16-chain form is the kernel of nuts_tile.h).
 // The number of chains decides between the two forms (wide_chains_per_block below).
 //
-// What bounds it: with 16 chains the matrix instructions (1000 rows x 120 features: 63.5 k of the gradient phase's 78 k ticks,
-// its logistic functions another 5 k); with 4 chains the operand stream, which every compute unit reads from L2 at about
-// 50 bytes per tick (1000 x 60: 1 MB in 19 k ticks, where the instructions would take 11 k).  Measured against the wave
-// kernel, which read X twice per chain and gradient with the vector ALUs: binary64, 512 chains, 5000 x 60: 1.1e5 -> 7e6
-// gradient evaluations per second; binary32, 250 chains, 700 x 17: 3.6e6 -> 3.6e7.
+// What bounds it: with 16 chains the matrix instructions (1000 rows x 120 features: 63.5 k of the gradient phase's 83 k ticks,
+// its logistic functions another 10 k; with few features the latter: 3000 x 5 in binary32 38 k of 58 k); with 4 chains the
+// operand stream, which every compute unit reads from L2 at about 50 bytes per tick (1000 x 60: 1 MB in 20 k ticks, where
+// the instructions would take 11 k).  Measured against the wave kernel, which read X twice per chain and gradient with the
+// vector ALUs: binary64, 512 chains, 5000 x 60: 1.1e5 -> 5.5e6 gradient evaluations per second; binary32, 250 chains, 700 x 17,
+// slice sampler, four steps a leaf: 3.6e6 -> 5.0e7.  What the residuals cost against the tile kernel's functions: 700 x 17 in
+// binary32, 4096 chains, 10 iterations 2.0 -> 2.5 ms; 1000 x 60, 4096 chains, 4 iterations 2.39 -> 2.55; 1000 x 120 3.74 -> 3.85;
+// with four chains per workgroup nothing to 6 % (3000 x 5: 19 %).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -37,12 +44,16 @@ struct WideShape {
     static constexpr int kCpl = (16 * MT + 31) / 32;     // components per lane
     static constexpr int kVec = kTileLanes * kCpl;       // elements of a stored vector
     static constexpr int kPitch = 16 * MT + 1;           // doubles per chain in the LDS tiles (odd: see nuts_tile.h)
+    // residuals (see above), or the functions of the tile kernel and its bits
+    static constexpr bool kResidual = sizeof(T) == 4 || MT > 2;
+    static constexpr int kTab = (kResidual ? 0 : kFtabDoubles) + kLogTabDoubles;
+    static constexpr int kQ = kResidual && NC == 16 ? 4 : 1;  // rows of a tile that a lane keeps log-likelihoods of apart
     // partial gradients: one slot per wave, or, where eight do not fit beside the tables, one per pair of waves
     static constexpr int kSlots = (NC == 16 && MT > 2) ? 4 : kTileWaves;
     // With more than two feature tiles the waves' partial sums are added in pairs (w, w + 4) first, in both forms.
     static constexpr bool kPairs = MT > 2;
     static constexpr int kFixed = (NC * kPitch + kSlots * NC * kPitch + kTileWaves * NC + 16 * MT +
-                                   kFtabDoubles + kLogTabDoubles) * 8 + 256;
+                                   kTab) * 8 + 256;
     static constexpr int kEntry = NC * 2 * kVec * (int)sizeof(T);  // one pool buffer or first-leaf slot of every chain
     static constexpr int kRoom = (kWideLds - kFixed) / kEntry;
     // The vectors that only the start and the end of a doubling or of an iteration touch (the other end of the trajectory,
@@ -58,6 +69,9 @@ struct WideShape {
     // of that many instructions covers the latency) half a tile ahead
     static constexpr bool kFullAhead = MT <= (NC == 4 ? 4 : 2);
 };
+
+// Which of the two the kernel takes for a target (elem: bytes of its dtype).
+inline bool wide_uses_residuals(int64_t d, size_t elem) { return elem == 4 || d > 32; }
 
 struct WideArgs {
     TileArgs ta;
@@ -109,9 +123,10 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
     __shared__ double sTheta[NC][S::kPitch];
     __shared__ double sG[S::kSlots][NC][S::kPitch];
     __shared__ double sLL[kTileWaves][NC];
-    __shared__ double sHalfCol[16 * MT];  // column sums of X~, halved
+    __shared__ double sHalfCol[S::kResidual ? 1 : 16 * MT];  // column sums of X~, halved
     __shared__ int sHalted;
-    __shared__ __align__(16) double sFtab[kFtabDoubles + kLogTabDoubles];
+    __shared__ __align__(16) double sFtab[S::kTab];
+    const double* const log_tab = sFtab + S::kTab - kLogTabDoubles;
     __shared__ T sPool[NC][kLP > 0 ? kLP : 1][2][kLP > 0 ? kVec : 1];
     __shared__ T sFirst[NC][kLF > 0 ? kLF : 1][2][kLF > 0 ? kVec : 1];
     __shared__ T sRest[NC][kRestCount][S::kRestLds ? kVec : 1];
@@ -171,15 +186,15 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
         }
     };
 
-    for (int i = tid; i < kFtabDoubles + kLogTabDoubles; i += kTileThreads) sFtab[i] = ta.ftab[i];
+    for (int i = tid; i < S::kTab; i += kTileThreads) sFtab[i] = ta.ftab[kFtabDoubles + kLogTabDoubles - S::kTab + i];
     for (int i = tid; i < NC * S::kPitch; i += kTileThreads) (&sTheta[0][0])[i] = 0.0;
-    for (int i = tid; i < 16 * MT; i += kTileThreads) sHalfCol[i] = 0.5 * ta.colsum[i];
+    for (int i = tid; i < (S::kResidual ? 0 : 16 * MT); i += kTileThreads) sHalfCol[i] = 0.5 * ta.colsum[i];
     if (tid == 0) sHalted = 0;
     __syncthreads();
 
     // where component i goes in the first GEMM's contraction (see feat1 in tile_pack_operands)
     auto slot_of = [&](int i) __attribute__((always_inline)) -> int {
-        return ta.z0_col < 0 ? i : (i == ta.z0_col ? d - 1 : (i == d - 1 ? ta.z0_col : i));
+        return S::kResidual || ta.z0_col < 0 ? i : (i == ta.z0_col ? d - 1 : (i == d - 1 ? ta.z0_col : i));
     };
     const __amdgpu_buffer_rsrc_t ops_rsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(ta.ops), 0, (int)ta.ops_bytes, 0x00020000);
@@ -215,7 +230,7 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
             double z0 = 0.0, z1 = 0.0;
             if (i < d) {
                 const Words4 w = draw(key, (uint32_t)(i >> 1), tag, 0, it, c.gchain);
-                const double rho = sqrt(-2.0 * log_unit(uniform52(w.w0, w.w1), sFtab + kFtabDoubles));
+                const double rho = sqrt(-2.0 * log_unit(uniform52(w.w0, w.w1), log_tab));
                 const double phi = 6.283185307179586476925286766559 * uniform52(w.w2, w.w3);
                 if (e < kCpl / 2 * 2) {
                     z0 = rho * circle_point(phi, false);
@@ -501,7 +516,10 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
                 if (NC == 16) G16[NC == 16 ? u : 0] = acc16{0.0, 0.0, 0.0, 0.0};
                 else G4[NC == 4 ? u : 0] = 0.0;
             }
-            double sum_abs = 0.0, prod = 1.0, log_prod = 0.0;
+            // sum of |z| (residual form: of |z| - z), and the product of sigma(|z|) as it stands and as logarithms
+            double sum_abs[S::kQ], prod[S::kQ], log_prod[S::kQ];
+#pragma unroll
+            for (int q = 0; q < S::kQ; ++q) sum_abs[q] = 0.0, prod[q] = 1.0, log_prod[q] = 0.0;
             // B operand of the first GEMM: component 4 s + lane/16 of the position of chain lane % NC
             const double* const b_src = &sTheta[lane & (NC - 1)][lane >> 4];
             double b1[S::kHoldTheta ? 4 * MT : 1];
@@ -509,7 +527,7 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
 #pragma unroll
                 for (int s = 0; s < 4 * MT; ++s) b1[s] = b_src[4 * s];
             }
-            const double z0 = ta.z0_col >= 0 ? ta.z0_val * sTheta[lane & (NC - 1)][d - 1] : 0.0;
+            const double z0 = !S::kResidual && ta.z0_col >= 0 ? ta.z0_val * sTheta[lane & (NC - 1)][d - 1] : 0.0;
             auto row_tile = [&](const int t, const bool ragged, const bool more) __attribute__((always_inline)) {
                 const int here = t * tile_bytes, next = (t + kTileWaves) * tile_bytes;
                 // (the positions are read from LDS again for every tile: kept across tiles they would fill 8 MT registers)
@@ -540,25 +558,38 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
                         if (i < 2 * MT - 2 || i < pairs1) a1[i] = load_at(next + i * 1024);
                 }
                 double sg[4];
-                if (NC == 16) {
+                if (S::kResidual) {
+                    // (an infinite or NaN logit makes the sum a NaN; rows beyond the last one count nothing)
+                    auto row = [&](const double zr, const int first, double& sum, double& product) __attribute__((always_inline)) -> double {
+                        double resid, sig;
+                        logistic_residual(zr, resid, sig);
+                        sum += fabs(zr) - zr;
+                        product *= (!ragged || first + (lane >> 4) < ta.rem_rows) ? sig : 1.0;
+                        return resid;
+                    };
+                    if (NC == 16) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            sg[q] = row(z[q], 4 * q, sum_abs[q < S::kQ ? q : 0], prod[q < S::kQ ? q : 0]);
+                            if (q == 1) __builtin_amdgcn_sched_barrier(0);  // (two at a time: fewer registers)
+                        }
+                    } else {
+                        const double x = row(z4, 4 * ((lane >> 2) & 3), sum_abs[0], prod[0]);
+                        sg[0] = spread_quad<0>(x);
+                        sg[1] = spread_quad<1>(x);
+                        sg[2] = spread_quad<2>(x);
+                        sg[3] = spread_quad<3>(x);
+                    }
+                } else if (NC == 16) {
                     const double zq[4] = {z[0], z[1], z[2], z[3]};
                     double slope[4];
-                    if (MT <= 2) {
-                        logistic_slopes<4>(zq, sFtab, slope);
-                    } else {  // (two at a time: fewer table coefficients in registers at once)
-                        const double za[2] = {zq[0], zq[1]}, zb[2] = {zq[2], zq[3]};
-                        double ra[2], rb[2];
-                        logistic_slopes<2>(za, sFtab, ra);
-                        __builtin_amdgcn_sched_barrier(0);
-                        logistic_slopes<2>(zb, sFtab, rb);
-                        slope[0] = ra[0], slope[1] = ra[1], slope[2] = rb[0], slope[3] = rb[1];
-                    }
+                    logistic_slopes<4>(zq, sFtab, slope);
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         sg[q] = __builtin_copysign(slope[q], zq[q]);
-                        asm("v_add_f64 %0, %0, |%1|" : "+v"(sum_abs) : "v"(zq[q]));
+                        asm("v_add_f64 %0, %0, |%1|" : "+v"(sum_abs[0]) : "v"(zq[q]));
                     }
-                    prod *= ((fabs(sg[0]) + 0.5) * (fabs(sg[1]) + 0.5)) * ((fabs(sg[2]) + 0.5) * (fabs(sg[3]) + 0.5));
+                    prod[0] *= ((fabs(sg[0]) + 0.5) * (fabs(sg[1]) + 0.5)) * ((fabs(sg[2]) + 0.5) * (fabs(sg[3]) + 0.5));
                 } else {
                     const double slope = logistic_slope(z4, sFtab);
                     const double x = __builtin_copysign(slope, z4);
@@ -572,8 +603,8 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
                     // run while the swizzles above are under way.  (1000 x 25, 512 chains, 20 iterations: 2.21 ms with a sum
                     // per lane, 2.39 so.)
                     const double a = fabs(z4), f = fabs(x) + 0.5, f2 = f * quad_after<1>(f);
-                    sum_abs = (((sum_abs + a) + quad_after<1>(a)) + quad_after<2>(a)) + quad_after<3>(a);
-                    prod *= f2 * quad_after<2>(f2);
+                    sum_abs[0] = (((sum_abs[0] + a) + quad_after<1>(a)) + quad_after<2>(a)) + quad_after<3>(a);
+                    prod[0] *= f2 * quad_after<2>(f2);
                     __builtin_amdgcn_sched_barrier(0);
                 }
 #pragma unroll
@@ -593,19 +624,35 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
                     for (int i = 0; i < 2 * MT; ++i) a2[i] = load_at(next + (pairs1 + i) * 1024);
                 }
             };
-            // (z0: a last tile that is not full is run after the loop, by the wave whose turn it is)
+            auto fold = [&]() __attribute__((always_inline)) {
+#pragma unroll
+                for (int q = 0; q < S::kQ; ++q) {
+                    const double l = log_unit(prod[q], log_tab);
+                    log_prod[q] += S::kResidual && prod[q] == 1.0 ? 0.0 : l;  // (log_unit(1) is off by the rounding of log 2)
+                    prod[q] = 1.0;
+                }
+            };
+            // (z0, residuals: a last tile that is not full is run after the loop, by the wave whose turn it is)
             const int n_loop = ta.rem_rows != 0 ? ta.n_tiles - 1 : ta.n_tiles;
             for (int t_chunk = wave; t_chunk < n_loop; t_chunk += 64 * kTileWaves) {
                 const int t_stop = min(n_loop, t_chunk + 64 * kTileWaves);
                 for (int t = t_chunk; t < t_stop; t += kTileWaves) row_tile(t, false, t + kTileWaves < ta.n_tiles);
-                if (t_chunk + 64 * kTileWaves < n_loop) {  // more follow: fold the product of sigmas
-                    log_prod += log_unit(prod, sFtab + kFtabDoubles);
-                    prod = 1.0;
-                }
+                if (t_chunk + 64 * kTileWaves < n_loop) fold();  // more follow
             }
             if (ta.rem_rows != 0 && wave == ((ta.n_tiles - 1) & (kTileWaves - 1))) row_tile(ta.n_tiles - 1, true, false);
-            log_prod += log_unit(prod, sFtab + kFtabDoubles);
-            double ll = log_prod - 0.5 * sum_abs;
+            fold();
+            double ll = log_prod[0] - 0.5 * sum_abs[0];
+            if (S::kResidual) {  // rows 4q + k of all tiles: q = (0 + 2) + (1 + 3); with 4 chains they are in four quads
+                if (NC == 16) {
+                    double l[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) l[q] = log_prod[q < S::kQ ? q : 0] - 0.5 * sum_abs[q < S::kQ ? q : 0];
+                    ll = (l[0] + l[2]) + (l[1] + l[3]);
+                } else {
+                    ll += quad_after<2>(ll);
+                    ll += quad_after<1>(ll);
+                }
+            }
             ll = add_other_row(ll);
             ll = add_other_half(ll);
             if (lane < NC) sLL[wave][lane] = ll;
@@ -658,10 +705,11 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
                     }
                 }
                 const double th = (double)c.tha[e];
-                const double hc = i < 16 * MT ? sHalfCol[i] : 0.0;
-                const T g = i < d ? (T)((hc - gsum) - th * ta.prior_prec) : (T)0;
-                // |theta|^2 for the prior, (1/2) colsum . theta = (1/2) sum z~ for the likelihood
-                sq += fma(th, th * (-0.5 * ta.prior_prec), hc * th);
+                const double hc = !S::kResidual && i < 16 * MT ? sHalfCol[S::kResidual ? 0 : i] : 0.0;
+                const T g = i < d ? (T)((S::kResidual ? gsum : hc - gsum) - th * ta.prior_prec) : (T)0;
+                // |theta|^2 for the prior (not residuals: (1/2) colsum . theta = (1/2) sum z~ for the likelihood)
+                if (S::kResidual) sq = fma(th, th * (-0.5 * ta.prior_prec), sq);
+                else sq += fma(th, th * (-0.5 * ta.prior_prec), hc * th);
                 if (at_leaf) {
                     const T r_new = c.ra[e] + half * g;
                     c.ra[e] = r_new;
@@ -676,7 +724,7 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
                 if (c.sub >= sa.leaf_steps) {  // otherwise the leaf is not finished: the chain stays at LEAF
                     c.sub = 0;
                     group_sum2(sq, kin);
-                    const double logp = ta.n_pad * 0.6931471805599453 + sq;
+                    const double logp = S::kResidual ? sq : ta.n_pad * 0.6931471805599453 + sq;
                     c.edge_logp = logp;
                     c.m += 1;
                     double delta = (-logp + 0.5 * kin) - c.H0;
@@ -707,7 +755,8 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
                 }
             } else {
                 rest_store(kRestTopG, c.ga);
-                c.top_logp = ta.n_pad * 0.6931471805599453 + group_sum(sq);
+                sq = group_sum(sq);
+                c.top_logp = S::kResidual ? sq : ta.n_pad * 0.6931471805599453 + sq;
                 n_extra += 1;
                 c.pc = kPcIterBegin;
             }

@@ -1388,3 +1388,47 @@ def test_chains_have_the_same_bits_in_either_lock_step_form_where_rounding_decid
     for k in range(3):
         differ = (few[k] != many[k][:, :w.n_chains])
         assert differ.sum() == 0, f"{differ.sum()} of {differ.size} values differ"
+
+
+@pytest.mark.parametrize("n_data,dim", [(37, 33), (300, 100), (2000, 60), (5000, 40)])
+def test_wide_kernel_gradients_are_as_exact_as_the_general_kernels(n_data, dim):
+    """One leaf of 64 leapfrog steps from points near the posterior, against the same steps in extended precision (64-bit
+    mantissa, 1e-19).  What separates a kernel's end state from those is its gradients' error: the sums of the general
+    wave kernel set the bar.  AUTO's kernel measured 0.98 to 1.02 times the wave kernel's error; 1.5 leaves room for chance
+    in the short sums of few rows.  (Half the column sums minus sums of sign(z) F'(|z|) in place of the residuals' sums
+    measured 1.5, 3.2, 8 and 17 times.)"""
+    rng = np.random.default_rng(n_data)
+    X, y, wt = W.logreg_data(n_data, dim, 0.5, rng, standardize=True)
+    nc, steps, eps = 24, 64, 0.15 / np.sqrt(n_data)
+    init = wt + rng.standard_normal((nc, dim)) * 1.5 / np.sqrt(n_data)
+    w = W.Workload("one_leaf", W.LOGREG, dim, np.dtype(np.float64), nc, 1, eps, 1, seed=41, X=X, y=y, prior_scale=1.0)
+    r0 = np.array([[z for i in range((dim + 1) // 2) for z in R.normal_pair(R.draw(w.seed, i, R.TAG_MOMENTUM, 0, 0, c))][:dim]
+                   for c in range(nc)])
+    Xl, yl = X.astype(np.longdouble), y.astype(np.longdouble)[:, None]
+
+    def grad(th):
+        return Xl.T @ (yl - 1 / (1 + np.exp(-(Xl @ th)))) - th
+
+    ends = []
+    for v in (1, -1):
+        th, r = init.T.astype(np.longdouble), r0.T.astype(np.longdouble)
+        g, h = grad(th), np.longdouble(v * eps)
+        for _ in range(steps):
+            r = r + h / 2 * g
+            th = th + h * r
+            g = grad(th)
+            r = r + h / 2 * g
+        ends.append(th.T)
+    tgt = gpu_target(w)
+    err = []
+    for variant in (0, N().NUTS_VARIANT_WAVE):
+        s, _, n, _ = gpu_run(w, tgt=tgt, variant=variant, init=init, leaf_steps=steps)
+        assert (n == steps).all()
+        diff = [np.asarray(s[0] - e, dtype=np.float64) for e in ends]
+        moved = (np.abs(s[0] - init) > 0).any(axis=1)
+        assert moved.sum() >= nc // 2
+        e2 = np.minimum(*[(d ** 2).sum(axis=1) for d in diff])[moved]
+        assert e2.max() < 1e-20
+        err.append(float(np.sqrt(e2.mean())))
+    report("one_leaf", n=n_data, d=dim, auto=err[0], wave=err[1])
+    assert err[0] <= 1.5 * err[1], f"error {err[0]:.2e} against the general kernel's {err[1]:.2e}"
