@@ -53,8 +53,9 @@ enum {
                                regression, binary64, dim <= 32, max_tree_depth <= 12); when dim = 1 mod 4
                                and a column of X is the same non-zero value in every row (an intercept),
                                that column's share of the logits is added ahead of the others' instead of
-                               in its place among them: another order of the same sum.  Up to 8 chains per
-                               compute unit it steps 4 chains per workgroup instead of 16 (the same bits).
+                               in its place among them: another order of the same sum.  Up to 4 chains per
+                               compute unit, and up to 8 in short runs on many rows, it steps 4 chains per
+                               workgroup instead of 16 (the same bits).
                                AUTO extends the family to dim <= 128 and to binary32 data sets that are too
                                small for the grid kernels, and reports it under this number                 */
     NUTS_VARIANT_ELEM = 3,  /* one wavefront per chain with the moving trajectory end held in registers

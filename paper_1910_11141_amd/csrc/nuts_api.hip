@@ -913,7 +913,7 @@ int launch_tile(nuts_target* t, nuts::DevSample sa)
 {
     int cus = 0;
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device), NUTS_E_DEVICE);
-    const int nc = nuts::wide_chains_per_block(sa.n_chains, cus);
+    const int nc = nuts::wide_chains_per_block(sa.n_chains, cus, sa.iter_end - sa.iter_begin, t->n, (int)t->dim, t->tile.residual);
     if (!tile_eligible(t, sa.max_depth) || nc == 4) return launch_wide(t, sa, nc, cus);
     nuts::TileLaunch tl;
     nuts::tile_plan(t->tile, sa.n_chains, sa.max_depth, &tl);

@@ -779,11 +779,30 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
     }
 }
 
-// Chains per workgroup for a run of n_chains on a chip of `cus` compute units (one workgroup each).  A round of 4 chains
-// takes a little less than half as long as one of 16 (1000 x 25: 14.5 k ticks against 27.7 k; 1000 x 60: 25 k against 52 k),
-// so up to 8 chains per compute unit - two rounds of 4 after one another - the small form wins (1792 chains: 2.0 ms
-// against 2.3; 1000 x 60: 3.4 against 4.2) and beyond it loses.
-inline int wide_chains_per_block(long n_chains, int cus) { return n_chains <= 8L * cus ? 4 : 16; }
+// Chains per workgroup for a launch of n_chains and `iters` iterations of n rows and d features on a chip of `cus` compute
+// units (one workgroup each).  Up to 4 chains per compute unit every group of four has one to itself, and 4 is never behind
+// (64 to 1024 chains, 10 to 1e6 rows x 5 to 32: 1 to 1.8 times as fast as 16).
+// Up to 8, the groups beyond the first `cus` take turns with them where sixteen would all run at once.  A chain's turn of 4 takes
+// between 0.45 (many rows) and 0.9 (few) of one of 16, so two turns lose in the long run; but a launch of few iterations
+// lasts as long as its longest chain, and the shorter ones leave room beside it.  Time with 4 over time with 16 at 1100, 1500
+// and 2048 chains, binary64, against the kernel of nuts_tile.h:
+//   rows x features     1 iteration        4                 16                64                200
+//   500 x 25         0.70 0.70 0.88   0.78 0.86 0.88   0.89 1.03 1.05   1.01 1.05 1.15   1.07 1.13 1.19
+//   2000 x 25        0.67 0.67 0.79   0.72 0.79 0.96   0.78 0.83 0.99   0.88 0.94 0.97   0.93 0.97 1.00
+//   10000 x 32       0.73 0.88 0.87   0.72 0.85 0.94   0.96 1.01 1.04   1.01 1.03 1.07   1.03 1.06 1.09
+//   2000 x 16        0.78 0.62 0.91   0.64 0.79 0.93   0.88 1.00 1.11   0.99 1.05 1.13   1.06 1.10 1.13
+//   8000 x 5         0.65 0.75 0.86   0.84 0.90 1.13   0.98 1.08 1.09   1.08 1.13 1.17   1.14 1.16 1.18
+// (100 x 25 and 1000 x 5, 20 iterations: 1.0 to 1.36; 200 000 x 25 0.70 to 1.01 up to 16 iterations; from 700 000 x 25 on the
+// stream leaves the last cache, 1.3, trajectories of one length.)  Against this kernel's own form with 16 and residuals, 4 to 20 iterations: 300 x 60
+// 0.7 to 0.93, 1000 x 60 0.52 to 0.75, binary32 700 x 17 0.49 to 0.75; 100 x 40 0.86 to 1.09, binary32 100 x 5 0.86 to 1.16.
+inline int wide_chains_per_block(long n_chains, int cus, long iters, long n, int d, bool residual)
+{
+    if (n_chains <= 4L * cus) return 4;
+    if (n_chains > 8L * cus) return 16;
+    if (residual) return n >= 200 ? 4 : 16;
+    const long most = n < 500 || n > 200000 ? 0 : d > 16 ? (n >= 2000 ? 64 : 16) : (n >= 2000 ? 4 : 0);  // iterations
+    return iters <= most ? 4 : 16;
+}
 
 inline size_t wide_block_bytes(int d, int dtype_bytes, int nc, int max_depth)
 {

@@ -1432,3 +1432,22 @@ def test_wide_kernel_gradients_are_as_exact_as_the_general_kernels(n_data, dim):
         err.append(float(np.sqrt(e2.mean())))
     report("one_leaf", n=n_data, d=dim, auto=err[0], wave=err[1])
     assert err[0] <= 1.5 * err[1], f"error {err[0]:.2e} against the general kernel's {err[1]:.2e}"
+
+
+@pytest.mark.parametrize("dtype,n_data,dim,n_iters,schedule,sixteen", [
+    (np.float64, 10, 5, 2, 0, True), (np.float64, 499, 25, 2, 0, True), (np.float64, 500, 25, 2, 0, False), (np.float64, 500, 25, 17, 0, True),
+    (np.float64, 500, 25, 17, 1, False), (np.float64, 1999, 16, 2, 0, True), (np.float64, 2000, 16, 4, 0, False), (np.float64, 2000, 16, 5, 0, True),
+    (np.float64, 199, 40, 2, 0, True), (np.float64, 200, 40, 2, 0, False), (np.float32, 199, 5, 2, 0, True), (np.float32, 200, 5, 2, 0, False)])
+def test_lock_step_form_between_four_and_eight_chains_per_compute_unit(dtype, n_data, dim, n_iters, schedule, sixteen):
+    """Where more groups of four run than there are compute units, few rows or many iterations a launch go to sixteen."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    w = wide_workload(n_data, dim, dtype, 8 * cus)
+    w.max_tree_depth = 4
+    tgt = gpu_target(w)
+    g = gpu_run(w, tgt=tgt, n_iters=n_iters, schedule=schedule)
+    assert g[3]["grid_blocks"] == (cus // 2 if sixteen else cus)
+    few = gpu_run(w, tgt=tgt, n_iters=n_iters, n_chains=4 * cus)
+    assert few[3]["grid_blocks"] == cus
+    for k in range(3):
+        assert np.array_equal(g[k][:, :4 * cus], few[k])
