@@ -27,7 +27,7 @@
 // many sets of 128 columns (one workgroup's worth) as that takes.  A column's sums do not depend on where it lies.  Two
 // streams of up to 512 chains with columns handed out against four of up to 256 with a column per slot: 10 000 x 100, 1024
 // chains, one iteration 6.9 -> 4.2 ms, 4 awaited ones 20.6 -> 11.8, 12 free ones 17.2 -> 15.2 (one stream: 17.3); 6052 x 7,
-// 1229 chains, 4 awaited iterations 10.0 -> 5.1.  A run of one set keeps a column per slot: its four waves run side by
+// 1229 chains, 4 awaited iterations 10.1 -> 5.3.  A run of one set keeps a column per slot: its four waves run side by
 // side whatever they hold, and the atomic would cost 3 % of a round; with one set on each of two streams idle waves leave
 // their SIMD to the other stream (100 000 x 100, 256 chains, one iteration 12.1 -> 11.1 ms).
 // Streams are independent: while one is in its control launch another one's gradient keeps the matrix units busy, and
@@ -55,7 +55,6 @@ constexpr int kGridRows = 32;    // data rows per MFMA tile
 constexpr int kGridGroup = 32;   // chains per wave
 constexpr int kGridWaves = 4;                          // waves per gradient workgroup
 constexpr int kGridSetChains = kGridGroup * kGridWaves;  // chains that step together
-constexpr int kGridMaxSets = kGridMaxChains / kGridSetChains;
 constexpr int kGridMaxStreams = 2;                     // the slots are divided between this many streams
 constexpr int kGridSumParts = 8;                       // a chain's slices are summed in this many interleaved parts
 constexpr int kGridFeatPad = 128;
@@ -146,8 +145,11 @@ inline void grid_pack_operands(const float* X, const float* y, int64_t n, int64_
 // Device buffers of one sampling call (all inside the target's workspace).
 struct GridBuffers {
     // (chain_stride = slots of this run, a multiple of 128)
-    float* theta_t;        // [kGridFeatPad][chain_stride]: positions, one column per chain slot
-    float* g_part;         // [slices][chain_stride][kGridFeatPad]: a chain's partial gradient is one 512-byte row per slice
+    // Positions and partial results are indexed by column: slot_base + the column of its stream that a slot took for the
+    // round (see `column`; with up to 128 slots its own).  A column is a slot's for that round only, and columns beyond the
+    // round's count hold what an earlier round left.
+    float* theta_t;        // [kGridFeatPad][chain_stride]: positions
+    float* g_part;         // [slices][chain_stride][kGridFeatPad]: a column's partial gradient is one 512-byte row per slice
     double* ll_part;       // [slices][chain_stride]
     int* active_all;       // [streams][kGridBatch]: columns that want a gradient in round r of the batch
     int* column;           // [kGridMaxChains]: the column (of its stream) that a slot's position was published in
