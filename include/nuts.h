@@ -65,8 +65,8 @@ enum {
                                (logistic regression, binary32, dim <= 128; up to 1024 chains are resident
                                at a time, further chains wait in a queue); this variant returns only when
                                sampling has finished; beyond 128 chains the resident ones are divided
-                               between two streams, the caller's and one that the target owns, forked
-                               from and joined to the caller's stream by events; chains that want a
+                               between two or four streams, the caller's and others that the target owns,
+                               forked from and joined to the caller's stream by events; chains that want a
                                gradient are packed together, so idle ones cost nothing beyond 128 columns  */
     NUTS_VARIANT_DENSE = 5, /* one wavefront per chain, moving trajectory end in registers, precision matrix in LDS
                                (dense Gaussian, dim <= 128)                                                 */

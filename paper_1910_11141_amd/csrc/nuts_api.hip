@@ -719,7 +719,7 @@ bool grid_eligible(const nuts_target* t)
 
 // Rounds of (control, gradient) launches, enqueued in batches; the host waits for each batch
 // and stops when every chain has halted, so this variant returns only when sampling is complete.
-// Slots beyond the first 128 may run on a second stream, which the target owns.
+// Slots beyond the first 128 may run on up to three further streams, which the target owns.
 int launch_grid(nuts_target* t, nuts::DevSample sa)
 {
     using namespace nuts;
@@ -729,7 +729,8 @@ int launch_grid(nuts_target* t, nuts::DevSample sa)
     const int n_slots = sa.n_chains >= kGridMaxChains ? kGridMaxChains : (int)((sa.n_chains + 3) / 4 * 4);
     const int n_sets = (n_slots + kGridSetChains - 1) / kGridSetChains;
     // consecutive sets share a stream: one control launch and one gradient launch serve them all
-    const int sets_per_stream = (n_sets + kGridMaxStreams - 1) / kGridMaxStreams;
+    const int most_streams = grid_streams(n_slots, t->n, (int)t->dim, (double)(sa.iter_end - sa.iter_begin) * (double)sa.n_chains);
+    const int sets_per_stream = (n_sets + most_streams - 1) / most_streams;
     const int n_streams = (n_sets + sets_per_stream - 1) / sets_per_stream;
     int cus = 0;
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device), NUTS_E_DEVICE);

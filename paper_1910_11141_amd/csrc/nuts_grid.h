@@ -21,7 +21,7 @@
 //             4x4x1 MFMAs of 16 blocks, four features at a time, whose B operand
 //             is again the accumulator register as it stands (block = four
 //             chains of one row) and which cost an eighth of a 32-feature tile.
-// The chains of a stream (up to 512) step together.  A chain that wants a gradient takes the next free column
+// The chains of a stream step together.  A chain that wants a gradient takes the next free column
 // of its stream's Theta, so the columns in use are the first ones however many chains have nothing to do (their
 // trajectories have different lengths: on average three quarters of the slots of a short run), and the gradient runs as
 // many sets of 128 columns (one workgroup's worth) as that takes.  A column's sums do not depend on where it lies.  Two
@@ -31,7 +31,8 @@
 // side whatever they hold, and the atomic would cost 3 % of a round; with one set on each of two streams idle waves leave
 // their SIMD to the other stream (100 000 x 100, 256 chains, one iteration 12.1 -> 11.1 ms).
 // Streams are independent: while one is in its control launch another one's gradient keeps the matrix units busy, and
-// two gradient workgroups fit on a compute unit together.
+// two gradient workgroups fit on a compute unit together.  Where gradients are long and all columns stay busy, four
+// streams overlap better than two (grid_streams below).
 // The host enqueues rounds in batches and looks at a "who has halted" array one
 // batch behind; rounds enqueued after the last chain of a set halted return at
 // once.
@@ -55,7 +56,7 @@ constexpr int kGridRows = 32;    // data rows per MFMA tile
 constexpr int kGridGroup = 32;   // chains per wave
 constexpr int kGridWaves = 4;                          // waves per gradient workgroup
 constexpr int kGridSetChains = kGridGroup * kGridWaves;  // chains that step together
-constexpr int kGridMaxStreams = 2;                     // the slots are divided between this many streams
+constexpr int kGridMaxStreams = 4;                     // the slots are divided between up to this many streams
 constexpr int kGridSumParts = 8;                       // a chain's slices are summed in this many interleaved parts
 constexpr int kGridFeatPad = 128;
 constexpr int kGridBatch = 32;   // rounds enqueued between two looks at the halted flags
@@ -170,6 +171,20 @@ struct GridArgs {
     const double* ftab;  // table of the logistic function for the weight merges, global memory
     GridBuffers b;
 };
+
+// Streams of a launch that steps n_slots chains at a time through `chain_iters` iterations in all: two, or four where packing
+// has little to gain.  With few iterations a slot the end of the launch, when ever fewer slots are busy, is most of it.  Time
+// with two over time with four, packed both: 10 000 x 100, 1024 and 4096 chains, 50 iterations 1.05 and 1.05, 12 iterations 1.03
+// and 1.05, one awaited 0.89 and 1.03; 512 chains, 50 iterations 0.99 to 1.01, one 0.80; 100 000 x 100, 512 to 1024 chains, 12
+// iterations 1.01 to 1.03; 3000 x 9 0.4 to 0.93 throughout (every launch has a cost of its own, and the host has to keep up:
+// 20 000 x 25, 512 to 4096 chains, 12 to 50 iterations 1.00 to 1.05 with a fast one, 0.86 to 0.93 with a slower one).
+// A target's first launch with four takes 5 ms more than with two, to create the streams: only launches of some 130 ms
+// (1.2e11 chain iterations x rows x features) save about as much.
+inline int grid_streams(int n_slots, long n, int d, double chain_iters)
+{
+    const double work = (double)n * d;
+    return n_slots > 512 && work >= 1e6 && chain_iters >= 12.0 * n_slots && chain_iters * work >= 1.2e11 ? 4 : 2;
+}
 
 // ------------------------------------------------------------------ gradient
 template <int kKs1, int kMt, int kTail>

@@ -1451,3 +1451,16 @@ def test_lock_step_form_between_four_and_eight_chains_per_compute_unit(dtype, n_
     assert few[3]["grid_blocks"] == cus
     for k in range(3):
         assert np.array_equal(g[k][:, :4 * cus], few[k])
+
+
+def test_grid_kernels_on_four_streams_give_the_bits_of_two():
+    """Long runs on many rows, all columns busy, take four streams where shorter ones take two."""
+    w = W.small_logreg(120000, 64, seed=78, dtype=np.float32)
+    w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = 1100, 18, 0.01, 2
+    tgt = gpu_target(w)
+    g = gpu_run(w, tgt=tgt)
+    assert g[3]["variant"] == N().NUTS_VARIANT_GRID and g[3]["leaf_slots_useful"] == g[2].sum()
+    few = gpu_run(w, tgt=tgt, n_chains=140, first_chain=960)
+    sync = gpu_run(w, tgt=tgt, schedule=1, n_iters=3)
+    for k in range(3):
+        assert np.array_equal(g[k][:, 960:], few[k]) and np.array_equal(g[k][:3], sync[k])
