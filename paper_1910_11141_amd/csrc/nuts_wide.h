@@ -46,6 +46,7 @@ struct WideShape {
     static constexpr int kPitch = 16 * MT + 1;           // doubles per chain in the LDS tiles (odd: see nuts_tile.h)
     // residuals (see above), or the functions of the tile kernel and its bits
     static constexpr bool kResidual = sizeof(T) == 4 || MT > 2;
+    static_assert(kResidual || NC == 4, "16 chains of a binary64 target with up to 32 features are the tile kernel's");
     static constexpr int kTab = (kResidual ? 0 : kFtabDoubles) + kLogTabDoubles;
     static constexpr int kQ = kResidual && NC == 16 ? 4 : 1;  // rows of a tile that a lane keeps log-likelihoods of apart
     // partial gradients: one slot per wave, or, where eight do not fit beside the tables, one per pair of waves
@@ -536,7 +537,7 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
                 double z4;
                 if (NC == 16) {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) z[q] = (!ragged || 4 * q + (lane >> 4) < ta.rem_rows) ? z0 : 0.0;
+                    for (int q = 0; q < 4; ++q) z[q] = 0.0;
                 } else {
                     z4 = (!ragged || 4 * ((lane >> 2) & 3) + (lane >> 4) < ta.rem_rows) ? z0 : 0.0;
                 }
@@ -557,55 +558,40 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
                     for (int i = 0; i < 2 * MT; ++i)
                         if (i < 2 * MT - 2 || i < pairs1) a1[i] = load_at(next + i * 1024);
                 }
+                // residual of one row, and its share of the log-likelihood (an infinite or NaN logit makes the sum a NaN; rows
+                // beyond the last one count nothing)
+                auto row = [&](const double zr, const int first, double& sum, double& product) __attribute__((always_inline)) -> double {
+                    double resid, sig;
+                    logistic_residual(zr, resid, sig);
+                    sum += fabs(zr) - zr;
+                    product *= (!ragged || first + (lane >> 4) < ta.rem_rows) ? sig : 1.0;
+                    return resid;
+                };
                 double sg[4];
-                if (S::kResidual) {
-                    // (an infinite or NaN logit makes the sum a NaN; rows beyond the last one count nothing)
-                    auto row = [&](const double zr, const int first, double& sum, double& product) __attribute__((always_inline)) -> double {
-                        double resid, sig;
-                        logistic_residual(zr, resid, sig);
-                        sum += fabs(zr) - zr;
-                        product *= (!ragged || first + (lane >> 4) < ta.rem_rows) ? sig : 1.0;
-                        return resid;
-                    };
-                    if (NC == 16) {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            sg[q] = row(z[q], 4 * q, sum_abs[q < S::kQ ? q : 0], prod[q < S::kQ ? q : 0]);
-                            if (q == 1) __builtin_amdgcn_sched_barrier(0);  // (two at a time: fewer registers)
-                        }
-                    } else {
-                        const double x = row(z4, 4 * ((lane >> 2) & 3), sum_abs[0], prod[0]);
-                        sg[0] = spread_quad<0>(x);
-                        sg[1] = spread_quad<1>(x);
-                        sg[2] = spread_quad<2>(x);
-                        sg[3] = spread_quad<3>(x);
-                    }
-                } else if (NC == 16) {
-                    const double zq[4] = {z[0], z[1], z[2], z[3]};
-                    double slope[4];
-                    logistic_slopes<4>(zq, sFtab, slope);
+                if (NC == 16) {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        sg[q] = __builtin_copysign(slope[q], zq[q]);
-                        asm("v_add_f64 %0, %0, |%1|" : "+v"(sum_abs[0]) : "v"(zq[q]));
+                        sg[q] = row(z[q], 4 * q, sum_abs[q < S::kQ ? q : 0], prod[q < S::kQ ? q : 0]);
+                        if (q == 1) __builtin_amdgcn_sched_barrier(0);  // (two at a time: fewer registers)
                     }
-                    prod[0] *= ((fabs(sg[0]) + 0.5) * (fabs(sg[1]) + 0.5)) * ((fabs(sg[2]) + 0.5) * (fabs(sg[3]) + 0.5));
                 } else {
-                    const double slope = logistic_slope(z4, sFtab);
-                    const double x = __builtin_copysign(slope, z4);
+                    const double x = S::kResidual ? row(z4, 4 * ((lane >> 2) & 3), sum_abs[0], prod[0])
+                                                  : __builtin_copysign(logistic_slope(z4, sFtab), z4);
                     // rows 4s + k of the tile sit in quad s: every block of the second GEMM wants them
                     sg[0] = spread_quad<0>(x);
                     sg[1] = spread_quad<1>(x);
                     sg[2] = spread_quad<2>(x);
                     sg[3] = spread_quad<3>(x);
-                    // Sums and products in the order of the 16-chain form, where one lane holds the tile's rows k, 4 + k, 8 + k and
-                    // 12 + k: here quad 0 of every row of 16 lanes gets them so (what the other quads add up is not used).  They
-                    // run while the swizzles above are under way.  (1000 x 25, 512 chains, 20 iterations: 2.21 ms with a sum
-                    // per lane, 2.39 so.)
-                    const double a = fabs(z4), f = fabs(x) + 0.5, f2 = f * quad_after<1>(f);
-                    sum_abs[0] = (((sum_abs[0] + a) + quad_after<1>(a)) + quad_after<2>(a)) + quad_after<3>(a);
-                    prod[0] *= f2 * quad_after<2>(f2);
-                    __builtin_amdgcn_sched_barrier(0);
+                    if (!S::kResidual) {
+                        // Sums and products in the order of the tile kernel, where one lane holds the tile's rows k, 4 + k, 8 + k
+                        // and 12 + k: here quad 0 of every row of 16 lanes gets them so (what the other quads add up is not used).
+                        // They run while the swizzles above are under way.  (1000 x 25, 512 chains, 20 iterations: 2.21 ms with
+                        // a sum per lane, 2.39 so.)
+                        const double a = fabs(z4), f = fabs(x) + 0.5, f2 = f * quad_after<1>(f);
+                        sum_abs[0] = (((sum_abs[0] + a) + quad_after<1>(a)) + quad_after<2>(a)) + quad_after<3>(a);
+                        prod[0] *= f2 * quad_after<2>(f2);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
 #pragma unroll
                 for (int u = 0; u < MT; ++u)
@@ -814,10 +800,14 @@ inline size_t wide_block_bytes(int d, int dtype_bytes, int nc, int max_depth)
 template <typename T, int MT>
 inline void wide_launch_mt(const WideArgs& wa, const DevSample& sa, int nc, int blocks, hipStream_t stream)
 {
-    if (nc == 4)
-        hipLaunchKernelGGL((nuts_wide_kernel<T, MT, 4>), dim3((unsigned)blocks), dim3(kTileThreads), 0, stream, wa, sa);
-    else
-        hipLaunchKernelGGL((nuts_wide_kernel<T, MT, 16>), dim3((unsigned)blocks), dim3(kTileThreads), 0, stream, wa, sa);
+    // (binary64 with up to 32 features: sixteen chains per workgroup are the tile kernel's)
+    if constexpr (sizeof(T) == 4 || MT > 2) {
+        if (nc == 16) {
+            hipLaunchKernelGGL((nuts_wide_kernel<T, MT, 16>), dim3((unsigned)blocks), dim3(kTileThreads), 0, stream, wa, sa);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((nuts_wide_kernel<T, MT, 4>), dim3((unsigned)blocks), dim3(kTileThreads), 0, stream, wa, sa);
 }
 template <typename T>
 inline void wide_launch(const WideArgs& wa, const DevSample& sa, int nc, int blocks, hipStream_t stream)
