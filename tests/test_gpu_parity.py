@@ -1464,3 +1464,43 @@ def test_grid_kernels_on_four_streams_give_the_bits_of_two():
     sync = gpu_run(w, tgt=tgt, schedule=1, n_iters=3)
     for k in range(3):
         assert np.array_equal(g[k][:, 960:], few[k]) and np.array_equal(g[k][:3], sync[k])
+
+
+@pytest.mark.parametrize("form,dim,dtype", [("wide", 40, np.float64), ("wide", 100, np.float64), ("wide", 17, np.float32), ("wide", 40, np.float32),
+                                            ("band", 130, np.float64), ("band", 300, np.float32), ("band", 1025, np.float64),
+                                            ("elem", 513, np.float64), ("elem", 1025, np.float32), ("elem", 2048, np.float64), ("elem", 64, np.float32)])
+def test_chains_that_start_far_out_or_not_finite(form, dim, dtype):
+    """Infinite, NaN and overflowing starting points: their chains stay where they are, the others do not notice."""
+    rng = np.random.default_rng(dim)
+    huge = 1e200 if dtype is np.float64 else 1e30
+    init = rng.standard_normal((13, dim)) * (3 if form == "wide" else 1)
+    init[3] = huge
+    init[5, dim // 2] = -huge
+    init[7] = np.inf
+    init[8, 0] = -np.inf
+    init[10, dim - 1] = np.nan
+    if form == "wide":
+        w = wide_workload(90, dim, dtype, 13)
+    elif form == "band":
+        w = W.Workload("far_band", W.GAUSS_DENSE, dim, np.dtype(dtype), 13, 4, 0.3, 6, seed=5, precision=W.ar1_precision(dim, 0.8).astype(dtype))
+    else:
+        w = W.Workload("far_elem", W.GAUSS_DIAG, dim, np.dtype(dtype), 13, 4, 0.3, 6, seed=5, scales=(10.0 ** rng.uniform(-1, 1, dim)).astype(dtype))
+    tgt = gpu_target(w)
+    for kw in (dict(), dict(sampler=SLICE, leaf_steps=3)):
+        g = gpu_run(w, tgt=tgt, init=init, **kw)
+        with np.errstate(all="ignore"):
+            r = ref_run(w, init=init, **kw)
+        assert np.array_equal(np.isfinite(g[0]), np.isfinite(r[0]))
+        assert np.array_equal(np.isnan(g[0]), np.isnan(r[0]))
+        out = [3, 5, 7, 8, 10]
+        assert np.array_equal(g[1][:, out], r[1][:, out]) and np.array_equal(g[2][:, out], r[2][:, out])
+        keep = [c for c in range(13) if c not in out]
+        if dtype is np.float64:
+            assert_parity([x[:, keep] for x in g[:3]], [x[:, keep] for x in r], F64_TOL, label=f"{w.name} {kw}")
+        else:
+            f32_parity([x[:, keep] for x in g[:3]], [x[:, keep] for x in r])
+        if form == "wide":                                    # sixteen chains per workgroup
+            more = np.concatenate([init, rng.standard_normal((2087, dim))])
+            many = gpu_run(w, tgt=tgt, init=more, n_chains=2100, n_iters=2, **kw)
+            for k in range(3):
+                assert np.array_equal(many[k][:, :13], g[k][:2], equal_nan=k == 0)

@@ -80,3 +80,57 @@ def test_static_entry_point_refuses_what_does_not_fit_or_would_allocate():
     b = B.nuts_sample(tgt, w.n_chains, 3, w.step_size, w.max_tree_depth, w.seed)
     torch.cuda.synchronize()
     assert all(bool(torch.equal(x, y)) for x, y in zip(a, b))
+
+
+def _stand_in(form):
+    """Targets whose automatic kernel stands in for the wave kernel, or is another form of the tile kernel."""
+    import paper_1910_11141_amd.binding as B
+    from paper_1910_11141_amd import workloads as W
+    f64, f32 = np.dtype(np.float64), np.dtype(np.float32)
+    if form == "band":
+        w = W.Workload("band", W.GAUSS_DENSE, 200, f64, 0, 0, 0.2, 7, seed=3, precision=W.ar1_precision(200, 0.8))
+    elif form == "block":
+        w = W.Workload("block", W.GAUSS_DENSE, 250, f64, 0, 0, 0.2, 7, seed=3, precision=W.random_spd_precision(250, 4))
+    elif form == "elem":
+        w = W.Workload("elem", W.GAUSS_DIAG, 1500, f32, 0, 0, 0.05, 7, seed=3, scales=np.linspace(0.5, 2.0, 1500).astype(np.float32))
+    elif form == "elem variant":
+        w = W.Workload("elem", W.GAUSS_DIAG, 1000, f32, 0, 0, 0.05, 7, seed=3, scales=np.linspace(0.5, 2.0, 1000).astype(np.float32))
+    elif form == "wide":
+        w = W.small_logreg(400, 60, seed=8)
+        w.step_size, w.max_tree_depth = 0.03, 7
+    elif form == "wide, binary32":
+        w = W.small_logreg(300, 17, seed=8, dtype=np.float32)
+        w.step_size, w.max_tree_depth = 0.03, 7
+    else:
+        w = W.small_logreg(300, 9, seed=8)
+        w.step_size, w.max_tree_depth = 0.03, 12
+    return B, w, B.Target(w.kind, w.dim, w.dtype, precision=w.precision, scales=w.scales, X=w.X, y=w.y, prior_scale=w.prior_scale)
+
+
+@pytest.mark.parametrize("form", ["band", "block", "elem", "elem variant", "wide", "wide, binary32", "four chains"])
+def test_static_entry_point_of_the_kernels_that_stand_in_for_others(form):
+    """The same outputs as the allocating entry point, and refused where the wave kernel's workspace (for the
+    element-wise variant its own formula) would not fit.  In between lie runs that are taken and do not fit as they
+    would like to: fewer workgroups run, the others' chains wait in the queue."""
+    B, w, tgt = _stand_in(form)
+    fewer, refused, taken, chains = 0, 0, 0, 8
+    while chains <= 8192 and not refused:
+        try:
+            got, st = _run(B, tgt, w, chains, 2, True)
+        except B.NutsError as e:
+            assert e.code == B.NUTS_E_UNSUPPORTED and "bytes of scratch" in str(e)
+            refused = chains
+            break
+        want, st_want = _run(B, tgt, w, chains, 2, False)
+        for a, b in zip(want, got):
+            assert np.array_equal(a, b)
+        assert st["variant"] == st_want["variant"] and st["leaf_slots_useful"] == st_want["leaf_slots_useful"]
+        fewer += st["grid_blocks"] < st_want["grid_blocks"]
+        taken = chains
+        chains = chains * 5 // 4 + 3
+    print(f"{form}: taken up to {taken} chains, refused {refused}, fewer workgroups in {fewer} runs", flush=True)
+    assert taken >= 8
+    if form in ("band", "block", "elem", "elem variant"):
+        assert refused
+    if form in ("elem", "elem variant"):
+        assert fewer
