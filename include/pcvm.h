@@ -98,8 +98,11 @@ int pcvm_run(const pcvm_program* program, int64_t batch, const int64_t* inputs, 
 /* The same, with members handed to lanes from a queue (Section 4.2 of the paper applied to the machine itself:
  * executions are batched across their boundaries).  At most as many groups as the chip holds at once are
  * started; a lane whose member has halted writes its output and takes the next unclaimed member, so the lanes
- * of a group stay busy until the batch runs dry, and the stacks need (n_vars * 8 + 4) * stack_depth bytes per
- * resident lane instead of per member.  Outputs are those of pcvm_run; which members share a group depends on
+ * that take members stay busy until the batch runs dry, and the stacks need (n_vars * 8 + 4) * stack_depth bytes per
+ * resident lane instead of per member.  A small program (up to 64 blocks and operations) with fewer members than 64
+ * per SIMD of the chip is spread over one group per SIMD in which only some lanes take members: members then wait less
+ * for each other, and issued_member_steps, which charges whole groups, makes utilisation small however little
+ * they diverge.  Outputs are those of pcvm_run; which members share a group depends on
  * timing, so steps and utilisation vary a little from run to run and there is no trace.  max_steps bounds the
  * group steps one member may stay in flight; policy is PCVM_SCHED_*. */
 int pcvm_run_queued(const pcvm_program* program, int64_t batch, const int64_t* inputs, int32_t stack_depth,

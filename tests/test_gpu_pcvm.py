@@ -215,3 +215,19 @@ def test_stack_rings_spill_and_refill_at_any_depth(depth):
         return
     for kw in (dict(), dict(queued=True), dict(queued=True, policy=1)):
         assert np.array_equal(gpu(P, ins, depth, **kw)[0], want)
+
+
+def test_queued_batches_around_the_number_of_lanes_that_take_members():
+    """The first member of a lane is handed out without the queue: batches of one member, of as many as there are lanes, of
+    one more and one less, at each of the group shapes."""
+    import torch
+    simds = 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    rng = np.random.default_rng(9)
+    P = PP.gcd()
+    for batch in (1, 2, 63, 64, 65, simds - 1, simds, simds + 1, 2 * simds, 7 * simds - 3, 64 * simds, 64 * simds + 1, 192 * simds - 1,
+                  192 * simds, 192 * simds + 1, 192 * simds + 4099):
+        ins = rng.integers(1, 10 ** 6, size=(2, batch))
+        want = np.gcd(ins[0], ins[1])
+        for policy in (0, 1):
+            out, stats, _ = gpu(P, ins, 40, queued=True, policy=policy)
+            assert np.array_equal(out, want), (batch, policy)
