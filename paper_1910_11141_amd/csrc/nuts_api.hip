@@ -943,7 +943,11 @@ int nuts_tile_pack(const double* X, const double* y, int64_t n, int64_t d, nuts_
     if (!nuts::tile_supports_shape(d, n)) return fail(NUTS_E_INVALID_ARG, "nuts_tile_pack: shape outside the tile variant's range");
     nuts::TileData td;
     std::vector<double> op, colsum;
-    nuts::tile_pack_operands(X, y, n, d, false, &td, &op, &colsum);
+    try {
+        nuts::tile_pack_operands(X, y, n, d, false, &td, &op, &colsum);
+    } catch (const std::bad_alloc&) {
+        return fail(NUTS_E_ALLOC, "out of host memory");
+    }
     layout->ks1 = td.ks1;
     layout->mt = td.mt;
     layout->n_tiles = td.n_tiles;
@@ -996,8 +1000,12 @@ int nuts_create_target(const nuts_target_desc* desc, nuts_target** out)
     const bool have_device = hipGetDeviceCount(&n_dev) == hipSuccess && n_dev >= 1;
     if (desc->kind != NUTS_TARGET_STD_NORMAL || have_device) {  // the standard normal has no data: it needs no device yet
         rc = ensure_device(t);
-        if (!rc) rc = desc->dtype == NUTS_F64 ? build_device_data<double>(t, desc) : build_device_data<float>(t, desc);
-        if (!rc && t->grid.ops) rc = ensure_ftab(t);
+        try {  // (operand streams take up to twice the data's size on the host)
+            if (!rc) rc = desc->dtype == NUTS_F64 ? build_device_data<double>(t, desc) : build_device_data<float>(t, desc);
+            if (!rc && t->grid.ops) rc = ensure_ftab(t);
+        } catch (const std::bad_alloc&) {
+            rc = fail(NUTS_E_ALLOC, "out of host memory");
+        }
         if (rc) {
             release(t);
             return rc;

@@ -3,6 +3,8 @@ on the host before touching a device.  No compute happens here."""
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -250,3 +252,25 @@ def test_tile_pack_rejects_bad_arguments_on_the_host():
     assert lay.operand_doubles > 8      # the layout is filled all the same
     rc = B.lib().nuts_tile_pack(None, y.ctypes.data_as(C.c_void_p), C.c_int64(10), C.c_int64(5), C.byref(lay), None, C.c_int64(0))
     assert rc == B.NUTS_E_INVALID_ARG
+
+
+def test_out_of_host_memory_is_an_error_code_and_no_exception():
+    """The packing of operands allocates on the host; in a process that may take little more memory that fails, and the
+    call says so."""
+    code = """
+import resource, sys
+import numpy as np
+import paper_1910_11141_amd.binding as B
+B.lib()
+X, y = np.ones((400000, 25)), np.ones(400000)
+X[::2] = 2.0
+used = int(open('/proc/self/statm').read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (used + (64 << 20), resource.RLIM_INFINITY))
+lay = B.nuts_tile_layout()
+import ctypes as C
+rc = B.lib().nuts_tile_pack(X.ctypes.data_as(C.c_void_p), y.ctypes.data_as(C.c_void_p), C.c_int64(400000), C.c_int64(25), C.byref(lay), None, C.c_int64(0))
+print(rc, B.nuts_last_error())
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr[-1000:]
+    assert r.stdout.split()[:1] == [str(B.NUTS_E_ALLOC)] and "memory" in r.stdout
