@@ -178,12 +178,12 @@ struct GridArgs {
 // and 1.05, one awaited 0.89 and 1.03; 512 chains, 50 iterations 0.99 to 1.01, one 0.80; 100 000 x 100, 512 to 1024 chains, 12
 // iterations 1.01 to 1.03; 3000 x 9 0.4 to 0.93 throughout (every launch has a cost of its own, and the host has to keep up:
 // 20 000 x 25, 512 to 4096 chains, 12 to 50 iterations 1.00 to 1.05 with a fast one, 0.86 to 0.93 with a slower one).
-// A target's first launch with four takes 5 ms more than with two, to create the streams: only launches of some 130 ms
-// (1.2e11 chain iterations x rows x features) save about as much.
+// A target's first launch with four takes 5 ms more than with two, to create the streams: only launches of some 110 ms
+// (1e11 chain iterations x rows x features) save as much.
 inline int grid_streams(int n_slots, long n, int d, double chain_iters)
 {
     const double work = (double)n * d;
-    return n_slots > 512 && work >= 1e6 && chain_iters >= 12.0 * n_slots && chain_iters * work >= 1.2e11 ? 4 : 2;
+    return n_slots > 512 && work >= 1e6 && chain_iters >= 12.0 * n_slots && chain_iters * work >= 1e11 ? 4 : 2;
 }
 
 // ------------------------------------------------------------------ gradient
