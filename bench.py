@@ -82,6 +82,24 @@ def profile_json(kind, kernel, workload_name):
     return json.load(open(path)) if os.path.exists(path) else None
 
 
+KERNEL_HEADERS = {"nuts_grid_grad_kernel": "nuts_grid.h"}  # where it is not the kernel's name
+
+
+def kernel_code_id(kernel, csrc=os.path.join(ROOT, "paper_1910_11141_amd", "csrc")):
+    """A hash over the headers that a kernel is made of, comments and white space left out: counters taken of other
+    code say nothing about this one."""
+    import hashlib
+    import re
+    todo, seen = [KERNEL_HEADERS.get(kernel, kernel.replace("_kernel", ".h"))], {}
+    while todo:
+        name = todo.pop()
+        if name not in seen:
+            text = open(os.path.join(csrc, name)).read()
+            todo += re.findall(r'#include "(nuts_\w+\.h)"', text)
+            seen[name] = "".join(re.sub(r"/\*.*?\*/|//[^\n]*", "", text, flags=re.S).split())
+    return hashlib.sha256("\0".join(f"{k}\0{v}" for k, v in sorted(seen.items())).encode()).hexdigest()[:16]
+
+
 def roofline_of(w, workloads, stats, n_grad, kernel_s, plain_run):
     """The roofline line of the kernel that ran, on the method's own work per gradient evaluation:
       logistic regression      4 N d flop (the two GEMMs) against the matrix peak of its dtype ("mfma");
@@ -91,7 +109,7 @@ def roofline_of(w, workloads, stats, n_grad, kernel_s, plain_run):
                                register kernel does these on the vector ALUs, one chain per wavefront, and what
                                limits it is the latency of one chain's serial step, not a throughput;
       element-wise Gaussians   4 d sizeof(T) bytes (position and momentum in and out) against HBM ("hbm").
-    `traffic` is the HBM-side bytes of one launch from the committed counter summary of the same kernel and
+    `traffic` is the HBM-side bytes of one launch from the committed counter summary of the same kernel code and
     chain count (bytes per gradient evaluation there x this launch's evaluations), or null; `wasted_traffic`
     the ratio of that to the algorithmic bytes.  Where the kernel moves fewer bytes than the basis charges
     (so that the basis fraction would exceed 1), `frac` is the fraction of the HBM peak it really draws."""
@@ -121,6 +139,9 @@ def roofline_of(w, workloads, stats, n_grad, kernel_s, plain_run):
     roof["frac"] = roof["achieved"] / roof["peak"]
     roof["traffic"] = None
     t = profile_json("traffic", kernel, w.name)
+    if t and t.get("code") != kernel_code_id(kernel):
+        roof["traffic_note"] = "the committed traffic counters are of other code than this kernel's"
+        t = None
     if t and "bytes_per_grad_eval" in t and t["n_chains"] == w.n_chains and plain_run:
         roof["traffic"] = t["bytes_per_grad_eval"] * n_grad
         roof["traffic_unit"] = ("bytes/launch: bytes per gradient evaluation from the committed rocprofv3 FETCH_SIZE + WRITE_SIZE "
@@ -232,8 +253,8 @@ def make_traffic_json(a):
         raise SystemExit("the databases hold no FETCH_SIZE / WRITE_SIZE dispatches of " + family)
     fs, ws = copy_scale(a.fetch_db, "FETCH_SIZE", a.copy_kib), copy_scale(a.write_db, "WRITE_SIZE", a.copy_kib)
     n_grad = line["grad_evals_per_step"]
-    out = {"kernel": kernel, "workload": line["config"]["workload"], "n_chains": line["config"]["n_chains"],
-           "n_iters": line["config"]["n_iters"], "grad_evals_per_launch": n_grad,
+    out = {"kernel": kernel, "code": kernel_code_id(kernel), "workload": line["config"]["workload"],
+           "n_chains": line["config"]["n_chains"], "n_iters": line["config"]["n_iters"], "grad_evals_per_launch": n_grad,
            "fetch_bytes_per_launch": fetch * fs * 1024.0, "write_bytes_per_launch": write * ws * 1024.0,
            "fetch_scale": fs, "write_scale": ws,
            "bytes_per_grad_eval": (fetch * fs + write * ws) * 1024.0 / n_grad,
