@@ -48,7 +48,8 @@ enum {
                                AUTO steps dense Gaussians of 128 < dim <= 512 whose matrix is not banded in
                                lock step, 4 or 8 wavefronts per workgroup with their products on the matrix
                                cores, and keeps those of banded ones (dim <= 2048) in registers; it reports
-                               both under this number                                                       */
+                               both under this number.  Asked for by it the general kernel runs: the same
+                               bits as for banded matrices, another order of the sums for the others        */
     NUTS_VARIANT_TILE = 2,  /* 16 chains per workgroup in lock step, gradient as MFMA GEMMs (logistic
                                regression, binary64, dim <= 32, max_tree_depth <= 12); when dim = 1 mod 4
                                and a column of X is the same non-zero value in every row (an intercept),

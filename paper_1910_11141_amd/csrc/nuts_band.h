@@ -6,8 +6,9 @@
 //
 // What bounds it: the latency of the chain program (few chains), or the vector instructions of gradient, leaf and merge.
 // Against nine entries of a row in the general wave kernel, which keeps every vector in memory: two iterations, AR(1), binary64: d = 129, 4
-// chains 0.50 -> 0.14 ms; d = 1000, 1024 chains 3.3 -> 0.68 ms; d = 2000, 4096 chains 21.4 -> 14.1 ms (there the state no
-// longer fits the registers).  Same outputs, bit for bit.
+// chains 0.50 -> 0.14 ms; d = 1000, 1024 chains 3.3 -> 0.68 ms; d = 2000, 4096 chains 21.4 -> 14.1 ms.  Beyond 512 dimensions in
+// binary64 and 1024 in binary32 the state no longer fits the registers: scratch memory per lane is 460 bytes at kC = 8 and 2880
+// at 16 in binary64, 1724 at 16 (and 80 at 4, for two workgroups per compute unit) in binary32.  Same outputs, bit for bit.
 #pragma once
 #include "nuts_row.h"
 

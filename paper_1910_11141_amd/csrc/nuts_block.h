@@ -12,7 +12,8 @@
 // What bounds it: the operand stream, which a compute unit takes from L2 at about 45 bytes per tick (d = 256: 0.5 MB in
 // 11.5 k ticks, of which the instructions of 4 chains need 4.1 k, of 8 chains 8.2 k), then the chain program (5 k ticks).
 // A form with 16 chains and v_mfma_f64_16x16x4 was matrix-bound at 21 k ticks, and its 16 waves left 128 registers to
-// the chain program, which then took 45 k.  Binary32 targets keep binary64 sums of binary32 values, as in the wave kernel.
+// the chain program, which then took 45 k.  (These forms keep 48 to 52 bytes a lane in scratch memory at kC = 2 in binary64, 164
+// to 172 at 3 and 396 at 4; in binary32 none, at 4 56.)  Binary32 targets keep binary64 sums of binary32 values, as in the wave kernel.
 // d = 250, binary64, 300 chains, every iteration awaited, 10 iterations: 34.3 ms (wave kernel) -> 2.5 ms.
 #pragma once
 #include <hip/hip_runtime.h>

@@ -46,9 +46,10 @@ constexpr int kQuadWaves = 4;      // wavefronts per workgroup, one per SIMD
 constexpr int kQuadThreads = kQuadWaves * kWave;
 constexpr int kQuadPitch = 144;    // doubles per chain in the LDS staging area (128 + 16: rows of different chains on different banks)
 constexpr int kQuadVecLen = 128;   // doubles per workspace vector
-constexpr long kQuadAutoChains = 2560;  // automatic choice: from this many chains on (10 per compute unit; measured
-                                        // at d = 100: level with the one-chain-per-wavefront kernel at 2048 chains,
-                                        // twice its rate from 4096 on)
+// Automatic choice: from this many chains on (10 per compute unit).  60 iterations at 2048, 2560 and 4096 chains, ms with the
+// one-chain-per-wavefront kernel and with this one: d = 30 6.5 / 7.2, 9.7 / 7.4, 13.0 / 7.8; d = 64 7.4 / 7.5, 11.0 / 7.6, 14.7 / 8.0;
+// d = 100 8.5 / 9.8, 12.6 / 9.8, 16.9 / 10.1; d = 128 11.0 / 11.1, 16.1 / 11.2, 21.9 / 11.5.
+constexpr long kQuadAutoChains = 2560;
 
 struct QuadData {
     double* ops = nullptr;  // device: P in MFMA operand order, see quad_pack_operands

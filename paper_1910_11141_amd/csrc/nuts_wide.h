@@ -25,7 +25,8 @@
 // vector ALUs: binary64, 512 chains, 5000 x 60: 1.1e5 -> 5.5e6 gradient evaluations per second; binary32, 250 chains, 700 x 17,
 // slice sampler, four steps a leaf: 3.6e6 -> 5.0e7.  What the residuals cost against the tile kernel's functions: 700 x 17 in
 // binary32, 4096 chains, 10 iterations 2.0 -> 2.5 ms; 1000 x 60, 4096 chains, 4 iterations 2.39 -> 2.55; 1000 x 120 3.74 -> 3.85;
-// with four chains per workgroup nothing to 6 % (3000 x 5: 19 %).
+// with four chains per workgroup nothing to 6 % (3000 x 5: 19 %).  Scratch memory per lane: with sixteen chains 48 bytes (MT = 3)
+// to 492 (MT = 8) in binary64, 32 to 412 in binary32 (none at MT = 1 and 3); with four at most 44.
 #pragma once
 #include <hip/hip_runtime.h>
 

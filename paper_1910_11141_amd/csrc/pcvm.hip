@@ -269,7 +269,7 @@ __global__ __launch_bounds__(kWave* kWavesPerBlock) void pcvm_kernel(VmArgs va)
 //     to a spare row), jumps, branches and calls; what is rare is out of line,
 //   * the block most lanes wait for is found by counting lanes block by block, eight at a time.
 // That step takes 2280 ticks (1690 with one group per SIMD).  200 000 members: fibonacci 71.5 -> 33.8 ms in fixed groups,
-// 46.6 -> 39.8 queued with MOST_WAITING; collatz_steps 1.62 -> 0.86; binomial (176 408, queued) 6.4 -> 4.7.
+// 46.6 -> 38.4 queued with MOST_WAITING; collatz_steps 1.62 -> 0.86; binomial (176 408, queued) 6.4 -> 4.7.
 constexpr int kSmallMax = 64;
 
 // Operation classes.  Move, add and subtract are one expression, (a & keep) + (b ^ flip) - flip; immediates lie in LDS
