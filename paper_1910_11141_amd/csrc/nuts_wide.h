@@ -16,7 +16,7 @@
 //     of 4 features (second GEMM) of the 16x16x4 instruction's operands in the same lanes, and an element of the result
 //     is accumulated in the same order, as is the log-likelihood: a chain has the same bits whichever form stepped it
 //     (with up to 32 features and binary64 the 16-chain form is the kernel of nuts_tile.h).
-// The number of chains decides between the two forms (wide_chains_per_block below).
+// The numbers of chains, rows and iterations decide between the two forms (wide_chains_per_block below).
 //
 // What bounds it: with 16 chains the matrix instructions (1000 rows x 120 features: 63.5 k of the gradient phase's 83 k ticks,
 // its logistic functions another 10 k; with few features the latter: 3000 x 5 in binary32 38 k of 58 k); with 4 chains the
@@ -50,7 +50,7 @@ struct WideShape {
     static_assert(kResidual || NC == 4, "16 chains of a binary64 target with up to 32 features are the tile kernel's");
     static constexpr int kTab = (kResidual ? 0 : kFtabDoubles) + kLogTabDoubles;
     static constexpr int kQ = kResidual && NC == 16 ? 4 : 1;  // rows of a tile that a lane keeps log-likelihoods of apart
-    // partial gradients: one slot per wave, or, where eight do not fit beside the tables, one per pair of waves
+    // partial gradients: one slot per wave, or, where eight would take the tree levels' place, one per pair of waves
     static constexpr int kSlots = (NC == 16 && MT > 2) ? 4 : kTileWaves;
     // With more than two feature tiles the waves' partial sums are added in pairs (w, w + 4) first, in both forms.
     static constexpr bool kPairs = MT > 2;

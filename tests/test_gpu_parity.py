@@ -1218,7 +1218,7 @@ def test_wide_kernel_f32_small_data_sets_keep_the_sums_of_the_wave_kernel(n_data
 
 @pytest.mark.parametrize("n_chains", [1, 5, 1023])
 def test_tile_kernel_four_chain_form_deep_trees_divergences_and_options(n_chains):
-    """Up to 8 chains per compute unit the tile variant steps 4 chains per workgroup: the same bits as 16 per workgroup."""
+    """Up to 4 chains per compute unit the tile variant steps 4 chains per workgroup: the same bits as 16 per workgroup."""
     w = W.small_logreg(50, 5, seed=6)
     w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = n_chains, 8, 0.5, 7
     init = np.random.default_rng(1).standard_normal((n_chains, 5)) * 8
