@@ -122,33 +122,66 @@ __device__ __forceinline__ double read_lane(double x, int src_lane)
     return __hiloint2double(hi, lo);
 }
 
-// Sums over the 64 lanes of a wave (all lanes active).  Inside each row of 16 lanes: rotations by
-// 8, 4, 2, 1 (DPP, no LDS traffic; at each step the two partners add the same pair of values, so a
-// row's lanes end with the same bits).  The four row totals are then read as scalars and added in
-// one fixed order, so every lane of the wave holds the same bits.
-__device__ __forceinline__ double wave_sum(double x)
+// Sums over the 64 lanes of a wave (all lanes active), up to four of them in one pass.  The halves of the wave change places
+// first, then the rows of 16 lanes: where two sums are wanted each ends up with half of the lanes, of four each with a row, and
+// what is left - rotations by 8, 4, 2, 1 inside the rows (DPP, no LDS traffic) - is done once for all of them.  A sum's terms are
+// added in the same order whichever of these functions takes it, and both partners of a step add the same pair of values, so
+// every lane of a row ends with the same bits.  Two sums are 24 instructions (two by rotations alone and the four row totals
+// read as scalars: 48, half of them waiting for the one before), four are 29.
+__device__ __forceinline__ double fold_halves(double a, double b)  // lanes 0..31: a[l] + a[l + 32]; 32..63: b[l - 32] + b[l]
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+__device__ __forceinline__ double fold_rows(double x, double y)  // rows: x0 + x1, y0 + y1, x2 + x3, y2 + y3
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(x), (unsigned)__double2loint(y), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(y), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+__device__ __forceinline__ double row_sum(double x)
 {
     x += dpp_rotate<0x128>(x);  // row_ror:8
     x += dpp_rotate<0x124>(x);  // row_ror:4
     x += dpp_rotate<0x122>(x);  // row_ror:2
     x += dpp_rotate<0x121>(x);  // row_ror:1
-    return (read_lane(x, 0) + read_lane(x, 16)) + (read_lane(x, 32) + read_lane(x, 48));
+    return x;
+}
+// a in lanes 0..31, b in lanes 32..63
+__device__ __forceinline__ double wave_sum_halves(double a, double b)
+{
+    const double x = fold_halves(a, b);
+    return row_sum(fold_rows(x, x));
+}
+// rows of 16 lanes: a, c, b, d
+__device__ __forceinline__ double wave_sum_rows(double a, double b, double c, double d)
+{
+    return row_sum(fold_rows(fold_halves(a, b), fold_halves(c, d)));
 }
 
-__device__ __forceinline__ void wave_sum2(double& a, double& b)
+// What lanes 0..31 hold (all the same) in every lane, and what lanes 32..63 hold.  (Not through scalar registers: an
+// instruction that wants a scalar a vector instruction has just made waits some 50 ticks.)
+__device__ __forceinline__ void spread_halves(double x, double& lower, double& upper)
 {
-    a += dpp_rotate<0x128>(a);
-    b += dpp_rotate<0x128>(b);
-    a += dpp_rotate<0x124>(a);
-    b += dpp_rotate<0x124>(b);
-    a += dpp_rotate<0x122>(a);
-    b += dpp_rotate<0x122>(b);
-    a += dpp_rotate<0x121>(a);
-    b += dpp_rotate<0x121>(b);
-    a = (read_lane(a, 0) + read_lane(a, 16)) + (read_lane(a, 32) + read_lane(a, 48));
-    b = (read_lane(b, 0) + read_lane(b, 16)) + (read_lane(b, 32) + read_lane(b, 48));
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(x), (unsigned)__double2loint(x), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(x), false, false);
+    lower = __hiloint2double((int)hi[0], (int)lo[0]);
+    upper = __hiloint2double((int)hi[1], (int)lo[1]);
 }
+// Rows 0 and 2 in both rows of their half.
+__device__ __forceinline__ double spread_even_rows(double x)
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(x), (unsigned)__double2loint(x), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(x), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]);
+}
+
+__device__ __forceinline__ double wave_sum(double x) { return wave_sum_halves(x, x); }
+__device__ __forceinline__ void wave_sum2(double& a, double& b) { spread_halves(wave_sum_halves(a, b), a, b); }
 
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+// A condition that all lanes agree on, as a scalar: what is decided by it can stay in scalar registers.
+__device__ __forceinline__ bool agreed(bool x) { return __ballot(x) != 0; }
 
 }  // namespace nuts

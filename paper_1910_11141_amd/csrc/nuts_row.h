@@ -3,15 +3,19 @@
 // The recursion over the trajectory's tree needs no return stack here.  Leaf m (1-based) of a doubling of 2^j leaves
 // completes the subtrees of levels 1 .. ctz(m), and unless it is the last leaf the subtree it leaves behind is the left
 // half of the one of level ctz(m) + 1: the pair (j, m) says where the program stands, and a leaf or a span that must not
-// be continued ends the whole doubling.  The lanes of a wave agree on it, so every branch is a scalar one.
+// be continued ends the whole doubling.  The lanes of a wave agree on it; what is decided by vector arithmetic becomes a scalar
+// by a vote (agreed), so every branch is a scalar one and the program's state stays in scalar registers.
 //
 // A step of one chain is a serial chain of instructions, and with few chains its latency is all that counts (d = 100
-// banded, 1024 chains, one wave per SIMD: leaf 1315 ticks, merge 1080, left half 480).  What is done about it here:
+// banded, 1024 chains, one wave per SIMD: a step takes 0.9 us).  What is done about it here:
 //   * the lowest level of the tree stays in registers (an odd leaf is kept until its neighbour has been merged with it),
 //   * the first leaves of the next levels and the pool's first buffers are in LDS as far as it reaches (n_first, n_pool),
 //   * the other end of the trajectory and the proposal are in registers (kHeld),
-//   * the uniforms of the merges of four leaves come from one generator pass.
-// d = 100 banded, 1024 chains, 100 iterations: 15.3 ms (tree storage in global memory, a return stack) -> 10.6 ms.
+//   * the uniforms of the merges of four leaves come from one generator pass,
+//   * the sums of a leaf and of the two-leaf span it closes are taken together (wave_sum_rows), sums stay in vector registers,
+//     and memory is addressed in its own space: 10.8 -> 9.26 ms (d = 2, 4 chains: 673 -> 581 us; d = 1000 binary32, 16384 chains,
+//     where instructions bound it: 53.8 -> 48.0 ms).
+// d = 100 banded, 1024 chains, 100 iterations: 15.3 ms (tree storage in global memory, a return stack) -> 9.26 ms.
 #pragma once
 #include "nuts_dev.h"
 #include "nuts_fastmath.h"
@@ -60,12 +64,18 @@ inline RowLds row_lds_split(size_t bytes, int kc, size_t elem, int max_depth, bo
 template <typename T, int kC, bool kHeld, bool kGrad>
 struct RowChain {
     static constexpr int kVpl = 2 * kC, kPitch = 128 * kC;
-    typedef typename RowVec<T>::type Vec;
+    typedef T VecN __attribute__((ext_vector_type(2)));
+    // (pointers of their address spaces: where one of two addresses of different spaces is taken the compiler would
+    // otherwise make a generic pointer of both and flat instructions, which wait for both memories)
+    typedef __attribute__((address_space(1))) T* GlobalPtr;
+    typedef __attribute__((address_space(3))) T* LdsPtr;
+    static __device__ __forceinline__ __attribute__((address_space(1))) VecN* vec_at(GlobalPtr p) { return (__attribute__((address_space(1))) VecN*)p; }
+    static __device__ __forceinline__ __attribute__((address_space(3))) VecN* vec_at(LdsPtr p) { return (__attribute__((address_space(3))) VecN*)p; }
 
     const DevSample& sa;
     const int lane, d, D;
-    T* const ws;     // this slot's vectors in global memory
-    T* const lds;    // this slot's vectors in LDS: n_first pairs, then n_pool pairs
+    const GlobalPtr ws;  // this slot's vectors in global memory
+    const LdsPtr lds;    // this slot's vectors in LDS: n_first pairs, then n_pool pairs
     const RowLds rl;
 
     T th[kVpl], r[kVpl], g[kGrad ? kVpl : 1];     // the end of the trajectory that the current doubling extends
@@ -94,24 +104,26 @@ struct RowChain {
     unsigned long long n_leaf = 0, n_extra = 0;
 
     __device__ RowChain(const DevSample& sa_, int d_, int lane_, T* ws_, T* lds_, RowLds rl_)
-        : sa(sa_), lane(lane_), d(d_), D(sa_.max_depth), ws(ws_), lds(lds_), rl(rl_) {}
+        : sa(sa_), lane(lane_), d(d_), D(sa_.max_depth), ws((GlobalPtr)ws_), lds((LdsPtr)lds_), rl(rl_) {}
 
     __device__ int elem(int q, int e) const { return (q * kWave + lane) * 2 + e; }  // component of register 2q + e
     __device__ DrawKey key() const { return DrawKey{sa.key0, sa.key1}; }
 
-    __device__ __forceinline__ void load(const T* src, T (&dst)[kVpl]) const
+    template <typename P>
+    __device__ __forceinline__ void load(P src, T (&dst)[kVpl]) const
     {
 #pragma unroll
         for (int q = 0; q < kC; ++q) {
-            const Vec x = *reinterpret_cast<const Vec*>(src + elem(q, 0));
-            dst[2 * q] = x.x;
-            dst[2 * q + 1] = x.y;
+            const VecN x = *vec_at(src + elem(q, 0));
+            dst[2 * q] = x[0];
+            dst[2 * q + 1] = x[1];
         }
     }
-    __device__ __forceinline__ void store(T* dst, const T (&src)[kVpl]) const
+    template <typename P>
+    __device__ __forceinline__ void store(P dst, const T (&src)[kVpl]) const
     {
 #pragma unroll
-        for (int q = 0; q < kC; ++q) *reinterpret_cast<Vec*>(dst + elem(q, 0)) = Vec{src[2 * q], src[2 * q + 1]};
+        for (int q = 0; q < kC; ++q) *vec_at(dst + elem(q, 0)) = VecN{src[2 * q], src[2 * q + 1]};
     }
     __device__ __forceinline__ void copy(T (&dst)[kVpl], const T (&src)[kVpl]) const
     {
@@ -189,12 +201,11 @@ struct RowChain {
                 normal_pair(draw(key(), (uint32_t)(i >> 1), tag, 0, iteration, gchain), z0, z1);
                 if (i + 1 >= d) z1 = 0.0;
             }
+            // (the pairs move up by one each time: an index that depends on q would put the array in scratch memory)
 #pragma unroll
-            for (int p = 0; p < kC; ++p)
-                if (p == q) {
-                    out[2 * p] = (T)z0;
-                    out[2 * p + 1] = (T)z1;
-                }
+            for (int i = 0; i + 2 < kVpl; ++i) out[i] = out[i + 2];
+            out[kVpl - 2] = (T)z0;
+            out[kVpl - 1] = (T)z1;
         }
     }
 
@@ -215,18 +226,23 @@ struct RowChain {
         cur_idx = b;
     }
 
-    // (theta+ - theta-) . r at both ends of the span between the extended end and (xt, xr)
-    __device__ __forceinline__ bool no_uturn(const T (&xt)[kVpl], const T (&xr)[kVpl]) const
+    // This lane's shares of (theta+ - theta-) . r at both ends of the span between the extended end and (xt, xr), times the
+    // direction: the difference is taken edge minus (xt), and the sums' sign turned afterwards (negation is exact).
+    __device__ __forceinline__ void span_dots(const T (&xt)[kVpl], const T (&xr)[kVpl], double& da, double& db) const
     {
-        double da = 0.0, db = 0.0;
+        da = db = 0.0;
 #pragma unroll
         for (int i = 0; i < kVpl; ++i) {
-            const T delta = v > 0 ? th[i] - xt[i] : xt[i] - th[i];
+            const T delta = th[i] - xt[i];
             da = fma((double)delta, (double)xr[i], da);
             db = fma((double)delta, (double)r[i], db);
         }
-        wave_sum2(da, db);
-        return (da >= 0.0) && (db >= 0.0);
+    }
+    __device__ __forceinline__ bool no_uturn(const T (&xt)[kVpl], const T (&xr)[kVpl]) const
+    {
+        double da, db;
+        span_dots(xt, xr, da, db);
+        return __ballot((double)v * wave_sum_halves(da, db) >= 0.0) == ~0ull;
     }
 
     // Takes the next chain from the queue; false if there is none.  Its starting point is in th, and the caller owes
@@ -326,8 +342,8 @@ struct RowChain {
         for (int i = 0; i < kVpl; ++i) r[i] = r[i] + half * g[i];
     }
 
-    // One subtree's halves become one: weights added, proposal selected, U-turn test over its span.
-    __device__ __forceinline__ void merge(int level)
+    // One subtree's halves become one: weights added, proposal selected, U-turn test over its span (of two leaves: pair_ok).
+    __device__ __forceinline__ void merge(int level, bool pair_ok)
     {
         T xt[kVpl], xr[kVpl];
         if (level > 1) {
@@ -352,14 +368,14 @@ struct RowChain {
         const double u = read_lane(u_sub, uni((level & 15) + 16 * q));
         // right with probability w_R / (w_L + w_R) (never when both are zero)
         const double w_new = l_w + cur_w;
-        if (u * w_new < cur_w) {
+        if (agreed(u * w_new < cur_w)) {
             if (l_idx >= 0) free_mask |= (1u << l_idx);
         } else {
             if (cur_idx >= 0) free_mask |= (1u << cur_idx);
             cur_idx = l_idx;
         }
         cur_w = w_new;
-        cur_s = level > 1 ? no_uturn(xt, xr) : no_uturn(pth, pr);
+        cur_s = level > 1 ? no_uturn(xt, xr) : pair_ok;
     }
 
     // What follows a leaf's last leapfrog step (lp: this lane's share of theta . grad): its weight, then every merge it
@@ -369,19 +385,29 @@ struct RowChain {
         double kin = 0.0;
 #pragma unroll
         for (int i = 0; i < kVpl; ++i) kin = fma((double)r[i], (double)r[i], kin);
-        wave_sum2(lp, kin);
-        edge_logp = 0.5 * lp;
         m += 1;
+        // An even leaf, if it is valid, is merged with the one before it: that span's two sums go with the leaf's own.
+        bool pair_ok = false;
+        if (m & 1) {
+            wave_sum2(lp, kin);
+        } else {
+            double da, db;
+            span_dots(pth, pr, da, db);
+            const double x = wave_sum_rows(lp, kin, da, db);
+            pair_ok = ((__ballot((double)v * x >= 0.0) >> 16) & 0xffff0000ffffull) == 0xffff0000ffffull;
+            spread_halves(spread_even_rows(x), lp, kin);
+        }
+        edge_logp = 0.5 * lp;
         nleap += sa.leaf_steps;
         n_leaf += sa.leaf_steps;
         double delta = (-edge_logp + 0.5 * kin) - H0;
         if (!(fabs(delta) < INFINITY)) delta = INFINITY;
         if (sa.sampler == kSamplerSlice) {
             cur_w = (log_slice <= -delta) ? 1.0 : 0.0;
-            cur_s = (log_slice < kDeltaMax - delta);
+            cur_s = agreed(log_slice < kDeltaMax - delta);
         } else {
             double e = log_unit_w - delta;  // logarithm of the leaf's weight in the current unit
-            if (e > 600.0) {  // the energy has fallen far: this leaf becomes the unit
+            if (agreed(e > 600.0)) {  // the energy has fallen far: this leaf becomes the unit
                 const double shrink = exp_bounded(-e);
                 w_tree *= shrink;
                 frame_w *= shrink;
@@ -389,7 +415,7 @@ struct RowChain {
                 e = 0.0;
             }
             cur_w = exp_bounded(e);
-            cur_s = (delta <= kDeltaMax);
+            cur_s = agreed(delta <= kDeltaMax);
         }
         cur_idx = kInEdge;
         if (!cur_s) return false;
@@ -406,7 +432,7 @@ struct RowChain {
             if (s >= 2) first_store(s, th, r);
         } else {
             for (int level = 1; level <= n_done; ++level) {
-                merge(uni(level));
+                merge(uni(level), pair_ok);
                 if (!cur_s) return false;
             }
             if (n_done == j) return false;
@@ -425,7 +451,7 @@ struct RowChain {
         bool go_on = false;
         if (cur_s) {
             const double u = read_lane(u_top, uni(32 + j));
-            if (u * w_tree < cur_w) {  // accept the new half with probability min(1, w_new / w_tree)
+            if (agreed(u * w_tree < cur_w)) {  // accept the new half with probability min(1, w_new / w_tree)
                 if (cur_idx == kInEdge) {
                     rest_store(kRowTop, th);
                     if constexpr (kGrad) rest_store(kRowTopG, g);
@@ -434,7 +460,7 @@ struct RowChain {
                     rest_store(kRowTop, pth);
                     if constexpr (kGrad) rest_store(kRowTopG, pg);
                     top_logp = prev_logp;
-                } else {
+                        } else {
                     T t[kVpl], gr[kGrad ? kVpl : 1];
                     pool_load(cur_idx, t, gr);
                     rest_store(kRowTop, t);
