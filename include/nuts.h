@@ -65,10 +65,12 @@ enum {
     NUTS_VARIANT_GRID = 4,  /* every gradient round is a chip-wide binary32 MFMA GEMM over the data rows
                                (logistic regression, binary32, dim <= 128; up to 1024 chains are resident
                                at a time, further chains wait in a queue); this variant returns only when
-                               sampling has finished; beyond 128 chains the resident ones are divided
-                               between two or four streams, the caller's and others that the target owns,
-                               forked from and joined to the caller's stream by events; chains that want a
-                               gradient are packed together, so idle ones cost nothing beyond 128 columns  */
+                               sampling has finished.  Targets of up to 1.5e6 elements (of 17 to 32 features:
+                               12 000 rows) run in one launch that holds every compute unit, one such run at
+                               a time on a device; larger ones in two launches a round, beyond 128 chains
+                               divided between two or four streams, the caller's and others that the target
+                               owns, forked from and joined to the caller's stream by events; chains that want
+                               a gradient are packed together, so idle ones cost next to nothing           */
     NUTS_VARIANT_DENSE = 5, /* one wavefront per chain, moving trajectory end in registers, precision matrix in LDS
                                (dense Gaussian, dim <= 128)                                                 */
     NUTS_VARIANT_QUAD = 6   /* four chains per wavefront, their precision-matrix products together as MFMA blocks

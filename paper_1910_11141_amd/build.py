@@ -20,6 +20,11 @@ FLAGS = [
 ]
 
 
+# The chip kernel's instances keep a chain's state in registers through a loop that is long and deep: hoisting constants and
+# addresses out of it (the compiler's habit) fills the register file and spills the state itself (400 bytes a lane).
+EXTRA_FLAGS = {"nuts_chip.hip": ["-mllvm", "-disable-machine-licm", "-mllvm", "-sink-insts-to-avoid-spills=1"]}
+
+
 def sources():
     return [os.path.join(CSRC, f) for f in sorted(os.listdir(CSRC)) if f.endswith(".hip")]
 
@@ -49,7 +54,8 @@ def build(force: bool = True, verbose: bool = False) -> str:
     with tempfile.TemporaryDirectory() as tmp:
         objects = [os.path.join(tmp, os.path.basename(s) + ".o") for s in sources()]
         compile_flags = [f for f in FLAGS if f != "-shared"]
-        cmds = [[HIPCC] + compile_flags + ["-c", s, "-o", o] for s, o in zip(sources(), objects)]
+        cmds = [[HIPCC] + compile_flags + EXTRA_FLAGS.get(os.path.basename(s), []) + ["-c", s, "-o", o]
+                for s, o in zip(sources(), objects)]
         cmds.append([HIPCC] + FLAGS + [UBENCH_SRC, "-o", UBENCH_LIB])
         for cmd in cmds if verbose else []:
             print(" ".join(cmd), file=sys.stderr)

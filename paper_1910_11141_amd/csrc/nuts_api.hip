@@ -18,6 +18,7 @@
 #include "nuts_dev.h"
 #include "nuts_band.h"
 #include "nuts_block.h"
+#include "nuts_chip.h"
 #include "nuts_dense.h"
 #include "nuts_elem.h"
 #include "nuts_grid.h"
@@ -93,6 +94,7 @@ struct nuts_target {
     void* dY = nullptr;
     nuts::TileData tile;  // operand-order copies of X for the tile and wide kernels (logistic regression)
     nuts::GridData grid;  // operand-order copy of X for the grid kernels (binary32 logistic regression)
+    nuts::ChipData chip;  // padded copy of X~ for the chip kernel (binary32 logistic regression, in the grid kernels' place)
     nuts::QuadData quad;  // operand-order copy of P for the quad kernel (binary64 dense Gaussian, dim <= 128)
     nuts::BlockData block;  // operand-order copy of P for the block kernel (dense Gaussian, 128 < dim <= 512, not banded)
     // per-call scratch, grown on demand and kept
@@ -108,6 +110,7 @@ struct nuts_target {
     // grid kernels: the sets of chains beyond the first run their rounds on these streams
     hipStream_t side_stream[nuts::kGridMaxStreams - 1] = {};
     hipEvent_t ev_fork = nullptr, ev_join[nuts::kGridMaxStreams - 1] = {};
+    unsigned* chip_state = nullptr;     // chip kernel: pinned, how the last run ended
     int* halted_host = nullptr;         // grid kernels: pinned, two snapshots of the "halted" flags
     hipEvent_t ev_batch[2 * nuts::kGridMaxStreams] = {};  // [snapshot][stream]
     bool has_run = false;
@@ -156,6 +159,20 @@ bool grid_pays(int64_t n, int64_t d) { return n * d >= (1 << 14); }
 
 // Pairs of components per lane that the one-chain-per-wave kernels are instantiated for.
 int row_chunks(int64_t d) { return d <= 128 ? 1 : d <= 256 ? 2 : d <= 512 ? 4 : d <= 1024 ? 8 : 16; }
+
+// X~ for the chip kernel, from the target's own copies on the device ([n][d] and [n]); cd has the sizes.
+__global__ void chip_pack_kernel(const float* __restrict__ X, const float* __restrict__ y, nuts::ChipData cd)
+{
+    const int pitch = nuts::chip_pitch(cd.mt);
+    const size_t total = (size_t)cd.n_tiles * nuts::kChipRows * pitch;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
+        const size_t r = i / pitch;
+        const int k = (int)(i % pitch);
+        const bool there = (long)r < cd.n_rows && k < cd.d;
+        const float v = there ? X[r * cd.d + k] : 0.0f;
+        cd.x[i] = there && y[r] == 0.0f ? -v : v;
+    }
+}
 
 template <typename T>
 int build_device_data(nuts_target* t, const nuts_target_desc* desc)
@@ -252,13 +269,26 @@ int build_device_data(nuts_target* t, const nuts_target_desc* desc)
             if (rc) return rc;
             t->tile.ftab = static_cast<double*>(dev);
         }
-        if (sizeof(T) == sizeof(float) && nuts::grid_supports_shape(d)) {
-            std::vector<float> op;
-            nuts::grid_pack_operands(reinterpret_cast<const float*>(X), reinterpret_cast<const float*>(y), n, d, &t->grid, &op);
-            void* dev = nullptr;
-            rc = upload(op, &dev);
-            if (rc) return rc;
-            t->grid.ops = static_cast<float*>(dev);
+        if constexpr (sizeof(T) == sizeof(float)) {
+            if (nuts::chip_pays(n, d)) {
+                nuts::ChipData* const cd = &t->chip;
+                cd->d = (int)d;
+                cd->mt = (int)((d + 15) / 16);
+                cd->n_rows = (long)n;
+                cd->n_tiles = (int)((n + nuts::kChipRows - 1) / nuts::kChipRows);
+                HIP_TRY(hipMalloc((void**)&cd->x, (size_t)cd->n_tiles * nuts::kChipRows * nuts::chip_pitch(cd->mt) * sizeof(float)), NUTS_E_ALLOC);
+                hipLaunchKernelGGL(chip_pack_kernel, dim3(1024), dim3(256), 0, nullptr, static_cast<const float*>(t->dX),
+                                   static_cast<const float*>(t->dY), *cd);
+                HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
+                HIP_TRY(hipStreamSynchronize(nullptr), NUTS_E_DEVICE);
+            } else if (nuts::grid_supports_shape(d)) {
+                std::vector<float> op;
+                nuts::grid_pack_operands(X, y, n, d, &t->grid, &op);
+                void* dev = nullptr;
+                rc = upload(op, &dev);
+                if (rc) return rc;
+                t->grid.ops = static_cast<float*>(dev);
+            }
         }
         return NUTS_OK;
     }
@@ -307,6 +337,7 @@ void release(nuts_target* t)
         (void)hipFree(t->grid.ops);
         (void)hipFree(t->quad.ops);
         (void)hipFree(t->block.ops);
+        (void)hipFree(t->chip.x);
         (void)hipFree(t->tile.ftab);
         (void)hipFree(t->tile.colsum);
         (void)hipFree(t->workspace);
@@ -322,6 +353,7 @@ void release(nuts_target* t)
         for (hipEvent_t e : t->ev_batch)
             if (e) (void)hipEventDestroy(e);
         if (t->halted_host) (void)hipHostFree(t->halted_host);
+        if (t->chip_state) (void)hipHostFree(t->chip_state);
     }
     delete t;
 }
@@ -374,6 +406,11 @@ int ensure_ftab(nuts_target* t)
     if (t->static_call)
         return fail(NUTS_E_UNSUPPORTED, "the target was created without a GPU: nuts_sample_static cannot build its tables");
     return upload(softplus_table(), &t->dFtab);
+}
+
+__global__ void fill_words_kernel(unsigned* p, int n, unsigned value)
+{
+    for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = value;
 }
 
 __global__ void zero_counters_kernel(unsigned long long* c)
@@ -714,7 +751,7 @@ int launch_quad(nuts_target* t, nuts::DevSample sa)
 
 bool grid_eligible(const nuts_target* t)
 {
-    return t->kind == NUTS_TARGET_LOGISTIC_REGRESSION && t->dtype == NUTS_F32 && t->grid.ops != nullptr;
+    return t->kind == NUTS_TARGET_LOGISTIC_REGRESSION && t->dtype == NUTS_F32 && (t->grid.ops != nullptr || t->chip.x != nullptr);
 }
 
 // Rounds of (control, gradient) launches, enqueued in batches; the host waits for each batch
@@ -928,6 +965,65 @@ int launch_tile(nuts_target* t, nuts::DevSample sa)
     t->last_grid = tl.blocks;
     t->last_slots = 0;
     return NUTS_OK;
+}
+
+// One launch of the chip kernel, which needs all its workgroups at once: a cooperative launch, one at a time on a device (two of
+// them that each had a part of the chip would wait for each other).  Should the device be shared with another process so that
+// the workgroups cannot run together, the kernel gives up before it has done anything and is launched again.  As with the
+// grid kernels, this returns only when sampling is complete.
+std::mutex g_chip_mutex[kMaxDevices];
+
+int launch_chip(nuts_target* t, nuts::DevSample sa)
+{
+    using namespace nuts;
+    int cus = 0;
+    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device), NUTS_E_DEVICE);
+    const int mt = t->chip.mt;
+    ChipPlan cp{};
+    cp.blocks = cus < kChipMaxBlocks ? cus : kChipMaxBlocks;
+    chip_lds(mt, sa.max_depth, &cp);
+    ChipArgs ca{};
+    ca.x = t->chip.x;
+    ca.d = t->chip.d;
+    ca.n_rows = t->chip.n_rows;
+    ca.n_tiles = t->chip.n_tiles;
+    ca.n_blocks = cp.blocks;
+    ca.n_slices = chip_slices(ca.n_tiles, cp.blocks);
+    const long most = (long)cp.blocks * kChipOwners;
+    ca.n_slots = (int)(sa.n_chains < most ? sa.n_chains : most);
+    ca.prior_prec = 1.0 / (t->prior_scale * t->prior_scale);
+    ca.theta_bytes = (unsigned)((size_t)kChipColumns * 16 * mt * sizeof(float));
+    ca.g_bytes = (unsigned)((size_t)ca.n_slices * ca.theta_bytes);
+    size_t off = 0;
+    auto take = [&](size_t bytes) { const size_t o = off; off = (off + bytes + 255) & ~(size_t)255; return o; };
+    const size_t shared_words = (kChipCounters + 1) * kChipLine;
+    const size_t o_shared = take(shared_words * sizeof(unsigned));
+    const size_t o_theta = take(ca.theta_bytes), o_g = take(ca.g_bytes);
+    const size_t o_ll = take((size_t)ca.n_slices * kChipColumns * sizeof(double));
+    const size_t o_chains = take(cp.slot_bytes * (size_t)ca.n_slots);
+    int rc = ensure_workspace(t, off);
+    if (rc) return rc;
+    ca.shared = reinterpret_cast<unsigned*>(t->ws_cur + o_shared);
+    ca.theta = reinterpret_cast<float*>(t->ws_cur + o_theta);
+    ca.g_part = reinterpret_cast<float*>(t->ws_cur + o_g);
+    ca.ll_part = reinterpret_cast<double*>(t->ws_cur + o_ll);
+    sa.workspace = t->ws_cur + o_chains;
+    sa.slot_bytes = cp.slot_bytes;
+    if (!t->chip_state) HIP_TRY(hipHostMalloc((void**)&t->chip_state, sizeof(unsigned)), NUTS_E_ALLOC);
+    std::lock_guard<std::mutex> lock(g_chip_mutex[t->device]);
+    for (int attempt = 0; attempt < 30; ++attempt) {
+        hipLaunchKernelGGL(fill_words_kernel, dim3(1), dim3(256), 0, g_stream, ca.shared, (int)shared_words, 0u);
+        HIP_TRY(chip_launch(mt, ca, sa, cp, g_stream), NUTS_E_DEVICE);
+        HIP_TRY(hipMemcpyAsync(t->chip_state, ca.shared + kChipCounters * kChipLine, sizeof(unsigned), hipMemcpyDeviceToHost, g_stream), NUTS_E_DEVICE);
+        HIP_TRY(hipStreamSynchronize(g_stream), NUTS_E_DEVICE);
+        if (*t->chip_state == kChipNotStarted) continue;
+        if (*t->chip_state != kChipRunning) return fail(NUTS_E_DEVICE, "chip kernel: a workgroup did not reach a barrier in time");
+        t->last_variant = NUTS_VARIANT_GRID;
+        t->last_grid = cp.blocks;
+        t->last_slots = 0;
+        return NUTS_OK;
+    }
+    return fail(NUTS_E_DEVICE, "chip kernel: the device did not run all workgroups at once");
 }
 
 }  // namespace
@@ -1144,7 +1240,7 @@ int sample_impl(const nuts_target* target, int64_t n_chains, int64_t n_iters, do
         else if (use_tile)
             r = launch_tile(t, s);
         else if (use_grid)
-            r = launch_grid(t, s);
+            r = t->chip.x ? launch_chip(t, s) : launch_grid(t, s);
         else if (use_elem)
             r = t->dtype == NUTS_F64 ? launch_elem<double>(t, s, elem_variant) : launch_elem<float>(t, s, elem_variant);
         else

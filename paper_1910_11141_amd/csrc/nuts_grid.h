@@ -1,5 +1,6 @@
 // Grid kernels: logistic regression with many data rows and few chains
-// (binary32, dim <= 128, up to 1024 chains resident at a time).
+// (binary32, dim <= 128, up to 1024 chains resident at a time).  Smaller
+// targets are the chip kernel's (nuts_chip.h: chip_pays).
 //
 // Here one gradient evaluation of all chains is a pair of GEMMs that spans the
 // whole chip - Z = X~ Theta with N rows, G = X~' sigma(-Z) - so the lock-step

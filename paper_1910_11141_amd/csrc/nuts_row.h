@@ -61,7 +61,8 @@ inline RowLds row_lds_split(size_t bytes, int kc, size_t elem, int max_depth, bo
 }
 
 // kGrad: the gradient belongs to the state (otherwise the kernel recomputes it from the position and g is not touched).
-template <typename T, int kC, bool kHeld, bool kGrad>
+// kAhead: an iteration's random numbers that do not depend on where the trajectory goes may be drawn before it begins.
+template <typename T, int kC, bool kHeld, bool kGrad, bool kAhead = false>
 struct RowChain {
     static constexpr int kVpl = 2 * kC, kPitch = 128 * kC;
     typedef T VecN __attribute__((ext_vector_type(2)));
@@ -102,6 +103,10 @@ struct RowChain {
     double frame_w = 0, pool_logp = 0;  // lane k: level k / pool buffer k
     int frame_idx = 0;
     unsigned long long n_leaf = 0, n_extra = 0;
+    T r_next[kAhead ? kVpl : 1];  // drawn for iteration `ahead`: the momentum, |r|^2, and what dirbits, u_top and log_slice will be
+    double kin_next = 0, u_top_next = 0, log_slice_next = 0;
+    uint32_t dirbits_next = 0;
+    int ahead = -1;
 
     __device__ RowChain(const DevSample& sa_, int d_, int lane_, T* ws_, T* lds_, RowLds rl_)
         : sa(sa_), lane(lane_), d(d_), D(sa_.max_depth), ws((GlobalPtr)ws_), lds((LdsPtr)lds_), rl(rl_) {}
@@ -257,6 +262,7 @@ struct RowChain {
         chain = (long)c;
         gchain = (uint32_t)(sa.first_chain + chain);
         iter = sa.iter_begin;
+        ahead = -1;
         if (sa.init_states) {
             const T* src = (const T*)sa.init_states + (size_t)chain * d;
 #pragma unroll
@@ -276,28 +282,49 @@ struct RowChain {
         n_extra += 1;
     }
 
+    __device__ __forceinline__ void draw_iteration(int it, T (&momentum)[kVpl], double& kin, double& tops, double& slice, uint32_t& dirs) const
+    {
+        draw_normals(kDrawMomentum, (uint32_t)it, momentum);
+        kin = 0.0;
+#pragma unroll
+        for (int i = 0; i < kVpl; ++i) kin = fma((double)momentum[i], (double)momentum[i], kin);
+        kin = wave_sum(kin);
+        if (sa.sampler == kSamplerSlice) {
+            const Words4 w = draw(key(), 0, kDrawSlice, 0, (uint32_t)it, gchain);
+            slice = log(uniform52(w.w0, w.w1));
+        }
+        const Words4 wj = draw(key(), (uint32_t)(lane & 31), (lane & 32) ? kDrawTop : kDrawDirection, 0, (uint32_t)it, gchain);
+        dirs = (uint32_t)__ballot(wj.w0 >> 31);
+        tops = uniform52(wj.w0, wj.w1);
+    }
+    __device__ void draw_ahead(int it)
+    {
+        draw_iteration(it, r_next, kin_next, u_top_next, log_slice_next, dirbits_next);
+        ahead = it;
+    }
+
     __device__ void iter_begin()
     {
         rest_load(kRowTop, th);
         if constexpr (kGrad) rest_load(kRowTopG, g);
-        draw_normals(kDrawMomentum, (uint32_t)iter, r);
-        double kin = 0.0;
-#pragma unroll
-        for (int i = 0; i < kVpl; ++i) kin = fma((double)r[i], (double)r[i], kin);
+        double kin;
+        if constexpr (kAhead) {
+            if (ahead != iter) draw_ahead(iter);
+            copy(r, r_next);
+            kin = kin_next;
+            u_top = u_top_next;
+            log_slice = log_slice_next;
+            dirbits = dirbits_next;
+        } else {
+            draw_iteration(iter, r, kin, u_top, log_slice, dirbits);
+        }
         rest_store(kRowOtherTh, th);  // both ends of the trajectory start at the current point
         rest_store(kRowOtherR, r);
         if constexpr (kGrad) rest_store(kRowOtherG, g);
         v = 0;
-        H0 = -top_logp + 0.5 * wave_sum(kin);
+        H0 = -top_logp + 0.5 * kin;
         w_tree = 1.0;  // the starting point: weight exp(0), or the first candidate
         log_unit_w = 0.0;
-        if (sa.sampler == kSamplerSlice) {
-            const Words4 w = draw(key(), 0, kDrawSlice, 0, (uint32_t)iter, gchain);
-            log_slice = log(uniform52(w.w0, w.w1));
-        }
-        const Words4 wj = draw(key(), (uint32_t)(lane & 31), (lane & 32) ? kDrawTop : kDrawDirection, 0, (uint32_t)iter, gchain);
-        dirbits = (uint32_t)__ballot(wj.w0 >> 31);
-        u_top = uniform52(wj.w0, wj.w1);
         u_sub_leaf = kNoLeaf;
         j = 0;
         nleap = 0;

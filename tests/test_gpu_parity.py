@@ -546,6 +546,35 @@ def test_grid_kernels_many_sets_and_queued_chains(n_chains):
     both_schedules(w, B.NUTS_VARIANT_GRID)
 
 
+# rows at the edges of a tile of 16, of the eight tiles of a step and of one, two and more slices; features at the edges of a
+# feature tile and of a block of 16 bytes a lane; more chains than are resident
+@pytest.mark.parametrize("n_data,dim,n_chains", [(1, 1, 1), (16, 16, 5), (17, 17, 33), (128, 4, 20), (129, 128, 6), (385, 112, 17), (1025, 3, 1030),
+                                                 (2064, 48, 250), (40001, 2, 9)])
+def test_chip_kernel_edges_match_the_oracle_on_both_schedules(n_data, dim, n_chains):
+    B = N()
+    w = W.small_logreg(n_data, dim, seed=300 + n_data + dim, dtype=np.float32)
+    w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = n_chains, 4, 0.15 / np.sqrt(max(n_data, 1) / 10), 6
+    tgt = gpu_target(w)
+    free, sync = both_schedules(w, B.NUTS_VARIANT_GRID)
+    f32_parity(free, ref_run(w))
+    slice3 = gpu_run(w, tgt=tgt, variant=B.NUTS_VARIANT_GRID, sampler=SLICE, leaf_steps=3, n_iters=2)
+    f32_parity(slice3, ref_run(w, sampler=SLICE, leaf_steps=3, n_iters=2))
+
+
+# large enough for the two-launch grid kernels: left-over features of one and two groups of 4, none, and the largest
+@pytest.mark.parametrize("n_data,dim,n_chains", [(46000, 33, 3), (15700, 97, 40), (12100, 17, 6), (24000, 71, 5), (12500, 128, 3), (12001, 32, 130)])
+def test_grid_kernels_on_many_rows_match_the_oracle(n_data, dim, n_chains):
+    B = N()
+    w = W.small_logreg(n_data, dim, seed=400 + dim, dtype=np.float32)
+    w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = n_chains, 2, 0.5 / np.sqrt(n_data), 4
+    g = gpu_run(w)
+    assert g[3]["variant"] == B.NUTS_VARIANT_GRID and g[3]["leaf_slots_useful"] == g[2].sum()
+    f32_parity(g, ref_run(w))
+    few = gpu_run(w, n_chains=2)
+    for k in range(3):
+        assert np.array_equal(g[k][:, :2], few[k])
+
+
 # ------------------------------------------------------------------ independence of the schedule
 
 def test_chain_results_do_not_depend_on_batch_size_or_slot():
