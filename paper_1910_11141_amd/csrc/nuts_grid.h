@@ -43,6 +43,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
 #include <vector>
 
 #include "nuts_dev.h"
@@ -188,149 +189,271 @@ inline int grid_streams(int n_slots, long n, int d, double chain_iters)
 }
 
 // ------------------------------------------------------------------ gradient
-template <int kKs1, int kMt, int kTail>
+// With at least 8 tiles to a slice (kRuns) its rows are four consecutive runs of tiles, and its partial result is the sum of theirs, in
+// one order.  One or two groups of columns: every wave takes a run and one group after the other, its operands straight from
+// memory into registers, eight 16-byte operands ahead of their use, and the runs' sums meet in LDS; more columns: every wave takes
+// a group and all runs, whose operands the workgroup brings into LDS once.  With one group of 32 columns in use the second
+// way leaves three of four waves idle.  (Three groups one after the other would read X three times.)
+// 100 000 x 100, 256 chains from the prior, 4 iterations 15.1 -> 10.4 ms, 40 iterations from the posterior 86.8 -> 75.7; 600 000 x 32, 256
+// chains 12.8 -> 8.4; 8 chains 5.8 -> 3.5; 1024 chains 24.9 and 23.8.  Smaller slices are one run and the second way: their
+// launches are short, and the registers of the sums would cost waves in flight (20 000 x 25, 4096 chains 17.2 -> 19.2; 50 000 x 128,
+// 2048 chains 15.8 -> 16.1).
+template <int kKs1, int kMt, int kTail, bool kRuns>
 __global__ __launch_bounds__(kGridWaves * kWave, 2) void nuts_grid_grad_kernel(GridArgs ga, int round)
 {
     constexpr int kKg1 = (kKs1 + 3) / 4;
+    constexpr int kTails = kTail > 0 ? kTail : 1;
     // blockIdx.y: which set of 128 columns (the launch spans all that the stream can need)
     const int slot_base = ga.slot_base + (int)blockIdx.y * kGridSetChains;
     const int columns = ga.b.active_all[ga.stream * kGridBatch + round] - (int)blockIdx.y * kGridSetChains;
     if (columns <= 0) return;
     const int n_set_slots = columns < kGridSetChains ? columns : kGridSetChains;
+    const int n_groups = (n_set_slots + kGridGroup - 1) / kGridGroup;
     if (blockIdx.x == 0 && threadIdx.x == 0) {  // one gradient round of this set: what its waves compute
-        atomicAdd(&ga.counters[kCtrIssued], (unsigned long long)((n_set_slots + kGridGroup - 1) / kGridGroup * kGridGroup));
+        atomicAdd(&ga.counters[kCtrIssued], (unsigned long long)(n_groups * kGridGroup));
         atomicAdd(&ga.counters[kCtrRounds], 1ull);
     }
-    const int lane = threadIdx.x & (kWave - 1), grp = threadIdx.x >> 6;
-    const bool computes = grp * kGridGroup < n_set_slots;
+    const int lane = threadIdx.x & (kWave - 1), wave = uni((int)(threadIdx.x >> 6));
+    const int half = lane >> 5;
     const int slice = blockIdx.x;
     const int t0 = (int)((long)ga.n_tiles * slice / ga.n_slices), t1 = (int)((long)ga.n_tiles * (slice + 1) / ga.n_slices);
-    const int col = slot_base + grp * kGridGroup + (lane & 31), half = lane >> 5;
+    constexpr int n_runs = kRuns ? kGridWaves : 1;
+    auto run_end = [&](int r) __attribute__((always_inline)) -> int { return t0 + (t1 - t0) * (r + 1) / n_runs; };
+
+    constexpr int kGroups = grid_groups_per_tile(kKs1, kMt, kTail);
+    constexpr int kUsed = kKg1 + 4 * kMt + 4 * kTail;
+    __shared__ float4 s_ops[2][kGroups * 64];
+    __shared__ double s_ll[kGridWaves][kGridGroup];
 
     float b1[4 * kKg1];  // B[k][j] = Theta[feature 2s + lane/32][chain col]  (only the first kKs1 are used)
+    auto load_theta = [&](int col) __attribute__((always_inline)) {
 #pragma unroll
-    for (int s = 0; s < kKs1; ++s) b1[s] = ga.b.theta_t[(size_t)(2 * s + half) * ga.chain_stride + col];
-
+        for (int s = 0; s < kKs1; ++s) b1[s] = ga.b.theta_t[(size_t)(2 * s + half) * ga.chain_stride + col];
+    };
     v16f G[kMt];
+    // tail group g, register i: feature 32 kMt + 4g + i of chain `col`, summed over this lane half's rows;
+    // two accumulators per group, so that consecutive small MFMAs do not wait for each other
+    v4f T[kTails][2];
+    double ll = 0.0;
+    auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kMt; ++u)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) G[u][v] = 0.0f;
+#pragma unroll
+        for (int g = 0; g < kTails; ++g) T[g][0] = T[g][1] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        ll = 0.0;
+    };
+    // a run's left-over features (the two lane halves hold the sums over their own rows) and log-likelihood
+    auto tail_sum = [&](int g) __attribute__((always_inline)) -> v4f {
+        v4f s = T[g][0] + T[g][1];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[i] += __shfl_xor(s[i], 32, kWave);
+        return s;
+    };
+    // one tile, group by group of its operands: ops(i) is the i-th float4 of this lane
+    auto row_tile = [&](int t, auto&& ops) __attribute__((always_inline)) {
+        v16f z;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) z[v] = 0.0f;
+#pragma unroll
+        for (int kg = 0; kg < kKg1; ++kg) {
+            const float4 a = ops(std::integral_constant<int, 0>{}, kg);
+            z = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b1[4 * kg + 0], z, 0, 0, 0);
+            z = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b1[4 * kg + 1], z, 0, 0, 0);
+            if (4 * kg + 2 < kKs1) {
+                z = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b1[4 * kg + 2], z, 0, 0, 0);
+                z = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b1[4 * kg + 3], z, 0, 0, 0);
+            }
+        }
+        // logistic functions on the accumulator; rows past the end of the data contribute nothing.
+        // Vector instructions do not overlap with MFMAs on this chip, so every one of them counts:
+        // log(1 + e^-z) = max(-z, 0) + log(1 + e^-|z|), and the 16 second terms of a lane are taken as
+        // one logarithm of the product of their arguments (each in [1, 2]).
+        const bool ragged = (long)(t + 1) * kGridRows > ga.n_rows;
+        float sg[16], prod = 1.0f, hinge = 0.0f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const float zt = z[v];
+            // single hardware instructions: the arguments are in their safe ranges (2^x with x <= 0,
+            // reciprocal of a number in [1, 2]); a NaN logit makes every result NaN
+            const float e = __builtin_amdgcn_exp2f(fabsf(zt) * -1.44269504088896341f);
+            float tt = 1.0f + e;
+            const float inv = __builtin_amdgcn_rcpf(tt);
+            float s = (zt < 0.0f ? 1.0f : e) * inv;
+            if (ragged && (long)t * kGridRows + grid_acc_row(v) + 4 * half >= ga.n_rows) {
+                tt = 1.0f;  // the padded row has z = 0: no hinge term either
+                s = 0.0f;
+            }
+            prod *= tt;
+            hinge += fmaxf(-zt, 0.0f);
+            sg[v] = s;
+        }
+        ll -= (double)fmaf(__builtin_amdgcn_logf(prod), 0.69314718055994531f, hinge);
+#pragma unroll
+        for (int u = 0; u < kMt; ++u)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const float4 a = ops(std::integral_constant<int, 1>{}, kKg1 + u * 4 + q4);
+                G[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, sg[4 * q4 + 0], G[u], 0, 0, 0);
+                G[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, sg[4 * q4 + 1], G[u], 0, 0, 0);
+                G[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, sg[4 * q4 + 2], G[u], 0, 0, 0);
+                G[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, sg[4 * q4 + 3], G[u], 0, 0, 0);
+            }
+#pragma unroll
+        for (int g = 0; g < kTail; ++g)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const float4 a = ops(std::integral_constant<int, 1>{}, kKg1 + (kMt + g) * 4 + q4);
+                T[g][0] = __builtin_amdgcn_mfma_f32_4x4x1f32(a.x, sg[4 * q4 + 0], T[g][0], 0, 0, 0);
+                T[g][1] = __builtin_amdgcn_mfma_f32_4x4x1f32(a.y, sg[4 * q4 + 1], T[g][1], 0, 0, 0);
+                T[g][0] = __builtin_amdgcn_mfma_f32_4x4x1f32(a.z, sg[4 * q4 + 2], T[g][0], 0, 0, 0);
+                T[g][1] = __builtin_amdgcn_mfma_f32_4x4x1f32(a.w, sg[4 * q4 + 3], T[g][1], 0, 0, 0);
+            }
+    };
+
+    if constexpr (kRuns) if (2 * n_groups <= n_runs) {
+        // ---- a run of tiles per wave ----
+        // operands asked for ahead: a divisor of kGroups (an operand's register is known where it is used)
+        constexpr int kAhead = kGroups % 8 == 0 ? 8 : (kGroups % 9 == 0 ? 9 : (kGroups % 7 == 0 ? 7 : 5));
+        static_assert(kGroups % kAhead == 0, "");
+        constexpr int kPieces = 8 * kMt + kTail;  // float4 of a column's result
+        float4* const sums = &s_ops[0][0];        // [wave][column][piece]
+        static_assert(kGridWaves * kGridGroup * kPieces <= 2 * kGroups * 64, "the runs' sums fit where tiles are staged");
+        // (an even number of pieces a column would put the columns on the same banks)
+        auto at = [&](int w, int c, int piece) __attribute__((always_inline)) -> float4* {
+            return sums + (w * kGridGroup + c) * kPieces + (kTail == 0 ? piece ^ (c & 7) : piece);
+        };
+        const int ta = wave == 0 ? t0 : run_end(wave - 1), tb = run_end(wave);
+        for (int grp = 0; grp < n_groups; ++grp) {
+            const int col = slot_base + grp * kGridGroup + (lane & 31);
+            clear();
+            if (ta < tb) {
+                const float4* src = reinterpret_cast<const float4*>(ga.ops) + (size_t)ta * kGroups * 64 + lane;
+                float4 buf[kAhead];
+#pragma unroll
+                for (int i = 0; i < kAhead; ++i) buf[i] = src[i * 64];
+                load_theta(col);
+                for (int t = ta; t < tb; ++t) {
+                    row_tile(t, [&](auto, int i) __attribute__((always_inline)) -> float4 {
+                        const float4 a = buf[i % kAhead];
+                        const int next = i + kAhead;  // (the tile after the last one exists: a spare, all zeros)
+                        if (next % kGroups < kUsed) buf[i % kAhead] = src[next * 64];
+                        // what is asked for in the places of the padding groups at a tile's end
+                        if (i == kUsed - 1) {
+#pragma unroll
+                            for (int j = kUsed; j < kGroups; ++j) buf[j % kAhead] = src[(j + kAhead) * 64];
+                        }
+                        return a;
+                    });
+                    src += kGroups * 64;
+                }
+            }
+            // accumulator register v = 4w + r of feature tile u is G[feature 32u + 8w + r + 4*half][chain col]:
+            // four consecutive features per register quad
+#pragma unroll
+            for (int u = 0; u < kMt; ++u)
+#pragma unroll
+                for (int w = 0; w < 4; ++w)
+                    *at(wave, lane & 31, 8 * u + 2 * w + half) = make_float4(G[u][4 * w], G[u][4 * w + 1], G[u][4 * w + 2], G[u][4 * w + 3]);
+#pragma unroll
+            for (int g = 0; g < kTail; ++g) {
+                const v4f x = tail_sum(g);
+                if (half == 0) *at(wave, lane & 31, 8 * kMt + g) = make_float4(x[0], x[1], x[2], x[3]);
+            }
+            ll += __shfl_xor(ll, 32, kWave);
+            if (half == 0) s_ll[wave][lane] = ll;
+            __syncthreads();
+            for (int i = threadIdx.x; i < kGridGroup * kPieces; i += kGridWaves * kWave) {
+                const int c = i / kPieces, piece = i % kPieces;
+                float4 x = *at(0, c, piece);
+                for (int w = 1; w < n_runs; ++w) {
+                    const float4 y = *at(w, c, piece);
+                    x = make_float4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w);
+                }
+                *reinterpret_cast<float4*>(ga.b.g_part + ((size_t)slice * ga.chain_stride + slot_base + grp * kGridGroup + c) * kGridFeatPad + 4 * piece) = x;
+            }
+            if (threadIdx.x < kGridGroup) {
+                double x = s_ll[0][threadIdx.x];
+                for (int w = 1; w < n_runs; ++w) x += s_ll[w][threadIdx.x];
+                ga.b.ll_part[(size_t)slice * ga.chain_stride + slot_base + grp * kGridGroup + threadIdx.x] = x;
+            }
+            if (grp + 1 < n_groups) __syncthreads();
+        }
+        return;
+    }
+
+    // ---- a group of columns per wave ----
+    const bool computes = wave * kGridGroup < n_set_slots;
+    const int col = slot_base + wave * kGridGroup + (lane & 31);
+    load_theta(col);
+    clear();
+    v16f G_sum[kMt];
+    v4f T_sum[kTails];
+    double ll_sum = 0.0;
 #pragma unroll
     for (int u = 0; u < kMt; ++u)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) G[u][v] = 0.0f;
-    // tail group g, register i: feature 32 kMt + 4g + i of chain `col`, summed over this lane half's rows;
-    // two accumulators per group, so that consecutive small MFMAs do not wait for each other
-    v4f T[kTail > 0 ? kTail : 1][2];
+        for (int v = 0; v < 16; ++v) G_sum[u][v] = 0.0f;
 #pragma unroll
-    for (int g = 0; g < (kTail > 0 ? kTail : 1); ++g) T[g][0] = T[g][1] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-    double ll = 0.0;
+    for (int g = 0; g < kTails; ++g) T_sum[g] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
     // The operand groups of a tile are fetched once per workgroup, straight from global memory into LDS
     // (no registers in between): each wave requests its share of the next tile into the other stage
     // before it computes the current one, and waits for its requests before the barrier that ends the
     // tile, which also separates the two uses of a stage.
-    constexpr int kGroups = grid_groups_per_tile(kKs1, kMt, kTail);
     constexpr int kShare = kGroups / kGridWaves;
-    __shared__ float4 s_ops[2][kGroups * 64];
-    const float4* src = reinterpret_cast<const float4*>(ga.ops) + ((size_t)t0 * kGroups + grp * kShare) * 64 + lane;
+    const float4* src = reinterpret_cast<const float4*>(ga.ops) + ((size_t)t0 * kGroups + wave * kShare) * 64 + lane;
     auto fetch = [&](int stage) {
 #pragma unroll
         for (int i = 0; i < kShare; ++i)
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + i * 64),
-                                             (__attribute__((address_space(3))) void*)(&s_ops[stage][(grp * kShare + i) * 64]), 16, 0, 0);
+                                             (__attribute__((address_space(3))) void*)(&s_ops[stage][(wave * kShare + i) * 64]), 16, 0, 0);
     };
     fetch(0);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
-    for (int t = t0; t < t1; ++t) {
-        const int stage = (t - t0) & 1;
-        src += kGroups * 64;  // the tile after the last one exists (a spare, all zeros)
-        fetch(stage ^ 1);
-        if (computes) {
-            const float4* ops = &s_ops[stage][lane];
-            v16f z;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) z[v] = 0.0f;
-#pragma unroll
-            for (int kg = 0; kg < kKg1; ++kg) {
-                const float4 a = ops[kg * 64];
-                z = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b1[4 * kg + 0], z, 0, 0, 0);
-                z = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b1[4 * kg + 1], z, 0, 0, 0);
-                if (4 * kg + 2 < kKs1) {
-                    z = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b1[4 * kg + 2], z, 0, 0, 0);
-                    z = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b1[4 * kg + 3], z, 0, 0, 0);
-                }
+    int stage = 0;
+    for (int r = 0; r < n_runs; ++r) {
+        const int end = run_end(r);
+        for (int t = r == 0 ? t0 : run_end(r - 1); t < end; ++t) {
+            src += kGroups * 64;  // the tile after the last one exists (a spare, all zeros)
+            fetch(stage ^ 1);
+            if (computes) {
+                const float4* const staged = &s_ops[stage][lane];
+                row_tile(t, [&](auto, int i) __attribute__((always_inline)) -> float4 { return staged[i * 64]; });
             }
-            // logistic functions on the accumulator; rows past the end of the data contribute nothing.
-            // Vector instructions do not overlap with MFMAs on this chip, so every one of them counts:
-            // log(1 + e^-z) = max(-z, 0) + log(1 + e^-|z|), and the 16 second terms of a lane are taken as
-            // one logarithm of the product of their arguments (each in [1, 2]).
-            const bool ragged = (long)(t + 1) * kGridRows > ga.n_rows;
-            float sg[16], prod = 1.0f, hinge = 0.0f;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float zt = z[v];
-                // single hardware instructions: the arguments are in their safe ranges (2^x with x <= 0,
-                // reciprocal of a number in [1, 2]); a NaN logit makes every result NaN
-                const float e = __builtin_amdgcn_exp2f(fabsf(zt) * -1.44269504088896341f);
-                float tt = 1.0f + e;
-                const float inv = __builtin_amdgcn_rcpf(tt);
-                float s = (zt < 0.0f ? 1.0f : e) * inv;
-                if (ragged && (long)t * kGridRows + grid_acc_row(v) + 4 * half >= ga.n_rows) {
-                    tt = 1.0f;  // the padded row has z = 0: no hinge term either
-                    s = 0.0f;
-                }
-                prod *= tt;
-                hinge += fmaxf(-zt, 0.0f);
-                sg[v] = s;
-            }
-            ll -= (double)fmaf(__builtin_amdgcn_logf(prod), 0.69314718055994531f, hinge);
-#pragma unroll
-            for (int u = 0; u < kMt; ++u)
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
-                    const float4 a = ops[(kKg1 + u * 4 + q4) * 64];
-                    G[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, sg[4 * q4 + 0], G[u], 0, 0, 0);
-                    G[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, sg[4 * q4 + 1], G[u], 0, 0, 0);
-                    G[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, sg[4 * q4 + 2], G[u], 0, 0, 0);
-                    G[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, sg[4 * q4 + 3], G[u], 0, 0, 0);
-                }
-#pragma unroll
-            for (int g = 0; g < kTail; ++g)
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
-                    const float4 a = ops[(kKg1 + (kMt + g) * 4 + q4) * 64];
-                    T[g][0] = __builtin_amdgcn_mfma_f32_4x4x1f32(a.x, sg[4 * q4 + 0], T[g][0], 0, 0, 0);
-                    T[g][1] = __builtin_amdgcn_mfma_f32_4x4x1f32(a.y, sg[4 * q4 + 1], T[g][1], 0, 0, 0);
-                    T[g][0] = __builtin_amdgcn_mfma_f32_4x4x1f32(a.z, sg[4 * q4 + 2], T[g][0], 0, 0, 0);
-                    T[g][1] = __builtin_amdgcn_mfma_f32_4x4x1f32(a.w, sg[4 * q4 + 3], T[g][1], 0, 0, 0);
-                }
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+            stage ^= 1;
         }
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
+        // (the first run's sums are taken as they are, as the other way does)
+        if (r == 0) {
+#pragma unroll
+            for (int u = 0; u < kMt; ++u) G_sum[u] = G[u];
+#pragma unroll
+            for (int g = 0; g < kTail; ++g) T_sum[g] = tail_sum(g);
+            ll_sum = ll + __shfl_xor(ll, 32, kWave);
+        } else {
+#pragma unroll
+            for (int u = 0; u < kMt; ++u) G_sum[u] += G[u];
+#pragma unroll
+            for (int g = 0; g < kTail; ++g) T_sum[g] += tail_sum(g);
+            ll_sum += ll + __shfl_xor(ll, 32, kWave);
+        }
+        clear();
     }
     if (!computes) return;
-    // accumulator register v = 4w + r of feature tile u is G[feature 32u + 8w + r + 4*half][chain col]:
-    // four consecutive features per register quad
     float* gp = ga.b.g_part + ((size_t)slice * ga.chain_stride + col) * kGridFeatPad + 4 * half;
 #pragma unroll
     for (int u = 0; u < kMt; ++u)
 #pragma unroll
         for (int w = 0; w < 4; ++w)
-            *reinterpret_cast<float4*>(gp + 32 * u + 8 * w) = make_float4(G[u][4 * w], G[u][4 * w + 1], G[u][4 * w + 2], G[u][4 * w + 3]);
+            *reinterpret_cast<float4*>(gp + 32 * u + 8 * w) = make_float4(G_sum[u][4 * w], G_sum[u][4 * w + 1], G_sum[u][4 * w + 2], G_sum[u][4 * w + 3]);
 #pragma unroll
-    for (int g = 0; g < kTail; ++g) {  // the two lane halves hold the sums over their own rows
-        float4 s;
-        s.x = T[g][0][0] + T[g][1][0];
-        s.y = T[g][0][1] + T[g][1][1];
-        s.z = T[g][0][2] + T[g][1][2];
-        s.w = T[g][0][3] + T[g][1][3];
-        s.x += __shfl_xor(s.x, 32, kWave);
-        s.y += __shfl_xor(s.y, 32, kWave);
-        s.z += __shfl_xor(s.z, 32, kWave);
-        s.w += __shfl_xor(s.w, 32, kWave);
-        if (half == 0) *reinterpret_cast<float4*>(gp + 32 * kMt + 4 * g) = s;
-    }
-    ll += __shfl_xor(ll, 32, kWave);
-    if (half == 0) ga.b.ll_part[(size_t)slice * ga.chain_stride + col] = ll;
+    for (int g = 0; g < kTail; ++g)
+        if (half == 0) *reinterpret_cast<float4*>(gp + 32 * kMt + 4 * g) = make_float4(T_sum[g][0], T_sum[g][1], T_sum[g][2], T_sum[g][3]);
+    if (half == 0) ga.b.ll_part[(size_t)slice * ga.chain_stride + col] = ll_sum;
 }
 
 // ------------------------------------------------------------------ control
@@ -488,8 +611,9 @@ template <int kMt, int kTail>
 inline void grid_launch_grad(const GridArgs& ga, int round, hipStream_t stream)
 {
     const unsigned sets = (unsigned)((ga.n_span_slots + kGridSetChains - 1) / kGridSetChains);
-    hipLaunchKernelGGL((nuts_grid_grad_kernel<16 * kMt + 2 * kTail, kMt, kTail>), dim3((unsigned)ga.n_slices, sets),
-                       dim3(kGridWaves * kWave), 0, stream, ga, round);
+    constexpr int kKs1 = 16 * kMt + 2 * kTail;
+    hipLaunchKernelGGL((ga.n_tiles >= 8 * ga.n_slices ? nuts_grid_grad_kernel<kKs1, kMt, kTail, true> : nuts_grid_grad_kernel<kKs1, kMt, kTail, false>),
+                       dim3((unsigned)ga.n_slices, sets), dim3(kGridWaves * kWave), 0, stream, ga, round);
 }
 
 // (the shapes grid_shape() can return)

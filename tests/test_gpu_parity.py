@@ -561,8 +561,10 @@ def test_chip_kernel_edges_match_the_oracle_on_both_schedules(n_data, dim, n_cha
     f32_parity(slice3, ref_run(w, sampler=SLICE, leaf_steps=3, n_iters=2))
 
 
-# large enough for the two-launch grid kernels: left-over features of one and two groups of 4, none, and the largest
-@pytest.mark.parametrize("n_data,dim,n_chains", [(46000, 33, 3), (15700, 97, 40), (12100, 17, 6), (24000, 71, 5), (12500, 128, 3), (12001, 32, 130)])
+# large enough for the two-launch grid kernels: left-over features of one and two groups of 4, none, and the largest; from 65 505 rows on
+# a slice's four runs of tiles, with one, two and more groups of columns in use
+@pytest.mark.parametrize("n_data,dim,n_chains", [(46000, 33, 3), (15700, 97, 40), (12100, 17, 6), (24000, 71, 5), (12500, 128, 3), (12001, 32, 130),
+                                                 (65504, 36, 3), (65505, 36, 35), (65600, 128, 3), (70001, 24, 66), (66000, 72, 97)])
 def test_grid_kernels_on_many_rows_match_the_oracle(n_data, dim, n_chains):
     B = N()
     w = W.small_logreg(n_data, dim, seed=400 + dim, dtype=np.float32)
