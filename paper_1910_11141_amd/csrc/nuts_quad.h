@@ -130,6 +130,7 @@ struct QuadChain {
     int act_v;  // direction of the end held in tha/ra/ga (0: both ends are the same point)
     double tt[kQuadV], tg[kQuadV];  // the trajectory's current proposal and its gradient
     double rn[kQuadV];              // the momentum drawn ahead for iteration `ahead_iter`
+    double tp[kQuadV], rp[kQuadV];  // the last odd leaf: where the two-leaf span that the next one closes begins
     double kin_n;                   // |rn|^2
     int ahead_iter, u_sub_leaf;
     uint32_t dirbits, dirbits_n;    // bit j: direction of doubling j (this / the drawn-ahead iteration)
@@ -211,13 +212,19 @@ __global__ __launch_bounds__(kQuadThreads) void nuts_quad_kernel(QuadArgs qa, De
         c.cur_idx = b;
     };
     // ---- blocks of the chain program; each runs for the lanes whose chain waits at it ----
+    // (tf, rf): the first leaf of the subtree that is merged next.  The two-leaf subtree's is in registers, and where a leaf
+    // completes a larger one as well, that one's is asked for before the sums of this merge: control 4310 -> 4040 ticks of a
+    // round of 11.5 k (d = 100, 4096 chains, 100 iterations 16.96 -> 16.54 ms).
+    double tf[kQuadV], rf[kQuadV];
+    auto first_load = [&](int level) __attribute__((always_inline)) {
+        const int f = c.m - (1 << level) + 1;  // first leaf of the subtree, 1-based
+        const int s = (f == 1) ? c.j : min(__ffs(f - 1) - 1, c.j);
+        vload(first(s, 0), tf);
+        vload(first(s, 1), rf);
+    };
     auto block_after_right = [&]() __attribute__((always_inline)) {
         if (c.cur_s) {
-            const int f = c.m - (1 << c.level) + 1;  // first leaf of this subtree, 1-based
-            const int s = (f == 1) ? c.j : min(__ffs(f - 1) - 1, c.j);
-            double tf[kQuadV], rf[kQuadV];
-            vload(first(s, 0), tf);
-            vload(first(s, 1), rf);
+            const bool pair = c.level == 1;
             const double l_w = __shfl(c.frame_w, c.level, kQuadLanes);
             const int l_idx = __shfl(c.frame_idx, c.level, kQuadLanes);
             const double u = __shfl(c.u_sub, c.level, kQuadLanes);
@@ -235,10 +242,11 @@ __global__ __launch_bounds__(kQuadThreads) void nuts_quad_kernel(QuadArgs qa, De
             double da = 0.0, db = 0.0;
 #pragma unroll
             for (int e = 0; e < kQuadV; ++e) {
-                const double delta = c.tha[e] - tf[e];
-                da = fma(delta, rf[e], da);
+                const double delta = c.tha[e] - (pair ? c.tp[e] : tf[e]);
+                da = fma(delta, pair ? c.rp[e] : rf[e], da);
                 db = fma(delta, c.ra[e], db);
             }
+            if (((c.m >> c.level) & 1) == 0 && c.level < c.j) first_load(c.level + 1);
             quad_sum2(da, db);
             c.cur_s = (c.v * da >= 0.0) && (c.v * db >= 0.0);
         }
@@ -553,10 +561,17 @@ __global__ __launch_bounds__(kQuadThreads) void nuts_quad_kernel(QuadArgs qa, De
                     }
                     c.cur_idx = -1;  // the proposal of a one-leaf subtree is the edge itself
                     if ((c.m & 1) && c.j >= 1) {
-                        // first leaf of every open subtree it starts; one copy serves them all
+                        // the two-leaf subtree's first leaf stays in registers; one copy serves the larger ones that it starts
                         const int s = (c.m == 1) ? c.j : min(__ffs(c.m - 1) - 1, c.j);
-                        vstore(first(s, 0), c.tha);
-                        vstore(first(s, 1), c.ra);
+#pragma unroll
+                        for (int e = 0; e < kQuadV; ++e) {
+                            c.tp[e] = c.tha[e];
+                            c.rp[e] = c.ra[e];
+                        }
+                        if (s >= 2) {
+                            vstore(first(s, 0), c.tha);
+                            vstore(first(s, 1), c.ra);
+                        }
                     }
                     do_return();
                 }
