@@ -115,6 +115,8 @@ def roofline_of(w, workloads, stats, n_grad, kernel_s, plain_run):
     (so that the basis fraction would exceed 1), `frac` is the fraction of the HBM peak it really draws."""
     item = w.dtype.itemsize
     kernel = KERNEL_NAMES[stats["variant"]]
+    if kernel == "nuts_grid_grad_kernel" and sum(stats.get("phase_ticks") or [0]) > 0:
+        kernel = "nuts_chip_kernel"   # the same variant's kernel for smaller targets, which has a phase clock
     alg_bytes = None
     if w.kind == workloads.LOGREG:
         work = 4.0 * w.n_data * w.dim * n_grad

@@ -106,8 +106,8 @@ typedef struct {
     uint64_t extra_grad_evals;  /* gradient evaluations that are not leapfrog steps (initial points)   */
     uint64_t rounds;            /* lock-step rounds, summed over workgroups                            */
     double kernel_ms;           /* duration of the sampler kernel, from HIP events on its stream       */
-    uint64_t phase_ticks[3];    /* tile kernel: shader-clock ticks spent in {control, batched gradient,
-                                   step completion}, summed over workgroups (divide by `rounds`)       */
+    uint64_t phase_ticks[3];    /* kernels with a phase clock: shader-clock ticks spent in {control, batched
+                                   gradient, step completion}, summed as `rounds` is (divide by it)    */
     int32_t variant;            /* NUTS_VARIANT_* that ran                                             */
     int32_t grid_blocks;        /* workgroups launched                                                 */
 } nuts_stats;

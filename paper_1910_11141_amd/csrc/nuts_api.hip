@@ -152,9 +152,9 @@ int upload(const std::vector<T>& host, void** dev)
     return NUTS_OK;
 }
 
-// Binary32 logistic regression: the grid kernels pay two launches per round; measured against the wave kernel they win
-// from a few thousand multiply-adds per gradient upwards (N d = 800: 2-5 times slower; 25 000: 3-7 times faster, at 8 to
-// 1024 chains).
+// Binary32 logistic regression whose rows are worth spreading over the chip (chip or grid kernels) instead of giving a
+// group of chains to each compute unit (wide kernel).  The line was drawn for the grid kernels against the wave kernel (N d = 800:
+// 2-5 times slower; 25 000: 3-7 times faster, at 8 to 1024 chains) and stands because the kernels add up in different orders.
 bool grid_pays(int64_t n, int64_t d) { return n * d >= (1 << 14); }
 
 // Pairs of components per lane that the one-chain-per-wave kernels are instantiated for.
@@ -779,12 +779,11 @@ int launch_grid(nuts_target* t, nuts::DevSample sa)
     ga.tail = t->grid.tail;
     ga.n_tiles = t->grid.n_tiles;
     ga.n_rows = t->grid.n_rows;
-    // a slice per compute unit, but at least two row tiles per slice unless the data are tiny: a launch's
-    // fixed costs - operands of Theta, first tile, partial results - weigh more than its width (+13 % at
-    // 10 000 rows and 1024 chains).  The split depends on the target only, never on the number of chains:
-    // a chain's results must not change with the size of the batch it runs in.
-    const int min_tiles = ga.n_tiles >= 64 ? 2 : 1;
-    ga.n_slices = (ga.n_tiles + min_tiles - 1) / min_tiles;
+    // a slice per compute unit, but at least two row tiles per slice: a launch's fixed costs - operands of
+    // Theta, first tile, partial results - weigh more than its width (+13 % at 10 000 rows and 1024 chains).
+    // The split depends on the target only, never on the number of chains: a chain's results must not change
+    // with the size of the batch it runs in.
+    ga.n_slices = (ga.n_tiles + 1) / 2;
     if (ga.n_slices > cus) ga.n_slices = cus;
     if (ga.n_slices > kGridMaxSlices) ga.n_slices = kGridMaxSlices;
     ga.counters = sa.counters;

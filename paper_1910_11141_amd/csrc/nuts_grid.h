@@ -26,9 +26,9 @@
 // of its stream's Theta, so the columns in use are the first ones however many chains have nothing to do (their
 // trajectories have different lengths: on average three quarters of the slots of a short run), and the gradient runs as
 // many sets of 128 columns (one workgroup's worth) as that takes.  A column's sums do not depend on where it lies.  Two
-// streams of up to 512 chains with columns handed out against four of up to 256 with a column per slot: 10 000 x 100, 1024
-// chains, one iteration 6.9 -> 4.2 ms, 4 awaited ones 20.6 -> 11.8, 12 free ones 17.2 -> 15.2 (one stream: 17.3); 6052 x 7,
-// 1229 chains, 4 awaited iterations 10.1 -> 5.3.  A run of one set keeps a column per slot: its four waves run side by
+// streams of up to 512 chains with columns handed out against four of up to 256 with a column per slot (measured on a target that
+// is the chip kernel's now, 10 000 x 100, 1024 chains): one iteration 6.9 -> 4.2 ms, 4 awaited ones 20.6 -> 11.8, 12 free ones
+// 17.2 -> 15.2 (one stream: 17.3).  A run of one set keeps a column per slot: its four waves run side by
 // side whatever they hold, and the atomic would cost 3 % of a round; with one set on each of two streams idle waves leave
 // their SIMD to the other stream (100 000 x 100, 256 chains, one iteration 12.1 -> 11.1 ms).
 // Streams are independent: while one is in its control launch another one's gradient keeps the matrix units busy, and
@@ -176,10 +176,10 @@ struct GridArgs {
 
 // Streams of a launch that steps n_slots chains at a time through `chain_iters` iterations in all: two, or four where packing
 // has little to gain.  With few iterations a slot the end of the launch, when ever fewer slots are busy, is most of it.  Time
-// with two over time with four, packed both: 10 000 x 100, 1024 and 4096 chains, 50 iterations 1.05 and 1.05, 12 iterations 1.03
-// and 1.05, one awaited 0.89 and 1.03; 512 chains, 50 iterations 0.99 to 1.01, one 0.80; 100 000 x 100, 512 to 1024 chains, 12
-// iterations 1.01 to 1.03; 3000 x 9 0.4 to 0.93 throughout (every launch has a cost of its own, and the host has to keep up:
-// 20 000 x 25, 512 to 4096 chains, 12 to 50 iterations 1.00 to 1.05 with a fast one, 0.86 to 0.93 with a slower one).
+// with two over time with four, packed both: 100 000 x 100, 512 to 1024 chains, 12 iterations 1.01 to 1.03; 20 000 x 25, 512 to
+// 4096 chains, 12 to 50 iterations 1.00 to 1.05 with a fast host and 0.86 to 0.93 with a slower one, which has to keep up; on a
+// target that is the chip kernel's now, 10 000 x 100, 1024 and 4096 chains, 50 iterations 1.05, 12 iterations 1.03 and 1.05, one
+// awaited 0.89 and 1.03, 512 chains 0.80 to 1.01.
 // A target's first launch with four takes 5 ms more than with two, to create the streams: only launches of some 110 ms
 // (1e11 chain iterations x rows x features) save as much.
 inline int grid_streams(int n_slots, long n, int d, double chain_iters)
