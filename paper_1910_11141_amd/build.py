@@ -20,9 +20,11 @@ FLAGS = [
 ]
 
 
-# The chip kernel's instances keep a chain's state in registers through a loop that is long and deep: hoisting constants and
-# addresses out of it (the compiler's habit) fills the register file and spills the state itself (400 bytes a lane).
-EXTRA_FLAGS = {"nuts_chip.hip": ["-mllvm", "-disable-machine-licm", "-mllvm", "-sink-insts-to-avoid-spills=1"]}
+# Kernels whose instances keep a chain's state in registers through a loop that is long and deep: hoisting constants and
+# addresses out of it (the compiler's habit) fills the register file and spills the state itself (chip kernel: 400 bytes a
+# lane; the others: nuts_gauss.hip).
+NO_LICM = ["-mllvm", "-disable-machine-licm", "-mllvm", "-sink-insts-to-avoid-spills=1"]
+EXTRA_FLAGS = {"nuts_chip.hip": NO_LICM, "nuts_gauss.hip": NO_LICM}
 
 
 def sources():

@@ -7,8 +7,11 @@
 // What bounds it: the latency of the chain program (few chains), or the vector instructions of gradient, leaf and merge.
 // Against nine entries of a row in the general wave kernel, which keeps every vector in memory: two iterations, AR(1), binary64: d = 129, 4
 // chains 0.50 -> 0.14 ms; d = 1000, 1024 chains 3.3 -> 0.68 ms; d = 2000, 4096 chains 21.4 -> 14.1 ms.  Beyond 512 dimensions in
-// binary64 and 1024 in binary32 the state no longer fits the registers: scratch memory per lane is 460 bytes at kC = 8 and 2880
-// at 16 in binary64, 1724 at 16 (and 80 at 4, for two workgroups per compute unit) in binary32.  Same outputs, bit for bit.
+// binary64 and 1024 in binary32 the state hardly fits the registers: with constants and addresses hoisted out of the loops scratch
+// memory per lane was 476 bytes at kC = 8 and 2928 at 16 in binary64, 1640 at 16 in binary32; without (nuts_gauss.hip) it is 812 at
+// 16 in binary64, else none (but 40 at 4 in binary32, for two workgroups per compute unit): d = 2000, binary64, 4096 chains, six
+// iterations 226 -> 118 ms, 64 chains 29.3 -> 18.8; binary32, 2048 chains 73 -> 25; d = 1000, binary64, 1024 chains 7.66 -> 6.70.
+// Same outputs, bit for bit.
 #pragma once
 #include "nuts_row.h"
 
@@ -95,5 +98,12 @@ __global__ __launch_bounds__(256, (band_lane_bytes<T, kC>() <= 32 ? 2 : 1)) void
         atomicAdd(&sa.counters[kCtrRounds], ch.n_leaf + ch.n_extra);
     }
 }
+
+// Instances with the compiler flags of nuts_gauss.hip: those whose state does not fit the registers beside hoisted constants.  The
+// others are 3 to 6 % faster without (kC = 4 in binary64 only up to four chains per compute unit: beyond, the flags would give it
+// a second wave per SIMD and 1.4 to 1.5 times the speed).
+#define NUTS_BAND_INSTANCE(T, kC) template __global__ void nuts_band_kernel<T, kC>(DevTarget<T>, const T*, int, DevSample, RowLds);
+#define NUTS_BAND_INSTANCES(pre) pre NUTS_BAND_INSTANCE(float, 16) pre NUTS_BAND_INSTANCE(double, 8) pre NUTS_BAND_INSTANCE(double, 16)
+NUTS_BAND_INSTANCES(extern)
 
 }  // namespace nuts

@@ -12,8 +12,8 @@
 // What bounds it: the operand stream, which a compute unit takes from L2 at about 45 bytes per tick (d = 256: 0.5 MB in
 // 11.5 k ticks, of which the instructions of 4 chains need 4.1 k, of 8 chains 8.2 k), then the chain program (5 k ticks).
 // A form with 16 chains and v_mfma_f64_16x16x4 was matrix-bound at 21 k ticks, and its 16 waves left 128 registers to
-// the chain program, which then took 45 k.  (These forms keep 48 to 52 bytes a lane in scratch memory at kC = 2 in binary64, 164
-// to 172 at 3 and 396 at 4; in binary32 none, at 4 56.)  Binary32 targets keep binary64 sums of binary32 values, as in the wave kernel.
+// the chain program, which then took 45 k.  (Scratch memory per lane: 36 bytes at kC = 4 in binary64, else none; with
+// constants hoisted out of the loops 56, 212 and 428 at kC = 2, 3, 4 and d = 384, 2048 chains, four iterations 2.34 -> 2.75 ms.)  Binary32 targets keep binary64 sums of binary32 values, as in the wave kernel.
 // d = 250, binary64, 300 chains, every iteration awaited, 10 iterations: 34.3 ms (wave kernel) -> 2.5 ms.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -270,7 +270,7 @@ inline hipError_t block_launch_inst(const BlockArgs& ba, const DevSample& sa, co
     return hipGetLastError();
 }
 template <typename T>
-inline hipError_t block_launch(const BlockData& bd, const DevSample& sa, const BlockPlan& bp, hipStream_t stream)
+hipError_t block_launch(const BlockData& bd, const DevSample& sa, const BlockPlan& bp, hipStream_t stream)
 {
     const BlockArgs ba{bd.ops, (unsigned)(block_stream_doubles(bd.n_r, bd.pq) * sizeof(double)), bd.d, bd.n_r, bd.pq};
     switch (block_chunks(bd.d)) {
@@ -279,5 +279,7 @@ inline hipError_t block_launch(const BlockData& bd, const DevSample& sa, const B
     default: return block_launch_inst<T, 4, 4>(ba, sa, bp, stream);
     }
 }
+extern template hipError_t block_launch<float>(const BlockData&, const DevSample&, const BlockPlan&, hipStream_t);  // nuts_gauss.hip
+extern template hipError_t block_launch<double>(const BlockData&, const DevSample&, const BlockPlan&, hipStream_t);
 
 }  // namespace nuts

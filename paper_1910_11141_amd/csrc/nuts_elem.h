@@ -8,9 +8,10 @@
 // end with the other one (in registers too while a vector takes up to 32 bytes of a lane, else in memory).
 //
 // What bounds it: with few chains or dimensions the latency of the chain program, with many the vector instructions of
-// leaf and merge (the energies, kinetic terms and U-turn sums are binary64 sums of the elements): d = 1000 in binary32 565
-// vector instructions a step, one every 4.1 cycles of a SIMD, 3.4 KB of HBM traffic a step.  Scratch memory per lane: 72 bytes
-// at kC = 8 in binary32, 604 at 16 in binary64, none elsewhere.
+// leaf and merge (the energies, kinetic terms and U-turn sums are binary64 sums of the elements): d = 1000 in binary32 459
+// vector instructions a step, one every 4.5 cycles of a SIMD, 3.4 KB of HBM traffic a step.  Scratch memory per lane: 124 bytes
+// at 16 in binary64 (644 with constants hoisted out of the loops; d = 2000, 8192 chains, six iterations 12.5 -> 7.5 ms, 256 chains
+// 1.13 -> 0.78), none elsewhere.
 // Against the kernel before it (weights as logarithms through a table, 53 KB of LDS for that table, the random numbers
 // of a doubling drawn one by one, first leaves and both ends in memory), the same outputs bit for bit: d = 2 binary64, 4
 // chains, 100 iterations 1170 -> 670 us; d = 500 binary32 standard normal, 16384 chains, 20 iterations 10.0 -> 4.3 ms; d = 1000 binary32
@@ -113,5 +114,9 @@ __global__ __launch_bounds__(256, (elem_lane_bytes<T, kC>() <= 64 ? 2 : 1)) void
         atomicAdd(&sa.counters[kCtrRounds], ch.n_leaf + ch.n_extra);
     }
 }
+
+// The instance with the compiler flags of nuts_gauss.hip; with them d = 1000 takes 1.03 (binary32) to 1.06 times as long.
+#define NUTS_ELEM_INSTANCE(T, kC) template __global__ void nuts_elem_kernel<T, kC>(DevTarget<T>, DevSample, RowLds);
+extern NUTS_ELEM_INSTANCE(double, 16)
 
 }  // namespace nuts

@@ -616,18 +616,6 @@ inline hipError_t quad_launch_inst(const QuadArgs& qa, const DevSample& sa, int 
     return hipGetLastError();
 }
 
-inline hipError_t quad_launch(const QuadArgs& qa, const DevSample& sa, int blocks, size_t lds_bytes, hipStream_t stream)
-{
-    switch (qa.n_r) {
-    case 1: return quad_launch_inst<1>(qa, sa, blocks, lds_bytes, stream);
-    case 2: return quad_launch_inst<2>(qa, sa, blocks, lds_bytes, stream);
-    case 3: return quad_launch_inst<3>(qa, sa, blocks, lds_bytes, stream);
-    case 4: return quad_launch_inst<4>(qa, sa, blocks, lds_bytes, stream);
-    case 5: return quad_launch_inst<5>(qa, sa, blocks, lds_bytes, stream);
-    case 6: return quad_launch_inst<6>(qa, sa, blocks, lds_bytes, stream);
-    case 7: return quad_launch_inst<7>(qa, sa, blocks, lds_bytes, stream);
-    default: return quad_launch_inst<8>(qa, sa, blocks, lds_bytes, stream);
-    }
-}
+hipError_t quad_launch(const QuadArgs& qa, const DevSample& sa, int blocks, size_t lds_bytes, hipStream_t stream);  // nuts_gauss.hip
 
 }  // namespace nuts
