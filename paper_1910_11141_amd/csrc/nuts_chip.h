@@ -99,6 +99,29 @@ inline int chip_slices(int n_tiles, int blocks)
     return s;
 }
 
+// The control phase sums a chain's partial gradients in kChipMaxSlices / 16 steps: in step i the two halves of wave w take slices
+// 2w + 16i and the one after it.  Which of them there are: the halves' step, and the half in it.
+constexpr __host__ __device__ bool chip_step_there(int wave, int i, int n_slices) { return 2 * wave + 16 * i < n_slices; }
+constexpr __host__ __device__ bool chip_half_there(int half, int n_slices) { return half < n_slices; }
+constexpr bool chip_slices_taken_once()
+{
+    for (int n = 1; n <= kChipMaxSlices; n *= 2) {  // (what chip_slices can return)
+        int taken[kChipMaxSlices] = {};
+        for (int wave = 0; wave < kChipWaves; ++wave)
+            for (int i = 0; i < kChipMaxSlices / 16; ++i)
+                for (int half = 0; half < 2; ++half)
+                    if (chip_step_there(wave, i, n) && chip_half_there(half, n)) {
+                        const int s = 2 * wave + half + 16 * i;
+                        if (s >= n) return false;
+                        ++taken[s];
+                    }
+        for (int s = 0; s < n; ++s)
+            if (taken[s] != 1) return false;
+    }
+    return true;
+}
+static_assert(chip_slices_taken_once(), "every slice once, and none beyond the last");
+
 // What the workgroups share, one cache line per counter: {arrivals at the first barrier, columns handed out, arrivals at the
 // second barrier, arrivals at the start}.  Line kChipCounters: {state}.
 constexpr int kChipLine = 32;  // unsigned
@@ -272,8 +295,9 @@ __global__ __launch_bounds__(kChipThreads) void nuts_chip_kernel(ChipArgs ca, De
             // are under way together (of all four: 128 registers, and the chain's state is spilled)
             const int half = lane >> 5, piece = lane & 31;
             const unsigned row = (unsigned)(K * 4), per_slice = row * kChipColumns;
-            // (what is past the end of the buffer reads zeros: slices beyond the last, lanes beyond the last feature)
-            const int lane_off = piece < K / V ? (int)(half * per_slice + piece * 16) : (int)0xc0000000u;
+            // (lanes beyond the last feature, and the second half where there is one slice, read zeros: their own offset is past the
+            // end of the buffer)
+            const int lane_off = piece < K / V && chip_half_there(half, ca.n_slices) ? (int)(half * per_slice + piece * 16) : (int)0xc0000000u;
             constexpr int kMost = kChipMaxSlices / 16;
 #pragma unroll
             for (int o0 = 0; o0 < kChipOwners; o0 += 2) {
@@ -284,7 +308,7 @@ __global__ __launch_bounds__(kChipThreads) void nuts_chip_kernel(ChipArgs ca, De
                     int at = (int)(2 * wave * per_slice + (unsigned)uni(sColumn[o]) * row);
 #pragma unroll
                     for (int i = 0; i < kMost; ++i) {
-                        if (16 * i < ca.n_slices) p[o - o0][i] = __builtin_bit_cast(Piece, __builtin_amdgcn_raw_buffer_load_b128(g_rsrc, lane_off, at, kAgent));
+                        if (chip_step_there(wave, i, ca.n_slices)) p[o - o0][i] = __builtin_bit_cast(Piece, __builtin_amdgcn_raw_buffer_load_b128(g_rsrc, lane_off, at, kAgent));
                         at += (int)(16 * per_slice);
                     }
                 }
@@ -296,7 +320,7 @@ __global__ __launch_bounds__(kChipThreads) void nuts_chip_kernel(ChipArgs ca, De
                     for (int e = 0; e < V; ++e) a[e] = 0.0;
 #pragma unroll
                     for (int i = 0; i < kMost; ++i)
-                        if (16 * i < ca.n_slices)
+                        if (chip_step_there(wave, i, ca.n_slices))
 #pragma unroll
                             for (int e = 0; e < V; ++e) a[e] += (double)p[o - o0][i][e];
 #pragma unroll
