@@ -9,7 +9,7 @@
 //   gradient  every workgroup has a slice of the rows, and a share of the columns where there are fewer slices than workgroups.
 //             Its eight waves have tiles of 16 rows each, in LDS in one order that serves both GEMMs (and stay there
 //             from round to round if a wave has only one), take groups of 16 columns through 16x16x4 matrix instructions, and
-//             add their sums up in LDS in a fixed order: one partial gradient per slice and column.
+//             add their sums up in LDS in a fixed order, in binary64: one partial gradient per slice and column.
 // As in the tile kernel, X~ = diag(2y - 1) X, so the labels never reach the GPU arithmetic:
 // y z - log(1+e^z) = -log(1+e^{-z~}),  X'(y - sigma(z)) = X~' sigma(-z~).
 //
@@ -25,7 +25,7 @@
 // residue of the workgroup number modulo 8; flags that everybody polls: 3.1 to 5.5 us), the latency of the partial sums and of
 // the chain program.  10 000 x 100: a round takes 11.5 us with one chain, 26 us with 227 columns busy (control with its barrier 7 us,
 // positions 2.5, tiles 12, their sums and the second barrier 5).  1024 chains, 4 iterations of the slice sampler with four
-// steps a leaf: 10.9 ms with two launches a round (nuts_grid.h) -> 8.2.  256 vector registers, none in scratch memory.
+// steps a leaf: 10.9 ms with two launches a round (nuts_grid.h) -> 8.4.  185 to 238 vector registers, none in scratch memory.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -546,15 +546,26 @@ __global__ __launch_bounds__(kChipThreads) void nuts_chip_kernel(ChipArgs ca, De
                             }
                         }
                         ll_sum -= (double)fmaf(__builtin_amdgcn_logf(pr), 0.69314718055994531f, hinge);
+                        // A tile's 16 rows are one binary32 sum; tiles are added in binary32, the four waves of a slice and the slices
+                        // in binary64.  RMS error of the gradient over that of one binary32 sum per 64 rows (per 32 of fewer than 2048,
+                        // per 256th of more than 16 384), emulated, 130 x 128 to 90 000 x 16: 0.28 to 0.99.  With all of a wave's rows in one
+                        // binary32 sum, and the waves', it was 0.66 to 1.67 at 2.8 % less time (10 000 x 100, 1024 chains); with 32 rows a
+                        // sum 0.29 to 1.19.
+                        Acc t[2][N];
+                        auto add = [&](int u) __attribute__((always_inline)) { G[u] += N == 2 ? t[u & 1][0] + t[u & 1][N - 1] : t[u & 1][0]; };
 #pragma unroll
                         for (int u = 0; u < MT; ++u) {
                             if (u + 1 < MT) ask_tile(u + 1);
                             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                            for (int p = 0; p < N; ++p)
+                            for (int p = 0; p < N; ++p) t[u & 1][p] = Acc{0, 0, 0, 0};
 #pragma unroll
-                                for (int q = 0; q < 4; ++q) G[u] = mfma(xg[u & 1][p][q], sg[p][q], G[u]);
+                            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                                for (int p = 0; p < N; ++p) t[u & 1][p] = mfma(xg[u & 1][p][q], sg[p][q], t[u & 1][p]);
+                            if (u > 0) add(u - 1);
                         }
+                        add(MT - 1);
                     };
                     if (tile0 + 4 < t_end) tiles(std::integral_constant<int, 2>{});
                     else tiles(std::integral_constant<int, 1>{});
@@ -581,7 +592,9 @@ __global__ __launch_bounds__(kChipThreads) void nuts_chip_kernel(ChipArgs ca, De
                         Piece part[4];
 #pragma unroll
                         for (int r = 0; r < 4; ++r) part[r] = *reinterpret_cast<const Piece*>(w + r * S::kTile);
-                        const Piece sum = (part[0] + part[1]) + (part[2] + part[3]);
+                        Piece sum;
+#pragma unroll
+                        for (int e = 0; e < V; ++e) sum[e] = (float)(((double)part[0][e] + (double)part[1][e]) + ((double)part[2][e] + (double)part[3][e]));
                         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, sum), g_rsrc,
                                                                (int)((((unsigned)slice * kChipColumns + sCols[k]) * K + th_at[q]) * 4u), 0, kAgent);
                     }

@@ -561,6 +561,47 @@ def test_chip_kernel_edges_match_the_oracle_on_both_schedules(n_data, dim, n_cha
     f32_parity(slice3, ref_run(w, sampler=SLICE, leaf_steps=3, n_iters=2))
 
 
+def rows_summed_in_binary32(X, rows):
+    """X' / 2 with one binary32 sum per `rows` consecutive rows, of fused multiply-adds in order, and binary64 sums of those."""
+    n, d = X.shape
+    x = np.concatenate([X, np.zeros((-n % rows, d), np.float32)]).reshape(-1, rows, d)
+    acc = np.zeros(x.shape[::2], np.float32)
+    for i in range(rows):
+        acc = (acc.astype(np.float64) + 0.5 * x[:, i].astype(np.float64)).astype(np.float32)
+    return acc.astype(np.float64).sum(axis=0)
+
+
+@pytest.mark.parametrize("n_data,dim,rows", [(1500, 100, 32), (2040, 60, 32), (6000, 60, 64), (10000, 100, 64), (15000, 100, 64), (23000, 64, 96)])
+def test_chip_kernel_gradients_are_as_exact_as_sums_of_few_rows(n_data, dim, rows):
+    """The gradient at zero, where every residual is 1/2, out of the first leapfrog step of many chains that all start
+    there: theta = v eps (r + v eps / 2 g), so every chain shows the same g, and roundings of its own that average out.
+    The bar is one binary32 sum per 32 rows of fewer than 2048, else per 64 or a 256th of them, and binary64 beyond: what
+    sums in the order of the grid kernels' row slices amount to.  (One sum per wave over up to 180 rows, and of four waves in
+    binary32, is 1.1 to 1.4 times as far off.)"""
+    rng = np.random.default_rng(n_data)
+    X = np.concatenate([rng.standard_normal((n_data, dim - 1)), np.ones((n_data, 1))], axis=1).astype(np.float32)
+    y = (rng.random(n_data) < 0.5).astype(np.float32)
+    signed = np.where(y[:, None] != 0, X, -X)
+    exact = 0.5 * signed.astype(np.longdouble).sum(axis=0)
+    nc, eps = 1000, 2.0 ** round(np.log2(1.5 / np.sqrt(n_data)))
+    w = W.Workload("at_zero", W.LOGREG, dim, np.dtype(np.float32), nc, 1, eps, 1, seed=43, X=X, y=y, prior_scale=1.0)
+    s, _, n, st = gpu_run(w, variant=N().NUTS_VARIANT_GRID, init=np.zeros((nc, dim)))
+    assert (n == 1).all()
+    r0 = np.array([[z for i in range((dim + 1) // 2) for z in R.normal_pair(R.draw(w.seed, i, R.TAG_MOMENTUM, 0, 0, c))][:dim]
+                   for c in range(nc)]).astype(np.float32).astype(np.float64)
+    th = s[0].astype(np.float64)
+    seen = np.stack([(th - v * eps * r0) * 2 / eps ** 2 for v in (1, -1)])
+    off = np.abs(seen - exact.astype(np.float64)).max(axis=2)
+    moved = np.abs(th).max(axis=1) > 0
+    assert moved.sum() >= nc // 4
+    pick = off.argmin(axis=0)
+    g = seen[pick, np.arange(nc)][moved].mean(axis=0)
+    err = float(np.sqrt(np.mean((g - exact.astype(np.float64)) ** 2)))
+    bar = float(np.sqrt(np.mean((rows_summed_in_binary32(signed, rows).astype(np.float32) - exact.astype(np.float64)) ** 2)))
+    report("at_zero", n=n_data, d=dim, err=err, bar=bar)
+    assert err <= bar, f"error {err:.2e} against {bar:.2e}"
+
+
 # large enough for the two-launch grid kernels: left-over features of one and two groups of 4, none, and the largest; from 65 505 rows on
 # a slice's four runs of tiles, with one, two and more groups of columns in use
 @pytest.mark.parametrize("n_data,dim,n_chains", [(46000, 33, 3), (15700, 97, 40), (12100, 17, 6), (24000, 71, 5), (12500, 128, 3), (12001, 32, 130),
