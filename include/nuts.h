@@ -67,7 +67,10 @@ enum {
                                at a time, further chains wait in a queue); this variant returns only when
                                sampling has finished.  Targets of up to 1.5e6 elements (of 17 to 32 features:
                                12 000 rows) run in one launch that holds every compute unit, one such run at
-                               a time on a device; larger ones in two launches a round, beyond 128 chains
+                               a time on a device: calls of a process take turns, and a call waits while
+                               other work holds compute units (where that goes on, or the stream has
+                               only some of them, it runs on as many as it gets: the same bits);
+                               larger ones in two launches a round, beyond 128 chains
                                divided between two or four streams, the caller's and others that the target
                                owns, forked from and joined to the caller's stream by events; chains that want
                                a gradient are packed together, so idle ones cost next to nothing           */

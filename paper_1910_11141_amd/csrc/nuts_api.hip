@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdlib>
 #include <cstdarg>
@@ -12,6 +13,8 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <random>
+#include <thread>
 #include <vector>
 
 #include "../../include/nuts.h"
@@ -111,6 +114,8 @@ struct nuts_target {
     hipStream_t side_stream[nuts::kGridMaxStreams - 1] = {};
     hipEvent_t ev_fork = nullptr, ev_join[nuts::kGridMaxStreams - 1] = {};
     unsigned* chip_state = nullptr;     // chip kernel: pinned, how the last run ended
+    int chip_most = 0;                  // chip kernel: the most workgroups of the call's further launches, 0: no bound
+    int chip_refuse = 0, chip_bound = 0;  // nuts_debug_chip_starts
     int* halted_host = nullptr;         // grid kernels: pinned, two snapshots of the "halted" flags
     hipEvent_t ev_batch[2 * nuts::kGridMaxStreams] = {};  // [snapshot][stream]
     bool has_run = false;
@@ -966,11 +971,41 @@ int launch_tile(nuts_target* t, nuts::DevSample sa)
     return NUTS_OK;
 }
 
-// One launch of the chip kernel, which needs all its workgroups at once: a cooperative launch, one at a time on a device (two of
-// them that each had a part of the chip would wait for each other).  Should the device be shared with another process so that
-// the workgroups cannot run together, the kernel gives up before it has done anything and is launched again.  As with the
-// grid kernels, this returns only when sampling is complete.
+// One launch of the chip kernel, which needs all its workgroups at once, one at a time on a device (two of them that each had a
+// part of the chip would wait for each other).  A start that not all workgroups reach, because somebody else holds compute
+// units, ends after half a second, before anything has been done.  The host then waits until a compute unit has room for a workgroup, as
+// any launch would, and starts again; after three such starts with half as many workgroups, down to one, which waits for nobody.
+// So a busy device or a stream that has a part of it delays a call and never fails it, and the outputs are the same bits (the
+// rows are divided as for the whole chip).  As with the grid kernels, this returns only when sampling is complete.
 std::mutex g_chip_mutex[kMaxDevices];
+
+// Compute units that the call's stream may use (a stream can be created with a mask of them).
+int stream_compute_units(int cus)
+{
+    uint32_t mask[32] = {};
+    if (hipExtStreamGetCUMask(g_stream, 32, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return cus;
+    }
+    int n = 0;
+    for (uint32_t m : mask) n += __builtin_popcount(m);
+    return n >= 1 && n < cus ? n : cus;
+}
+
+__global__ void chip_room_kernel() {}
+
+// Returns when a compute unit has had room for a workgroup, and a moment later: that of two processes whose workgroups shared
+// the chip out among them one comes first.
+int await_chip_room(size_t lds_bytes, int attempt)
+{
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(chip_room_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes), NUTS_E_DEVICE);
+    hipLaunchKernelGGL(chip_room_kernel, dim3(1), dim3(nuts::kChipThreads), lds_bytes, g_stream);
+    HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
+    HIP_TRY(hipStreamSynchronize(g_stream), NUTS_E_DEVICE);
+    static thread_local std::minstd_rand random{std::random_device{}()};
+    std::this_thread::sleep_for(std::chrono::milliseconds(random() % (20u << std::min(attempt, 5))));
+    return NUTS_OK;
+}
 
 int launch_chip(nuts_target* t, nuts::DevSample sa)
 {
@@ -979,17 +1014,17 @@ int launch_chip(nuts_target* t, nuts::DevSample sa)
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device), NUTS_E_DEVICE);
     const int mt = t->chip.mt;
     ChipPlan cp{};
-    cp.blocks = cus < kChipMaxBlocks ? cus : kChipMaxBlocks;
+    const int whole = cus < kChipMaxBlocks ? cus : kChipMaxBlocks;
+    cp.blocks = std::min(whole, stream_compute_units(cus));
+    if (t->chip_most > 0 && t->chip_most < cp.blocks) cp.blocks = t->chip_most;
     chip_lds(mt, sa.max_depth, &cp);
     ChipArgs ca{};
     ca.x = t->chip.x;
     ca.d = t->chip.d;
     ca.n_rows = t->chip.n_rows;
     ca.n_tiles = t->chip.n_tiles;
-    ca.n_blocks = cp.blocks;
-    ca.n_slices = chip_slices(ca.n_tiles, cp.blocks);
-    const long most = (long)cp.blocks * kChipOwners;
-    ca.n_slots = (int)(sa.n_chains < most ? sa.n_chains : most);
+    ca.n_slices = chip_slices(ca.n_tiles, whole);
+    const size_t most_slots = (size_t)std::min<long>(sa.n_chains, (long)cp.blocks * kChipOwners);
     ca.prior_prec = 1.0 / (t->prior_scale * t->prior_scale);
     ca.theta_bytes = (unsigned)((size_t)kChipColumns * 16 * mt * sizeof(float));
     ca.g_bytes = (unsigned)((size_t)ca.n_slices * ca.theta_bytes);
@@ -999,7 +1034,7 @@ int launch_chip(nuts_target* t, nuts::DevSample sa)
     const size_t o_shared = take(shared_words * sizeof(unsigned));
     const size_t o_theta = take(ca.theta_bytes), o_g = take(ca.g_bytes);
     const size_t o_ll = take((size_t)ca.n_slices * kChipColumns * sizeof(double));
-    const size_t o_chains = take(cp.slot_bytes * (size_t)ca.n_slots);
+    const size_t o_chains = take(cp.slot_bytes * most_slots);
     int rc = ensure_workspace(t, off);
     if (rc) return rc;
     ca.shared = reinterpret_cast<unsigned*>(t->ws_cur + o_shared);
@@ -1010,19 +1045,28 @@ int launch_chip(nuts_target* t, nuts::DevSample sa)
     sa.slot_bytes = cp.slot_bytes;
     if (!t->chip_state) HIP_TRY(hipHostMalloc((void**)&t->chip_state, sizeof(unsigned)), NUTS_E_ALLOC);
     std::lock_guard<std::mutex> lock(g_chip_mutex[t->device]);
-    for (int attempt = 0; attempt < 30; ++attempt) {
+    for (int attempt = 0;; ++attempt) {
+        ca.n_blocks = cp.blocks;
+        ca.n_slots = (int)std::min<long>(sa.n_chains, (long)cp.blocks * kChipOwners);
         hipLaunchKernelGGL(fill_words_kernel, dim3(1), dim3(256), 0, g_stream, ca.shared, (int)shared_words, 0u);
+        unsigned* const state = ca.shared + kChipCounters * kChipLine;
+        if (t->chip_refuse > 0) {
+            t->chip_refuse -= 1;
+            hipLaunchKernelGGL(fill_words_kernel, dim3(1), dim3(64), 0, g_stream, state, 1, (unsigned)kChipNotStarted);
+        }
         HIP_TRY(chip_launch(mt, ca, sa, cp, g_stream), NUTS_E_DEVICE);
-        HIP_TRY(hipMemcpyAsync(t->chip_state, ca.shared + kChipCounters * kChipLine, sizeof(unsigned), hipMemcpyDeviceToHost, g_stream), NUTS_E_DEVICE);
+        HIP_TRY(hipMemcpyAsync(t->chip_state, state, sizeof(unsigned), hipMemcpyDeviceToHost, g_stream), NUTS_E_DEVICE);
         HIP_TRY(hipStreamSynchronize(g_stream), NUTS_E_DEVICE);
-        if (*t->chip_state == kChipNotStarted) continue;
-        if (*t->chip_state != kChipRunning) return fail(NUTS_E_DEVICE, "chip kernel: a workgroup did not reach a barrier in time");
-        t->last_variant = NUTS_VARIANT_GRID;
-        t->last_grid = cp.blocks;
-        t->last_slots = 0;
-        return NUTS_OK;
+        if (*t->chip_state == kChipRunning) break;
+        if (*t->chip_state != kChipNotStarted) return fail(NUTS_E_DEVICE, "chip kernel: a workgroup did not reach a barrier in time");
+        rc = await_chip_room(cp.lds_bytes, attempt);
+        if (rc) return rc;
+        if (attempt % 3 == 2) t->chip_most = cp.blocks = (cp.blocks + 1) / 2;  // (for the rest of the call)
     }
-    return fail(NUTS_E_DEVICE, "chip kernel: the device did not run all workgroups at once");
+    t->last_variant = NUTS_VARIANT_GRID;
+    t->last_grid = cp.blocks;
+    t->last_slots = 0;
+    return NUTS_OK;
 }
 
 }  // namespace
@@ -1030,6 +1074,16 @@ int launch_chip(nuts_target* t, nuts::DevSample sa)
 extern "C" {
 
 const char* nuts_last_error(void) { return g_err; }
+
+// For tests of what a busy device does to the chip kernel's runs on a target (not part of the interface): its next `refused` starts
+// end as starts do that not all workgroups reach, and its calls take at most `most_blocks` workgroups (0: no bound).
+int nuts_debug_chip_starts(nuts_target* t, int refused, int most_blocks)
+{
+    if (!t || refused < 0 || most_blocks < 0) return fail(NUTS_E_INVALID_ARG, "nuts_debug_chip_starts: bad argument");
+    t->chip_refuse = refused;
+    t->chip_bound = most_blocks;
+    return NUTS_OK;
+}
 
 int nuts_tile_pack(const double* X, const double* y, int64_t n, int64_t d, nuts_tile_layout* layout, double* operands,
                    int64_t capacity)
@@ -1204,6 +1258,7 @@ int sample_impl(const nuts_target* target, int64_t n_chains, int64_t n_iters, do
         if (rc) return rc;
     }
     t->static_call = use_static;
+    t->chip_most = t->chip_bound;
     t->counters_cur = use_static ? reinterpret_cast<unsigned long long*>(g_scratch_ptr[t->device]) : t->counters;
 
     nuts::DevSample sa{};

@@ -1,4 +1,5 @@
-// Chip kernel: logistic regression whose rows are spread over the whole chip, one persistent workgroup per compute unit.
+// Chip kernel: logistic regression whose rows are spread over the whole chip, one persistent workgroup per compute unit (fewer
+// where something else holds compute units; then a workgroup has several slices of the rows, and every chain the same bits).
 //
 // The chains step together, as in the wide kernel, but a round's two GEMMs  Z = X~ Theta,  G = X~' sigma(-Z)  are shared by all
 // compute units, and a round is two phases of one launch that are separated by barriers over all workgroups:
@@ -82,7 +83,7 @@ constexpr int chip_pitch(int mt) { return 16 * mt + 4; }
 // 0.93, 50 000 x 25 0.82.
 inline bool chip_pays(int64_t n, int64_t d) { return d <= kChipMaxDim && (d > 16 && d <= 32 ? n <= 12000 : n * d <= 1500000); }
 
-// Into how many slices a chip of `blocks` workgroups divides a target's tiles (the workgroups share the columns of a slice).  Few
+// Into how many slices a chip with room for `blocks` workgroups divides a target's tiles (the workgroups share the columns of a slice).  Few
 // slices make long passes, whose sums and positions cost less, and few partial results: better with all columns busy; many
 // make the rounds short in which few chains are left.  The largest power of two (which divides the chip evenly) whose
 // square is at most 2.7 times the number of tiles, up to 128.  ms with 8, 16, 32, 64, 128, 256 slices, and what the rule takes:
@@ -151,11 +152,11 @@ constexpr int kAgent = 16;  // cache policy of a buffer instruction: agent scope
 
 // Waits (first wave of a workgroup) until word `word` of every counter's line has reached target[counter]; returns false if
 // the run is over for another reason.  Every wait ends: a start that not all workgroups reach (the chip is shared with
-// somebody) is given up after 2 s, any other wait after 60 s.
+// somebody) is given up after half a second, any other wait after 60 s.
 __device__ inline bool chip_wait(const ChipArgs& ca, int lane, int word, unsigned target, bool start, v4u& seen)
 {
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(ca.shared, 0, (kChipCounters + 1) * kChipLine * 4, 0x00020000);
-    const long long t0 = wall_clock64(), limit = start ? 200000000ll : 6000000000ll;  // (100 MHz)
+    const long long t0 = wall_clock64(), limit = start ? 50000000ll : 6000000000ll;  // (100 MHz)
     for (;;) {
         // (lanes beyond the last line read zeros)
         seen = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * kChipLine * 4, 0, kAgent));
@@ -186,7 +187,9 @@ __device__ inline bool chip_wait(const ChipArgs& ca, int lane, int word, unsigne
     }
 }
 
-template <int MT>
+// kSeveral: there are fewer workgroups than slices.  (An instance of its own: the slice as a variable costs up to 28 registers, and the
+// largest instances some of their state.)
+template <int MT, bool kSeveral>
 __global__ __launch_bounds__(kChipThreads) void nuts_chip_kernel(ChipArgs ca, DevSample sa, RowLds rl)
 {
     typedef ChipShape<MT> S;
@@ -224,11 +227,17 @@ __global__ __launch_bounds__(kChipThreads) void nuts_chip_kernel(ChipArgs ca, De
     __syncthreads();
     if (!sOk) return;
 
-    // ---- this workgroup's rows and columns ----
-    const int slice = (int)blockIdx.x % ca.n_slices, share = (int)blockIdx.x / ca.n_slices, n_shares = ca.n_blocks / ca.n_slices;
+    // ---- this workgroup's rows and columns: a slice and a share of the columns, or, of fewer workgroups than slices, several slices ----
+    const int share = (int)blockIdx.x / ca.n_slices, n_shares = kSeveral ? 1 : ca.n_blocks / ca.n_slices;
     const bool computes = share < n_shares;
-    const int t_first = (int)((long)ca.n_tiles * slice / ca.n_slices), t_end = (int)((long)ca.n_tiles * (slice + 1) / ca.n_slices);
-    const int n_steps = computes ? (t_end - t_first + kChipWaves - 1) / kChipWaves : 0;  // of eight tiles
+    int slice, t_first, t_end, n_steps;
+    auto take_slice = [&](int s) __attribute__((always_inline)) {
+        slice = s;
+        t_first = (int)((long)ca.n_tiles * s / ca.n_slices);
+        t_end = (int)((long)ca.n_tiles * (s + 1) / ca.n_slices);
+        n_steps = computes ? (t_end - t_first + kChipWaves - 1) / kChipWaves : 0;  // of eight tiles
+    };
+    take_slice((int)blockIdx.x % ca.n_slices);
     // a wave works on two of a step's tiles (four apart), for one of a pass's two groups of columns
     const int quarter = wave & 3, my_group = wave >> 2;
     const int tail_steps = (ca.d - 16 * (MT - 1) + 3) / 4;  // contraction steps of the last 16 features
@@ -447,6 +456,7 @@ __global__ __launch_bounds__(kChipThreads) void nuts_chip_kernel(ChipArgs ca, De
                     th_next[q] = __builtin_bit_cast(Piece, __builtin_amdgcn_raw_buffer_load_b128(theta_rsrc, (int)off, 0, kAgent));
                 }
             };
+            for (;;) {
             ask_theta(share);
             for (int g = share; g < n_groups; g += NG * n_shares) {
 #pragma unroll
@@ -580,7 +590,7 @@ __global__ __launch_bounds__(kChipThreads) void nuts_chip_kernel(ChipArgs ca, De
 #pragma unroll
                 for (int u = 0; u < MT; ++u) *reinterpret_cast<Piece*>(mine + 16 * u + 4 * h) = G[u];
                 chip_barrier();
-                if (n_steps > 1) {
+                if (n_steps > 1 && (!kSeveral || more)) {
                     fetch(0);  // for the next pass or round
                     fetching = true;
                 }
@@ -610,6 +620,14 @@ __global__ __launch_bounds__(kChipThreads) void nuts_chip_kernel(ChipArgs ca, De
                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     }
                 }
+            }
+            if constexpr (!kSeveral) break;
+            // (nobody reads stage 0 since the barrier before the sums)
+            const bool again = slice + ca.n_blocks < ca.n_slices;
+            take_slice(again ? slice + ca.n_blocks : (int)blockIdx.x);
+            fetch(0);
+            fetching = true;
+            if (!again) break;
             }
         }
         __builtin_amdgcn_s_waitcnt(0);
@@ -652,14 +670,19 @@ inline void chip_lds_inst(int max_depth, ChipPlan* cp)
     cp->slot_bytes = ((size_t)row_num_vectors(max_depth) * 128 * sizeof(float) + 255) & ~(size_t)255;
 }
 
-template <int MT>
-inline hipError_t chip_launch_inst(ChipArgs ca, DevSample sa, ChipPlan cp, hipStream_t stream)
+template <int MT, bool kSeveral>
+inline hipError_t chip_launch_inst(const ChipArgs& ca, const DevSample& sa, const ChipPlan& cp, hipStream_t stream)
 {
-    const void* fn = reinterpret_cast<const void*>(nuts_chip_kernel<MT>);
+    const void* fn = reinterpret_cast<const void*>(nuts_chip_kernel<MT, kSeveral>);
     const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)cp.lds_bytes);
     if (e != hipSuccess) return e;
-    void* args[] = {&ca, &sa, &cp.rl};
-    return hipLaunchCooperativeKernel(fn, dim3((unsigned)cp.blocks), dim3(kChipThreads), args, (unsigned)cp.lds_bytes, stream);
+    hipLaunchKernelGGL((nuts_chip_kernel<MT, kSeveral>), dim3((unsigned)cp.blocks), dim3(kChipThreads), cp.lds_bytes, stream, ca, sa, cp.rl);
+    return hipGetLastError();
+}
+template <int MT>
+inline hipError_t chip_launch_inst(const ChipArgs& ca, const DevSample& sa, const ChipPlan& cp, hipStream_t stream)
+{
+    return ca.n_blocks < ca.n_slices ? chip_launch_inst<MT, true>(ca, sa, cp, stream) : chip_launch_inst<MT, false>(ca, sa, cp, stream);
 }
 // (in a translation unit of its own)
 void chip_lds(int mt, int max_depth, ChipPlan* cp);

@@ -602,6 +602,147 @@ def test_chip_kernel_gradients_are_as_exact_as_sums_of_few_rows(n_data, dim, row
     assert err <= bar, f"error {err:.2e} against {bar:.2e}"
 
 
+def chip_starts(tgt, refused=0, most_blocks=0):
+    import ctypes as C
+    B = N()
+    B._check(B.lib().nuts_debug_chip_starts(tgt.handle, C.c_int(refused), C.c_int(most_blocks)))
+
+
+def compute_units():
+    import torch
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+@pytest.mark.parametrize("n_data,dim,n_chains", [(300, 40, 9), (2064, 48, 250), (3000, 9, 1030), (10000, 100, 40), (23000, 64, 3), (700, 128, 5)])
+def test_chip_kernel_with_fewer_workgroups_than_compute_units(n_data, dim, n_chains):
+    """On part of the chip, where a workgroup has several slices of the rows and holds fewer chains, chains have the same bits."""
+    w = W.small_logreg(n_data, dim, seed=500 + dim, dtype=np.float32)
+    w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = n_chains, 2, 0.5 / np.sqrt(n_data), 4
+    tgt = gpu_target(w)
+    whole = gpu_run(w, tgt=tgt, variant=N().NUTS_VARIANT_GRID)
+    assert whole[3]["grid_blocks"] == min(compute_units(), 256)
+    for most in (100, 31, 12, 7, 1):
+        chip_starts(tgt, most_blocks=most)
+        for kw in (dict(), dict(schedule=1)) if most == 12 else (dict(),):
+            part = gpu_run(w, tgt=tgt, variant=N().NUTS_VARIANT_GRID, **kw)
+            assert part[3]["grid_blocks"] == most and part[3]["leaf_slots_useful"] == part[2].sum()
+            for k in range(3):
+                assert np.array_equal(whole[k], part[k])
+
+
+@pytest.mark.parametrize("refused", [1, 2, 3, 7])
+def test_chip_kernel_starts_again_when_compute_units_are_taken(refused):
+    """A start that not all workgroups reach is tried again, after three with half as many workgroups."""
+    w = W.small_logreg(3000, 20, seed=83, dtype=np.float32)
+    w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = 300, 3, 0.02, 5
+    tgt = gpu_target(w)
+    want = gpu_run(w, tgt=tgt)
+    for kw in (dict(), dict(schedule=1)):
+        chip_starts(tgt, refused=refused)
+        got = gpu_run(w, tgt=tgt, **kw)
+        blocks = want[3]["grid_blocks"]
+        for _ in range(refused // 3):
+            blocks = (blocks + 1) // 2
+        assert got[3]["grid_blocks"] == blocks
+        for k in range(3):
+            assert np.array_equal(want[k], got[k])
+    again = gpu_run(w, tgt=tgt)
+    assert again[3]["grid_blocks"] == want[3]["grid_blocks"]
+
+
+def test_chip_kernel_waits_for_a_device_that_is_busy():
+    """A run of another kernel that holds every compute unit, on another stream: the chip kernel's call takes longer, no more."""
+    import torch
+    B = N()
+    busy = W.make(3, n_iters=4000)
+    holder = gpu_target(busy)
+    w = W.small_logreg(3000, 20, seed=83, dtype=np.float32)
+    w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = 300, 3, 0.02, 5
+    tgt = gpu_target(w)
+    want = gpu_run(w, tgt=tgt)
+    first, second = torch.cuda.Stream(), torch.cuda.Stream()
+    try:
+        B.nuts_set_stream(first)
+        with torch.cuda.stream(first):
+            _, _, n_busy = B.nuts_sample(holder, busy.n_chains, busy.n_iters, busy.step_size, busy.max_tree_depth, busy.seed, want_states=False)
+        B.nuts_set_stream(second)
+        with torch.cuda.stream(second):
+            got = gpu_run(w, tgt=tgt)
+    finally:
+        B.nuts_set_stream(None)
+    torch.cuda.synchronize()
+    for k in range(3):
+        assert np.array_equal(want[k], got[k])
+    assert B.nuts_get_stats(holder)["leaf_slots_useful"] == int(n_busy.sum(dtype=torch.int64))
+
+
+def test_chip_kernel_on_a_stream_with_part_of_the_compute_units():
+    import ctypes as C
+
+    import torch
+    B = N()
+    w = W.small_logreg(10000, 100, seed=85, dtype=np.float32)
+    w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = 300, 3, 0.005, 5
+    tgt = gpu_target(w)
+    want = gpu_run(w, tgt=tgt)
+    with open("/proc/self/maps") as f:
+        hip = C.CDLL([line.split()[-1] for line in f if "libamdhip64" in line][0])
+    cus = compute_units()
+    words = (cus + 31) // 32
+    mask = (C.c_uint32 * words)(*([0xffffffff] * (words // 2) + [0] * (words - words // 2)))
+    raw = C.c_void_p()
+    assert hip.hipExtStreamCreateWithCUMask(C.byref(raw), C.c_uint32(words), mask) == 0
+    B.nuts_set_stream(raw.value)
+    try:
+        with torch.cuda.stream(torch.cuda.ExternalStream(raw.value)):
+            got = gpu_run(w, tgt=tgt)
+    finally:
+        B.nuts_set_stream(None)
+        torch.cuda.synchronize()
+        hip.hipStreamDestroy(raw)
+    assert got[3]["grid_blocks"] == words // 2 * 32
+    for k in range(3):
+        assert np.array_equal(want[k], got[k])
+
+
+def test_chip_kernel_called_by_two_threads_at_once():
+    """Runs of the chip kernel on one device take turns: two threads with a target and a stream each."""
+    import threading
+
+    import torch
+    B = N()
+    ws = []
+    for n_data, dim in ((3000, 20), (6000, 60)):
+        w = W.small_logreg(n_data, dim, seed=84, dtype=np.float32)
+        w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = 300, 4, 0.01, 5
+        ws.append(w)
+    want = [gpu_run(w) for w in ws]
+    targets, got, failed = [gpu_target(w) for w in ws], [[], []], []
+
+    def call(i):
+        try:
+            s = torch.cuda.Stream()
+            B.nuts_set_stream(s)
+            with torch.cuda.stream(s):
+                for kw in (dict(), dict(schedule=1), dict()):
+                    got[i].append(gpu_run(ws[i], tgt=targets[i], **kw))
+        except Exception as e:  # noqa: BLE001
+            failed.append(e)
+        finally:
+            B.nuts_set_stream(None)
+
+    threads = [threading.Thread(target=call, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed, failed
+    for i in range(2):
+        for run in got[i]:
+            for k in range(3):
+                assert np.array_equal(want[i][k], run[k])
+
+
 # large enough for the two-launch grid kernels: left-over features of one and two groups of 4, none, and the largest; from 65 505 rows on
 # a slice's four runs of tiles, with one, two and more groups of columns in use
 @pytest.mark.parametrize("n_data,dim,n_chains", [(46000, 33, 3), (15700, 97, 40), (12100, 17, 6), (24000, 71, 5), (12500, 128, 3), (12001, 32, 130),
