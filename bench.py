@@ -86,11 +86,14 @@ KERNEL_HEADERS = {"nuts_grid_grad_kernel": "nuts_grid.h"}  # where it is not the
 
 
 def kernel_code_id(kernel, csrc=os.path.join(ROOT, "paper_1910_11141_amd", "csrc")):
-    """A hash over the headers that a kernel is made of, comments and white space left out: counters taken of other
-    code say nothing about this one."""
+    """A hash over the headers that a kernel is made of, comments and white space left out, and the compiler flags of the
+    translation units that its own header is in: counters taken of other code say nothing about this one."""
     import hashlib
     import re
-    todo, seen = [KERNEL_HEADERS.get(kernel, kernel.replace("_kernel", ".h"))], {}
+    from paper_1910_11141_amd import build
+    own = KERNEL_HEADERS.get(kernel, kernel.replace("_kernel", ".h"))
+    units = [f for f in sorted(os.listdir(csrc)) if f.endswith(".hip") and f'#include "{own}"' in open(os.path.join(csrc, f)).read()]
+    todo, seen = [own], {f: " ".join(build.flags_of(f)) for f in units}
     while todo:
         name = todo.pop()
         if name not in seen:

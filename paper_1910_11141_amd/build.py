@@ -27,6 +27,11 @@ NO_LICM = ["-mllvm", "-disable-machine-licm", "-mllvm", "-sink-insts-to-avoid-sp
 EXTRA_FLAGS = {"nuts_chip.hip": NO_LICM, "nuts_gauss.hip": NO_LICM}
 
 
+def flags_of(source):
+    """The compiler flags of a translation unit."""
+    return [f for f in FLAGS if f != "-shared"] + EXTRA_FLAGS.get(os.path.basename(source), [])
+
+
 def sources():
     return [os.path.join(CSRC, f) for f in sorted(os.listdir(CSRC)) if f.endswith(".hip")]
 
@@ -41,7 +46,7 @@ def is_stale() -> bool:
     if not os.path.exists(LIB_PATH):
         return True
     t = os.path.getmtime(LIB_PATH)
-    return any(os.path.getmtime(p) > t for p in sources() + headers())
+    return any(os.path.getmtime(p) > t for p in sources() + headers() + [os.path.abspath(__file__)])  # (the flags are here)
 
 
 UBENCH_SRC = os.path.join(CSRC, "ubench", "issue_ubench.hip")
@@ -55,9 +60,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
         return LIB_PATH
     with tempfile.TemporaryDirectory() as tmp:
         objects = [os.path.join(tmp, os.path.basename(s) + ".o") for s in sources()]
-        compile_flags = [f for f in FLAGS if f != "-shared"]
-        cmds = [[HIPCC] + compile_flags + EXTRA_FLAGS.get(os.path.basename(s), []) + ["-c", s, "-o", o]
-                for s, o in zip(sources(), objects)]
+        cmds = [[HIPCC] + flags_of(s) + ["-c", s, "-o", o] for s, o in zip(sources(), objects)]
         cmds.append([HIPCC] + FLAGS + [UBENCH_SRC, "-o", UBENCH_LIB])
         for cmd in cmds if verbose else []:
             print(" ".join(cmd), file=sys.stderr)

@@ -43,3 +43,28 @@ def test_code_id_follows_the_code_of_all_headers_and_not_their_comments(tmp_path
     append("nuts_row.h", "namespace nuts { constexpr int kMore = 1; }\n")
     changed = {k for k in ids if bench.kernel_code_id(k, csrc) != ids[k]}
     assert changed == {"nuts_elem_kernel", "nuts_dense_kernel"}
+
+
+def test_code_id_follows_the_flags_of_the_kernels_translation_units(monkeypatch):
+    from paper_1910_11141_amd import build
+    names = list(bench.KERNEL_NAMES.values()) + ["nuts_chip_kernel"]
+    ids = {k: bench.kernel_code_id(k) for k in names}
+    monkeypatch.setitem(build.EXTRA_FLAGS, "nuts_chip.hip", [])
+    assert {k for k in names if bench.kernel_code_id(k) != ids[k]} == {"nuts_chip_kernel"}
+    monkeypatch.setitem(build.EXTRA_FLAGS, "nuts_gauss.hip", [])
+    assert {k for k in names if bench.kernel_code_id(k) != ids[k]} == {"nuts_chip_kernel", "nuts_quad_kernel", "nuts_elem_kernel"}
+    monkeypatch.setattr(build, "FLAGS", build.FLAGS + ["-DMORE"])
+    assert all(bench.kernel_code_id(k) != ids[k] for k in names)
+
+
+def test_a_library_older_than_the_flags_is_stale(monkeypatch, tmp_path):
+    from paper_1910_11141_amd import build
+    lib = tmp_path / "lib.so"
+    lib.write_bytes(b"")
+    monkeypatch.setattr(build, "LIB_PATH", str(lib))
+    monkeypatch.setattr(build, "sources", lambda: [])
+    monkeypatch.setattr(build, "headers", lambda: [])
+    flags = os.path.getmtime(build.__file__)
+    for age, stale in ((-10, True), (10, False)):
+        os.utime(lib, (flags + age, flags + age))
+        assert build.is_stale() == stale
