@@ -451,7 +451,17 @@ def test_tile_kernel_queues_chains_beyond_its_resident_slots_and_is_schedule_ind
         assert np.array_equal(g[k], again[k])
 
 
-# ------------------------------------------------------------------ grid kernels (binary32, chip-wide GEMM per round)
+# ------------------------------------------------------------------ chip and grid kernels (binary32, rows spread over the chip)
+
+def assert_chip(stats):
+    """The run was the chip kernel's: the one kernel of its variant that has a phase clock."""
+    assert stats["variant"] == N().NUTS_VARIANT_GRID and sum(stats["phase_ticks"]) > 0
+
+
+def assert_grid(stats):
+    """The run was the two-launch grid kernels'."""
+    assert stats["variant"] == N().NUTS_VARIANT_GRID and sum(stats["phase_ticks"]) == 0
+
 
 def f32_parity(g, r, min_agree=0.99, min_chains=0.95):
     """binary32: a decision that falls the other way in rounding changes a chain's whole future, so integer outputs
@@ -472,12 +482,12 @@ def f32_parity(g, r, min_agree=0.99, min_chains=0.95):
                                                  (257, 128, 9), (4100, 65, 256), (31, 96, 5),
                                                  (600, 20, 129), (900, 40, 131), (2000, 100, 200),
                                                  (500, 72, 33), (700, 104, 17), (300, 97, 10)])
-def test_logreg_f32_grid_kernels_ragged_shapes(n_data, dim, n_chains):
+def test_logreg_f32_chip_kernel_ragged_shapes(n_data, dim, n_chains):
     w = W.small_logreg(n_data, dim, seed=200 + n_data, dtype=np.float32)
     w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = n_chains, 6, 0.15 / np.sqrt(max(n_data, 1) / 10), 6
     B = N()
     g = gpu_run(w, variant=B.NUTS_VARIANT_GRID)
-    assert g[3]["variant"] == B.NUTS_VARIANT_GRID
+    assert_chip(g[3])
     r = ref_run(w)
     check_invariants(w, g[1], g[2])
     f32_parity(g, r)
@@ -486,13 +496,12 @@ def test_logreg_f32_grid_kernels_ragged_shapes(n_data, dim, n_chains):
 
 def test_config4_large_logreg_f32_grid_kernels():
     w = W.make(4, n_chains=8, n_iters=10)
-    B = N()
     g = gpu_run(w)
-    assert g[3]["variant"] == B.NUTS_VARIANT_GRID      # chosen automatically for a chip-sized gradient
+    assert_grid(g[3])                                  # chosen automatically for a chip-sized gradient
     f32_parity(g, ref_run(w))
 
 
-def test_grid_kernels_are_schedule_independent_and_deterministic():
+def test_chip_kernel_is_schedule_independent_and_deterministic():
     w = W.small_logreg(2000, 20, seed=77, dtype=np.float32)
     w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = 100, 5, 0.02, 6
     B = N()
@@ -501,14 +510,14 @@ def test_grid_kernels_are_schedule_independent_and_deterministic():
     b = gpu_run(w, variant=B.NUTS_VARIANT_GRID, tgt=tgt)
     c = gpu_run(w, variant=B.NUTS_VARIANT_GRID, tgt=tgt, n_chains=37)
     o = gpu_run(w, variant=B.NUTS_VARIANT_GRID, tgt=tgt, n_chains=10, first_chain=50)
+    assert_chip(a[3])
     for k in range(3):
         assert np.array_equal(a[k], b[k])
         assert np.array_equal(a[k][:, :37], c[k])
         assert np.array_equal(a[k][:, 50:60], o[k])
 
 
-def test_grid_kernels_two_sets_of_chains_equal_one_set():
-    # beyond 128 chains the grid kernels step two sets of chains on two streams: same bytes as one set at a time
+def test_chip_kernel_200_chains_equal_128_and_72():
     w = W.small_logreg(1500, 30, seed=78, dtype=np.float32)
     w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = 200, 5, 0.03, 6
     B = N()
@@ -522,22 +531,23 @@ def test_grid_kernels_two_sets_of_chains_equal_one_set():
         assert np.array_equal(a[k][:, :128], lo[k])
         assert np.array_equal(a[k][:, 128:], hi[k])
     st = a[3]
+    assert_chip(st)
     assert st["leaf_slots_useful"] == a[2].sum() and st["leaf_slots_issued"] >= st["leaf_slots_useful"]
 
 
 @pytest.mark.parametrize("n_chains", [700, 1300])
-def test_grid_kernels_many_sets_and_queued_chains(n_chains):
-    # 700 chains: six sets on four streams; 1300: more chains than the 1024 resident slots, the rest are queued
+def test_chip_kernel_many_and_queued_chains(n_chains):
+    # 700 chains: two or three a workgroup; 1300: more chains than the 1024 resident ones, the rest are queued
     w = W.small_logreg(800, 12, seed=79, dtype=np.float32)
     w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = n_chains, 4, 0.05, 5
     B = N()
     tgt = gpu_target(w)
     a = gpu_run(w, variant=B.NUTS_VARIANT_GRID, tgt=tgt)
-    assert a[3]["variant"] == B.NUTS_VARIANT_GRID
+    assert_chip(a[3])
     check_invariants(w, a[1], a[2])
     f32_parity(a, ref_run(w))
     assert a[3]["leaf_slots_useful"] == a[2].sum() and a[3]["extra_grad_evals"] == n_chains
-    # which slot takes which chain depends on timing; the chains' results do not
+    # which workgroup takes which chain depends on timing; the chains' results do not
     b = gpu_run(w, variant=B.NUTS_VARIANT_GRID, tgt=tgt)
     c = gpu_run(w, variant=B.NUTS_VARIANT_GRID, tgt=tgt, n_chains=300)
     for k in range(3):
@@ -556,6 +566,7 @@ def test_chip_kernel_edges_match_the_oracle_on_both_schedules(n_data, dim, n_cha
     w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = n_chains, 4, 0.15 / np.sqrt(max(n_data, 1) / 10), 6
     tgt = gpu_target(w)
     free, sync = both_schedules(w, B.NUTS_VARIANT_GRID)
+    assert_chip(free[3])
     f32_parity(free, ref_run(w))
     slice3 = gpu_run(w, tgt=tgt, variant=B.NUTS_VARIANT_GRID, sampler=SLICE, leaf_steps=3, n_iters=2)
     f32_parity(slice3, ref_run(w, sampler=SLICE, leaf_steps=3, n_iters=2))
@@ -586,6 +597,7 @@ def test_chip_kernel_gradients_are_as_exact_as_sums_of_few_rows(n_data, dim, row
     nc, eps = 1000, 2.0 ** round(np.log2(1.5 / np.sqrt(n_data)))
     w = W.Workload("at_zero", W.LOGREG, dim, np.dtype(np.float32), nc, 1, eps, 1, seed=43, X=X, y=y, prior_scale=1.0)
     s, _, n, st = gpu_run(w, variant=N().NUTS_VARIANT_GRID, init=np.zeros((nc, dim)))
+    assert_chip(st)
     assert (n == 1).all()
     r0 = np.array([[z for i in range((dim + 1) // 2) for z in R.normal_pair(R.draw(w.seed, i, R.TAG_MOMENTUM, 0, 0, c))][:dim]
                    for c in range(nc)]).astype(np.float32).astype(np.float64)
@@ -620,6 +632,7 @@ def test_chip_kernel_with_fewer_workgroups_than_compute_units(n_data, dim, n_cha
     w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = n_chains, 2, 0.5 / np.sqrt(n_data), 4
     tgt = gpu_target(w)
     whole = gpu_run(w, tgt=tgt, variant=N().NUTS_VARIANT_GRID)
+    assert_chip(whole[3])
     assert whole[3]["grid_blocks"] == min(compute_units(), 256)
     for most in (100, 31, 12, 7, 1):
         chip_starts(tgt, most_blocks=most)
@@ -748,15 +761,34 @@ def test_chip_kernel_called_by_two_threads_at_once():
 @pytest.mark.parametrize("n_data,dim,n_chains", [(46000, 33, 3), (15700, 97, 40), (12100, 17, 6), (24000, 71, 5), (12500, 128, 3), (12001, 32, 130),
                                                  (65504, 36, 3), (65505, 36, 35), (65600, 128, 3), (70001, 24, 66), (66000, 72, 97)])
 def test_grid_kernels_on_many_rows_match_the_oracle(n_data, dim, n_chains):
-    B = N()
     w = W.small_logreg(n_data, dim, seed=400 + dim, dtype=np.float32)
     w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = n_chains, 2, 0.5 / np.sqrt(n_data), 4
     g = gpu_run(w)
-    assert g[3]["variant"] == B.NUTS_VARIANT_GRID and g[3]["leaf_slots_useful"] == g[2].sum()
+    assert_grid(g[3])
+    assert g[3]["leaf_slots_useful"] == g[2].sum()
     f32_parity(g, ref_run(w))
     few = gpu_run(w, n_chains=2)
     for k in range(3):
         assert np.array_equal(g[k][:, :2], few[k])
+
+
+# just above the chip kernel's line: one set of columns, one set on each of two streams (129 chains), two sets a stream with columns
+# handed out, and more chains than are resident; the last target's slices are four runs of tiles
+@pytest.mark.parametrize("n_data,dim,n_chains", [(12001, 17, 40), (12001, 17, 129), (12001, 17, 260), (12001, 17, 1100), (24000, 71, 9), (24000, 71, 300),
+                                                 (65505, 36, 260)])
+def test_grid_kernels_slice_sampler_several_steps_a_leaf_and_both_schedules(n_data, dim, n_chains):
+    B = N()
+    w = W.small_logreg(n_data, dim, seed=420 + dim, dtype=np.float32)
+    w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = n_chains, 3, 0.3 / np.sqrt(n_data), 3
+    pick = np.unique(np.array([0, 1, n_chains // 2, n_chains - 1]))
+    for kw in (dict(), dict(sampler=SLICE, leaf_steps=3)):
+        free, sync = both_schedules(w, B.NUTS_VARIANT_GRID, **kw)
+        assert_grid(free[3])
+        assert_grid(sync[3])
+        f32_parity([x[:, pick] for x in free[:3]], ref_run(w, chain_ids=pick, **kw))
+        few = gpu_run(w, n_chains=6, first_chain=n_chains - 6, **kw)
+        for k in range(3):
+            assert np.array_equal(free[k][:, n_chains - 6:], few[k])
 
 
 # ------------------------------------------------------------------ independence of the schedule
@@ -810,13 +842,14 @@ def test_runs_on_a_caller_stream():
     assert_parity(g, ref_run(w), F64_TOL, label="stream")
 
 
-def test_grid_kernels_on_a_caller_stream_back_to_back_calls():
-    # the grid path forks to streams of its own and joins them to the caller's: calls of different sizes in a row
-    # (the workspace grows between them) on a caller's stream must equal the same calls on the default stream
+@pytest.mark.parametrize("n_data,dim,which", [(700, 10, assert_chip), (12001, 17, assert_grid)])
+def test_chip_and_grid_kernels_on_a_caller_stream_back_to_back_calls(n_data, dim, which):
+    # calls of different sizes in a row on a caller's stream must equal the same calls on the default stream: the workspace
+    # grows between them, and the grid kernels fork to streams of their own and join them to the caller's
     import torch
     B = N()
-    w = W.small_logreg(700, 10, seed=81, dtype=np.float32)
-    w.n_iters, w.step_size, w.max_tree_depth = 4, 0.05, 5
+    w = W.small_logreg(n_data, dim, seed=81, dtype=np.float32)
+    w.n_iters, w.step_size, w.max_tree_depth = 4, 1.3 / np.sqrt(n_data), 5
     tgt = gpu_target(w)
     ref = [gpu_run(w, variant=B.NUTS_VARIANT_GRID, tgt=gpu_target(w), n_chains=c) for c in (40, 600, 130)]
     s = torch.cuda.Stream()
@@ -827,6 +860,8 @@ def test_grid_kernels_on_a_caller_stream_back_to_back_calls():
     finally:
         B.nuts_set_stream(None)
     for a, b in zip(ref, got):
+        which(a[3])
+        which(b[3])
         for k in range(3):
             assert np.array_equal(a[k], b[k])
 
@@ -898,12 +933,13 @@ def test_leaf_steps_with_divergences_tile_kernel():
 
 
 @pytest.mark.parametrize("n_data,dim,n_chains,k", [(100, 7, 8, 2), (1000, 33, 40, 4), (257, 128, 9, 3)])
-def test_leaf_steps_logreg_f32_grid_kernels(n_data, dim, n_chains, k):
+def test_leaf_steps_logreg_f32_chip_kernel(n_data, dim, n_chains, k):
     w = W.small_logreg(n_data, dim, seed=200 + n_data, dtype=np.float32)
     w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = n_chains, 6, 0.3 / k / np.sqrt(max(n_data, 1) / 10), 6
     B = N()
     g = gpu_run(w, variant=B.NUTS_VARIANT_GRID, leaf_steps=k)
-    assert g[3]["variant"] == B.NUTS_VARIANT_GRID and g[3]["leaf_slots_useful"] == g[2].sum()
+    assert_chip(g[3])
+    assert g[3]["leaf_slots_useful"] == g[2].sum()
     check_leaf_invariants(w, g[1], g[2], k)
     f32_parity(g, ref_run(w, leaf_steps=k))
 
@@ -969,11 +1005,13 @@ def test_schedules_agree_logreg_tile_and_wave_kernels(n_data, dim):
     assert sync[3]["occupancy"] <= 1.0
 
 
-def test_schedules_agree_logreg_f32_grid_kernels():
+def test_schedules_agree_logreg_f32_chip_kernel():
     w = W.small_logreg(1000, 33, seed=1200, dtype=np.float32)
     w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = 12, 5, 0.015, 6
     B = N()
-    both_schedules(w, B.NUTS_VARIANT_GRID)
+    free, sync = both_schedules(w, B.NUTS_VARIANT_GRID)
+    assert_chip(free[3])
+    assert_chip(sync[3])
 
 
 def test_trajectory_schedule_with_leaf_steps_init_states_offsets_and_no_state_output():
@@ -1076,12 +1114,12 @@ def test_slice_sampler_tile_kernel_divergences_and_deep_trees():
     assert_parity(gpu_run(w, variant=B.NUTS_VARIANT_TILE, sampler=SLICE), r, F64_TOL, label="tile depth 12, slice")
 
 
-def test_slice_sampler_logreg_f32_grid_kernels_and_bad_argument():
+def test_slice_sampler_logreg_f32_chip_kernel_and_bad_argument():
     w = W.small_logreg(1000, 33, seed=1200, dtype=np.float32)
     w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = 40, 6, 0.015, 6
     B = N()
     g = gpu_run(w, variant=B.NUTS_VARIANT_GRID, sampler=SLICE)
-    assert g[3]["variant"] == B.NUTS_VARIANT_GRID
+    assert_chip(g[3])
     f32_parity(g, ref_run(w, sampler=SLICE))
     with pytest.raises(B.NutsError):
         B.nuts_sample(gpu_target(w), 2, 2, 0.1, 3, 1, sampler=2)
@@ -1541,14 +1579,16 @@ def test_elementwise_targets_up_to_and_beyond_the_register_kernel(dim, dtype):
 
 
 @pytest.mark.parametrize("n_chains", [128, 129, 256, 260, 700, 1100])
-def test_grid_kernels_pack_the_chains_that_want_a_gradient(n_chains):
-    """Columns are handed out round by round beyond 128 chains per stream: a chain's results have the same bits in any
-    company, on either schedule, whichever column its gradient was computed in."""
+@pytest.mark.parametrize("n_data,dim,which", [(3000, 9, assert_chip), (12001, 17, assert_grid)])
+def test_chip_and_grid_kernels_pack_the_chains_that_want_a_gradient(n_data, dim, which, n_chains):
+    """Columns are handed out round by round (by the grid kernels beyond 128 chains per stream): a chain's results have the same
+    bits in any company, on either schedule, whichever column its gradient was computed in."""
     B = N()
-    w = W.small_logreg(3000, 9, seed=77, dtype=np.float32)
-    w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = n_chains, 4, 0.02, 7
+    w = W.small_logreg(n_data, dim, seed=77, dtype=np.float32)
+    w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = n_chains, 4, 1.1 / np.sqrt(n_data), 7 if which is assert_chip else 5
     tgt = gpu_target(w)
     g = gpu_run(w, tgt=tgt, variant=B.NUTS_VARIANT_GRID)
+    which(g[3])
     assert g[3]["leaf_slots_issued"] >= g[3]["leaf_slots_useful"] + g[3]["extra_grad_evals"]
     assert len(set(g[2].sum(axis=0))) > 3                       # trajectories of different lengths: idle slots in between
     sync = gpu_run(w, tgt=tgt, variant=B.NUTS_VARIANT_GRID, schedule=1)
@@ -1672,7 +1712,8 @@ def test_grid_kernels_on_four_streams_give_the_bits_of_two():
     w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = 1100, 18, 0.01, 2
     tgt = gpu_target(w)
     g = gpu_run(w, tgt=tgt)
-    assert g[3]["variant"] == N().NUTS_VARIANT_GRID and g[3]["leaf_slots_useful"] == g[2].sum()
+    assert_grid(g[3])
+    assert g[3]["leaf_slots_useful"] == g[2].sum()
     few = gpu_run(w, tgt=tgt, n_chains=140, first_chain=960)
     sync = gpu_run(w, tgt=tgt, schedule=1, n_iters=3)
     for k in range(3):
@@ -1681,6 +1722,7 @@ def test_grid_kernels_on_four_streams_give_the_bits_of_two():
 
 @pytest.mark.parametrize("form,dim,dtype", [("wide", 40, np.float64), ("wide", 100, np.float64), ("wide", 17, np.float32), ("wide", 40, np.float32),
                                             ("band", 130, np.float64), ("band", 300, np.float32), ("band", 1025, np.float64),
+                                            ("chip", 20, np.float32), ("chip", 101, np.float32), ("grid", 17, np.float32), ("grid", 71, np.float32),
                                             ("elem", 513, np.float64), ("elem", 1025, np.float32), ("elem", 2048, np.float64), ("elem", 64, np.float32)])
 def test_chains_that_start_far_out_or_not_finite(form, dim, dtype):
     """Infinite, NaN and overflowing starting points: their chains stay where they are, the others do not notice."""
@@ -1694,6 +1736,9 @@ def test_chains_that_start_far_out_or_not_finite(form, dim, dtype):
     init[10, dim - 1] = np.nan
     if form == "wide":
         w = wide_workload(90, dim, dtype, 13)
+    elif form in ("chip", "grid"):
+        w = wide_workload(24000 if form == "grid" else 1700 if dim == 20 else 1003, dim, dtype, 13)
+        w.n_iters, w.max_tree_depth = 4, 4
     elif form == "band":
         w = W.Workload("far_band", W.GAUSS_DENSE, dim, np.dtype(dtype), 13, 4, 0.3, 6, seed=5, precision=W.ar1_precision(dim, 0.8).astype(dtype))
     else:
@@ -1703,6 +1748,8 @@ def test_chains_that_start_far_out_or_not_finite(form, dim, dtype):
         g = gpu_run(w, tgt=tgt, init=init, **kw)
         with np.errstate(all="ignore"):
             r = ref_run(w, init=init, **kw)
+        if form in ("chip", "grid"):
+            (assert_chip if form == "chip" else assert_grid)(g[3])
         assert np.array_equal(np.isfinite(g[0]), np.isfinite(r[0]))
         assert np.array_equal(np.isnan(g[0]), np.isnan(r[0]))
         out = [3, 5, 7, 8, 10]
