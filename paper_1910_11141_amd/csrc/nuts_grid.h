@@ -43,7 +43,6 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
-#include <type_traits>
 #include <vector>
 
 #include "nuts_dev.h"
@@ -258,7 +257,7 @@ __global__ __launch_bounds__(kGridWaves * kWave, 2) void nuts_grid_grad_kernel(G
         for (int v = 0; v < 16; ++v) z[v] = 0.0f;
 #pragma unroll
         for (int kg = 0; kg < kKg1; ++kg) {
-            const float4 a = ops(std::integral_constant<int, 0>{}, kg);
+            const float4 a = ops(kg);
             z = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b1[4 * kg + 0], z, 0, 0, 0);
             z = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b1[4 * kg + 1], z, 0, 0, 0);
             if (4 * kg + 2 < kKs1) {
@@ -294,7 +293,7 @@ __global__ __launch_bounds__(kGridWaves * kWave, 2) void nuts_grid_grad_kernel(G
         for (int u = 0; u < kMt; ++u)
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
-                const float4 a = ops(std::integral_constant<int, 1>{}, kKg1 + u * 4 + q4);
+                const float4 a = ops(kKg1 + u * 4 + q4);
                 G[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, sg[4 * q4 + 0], G[u], 0, 0, 0);
                 G[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, sg[4 * q4 + 1], G[u], 0, 0, 0);
                 G[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, sg[4 * q4 + 2], G[u], 0, 0, 0);
@@ -304,7 +303,7 @@ __global__ __launch_bounds__(kGridWaves * kWave, 2) void nuts_grid_grad_kernel(G
         for (int g = 0; g < kTail; ++g)
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
-                const float4 a = ops(std::integral_constant<int, 1>{}, kKg1 + (kMt + g) * 4 + q4);
+                const float4 a = ops(kKg1 + (kMt + g) * 4 + q4);
                 T[g][0] = __builtin_amdgcn_mfma_f32_4x4x1f32(a.x, sg[4 * q4 + 0], T[g][0], 0, 0, 0);
                 T[g][1] = __builtin_amdgcn_mfma_f32_4x4x1f32(a.y, sg[4 * q4 + 1], T[g][1], 0, 0, 0);
                 T[g][0] = __builtin_amdgcn_mfma_f32_4x4x1f32(a.z, sg[4 * q4 + 2], T[g][0], 0, 0, 0);
@@ -335,7 +334,7 @@ __global__ __launch_bounds__(kGridWaves * kWave, 2) void nuts_grid_grad_kernel(G
                 for (int i = 0; i < kAhead; ++i) buf[i] = src[i * 64];
                 load_theta(col);
                 for (int t = ta; t < tb; ++t) {
-                    row_tile(t, [&](auto, int i) __attribute__((always_inline)) -> float4 {
+                    row_tile(t, [&](int i) __attribute__((always_inline)) -> float4 {
                         const float4 a = buf[i % kAhead];
                         const int next = i + kAhead;  // (the tile after the last one exists: a spare, all zeros)
                         if (next % kGroups < kUsed) buf[i % kAhead] = src[next * 64];
@@ -421,7 +420,7 @@ __global__ __launch_bounds__(kGridWaves * kWave, 2) void nuts_grid_grad_kernel(G
             fetch(stage ^ 1);
             if (computes) {
                 const float4* const staged = &s_ops[stage][lane];
-                row_tile(t, [&](auto, int i) __attribute__((always_inline)) -> float4 { return staged[i * 64]; });
+                row_tile(t, [&](int i) __attribute__((always_inline)) -> float4 { return staged[i * 64]; });
             }
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();

@@ -487,7 +487,7 @@ struct RowChain {
                     rest_store(kRowTop, pth);
                     if constexpr (kGrad) rest_store(kRowTopG, pg);
                     top_logp = prev_logp;
-                        } else {
+                } else {
                     T t[kVpl], gr[kGrad ? kVpl : 1];
                     pool_load(cur_idx, t, gr);
                     rest_store(kRowTop, t);
