@@ -24,9 +24,9 @@
 // What bounds it: with all columns busy the matrix instructions (53 of 32 ticks per 16 x 16 tile at d = 100) and the vector ones of
 // the logistic functions beside them (290 ticks); with few the two barriers (1.7 us each over 256 workgroups, a counter per
 // residue of the workgroup number modulo 8; flags that everybody polls: 3.1 to 5.5 us), the latency of the partial sums and of
-// the chain program.  10 000 x 100: a round takes 11.5 us with one chain, 26 us with 227 columns busy (control with its barrier 7 us,
-// positions 2.5, tiles 12, their sums and the second barrier 5).  1024 chains, 4 iterations of the slice sampler with four
-// steps a leaf: 10.9 ms with two launches a round (nuts_grid.h) -> 8.4.  185 to 238 vector registers, none in scratch memory.
+// the chain program.  10 000 x 100: a round takes 11.5 us with one chain, 27 us with 227 columns busy (control with its barrier 7 us,
+// positions 2.5, tiles 13, their sums and the second barrier 5).  1024 chains, 4 iterations of the slice sampler with four
+// steps a leaf: 10.9 ms with two launches a round (nuts_grid.h) -> 8.4 (8.2 with the sums of a wave's rows in one accumulator).  185 to 238 vector registers, none in scratch memory.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -76,7 +76,8 @@ constexpr int chip_pitch(int mt) { return 16 * mt + 4; }
 
 // Whether a target's runs are the chip kernel's or those of the grid kernels (nuts_grid.h), which overlap a set of chains'
 // control with another's gradient: long gradients with all columns busy are theirs.  By the target alone: a chain's
-// results must not change with the batch it runs in.  Time with the grid kernels over time here: 10 000 x 100, 64 to 4096
+// results must not change with the batch it runs in.  Time with the grid kernels over time here (and the table below, taken with
+// sums of a wave's rows that were less exact and 3 % faster): 10 000 x 100, 64 to 4096
 // chains, 4 to 50 iterations 1.01 to 1.7; 3000 x 9 and 1000 x 20, 16 to 4096 chains 1.3 to 1.8; 6052 x 7, awaited iterations 2.5;
 // 40 000 x 10 1.1; 15 000 x 100 1.1; 20 000 x 48 and x 64, 4096 chains 1.14 and 1.00; 100 000 x 100, 256 chains, 40 iterations 0.80;
 // 50 000 x 128, 2048 chains 0.89.  With 17 to 32 features, which are one tile of 32 there: 8000 x 32 1.1, 12 000 x 25 1.00, 20 000 x 25

@@ -466,8 +466,8 @@ def assert_grid(stats):
 def f32_parity(g, r, min_agree=0.99, min_chains=0.95):
     """binary32: a decision that falls the other way in rounding changes a chain's whole future, so integer outputs
     are compared as a rate, and states on the chains whose decisions all agree (per coordinate, see state_error).
-    Measured over every binary32 comparison of this file (27 of them, 3 to 256 chains, up to 20 iterations): all
-    integer outputs agree and no chain leaves the oracle's decisions; largest state error 2.5e-6.  The floors below
+    Measured over every binary32 comparison of this file (131 of them, 1 to 1300 chains, up to 20 iterations): all
+    integer outputs agree and no chain leaves the oracle's decisions; largest state error 2.0e-6.  The floors below
     leave room for one flipped decision in a hundred, not more."""
     same = (g[1] == r[1]) & (g[2] == r[2])
     ok = same.all(axis=0)
