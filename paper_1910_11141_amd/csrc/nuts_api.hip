@@ -13,7 +13,6 @@
 #include <cstring>
 #include <mutex>
 #include <new>
-#include <random>
 #include <thread>
 #include <vector>
 
@@ -1002,8 +1001,10 @@ int await_chip_room(size_t lds_bytes, int attempt)
     hipLaunchKernelGGL(chip_room_kernel, dim3(1), dim3(nuts::kChipThreads), lds_bytes, g_stream);
     HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
     HIP_TRY(hipStreamSynchronize(g_stream), NUTS_E_DEVICE);
-    static thread_local std::minstd_rand random{std::random_device{}()};
-    std::this_thread::sleep_for(std::chrono::milliseconds(random() % (20u << std::min(attempt, 5))));
+    // (of the clock and this process's address space: no source of random numbers that could throw)
+    const uint64_t seed = (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() ^ (uint64_t)reinterpret_cast<uintptr_t>(&g_stream);
+    const unsigned span_us = 20000u << std::min(attempt, 5);
+    std::this_thread::sleep_for(std::chrono::microseconds((seed * 0x9e3779b97f4a7c15ull >> 33) % span_us));
     return NUTS_OK;
 }
 
