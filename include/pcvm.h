@@ -43,7 +43,8 @@ enum { PCVM_JUMP = 0, PCVM_BRANCH = 1, PCVM_PUSHJUMP = 2, PCVM_RETURN = 3 }; /* 
 /* Which block a group runs next.  Any choice that starves nobody is correct (Section 2 of the paper).
  * EARLIEST: the lowest-numbered block anyone waits for (Algorithm 2 as printed).
  * MOST_WAITING: the block most lanes wait for (lowest on a tie): fewer, fuller steps; a lone lane can wait
- *   while the queue still feeds the others, but not beyond the end of the batch. */
+ *   while the queue still feeds the others, but not beyond the end of the batch.  A block that is entered by a jump or a
+ *   call may run together with the block before it, without a choice between them. */
 enum { PCVM_SCHED_EARLIEST = 0, PCVM_SCHED_MOST_WAITING = 1 };
 
 #define PCVM_MAX_VARS 16

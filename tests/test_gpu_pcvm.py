@@ -231,3 +231,63 @@ def test_queued_batches_around_the_number_of_lanes_that_take_members():
         for policy in (0, 1):
             out, stats, _ = gpu(P, ins, 40, queued=True, policy=policy)
             assert np.array_equal(out, want), (batch, policy)
+
+
+def call_program(n_pad, n_deep):
+    """A recursion that pushes the value of every function and calls from joined blocks; n_pad blocks that only jump
+    lengthen the chains and the table, and n_deep is how much deeper a call goes for each unit of its argument."""
+    b = PP._Builder("calls", ["n", "x", "y", "c", "s", "t"], 1, "s")
+    b.block("f", 1, [PP.update("c", PP.LEI, "n", imm=0)], (PP.BRANCH, "c", "base", "go"))
+    b.block("base", 2, [PP.update("s", PP.ADDI, "s", imm=1), PP.pop("n")], (PP.RETURN,))
+    pushes = [PP.push("x", PP.MUL, "n", "s"), PP.push("y", PP.MULI, "n", imm=-7), PP.push("t", PP.MOD, "x", "y"), PP.push("x", PP.SUB, "x", "t"),
+              PP.push("y", PP.LT, "x", "y"), PP.push("t", PP.SHRI, "x", imm=2), PP.push("x", PP.EQI, "n", imm=2), PP.push("y", PP.LE, "t", "n")]
+    pops = [PP.update("s", PP.ADD, "s", v) for v in ("x", "y", "t")] + [PP.pop(v) for v in ("y", "x", "t", "y", "x", "t", "y", "x")]
+    b.block("go", 3, pushes, (PP.JUMP, "pad0" if n_pad else "call"))
+    for i in range(n_pad):
+        b.block(f"pad{i}", 10 + i, [], (PP.JUMP, f"pad{i + 1}" if i + 1 < n_pad else "call"))
+    b.block("call", 4, [PP.push("n", PP.ADDI, "n", imm=-1)], (PP.PUSHJUMP, "f", "back"))
+    b.block("back", 5, pops + [PP.update("c", PP.ANDI, "n", imm=n_deep)], (PP.BRANCH, "c", "again", "leave"))
+    b.block("again", 6, [PP.update("n", PP.ADDI, "n", imm=-2)], (PP.PUSHJUMP, "f", "out"))
+    b.block("leave", 7, [PP.pop("n")], (PP.RETURN,))
+    b.block("out", 8, [], (PP.RETURN,))
+    return b.build()
+
+
+@pytest.mark.parametrize("n_pad,n_deep,top", [(0, 0, 40), (0, 3, 12), (23, 3, 12), (30, 1, 12), (31, 1, 12), (55, 0, 40)])
+def test_calls_and_pushed_values_match_the_oracle(n_pad, n_deep, top):
+    """Return addresses of 4 to 6 bits in 16 to 10 places of a register pair, spilled and read back; tables of entries in one
+    set of registers and in two (from 39 blocks on); records that join up to four blocks, with and without a call."""
+    P = call_program(n_pad, n_deep)
+    ins = np.random.default_rng(n_pad).integers(0, top, size=130)
+    for depth in (top // 2, 2 * top + 8, 4 * top + 40):
+        try:
+            want, st, trace = V.run(P, ins, depth, group=64)
+        except V.StackOverflow:
+            from paper_1910_11141_amd import pcvm
+            for kw in (dict(), dict(queued=True), dict(queued=True, policy=1)):
+                with pytest.raises(pcvm.PcvmError) as e:
+                    gpu(P, ins, depth, **kw)
+                assert e.value.code == pcvm.PCVM_E_STACK_OVERFLOW
+            continue
+        out, stats, tr = gpu(P, ins, depth, trace_capacity=len(trace))
+        assert np.array_equal(out, want) and stats["steps"] == st["steps"]
+        assert [tuple(r) for r in tr] == trace
+        for policy in (0, 1):
+            out, stats, _ = gpu(P, ins, depth, queued=True, policy=policy)
+            assert np.array_equal(out, want) and stats["active_member_steps"] == st["active_member_steps"]
+
+
+def test_remainders_of_small_large_and_negative_numbers():
+    """Numbers below 2^32 (a reciprocal in binary64) and all others, in one wave and apart, at the edges of a quotient."""
+    P = PP.gcd()
+    rng = np.random.default_rng(3)
+    small = np.array([0, 1, 2, 3, 2 ** 31 - 1, 2 ** 31, 2 ** 31 + 1, 2 ** 32 - 2, 2 ** 32 - 1])
+    b = np.concatenate([rng.integers(1, 2 ** 32, 2000), rng.integers(1, 2 ** 16, 2000)])
+    edges = np.minimum(b * rng.integers(1, 2 ** 16, b.size) + rng.integers(-1, 2, b.size), 2 ** 32 - 1)
+    wide = np.array([-1, -2, 2 ** 32, 2 ** 33 + 5, -2 ** 63, 2 ** 63 - 1, 2 ** 53 + 1, -7])
+    for x, y in ((np.repeat(small, small.size), np.tile(small, small.size)), (edges, b), (np.maximum(edges, 0), rng.permutation(b)),
+                 (np.repeat(wide, wide.size), np.tile(wide, wide.size)), (rng.permutation(np.tile(small, 8)), rng.permutation(np.tile(wide, 9)))):
+        ins = np.stack([x, y])
+        want = V.run(P, ins, 120)[0]
+        for kw in (dict(), dict(queued=True, policy=1)):
+            assert np.array_equal(gpu(P, ins, 120, **kw)[0], want)
