@@ -115,6 +115,7 @@ struct nuts_target {
     unsigned* chip_state = nullptr;     // chip kernel: pinned, how the last run ended
     int chip_most = 0;                  // chip kernel: the most workgroups of the call's further launches, 0: no bound
     int chip_refuse = 0, chip_bound = 0;  // nuts_debug_chip_starts
+    bool wide_apart = false;              // nuts_debug_wide_apart
     int* halted_host = nullptr;         // grid kernels: pinned, two snapshots of the "halted" flags
     hipEvent_t ev_batch[2 * nuts::kGridMaxStreams] = {};  // [snapshot][stream]
     bool has_run = false;
@@ -374,7 +375,8 @@ int ensure_device(nuts_target* t)
     t->device = dev;
     int rc = resolve_scratch(dev);
     if (rc) return rc;
-    if (!t->counters) HIP_TRY(hipMalloc((void**)&t->counters, nuts::kCtrCount * sizeof(unsigned long long)), NUTS_E_ALLOC);
+    if (!t->counters)
+        HIP_TRY(hipMalloc((void**)&t->counters, nuts::kCtrCount * sizeof(unsigned long long) + nuts::kWideMaxPairs * sizeof(unsigned)), NUTS_E_ALLOC);
     if (!t->ev_start) HIP_TRY(hipEventCreate(&t->ev_start), NUTS_E_DEVICE);
     if (!t->ev_stop) HIP_TRY(hipEventCreate(&t->ev_stop), NUTS_E_DEVICE);
     return NUTS_OK;
@@ -417,15 +419,18 @@ __global__ void fill_words_kernel(unsigned* p, int n, unsigned value)
     for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = value;
 }
 
-__global__ void zero_counters_kernel(unsigned long long* c)
+// (behind the counters: the words at which the wide kernel's pairs of workgroups meet, of which a call without them has none)
+__global__ void zero_counters_kernel(unsigned long long* c, int words)
 {
     if (threadIdx.x < nuts::kCtrCount) c[threadIdx.x] = 0ull;
+    for (int i = threadIdx.x; i < words; i += blockDim.x) reinterpret_cast<unsigned*>(c + nuts::kCtrCount)[i] = 0u;
 }
 
 // After every launch: the wave and element-wise kernels hold `slots` chain slots for as long as the
 // busiest of them works, so that many slots x its gradient count were issued; the chain queue restarts.
-__global__ void close_launch_kernel(unsigned long long* c, unsigned long long slots)
+__global__ void close_launch_kernel(unsigned long long* c, unsigned long long slots, int words)
 {
+    for (int i = threadIdx.x; i < words; i += blockDim.x) reinterpret_cast<unsigned*>(c + nuts::kCtrCount)[i] = 0u;
     if (threadIdx.x == 0) {
         c[nuts::kCtrIssued] += slots * c[nuts::kCtrSlotMax];
         c[nuts::kCtrSlotMax] = 0ull;
@@ -931,17 +936,23 @@ int launch_wide(nuts_target* t, nuts::DevSample sa, int nc, int cus)
     const size_t block = nuts::wide_block_bytes((int)t->dim, t->dtype == NUTS_F64 ? 8 : 4, nc, sa.max_depth);
     long blocks = (sa.n_chains + nc - 1) / nc;
     if (blocks > cus) blocks = cus;  // one workgroup per compute unit; further chains wait in the queue
+    // (nuts_sample_static has no words for pairs to meet at)
+    const bool split = !t->static_call && nc == 4 && blocks <= nuts::kWideMaxPairs && nuts::wide_split_pays(sa.n_chains, cus, t->n);
+    const long pairs = split ? blocks : 0;
+    if (split) blocks *= 2;
     if (t->static_call) {
         int rc = tile_eligible(t, sa.max_depth) ? NUTS_OK : static_check(t, sa);
         if (rc) return rc;
         const long fit = (long)(((size_t)NUTS_STATIC_SCRATCH_BYTES - kStaticHeader) / block);
         if (fit >= 1 && blocks > fit) blocks = fit;
     }
-    int rc = ensure_workspace(t, block * (size_t)blocks);
+    const size_t slots = (block * (size_t)blocks + 255) & ~(size_t)255;
+    int rc = ensure_workspace(t, slots + (size_t)pairs * 2 * nuts::wide_exchange_half(t->tile.mt));
     if (rc) return rc;
     sa.workspace = t->ws_cur;
     sa.slot_bytes = block;
-    const nuts::WideArgs wa{nuts::tile_args(t->tile, 1.0 / (t->prior_scale * t->prior_scale)), t->tile.ks1};
+    const nuts::WideArgs wa{nuts::tile_args(t->tile, 1.0 / (t->prior_scale * t->prior_scale)), t->tile.ks1, (int)pairs,
+                            reinterpret_cast<unsigned*>(t->counters_cur + nuts::kCtrCount), t->ws_cur + slots, t->wide_apart ? 1 : 0};
     (t->dtype == NUTS_F64 ? nuts::wide_launch_f64 : nuts::wide_launch_f32)(wa, sa, nc, (int)blocks, g_stream);
     HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
     t->last_variant = NUTS_VARIANT_TILE;
@@ -1083,6 +1094,14 @@ int nuts_debug_chip_starts(nuts_target* t, int refused, int most_blocks)
     if (!t || refused < 0 || most_blocks < 0) return fail(NUTS_E_INVALID_ARG, "nuts_debug_chip_starts: bad argument");
     t->chip_refuse = refused;
     t->chip_bound = most_blocks;
+    return NUTS_OK;
+}
+
+// For tests: the wide kernel's pairs of workgroups do not meet; the first takes all rows.
+int nuts_debug_wide_apart(nuts_target* t, int apart)
+{
+    if (!t) return fail(NUTS_E_INVALID_ARG, "nuts_debug_wide_apart: bad argument");
+    t->wide_apart = apart != 0;
     return NUTS_OK;
 }
 
@@ -1278,8 +1297,9 @@ int sample_impl(const nuts_target* target, int64_t n_chains, int64_t n_iters, do
     sa.init_states = opt.init_states;
     sa.counters = t->counters_cur;
 
+    const int pair_words = !use_static && use_tile ? nuts::kWideMaxPairs : 0;
     // the counters start at zero (a fill kernel, so that the call can sit inside a captured graph)
-    hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(64), 0, g_stream, t->counters_cur);
+    hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(64), 0, g_stream, t->counters_cur, pair_words);
     HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
 
     auto launch = [&](const nuts::DevSample& s) -> int {
@@ -1301,7 +1321,7 @@ int sample_impl(const nuts_target* target, int64_t n_chains, int64_t n_iters, do
         else
             r = t->dtype == NUTS_F64 ? launch_wave<double>(t, s) : launch_wave<float>(t, s);
         if (r) return r;
-        hipLaunchKernelGGL(close_launch_kernel, dim3(1), dim3(64), 0, g_stream, t->counters_cur, (unsigned long long)t->last_slots);
+        hipLaunchKernelGGL(close_launch_kernel, dim3(1), dim3(64), 0, g_stream, t->counters_cur, (unsigned long long)t->last_slots, pair_words);
         HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
         return NUTS_OK;
     };

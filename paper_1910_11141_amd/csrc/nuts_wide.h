@@ -16,12 +16,19 @@
 //     of 4 features (second GEMM) of the 16x16x4 instruction's operands in the same lanes, and an element of the result
 //     is accumulated in the same order, as is the log-likelihood: a chain has the same bits whichever form stepped it
 //     (with up to 32 features and binary64 the 16-chain form is the kernel of nuts_tile.h).
-// The numbers of chains, rows and iterations decide between the two forms (wide_chains_per_block below).
+//   * NC = 4 with kSplit: the rows of a group of four chains go to two workgroups of four waves, each of which has a SIMD to
+//     itself and one of the eight sums over rows that a wave of the undivided form has, so the bits are the same.  Both workgroups
+//     run the chain program of all four chains (it is deterministic: nothing but the sums has to be exchanged, once a round, and
+//     one of them writes the outputs).
+// The numbers of chains, rows and iterations decide between the forms (wide_chains_per_block, wide_split_pays below).
 //
 // What bounds it: with 16 chains the matrix instructions (1000 rows x 120 features: 63.5 k of the gradient phase's 83 k ticks,
 // its logistic functions another 10 k; with few features the latter: 3000 x 5 in binary32 38 k of 58 k); with 4 chains the
 // operand stream, which every compute unit reads from L2 at about 50 bytes per tick (1000 x 60: 1 MB in 20 k ticks, where
-// the instructions would take 11 k).  Measured against the wave kernel, which read X twice per chain and gradient with the
+// the instructions would take 11 k) and, with few features, the instructions of two waves that share a SIMD: a tile of 1000 x 25 takes
+// a wave 1310 ticks, and its transposition through LDS in place of half the stream made that 1620.  Divided, a wave issues alone:
+// 770 ticks a tile of 25 features, two tiles interleaved, and 1340 of 60 (2450); the exchange takes 2.5 k ticks a round (3.0 k with
+// more than 32 features).  5000 x 60, 512 chains: a round 101 k -> 63 k ticks; 20 000 x 25, 64 chains, 8.5 -> 4.4 ms.  Measured against the wave kernel, which read X twice per chain and gradient with the
 // vector ALUs: binary64, 512 chains, 5000 x 60: 1.1e5 -> 5.5e6 gradient evaluations per second; binary32, 250 chains, 700 x 17,
 // slice sampler, four steps a leaf: 3.6e6 -> 5.0e7.  What the residuals cost against the tile kernel's functions: 700 x 17 in
 // binary32, 4096 chains, 10 iterations 2.0 -> 2.5 ms; 1000 x 60, 4096 chains, 4 iterations 2.39 -> 2.55; 1000 x 120 3.74 -> 3.85;
@@ -40,8 +47,10 @@ namespace nuts {
 constexpr int kWideLds = 160 * 1024;
 
 // Shape-dependent constants of one instantiation.
-template <typename T, int MT, int NC>
+template <typename T, int MT, int NC, bool kSplit = false>
 struct WideShape {
+    static constexpr int kWaves = kSplit ? kTileWaves / 2 : kTileWaves;  // of a workgroup
+    static constexpr int kTilesAtOnce = kSplit ? 2 : 1;                   // of a wave
     static constexpr int kCpl = (16 * MT + 31) / 32;     // components per lane
     static constexpr int kVec = kTileLanes * kCpl;       // elements of a stored vector
     static constexpr int kPitch = 16 * MT + 1;           // doubles per chain in the LDS tiles (odd: see nuts_tile.h)
@@ -55,7 +64,7 @@ struct WideShape {
     // With more than two feature tiles the waves' partial sums are added in pairs (w, w + 4) first, in both forms.
     static constexpr bool kPairs = MT > 2;
     static constexpr int kFixed = (NC * kPitch + kSlots * NC * kPitch + kTileWaves * NC + 16 * MT +
-                                   kTab) * 8 + 256;
+                                   kTab + (kSplit ? 2 * kWaves * kWave : 0)) * 8 + 256;
     static constexpr int kEntry = NC * 2 * kVec * (int)sizeof(T);  // one pool buffer or first-leaf slot of every chain
     static constexpr int kRoom = (kWideLds - kFixed) / kEntry;
     // The vectors that only the start and the end of a doubling or of an iteration touch (the other end of the trajectory,
@@ -66,7 +75,7 @@ struct WideShape {
     static constexpr int kEntries = kRoom - (kRestLds ? 3 : 0);
     static constexpr int kLdsPool = kEntries >= 9 ? 5 : (kEntries + 1) / 2;   // shallow tree levels that live in LDS
     static constexpr int kLdsFirst = kEntries >= 9 ? 4 : kEntries / 2;
-    static constexpr bool kHoldTheta = MT <= 2;          // positions as operands in registers across a round's tiles
+    static constexpr bool kHoldTheta = MT <= (kSplit ? 4 : 2);          // positions as operands in registers across a round's tiles
     // operands of a whole tile are requested one tile ahead, or (many features: not enough registers, and half a tile
     // of that many instructions covers the latency) half a tile ahead
     static constexpr bool kFullAhead = MT <= (NC == 4 ? 4 : 2);
@@ -78,7 +87,46 @@ inline bool wide_uses_residuals(int64_t d, size_t elem) { return elem == 4 || d 
 struct WideArgs {
     TileArgs ta;
     int ks1;  // k-steps of the first GEMM, 4 MT - 4 < ks1 <= 4 MT (with a constant column possibly 4 MT - 4)
+    // divided rows (kSplit): the groups of four chains, a word of each for its workgroups to meet at, and their exchange buffers
+    int n_pairs;
+    unsigned* meet;
+    char* exchange;
+    int apart;  // (for tests: the second of two workgroups behaves as if it had come too late)
 };
+
+// Exchange between the two workgroups of a group of chains: [half][parity of the round][wave][vector][lane]{low, tag, high, tag}, a
+// vector per feature tile and one of log-likelihoods.
+__host__ __device__ constexpr int wide_exchange_half(int mt) { return 2 * (kTileWaves / 2) * (mt + 1) * kWave * 16; }  // bytes
+constexpr int kWideAgent = 16;                       // cache policy of a buffer instruction: agent scope (sc1)
+constexpr long long kWideMeetLimit = 20000;          // 0.2 ms (100 MHz)
+constexpr long long kWideLostLimit = 6000000000ll;   // 60 s
+enum : unsigned { kMeetAlone = 4u };                 // beside bit h: half h has come
+
+// A workgroup that waits for its partner must have it resident: each announces itself before anything is done, and one whose
+// partner has not come within 0.2 ms (a device or a mask of compute units without room for both) takes the whole group's rows, part
+// after part; the partner, when it starts, finds that and returns.  Two that have met are both running and stay so.
+//
+// The other half of the group: true if it has come, and both go on together; false if this one goes on alone (`late`: not at
+// all, the other one has gone on alone).
+__device__ inline bool wide_meet(unsigned* word, int half, bool& late)
+{
+    const unsigned mine = 1u << half, other = 2u >> half;
+    unsigned seen = __hip_atomic_fetch_or(word, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    late = (seen & kMeetAlone) != 0;
+    if (late) return false;
+    const long long t0 = wall_clock64();
+    for (;;) {
+        if (seen & other) return true;
+        if (wall_clock64() - t0 > kWideMeetLimit) {
+            unsigned expected = mine;
+            if (__hip_atomic_compare_exchange_strong(word, &expected, mine | kMeetAlone, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                return false;
+            return true;  // (it has come in between)
+        }
+        __builtin_amdgcn_s_sleep(1);
+        seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
 
 // Vectors of a chain that are kept outside the registers when !kHeld (after the level-indexed ones in the workspace).
 enum : int { kRestOtherTh = 0, kRestOtherR = 1, kRestOtherG = 2, kRestTop = 3, kRestTopG = 4, kRestNext = 5, kRestCount = 6 };
@@ -116,17 +164,19 @@ __device__ __forceinline__ double quad_after(double x)
     return dpp_rotate<0x130 - 4 * s>(x);  // row_ror: 16 - 4 s
 }
 
-template <typename T, int MT, int NC>
-__global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, DevSample sa)
+template <typename T, int MT, int NC, bool kSplit>
+__global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) void nuts_wide_kernel(WideArgs wa, DevSample sa)
 {
-    typedef WideShape<T, MT, NC> S;
+    typedef WideShape<T, MT, NC, kSplit> S;
+    constexpr int kThreads = S::kWaves * kWave;
     constexpr int kCpl = S::kCpl, kVec = S::kVec, kLP = S::kLdsPool, kLF = S::kLdsFirst;
     const TileArgs& ta = wa.ta;
     __shared__ double sTheta[NC][S::kPitch];
     __shared__ double sG[S::kSlots][NC][S::kPitch];
     __shared__ double sLL[kTileWaves][NC];
     __shared__ double sHalfCol[S::kResidual ? 1 : 16 * MT];  // column sums of X~, halved
-    __shared__ int sHalted;
+    __shared__ __align__(16) double sSpread[kSplit ? S::kWaves : 1][S::kTilesAtOnce][kSplit ? kWave : 1];
+    __shared__ int sHalted, sMeet, sLost;
     __shared__ __align__(16) double sFtab[S::kTab];
     const double* const log_tab = sFtab + S::kTab - kLogTabDoubles;
     __shared__ T sPool[NC][kLP > 0 ? kLP : 1][2][kLP > 0 ? kVec : 1];
@@ -148,7 +198,11 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
         return e < kCpl / 2 * 2 ? 64 * (e / 2) + 2 * k + (e & 1) : 64 * (kCpl / 2) + k;
     };
 
-    T* const wsc = reinterpret_cast<T*>(sa.workspace + (size_t)blockIdx.x * sa.slot_bytes) +
+    // divided rows: workgroups b and b + 8 of every sixteen (which start on one XCD, one soon after the other) are a pair
+    const int pair = kSplit ? (int)(blockIdx.x / 16 * 8 + blockIdx.x % 8) : 0, half_id = kSplit ? (int)(blockIdx.x / 8 % 2) : 0;
+    if (kSplit && pair >= wa.n_pairs) return;
+    const int wg = kSplit ? 2 * pair + half_id : (int)blockIdx.x;
+    T* const wsc = reinterpret_cast<T*>(sa.workspace + (size_t)wg * sa.slot_bytes) +
                    (size_t)grp * wide_num_vectors(D) * kVec + k;
     // level-indexed tree storage: shallow levels in LDS, the others in global memory (a lane reads what it wrote itself)
     auto pool_load = [&](int b, int c, T (&v)[kCpl]) __attribute__((always_inline)) {
@@ -188,11 +242,37 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
         }
     };
 
-    for (int i = tid; i < S::kTab; i += kTileThreads) sFtab[i] = ta.ftab[kFtabDoubles + kLogTabDoubles - S::kTab + i];
-    for (int i = tid; i < NC * S::kPitch; i += kTileThreads) (&sTheta[0][0])[i] = 0.0;
-    for (int i = tid; i < (S::kResidual ? 0 : 16 * MT); i += kTileThreads) sHalfCol[i] = 0.5 * ta.colsum[i];
-    if (tid == 0) sHalted = 0;
-    __syncthreads();
+    for (int i = tid; i < S::kTab; i += kThreads) sFtab[i] = ta.ftab[kFtabDoubles + kLogTabDoubles - S::kTab + i];
+    for (int i = tid; i < NC * S::kPitch; i += kThreads) (&sTheta[0][0])[i] = 0.0;
+    for (int i = tid; i < (S::kResidual ? 0 : 16 * MT); i += kThreads) sHalfCol[i] = 0.5 * ta.colsum[i];
+    if (tid == 0) sHalted = 0, sLost = 0;
+    constexpr int kHalfBytes = wide_exchange_half(MT);
+    const __amdgpu_buffer_rsrc_t other_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        wa.exchange + (size_t)(2 * pair + (1 - half_id)) * kHalfBytes, 0, kSplit ? kHalfBytes : 0, 0x00020000);
+    const __amdgpu_buffer_rsrc_t own_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        wa.exchange + (size_t)(2 * pair + half_id) * kHalfBytes, 0, kSplit ? kHalfBytes : 0, 0x00020000);
+    typedef __attribute__((ext_vector_type(4))) unsigned v4u;
+    bool alone = true;  // (this workgroup has all rows)
+    if (kSplit) {
+        // Tags of an earlier launch go before the other half may look: rounds count from 1 in every launch.
+        for (int i = tid * 16; i < kHalfBytes; i += kThreads * 16) __builtin_amdgcn_raw_buffer_store_b128(v4u{0, 0, 0, 0}, own_rsrc, i, 0, kWideAgent);
+        __threadfence();
+        __syncthreads();
+        if (tid == 0) {
+            bool late = false;
+            const bool both = !wa.apart && wide_meet(wa.meet + pair, half_id, late);
+            sMeet = (wa.apart ? half_id == 1 : late) ? 2 : both ? 1 : 0;
+        }
+        __syncthreads();
+        const int met = uni(sMeet);
+        if (met == 2) return;
+        alone = met == 0;
+    } else {
+        __syncthreads();
+    }
+    const bool lead = !kSplit || alone || half_id == 0;  // writes what the call returns
+    const int first_part = alone ? 0 : half_id, last_part = kSplit && alone ? 1 : first_part;
+    unsigned round = 0;
 
     // where component i goes in the first GEMM's contraction (see feat1 in tile_pack_operands)
     auto slot_of = [&](int i) __attribute__((always_inline)) -> int {
@@ -221,6 +301,7 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
     };
     unsigned long long n_leaf = 0, n_rounds = 0;
     unsigned n_extra = 0;
+    bool taken = false;
     long long cyc_control = 0, cyc_grad = 0, cyc_post = 0;
 
     // standard normals for this lane's components, in the dtype of the state
@@ -345,7 +426,7 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
     };
     auto block_iter_end = [&]() __attribute__((always_inline)) {
         const size_t row = (size_t)c.iter * (size_t)sa.n_chains + (size_t)(c.gchain - (uint32_t)sa.first_chain);
-        if (sa.out_states) {
+        if (lead && sa.out_states) {
             T* dst = static_cast<T*>(sa.out_states) + row * d;
             T t[kCpl];
             rest_load(kRestTop, t);
@@ -353,7 +434,7 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
             for (int e = 0; e < kCpl; ++e)
                 if (comp(e) < d) dst[comp(e)] = t[e];
         }
-        if (k == 0) {
+        if (lead && k == 0) {
             if (sa.out_depths) sa.out_depths[row] = c.j;
             if (sa.out_nleap) sa.out_nleap[row] = c.nleap;
         }
@@ -362,8 +443,13 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
     };
     auto block_fetch = [&]() __attribute__((always_inline)) {
         unsigned long long q = 0;
-        if (k == 0) q = atomicAdd(&sa.counters[kCtrQueue], 1ull);
-        q = __shfl(q, 0, kTileLanes);
+        if (kSplit) {  // (both halves have to know: a chain for every lane group, and no queue)
+            q = taken ? (unsigned long long)sa.n_chains : (unsigned long long)(NC * pair + grp);
+            taken = true;
+        } else {
+            if (k == 0) q = atomicAdd(&sa.counters[kCtrQueue], 1ull);
+            q = __shfl(q, 0, kTileLanes);
+        }
         T t[kCpl];
 #pragma unroll
         for (int e = 0; e < kCpl; ++e) t[e] = (T)0;
@@ -494,8 +580,37 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
                 if (comp(e) < 16 * MT) sTheta[grp][slot_of(comp(e))] = (at_leaf || at_init) ? (double)c.tha[e] : 0.0;
             }
         }
-        double2 a1[2 * MT], a2[S::kFullAhead ? 2 * MT : 1];
-        {
+        constexpr bool kTwo = S::kTilesAtOnce == 2;
+        double2 a1[2 * MT], a2[S::kFullAhead ? 2 * MT : 1], b1_[kTwo ? 2 * MT : 1], b2_[kTwo && S::kFullAhead ? 2 * MT : 1];
+        // divided rows: operands of tiles t and t + kTileWaves (what is asked for beyond the last tile is that tile's)
+        auto offset_of = [&](int t) __attribute__((always_inline)) -> int { return min(t, ta.n_tiles - 1) * tile_bytes; };
+        auto ask_first = [&](int t) __attribute__((always_inline)) {
+            const int p = offset_of(t), q = offset_of(t + kTileWaves);
+#pragma unroll
+            for (int i = 0; i < 2 * MT; ++i)
+                if (i < 2 * MT - 2 || i < pairs1) {
+                    a1[i] = load_at(p + i * 1024);
+                    if (kTwo) b1_[kTwo ? i : 0] = load_at(q + i * 1024);
+                }
+        };
+        auto ask_second = [&](int t) __attribute__((always_inline)) {
+            if (!S::kFullAhead) return;
+            const int p = offset_of(t) + pairs1 * 1024, q = offset_of(t + kTileWaves) + pairs1 * 1024;
+#pragma unroll
+            for (int i = 0; i < 2 * MT; ++i) {
+                a2[S::kFullAhead ? i : 0] = load_at(p + i * 1024);
+                if (kTwo) b2_[kTwo && S::kFullAhead ? i : 0] = load_at(q + i * 1024);
+            }
+        };
+        // (not all operands fit ahead: the second GEMM's take the registers that the first has just used up)
+        auto ask_second_pair = [&](int t, int p) __attribute__((always_inline)) {
+            a1[p] = load_at(offset_of(t) + (pairs1 + p) * 1024);
+            if (kTwo) b1_[kTwo ? p : 0] = load_at(offset_of(t + kTileWaves) + (pairs1 + p) * 1024);
+        };
+        if (kSplit) {
+            ask_first(first_part * S::kWaves + wave);
+            ask_second(first_part * S::kWaves + wave);
+        } else {
             const int base = wave * tile_bytes;
 #pragma unroll
             for (int i = 0; i < 2 * MT; ++i)
@@ -507,9 +622,17 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
         }
         tile_lds_barrier();
         if (*const_cast<volatile int*>(&sHalted) == NC) break;  // every chain of the workgroup has halted
+        if (kSplit && *const_cast<volatile int*>(&sLost)) break;
         n_rounds += 1;
+        round += 1;
         const long long t1 = clock64();
-        {
+        // (divided rows, alone: the other half's four sums, too)
+        for (int part = first_part; part <= last_part; ++part) {
+            const int turn = kSplit ? part * S::kWaves + wave : wave;  // which of the eight sums
+            if (kSplit && part != first_part) {
+                ask_first(turn);
+                ask_second(turn);
+            }
             typedef __attribute__((ext_vector_type(4))) double acc16;
             acc16 G16[NC == 16 ? MT : 1];
             double G4[NC == 4 ? MT : 1];
@@ -611,6 +734,77 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
                     for (int i = 0; i < 2 * MT; ++i) a2[i] = load_at(next + (pairs1 + i) * 1024);
                 }
             };
+            // Divided rows: two tiles, t and t + kTileWaves, step by step (one wave has the SIMD to itself, and would wait for every
+            // result of a single tile).  `last`: the second may not exist, one of them may be ragged.
+            auto two_tiles = [&](const int t, const bool last) __attribute__((always_inline)) {
+                const bool second = !last || t + kTileWaves < ta.n_tiles;
+                const int my_row = 4 * ((lane >> 2) & 3) + (lane >> 4);
+                bool real[2];
+                double z[2], x[2], sig[2], sg[2][4];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    real[q] = !last || ta.rem_rows == 0 || t + q * kTileWaves != ta.n_tiles - 1 || my_row < ta.rem_rows;
+                    z[q] = real[q] ? z0 : 0.0;
+                }
+                if (!S::kHoldTheta) asm volatile("" ::: "memory");
+#pragma unroll
+                for (int s = 0; s < 4 * MT; ++s)
+                    if (s < 4 * MT - 4 || s < wa.ks1) {
+                        const double b = S::kHoldTheta ? b1[S::kHoldTheta ? s : 0] : b_src[4 * s];
+#pragma unroll
+                        for (int q = 0; q < 2; ++q) {
+                            const double2 pr = q ? b1_[kTwo ? s >> 1 : 0] : a1[s >> 1];
+                            z[q] = __builtin_amdgcn_mfma_f64_4x4x4f64((s & 1) ? pr.y : pr.x, b, z[q], 0, 0, 0);
+                        }
+                        if (!S::kFullAhead && (s & 1)) ask_second_pair(t, s >> 1);
+                    } else if (!S::kFullAhead && (s & 1)) {
+                        ask_second_pair(t, s >> 1);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+                if (S::kFullAhead) ask_first(t + 2 * kTileWaves);
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    if (S::kResidual) logistic_residual(z[q], x[q], sig[q]);
+                    else x[q] = __builtin_copysign(logistic_slope(z[q], sFtab), z[q]);
+                }
+                // rows 4s + k of the tile, which sit in quad s, for every block of the second GEMM (through LDS of the wave's own, in
+                // order: six instructions where swizzles are sixteen)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) sSpread[kTwo ? wave : 0][kTwo ? q : 0][kTwo ? lane : 0] = x[q];
+                asm volatile("" ::: "memory");
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) sg[q][s] = sSpread[kTwo ? wave : 0][kTwo ? q : 0][kTwo ? (lane & 0x33) + 4 * s : 0];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {  // (in the order of row_tile)
+                    if (q && !second) break;
+                    if (S::kResidual) {
+                        sum_abs[0] += fabs(z[q]) - z[q];
+                        prod[0] *= real[q] ? sig[q] : 1.0;
+                    } else {
+                        const double a = fabs(z[q]);
+                        sum_abs[0] = (((sum_abs[0] + a) + quad_after<1>(a)) + quad_after<2>(a)) + quad_after<3>(a);
+                        prod[0] *= ((fabs(sg[q][0]) + 0.5) * (fabs(sg[q][1]) + 0.5)) * ((fabs(sg[q][2]) + 0.5) * (fabs(sg[q][3]) + 0.5));
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    if (q && !second) break;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int u = 0; u < MT; ++u) {
+                            const int p = u * 2 + h;
+                            const double2 pr = S::kFullAhead ? (q ? b2_[kTwo && S::kFullAhead ? p : 0] : a2[S::kFullAhead ? p : 0]) : (q ? b1_[kTwo ? p : 0] : a1[p]);
+                            G4[NC == 4 ? u : 0] = __builtin_amdgcn_mfma_f64_4x4x4f64(pr.x, sg[q][2 * h], G4[NC == 4 ? u : 0], 0, 0, 0);
+                            G4[NC == 4 ? u : 0] = __builtin_amdgcn_mfma_f64_4x4x4f64(pr.y, sg[q][2 * h + 1], G4[NC == 4 ? u : 0], 0, 0, 0);
+                            if (!S::kFullAhead) (q ? b1_[kTwo ? p : 0] : a1[p]) = load_at(offset_of(t + (2 + q) * kTileWaves) + p * 1024);
+                        }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                ask_second(t + 2 * kTileWaves);
+            };
             auto fold = [&]() __attribute__((always_inline)) {
 #pragma unroll
                 for (int q = 0; q < S::kQ; ++q) {
@@ -621,12 +815,27 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
             };
             // (z0, residuals: a last tile that is not full is run after the loop, by the wave whose turn it is)
             const int n_loop = ta.rem_rows != 0 ? ta.n_tiles - 1 : ta.n_tiles;
-            for (int t_chunk = wave; t_chunk < n_loop; t_chunk += 64 * kTileWaves) {
+            if constexpr (kTwo) {
+                int t = turn, left = 64;  // tiles until the products become logarithms
+                for (; t + kTileWaves < n_loop; t += 2 * kTileWaves) {
+                    if (left == 0) {
+                        fold();
+                        left = 64;
+                    }
+                    two_tiles(t, false);
+                    left -= 2;
+                }
+                if (t < ta.n_tiles) {
+                    if (left == 0 && t < n_loop) fold();
+                    two_tiles(t, true);
+                }
+            }
+            for (int t_chunk = kTwo ? n_loop : turn; t_chunk < n_loop; t_chunk += 64 * kTileWaves) {
                 const int t_stop = min(n_loop, t_chunk + 64 * kTileWaves);
                 for (int t = t_chunk; t < t_stop; t += kTileWaves) row_tile(t, false, t + kTileWaves < ta.n_tiles);
                 if (t_chunk + 64 * kTileWaves < n_loop) fold();  // more follow
             }
-            if (ta.rem_rows != 0 && wave == ((ta.n_tiles - 1) & (kTileWaves - 1))) row_tile(ta.n_tiles - 1, true, false);
+            if (!kTwo && ta.rem_rows != 0 && turn == ((ta.n_tiles - 1) & (kTileWaves - 1))) row_tile(ta.n_tiles - 1, true, false);
             fold();
             double ll = log_prod[0] - 0.5 * sum_abs[0];
             if (S::kResidual) {  // rows 4q + k of all tiles: q = (0 + 2) + (1 + 3); with 4 chains they are in four quads
@@ -642,7 +851,7 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
             }
             ll = add_other_row(ll);
             ll = add_other_half(ll);
-            if (lane < NC) sLL[wave][lane] = ll;
+            if (lane < NC) sLL[turn][lane] = ll;
             // partial gradients to LDS: element (u, q) of the accumulators is feature 16u + 4q + lane/16 (16 chains) or
             // 16u + 4((lane/4) % 4) + lane/16 (4 chains) of chain lane % NC
             auto put = [&](double* dst, bool add) __attribute__((always_inline)) {
@@ -661,11 +870,50 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
             };
             const int off = NC == 16 ? (lane >> 4) : 4 * ((lane >> 2) & 3) + (lane >> 4);
             if (S::kSlots == kTileWaves) {
-                put(&sG[wave & (S::kSlots - 1)][lane & (NC - 1)][off], false);
+                put(&sG[turn & (S::kSlots - 1)][lane & (NC - 1)][off], false);
             } else {  // two waves share a slot, one after the other
                 if (wave < 4) put(&sG[wave & 3][lane & (NC - 1)][off], false);
                 tile_lds_barrier();
                 if (wave >= 4) put(&sG[wave & 3][lane & (NC - 1)][off], true);
+            }
+            if constexpr (kSplit) {
+                // This wave's sums to the other half's wave, and that one's here.  Every 8 bytes carry the round's number beside
+                // half a value, so a value that is there needs no flag and no fence; two buffers in turn, as neither half is more
+                // than a round ahead of the other.
+                if (!alone) {
+                    const int at = (((int)(round & 1) * S::kWaves + wave) * (MT + 1)) * kWave * 16;
+                    auto send = [&](double v, int i) __attribute__((always_inline)) {
+                        const v4u w{(unsigned)__double2loint(v), round, (unsigned)__double2hiint(v), round};
+                        __builtin_amdgcn_raw_buffer_store_b128(w, own_rsrc, lane * 16, at + i * kWave * 16, kWideAgent);
+                    };
+#pragma unroll
+                    for (int u = 0; u < MT; ++u) send(G4[NC == 4 ? u : 0], u);
+                    send(ll, MT);
+                    v4u in[MT + 1];
+                    long long t0 = 0;
+                    for (int looks = 1;; ++looks) {
+                        asm volatile("" ::: "memory");
+                        bool there = true;
+#pragma unroll
+                        for (int i = 0; i <= MT; ++i)
+                            in[i] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(other_rsrc, lane * 16, at + i * kWave * 16, kWideAgent));
+#pragma unroll
+                        for (int i = 0; i <= MT; ++i) there = there && in[i][1] == round && in[i][3] == round;
+                        if (__all(there)) break;
+                        if ((looks & 255) == 0) {  // (no wait is without an end)
+                            const long long now = wall_clock64();
+                            if (t0 == 0) t0 = now;
+                            if (now - t0 > kWideLostLimit) {
+                                sLost = 1;
+                                break;
+                            }
+                        }
+                    }
+                    const int theirs = (1 - half_id) * S::kWaves + wave;
+#pragma unroll
+                    for (int u = 0; u < MT; ++u) sG[theirs & (S::kSlots - 1)][lane & (NC - 1)][off + 16 * u] = __hiloint2double((int)in[u][2], (int)in[u][0]);
+                    if (lane < NC) sLL[theirs][lane] = __hiloint2double((int)in[MT][2], (int)in[MT][0]);
+                }
             }
         }
         tile_lds_barrier();
@@ -753,6 +1001,9 @@ __global__ __launch_bounds__(kTileThreads) void nuts_wide_kernel(WideArgs wa, De
         cyc_post += clock64() - t2;
     }
 
+    if (kSplit && sLost && lead && owns && k == 0 && c.pc != kPcHalt && sa.out_depths)  // (it shows: no tree has this depth)
+        sa.out_depths[(size_t)c.iter * (size_t)sa.n_chains + (size_t)(c.gchain - (uint32_t)sa.first_chain)] = -1;
+    if (!lead) return;
     if (owns && k == 0) {
         atomicAdd(&sa.counters[kCtrUseful], n_leaf);
         atomicAdd(&sa.counters[kCtrExtra], (unsigned long long)n_extra);
@@ -791,6 +1042,18 @@ inline int wide_chains_per_block(long n_chains, int cus, long iters, long n, int
     return iters <= most ? 4 : 16;
 }
 
+// Whether the rows are divided: compute units for two workgroups of every four chains, and rows enough.  Time undivided over time
+// divided, binary64, 64 and 512 chains (binary32 alike):
+//   features      700 rows       1000           2000           5000           20 000
+//   9             0.94 0.91      1.04 1.01      1.15 1.08      1.27 1.22      1.41 1.32
+//   25            0.93 0.91      1.04 1.01      1.18 1.11      1.30 1.25      1.92 1.73
+//   60            1.00 0.96      1.18 1.12      1.39 1.28      1.64 1.59      1.80 1.87
+//   90            1.10 1.02      1.25 1.13      1.41 1.21      1.65 1.45
+//   128           1.15 1.06      1.33 1.18      1.42 1.27      1.73 1.49
+// (100 rows: 0.6 to 0.8.)
+constexpr int kWideMaxPairs = 256;
+inline bool wide_split_pays(long n_chains, int cus, long n) { return n >= 1000 && (n_chains + 3) / 4 * 2 <= cus; }
+
 inline size_t wide_block_bytes(int d, int dtype_bytes, int nc, int max_depth)
 {
     const int cpl = ((d + 15) / 16 * 16 + 31) / 32;
@@ -804,11 +1067,15 @@ inline void wide_launch_mt(const WideArgs& wa, const DevSample& sa, int nc, int 
     // (binary64 with up to 32 features: sixteen chains per workgroup are the tile kernel's)
     if constexpr (sizeof(T) == 4 || MT > 2) {
         if (nc == 16) {
-            hipLaunchKernelGGL((nuts_wide_kernel<T, MT, 16>), dim3((unsigned)blocks), dim3(kTileThreads), 0, stream, wa, sa);
+            hipLaunchKernelGGL((nuts_wide_kernel<T, MT, 16, false>), dim3((unsigned)blocks), dim3(kTileThreads), 0, stream, wa, sa);
             return;
         }
     }
-    hipLaunchKernelGGL((nuts_wide_kernel<T, MT, 4>), dim3((unsigned)blocks), dim3(kTileThreads), 0, stream, wa, sa);
+    if (wa.n_pairs > 0) {
+        hipLaunchKernelGGL((nuts_wide_kernel<T, MT, 4, true>), dim3((unsigned)(wa.n_pairs + 7) / 8 * 16), dim3(kTileThreads / 2), 0, stream, wa, sa);
+        return;
+    }
+    hipLaunchKernelGGL((nuts_wide_kernel<T, MT, 4, false>), dim3((unsigned)blocks), dim3(kTileThreads), 0, stream, wa, sa);
 }
 template <typename T>
 inline void wide_launch(const WideArgs& wa, const DevSample& sa, int nc, int blocks, hipStream_t stream)

@@ -1643,6 +1643,35 @@ def test_chains_have_the_same_bits_in_either_lock_step_form_where_rounding_decid
         assert differ.sum() == 0, f"{differ.sum()} of {differ.size} values differ"
 
 
+# rows at the edges of a tile of 16, of the eight sums and of the pairs of tiles (the last of a wave's tiles alone, ragged, or with a
+# ragged one beside it), on either side of 64 tiles per sum; features at the edges of the feature tiles, with and without a
+# constant column, where operands are asked for a tile and half a tile ahead
+@pytest.mark.parametrize("n_data,dim,dtype", [(1000, 25, np.float64), (1000, 1, np.float64), (1024, 16, np.float64), (1025, 17, np.float64), (1137, 9, np.float32),
+                                              (1152, 32, np.float64), (1153, 33, np.float64), (8192, 13, np.float64), (8193, 5, np.float64), (8320, 21, np.float64),
+                                              (1040, 64, np.float64), (1263, 65, np.float64), (1279, 80, np.float64), (8321, 90, np.float64), (1000, 97, np.float64),
+                                              (1111, 128, np.float64), (5000, 60, np.float64), (1007, 4, np.float32)])
+def test_rows_divided_between_two_workgroups_give_the_same_bits(n_data, dim, dtype):
+    import ctypes as C
+    w = W.small_logreg(n_data, dim, seed=dim, dtype=dtype)
+    w.X[:, dim // 2] = 1.0                                        # a constant column (out of the first GEMM where dim % 4 == 1)
+    w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = 11, 3, 0.7 / np.sqrt(n_data), 5
+    tgt = gpu_target(w)
+    pairs = gpu_run(w, tgt=tgt)
+    assert pairs[3]["variant"] == N().NUTS_VARIANT_TILE and pairs[3]["grid_blocks"] == 6
+    assert pairs[3]["leaf_slots_useful"] == pairs[2].sum() and pairs[3]["extra_grad_evals"] == w.n_chains
+    whole = gpu_run(w, tgt=tgt, n_chains=1000)                    # too many chains for two workgroups of every four
+    assert whole[3]["grid_blocks"] <= 250
+    B = N()
+    runs = [gpu_run(w, tgt=tgt, schedule=1), gpu_run(w, tgt=tgt)]
+    B._check(B.lib().nuts_debug_wide_apart(tgt.handle, C.c_int(1)))   # one of the two workgroups does all
+    runs.append(gpu_run(w, tgt=tgt))
+    for k in range(3):
+        assert np.array_equal(whole[k][:, :w.n_chains], pairs[k])
+        for r in runs:
+            assert np.array_equal(r[k], pairs[k])
+    assert_parity(pairs, ref_run(w), F64_TOL if dtype == np.float64 else F32_TOL, exact_ints=dtype == np.float64, label="rows divided")
+
+
 @pytest.mark.parametrize("n_data,dim", [(37, 33), (300, 100), (2000, 60), (5000, 40)])
 def test_wide_kernel_gradients_are_as_exact_as_the_general_kernels(n_data, dim):
     """One leaf of 64 leapfrog steps from points near the posterior, against the same steps in extended precision (64-bit
