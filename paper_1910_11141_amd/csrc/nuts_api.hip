@@ -419,6 +419,13 @@ __global__ void fill_words_kernel(unsigned* p, int n, unsigned value)
     for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = value;
 }
 
+__global__ void begin_turns_kernel(unsigned* words, nuts::RowTurns plan)
+{
+    for (int i = threadIdx.x; i < nuts::kTurnPlan; i += blockDim.x) words[i] = 0u;
+    for (unsigned i = threadIdx.x; i <= plan.mask; i += blockDim.x) words[nuts::kTurnRing + i] = 0u;
+    if (threadIdx.x == 0) *reinterpret_cast<nuts::RowTurns*>(words + nuts::kTurnPlan) = plan;
+}
+
 // (behind the counters: the words at which the wide kernel's pairs of workgroups meet, of which a call without them has none)
 __global__ void zero_counters_kernel(unsigned long long* c, int words)
 {
@@ -549,19 +556,64 @@ nuts::RowLds row_lds(long blocks, int cus, size_t base, int kc, size_t elem, int
     return nuts::row_lds_split(budget > base ? (budget - base) / 4 : 0, kc, elem, max_depth, grad);
 }
 
-template <typename T, int kC>
+// Where chains wait for slots the call's last ones take turns (nuts_row.h).  The memory does not depend on the number of iterations, so that a
+// call of one iteration prepares for one of many (which may then be captured); it is at most about a third of what the slots take,
+// and a call that cannot have it does without.  nuts_sample_static does without too: its memory is fixed.
+int row_workspace(nuts_target* t, nuts::DevSample& sa, size_t slot, long slots, int kc, size_t elem, bool grad, bool take, unsigned** turns)
+{
+    nuts::RowTurns plan{};
+    *turns = nullptr;
+    const size_t base = slot * (size_t)slots;
+    size_t words = 0, rows = 0;
+    if (!t->static_call && sa.n_chains > slots && 2 * kc * elem <= (size_t)nuts::kTurnLaneBytes) {
+        const long n = std::min(sa.n_chains, nuts::kTurnChains * slots);
+        unsigned ring = 1;
+        while ((long)ring < n) ring *= 2;
+        plan.mask = ring - 1;
+        plan.row_bytes = (unsigned)nuts::row_turn_bytes(kc, elem, grad);
+        plan.first = sa.n_chains - n;
+        words = ((nuts::kTurnRing + (size_t)ring) * sizeof(unsigned) + 255) & ~(size_t)255;
+        rows = (size_t)plan.row_bytes * (size_t)n;
+    }
+    if (words && base + words + rows > t->workspace_bytes && base <= t->workspace_bytes) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;  // nothing can be allocated while a graph is captured
+        if (hipStreamIsCapturing(g_stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) words = rows = 0;
+    }
+    int rc = ensure_workspace(t, base + words + rows);
+    if (rc == NUTS_E_ALLOC && words) {
+        (void)hipGetLastError();
+        rc = ensure_workspace(t, base);
+        words = 0;
+    }
+    if (rc) return rc;
+    sa.workspace = t->ws_cur;
+    sa.slot_bytes = slot;
+    if (words && take) {
+        *turns = reinterpret_cast<unsigned*>(t->ws_cur + base);
+        plan.rows = t->ws_cur + base + words;
+        hipLaunchKernelGGL(begin_turns_kernel, dim3(1), dim3(1024), 0, g_stream, *turns, plan);
+        HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
+    }
+    return NUTS_OK;
+}
+
+bool takes_turns(const nuts_target* t, const nuts::DevSample& sa, long slots) { return !t->static_call && sa.n_chains > slots && sa.iter_end - sa.iter_begin > 1; }
+
+template <typename T, int kC, bool kTurns = false>
 int launch_elem_inst(nuts_target* t, nuts::DevSample sa, int variant)
 {
     const nuts::DevTarget<T> tg = dev_target<T>(t);
     size_t slot = (size_t)nuts::row_num_vectors(sa.max_depth) * 128 * kC * sizeof(T);
     slot = (slot + 255) & ~(size_t)255;
-    const void* fn = reinterpret_cast<const void*>(nuts::nuts_elem_kernel<T, kC>);
+    const void* fn = reinterpret_cast<const void*>(nuts::nuts_elem_kernel<T, kC, kTurns>);
     HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes), NUTS_E_DEVICE);
     size_t lds_bytes = nuts::elem_lane_bytes<T, kC>() <= 32 ? 0 : 128 * kC * sizeof(T);
     int per_cu = 0, cus = 0;
-    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (nuts::nuts_elem_kernel<T, kC>), 256, lds_bytes), NUTS_E_DEVICE);
+    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (nuts::nuts_elem_kernel<T, kC, kTurns>), 256, lds_bytes), NUTS_E_DEVICE);
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device), NUTS_E_DEVICE);
     if (per_cu < 1) per_cu = 1;
+    if constexpr (!kTurns && nuts::row_takes_turns<T, kC>())
+        if (takes_turns(t, sa, 4L * per_cu * cus)) return launch_elem_inst<T, kC, true>(t, sa, variant);
     long blocks = (sa.n_chains + 3) / 4;
     if (blocks > (long)per_cu * cus) blocks = (long)per_cu * cus;
     if (t->static_call) {
@@ -581,11 +633,10 @@ int launch_elem_inst(nuts_target* t, nuts::DevSample sa, int variant)
     }
     const nuts::RowLds rl = row_lds(blocks, cus, lds_bytes, kC, sizeof(T), sa.max_depth, false);
     lds_bytes += (size_t)4 * (rl.n_first + rl.n_pool) * nuts::row_entry_bytes(kC, sizeof(T));
-    int rc = ensure_workspace(t, slot * (size_t)blocks * 4);
+    unsigned* turns;
+    int rc = row_workspace(t, sa, slot, blocks * 4, kC, sizeof(T), false, kTurns, &turns);
     if (rc) return rc;
-    sa.workspace = t->ws_cur;
-    sa.slot_bytes = slot;
-    hipLaunchKernelGGL((nuts::nuts_elem_kernel<T, kC>), dim3((unsigned)blocks), dim3(256), lds_bytes, g_stream, tg, sa, rl);
+    hipLaunchKernelGGL((nuts::nuts_elem_kernel<T, kC, kTurns>), dim3((unsigned)blocks), dim3(256), lds_bytes, g_stream, tg, sa, rl, turns);
     HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
     t->last_variant = variant;
     t->last_grid = (int)blocks;
@@ -610,7 +661,7 @@ bool dense_eligible(const nuts_target* t)
     return t->kind == NUTS_TARGET_GAUSS_DENSE_PRECISION && t->dim <= nuts::kDenseMaxDim;
 }
 
-template <typename T, bool kBanded>
+template <typename T, bool kBanded, bool kTurns = false>
 int launch_dense_inst(nuts_target* t, nuts::DevSample sa)
 {
     using namespace nuts;
@@ -618,24 +669,25 @@ int launch_dense_inst(nuts_target* t, nuts::DevSample sa)
     const int threads = kDenseWaves * kWave;
     size_t lds_bytes = dense_base_elems(kBanded ? 0 : (int)t->dim) * sizeof(T);
     lds_bytes = (lds_bytes + 15) & ~(size_t)15;
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(nuts_dense_kernel<T, kBanded>),
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(nuts_dense_kernel<T, kBanded, kTurns>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes), NUTS_E_DEVICE);
     size_t slot = (size_t)row_num_vectors(sa.max_depth) * kDensePitch * sizeof(T);
     slot = (slot + 255) & ~(size_t)255;
     int per_cu = 0, cus = 0;
-    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (nuts_dense_kernel<T, kBanded>), threads, lds_bytes), NUTS_E_DEVICE);
+    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (nuts_dense_kernel<T, kBanded, kTurns>), threads, lds_bytes), NUTS_E_DEVICE);
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device), NUTS_E_DEVICE);
     if (per_cu < 1) per_cu = 1;
+    if constexpr (!kTurns)
+        if (takes_turns(t, sa, (long)kDenseWaves * per_cu * cus)) return launch_dense_inst<T, kBanded, true>(t, sa);
     long blocks = (sa.n_chains + kDenseWaves - 1) / kDenseWaves;
     const long resident = (long)per_cu * cus;
     if (blocks > resident) blocks = resident;
     const RowLds rl = row_lds(blocks, cus, lds_bytes, 1, sizeof(T), sa.max_depth, true);
     lds_bytes += (size_t)kDenseWaves * (rl.n_first + rl.n_pool) * row_entry_bytes(1, sizeof(T));
-    int rc = ensure_workspace(t, slot * (size_t)blocks * kDenseWaves);
+    unsigned* turns;
+    int rc = row_workspace(t, sa, slot, blocks * kDenseWaves, 1, sizeof(T), true, kTurns, &turns);
     if (rc) return rc;
-    sa.workspace = t->ws_cur;
-    sa.slot_bytes = slot;
-    hipLaunchKernelGGL((nuts_dense_kernel<T, kBanded>), dim3((unsigned)blocks), dim3(threads), lds_bytes, g_stream, tg, sa, rl);
+    hipLaunchKernelGGL((nuts_dense_kernel<T, kBanded, kTurns>), dim3((unsigned)blocks), dim3(threads), lds_bytes, g_stream, tg, sa, rl, turns);
     HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
     t->last_variant = NUTS_VARIANT_DENSE;
     t->last_grid = (int)blocks;
@@ -649,19 +701,21 @@ int launch_dense(nuts_target* t, const nuts::DevSample& sa)
     return t->dBand ? launch_dense_inst<T, true>(t, sa) : launch_dense_inst<T, false>(t, sa);
 }
 
-template <typename T, int kC>
+template <typename T, int kC, bool kTurns = false>
 int launch_band_inst(nuts_target* t, nuts::DevSample sa)
 {
     const nuts::DevTarget<T> tg = dev_target<T>(t);
     size_t slot = (size_t)nuts::row_num_vectors(sa.max_depth) * 128 * kC * sizeof(T);
     slot = (slot + 255) & ~(size_t)255;
-    const void* fn = reinterpret_cast<const void*>(nuts::nuts_band_kernel<T, kC>);
+    const void* fn = reinterpret_cast<const void*>(nuts::nuts_band_kernel<T, kC, kTurns>);
     HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes), NUTS_E_DEVICE);
     size_t lds_bytes = (size_t)4 * nuts::band_bcast(kC) * sizeof(T);
     int per_cu = 0, cus = 0;
-    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (nuts::nuts_band_kernel<T, kC>), 256, lds_bytes), NUTS_E_DEVICE);
+    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (nuts::nuts_band_kernel<T, kC, kTurns>), 256, lds_bytes), NUTS_E_DEVICE);
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device), NUTS_E_DEVICE);
     if (per_cu < 1) per_cu = 1;
+    if constexpr (!kTurns && nuts::row_takes_turns<T, kC>())
+        if (takes_turns(t, sa, 4L * per_cu * cus)) return launch_band_inst<T, kC, true>(t, sa);
     long blocks = (sa.n_chains + 3) / 4;
     if (blocks > (long)per_cu * cus) blocks = (long)per_cu * cus;
     if (t->static_call) {
@@ -672,12 +726,11 @@ int launch_band_inst(nuts_target* t, nuts::DevSample sa)
     }
     const nuts::RowLds rl = row_lds(blocks, cus, lds_bytes, kC, sizeof(T), sa.max_depth, true);
     lds_bytes += (size_t)4 * (rl.n_first + rl.n_pool) * nuts::row_entry_bytes(kC, sizeof(T));
-    int rc = ensure_workspace(t, slot * (size_t)blocks * 4);
+    unsigned* turns;
+    int rc = row_workspace(t, sa, slot, blocks * 4, kC, sizeof(T), true, kTurns, &turns);
     if (rc) return rc;
-    sa.workspace = t->ws_cur;
-    sa.slot_bytes = slot;
-    hipLaunchKernelGGL((nuts::nuts_band_kernel<T, kC>), dim3((unsigned)blocks), dim3(256), lds_bytes, g_stream, tg,
-                       static_cast<const T*>(t->dDiag), t->diag_present, sa, rl);
+    hipLaunchKernelGGL((nuts::nuts_band_kernel<T, kC, kTurns>), dim3((unsigned)blocks), dim3(256), lds_bytes, g_stream, tg,
+                       static_cast<const T*>(t->dDiag), t->diag_present, sa, rl, turns);
     HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
     t->last_variant = NUTS_VARIANT_WAVE;
     t->last_grid = (int)blocks;

@@ -104,8 +104,9 @@ __host__ __device__ inline size_t dense_base_elems(int mat_rows)
     return (size_t)mat_rows * kDensePitch + (size_t)kDenseWaves * kDenseBcast;
 }
 
-template <typename T, bool kBanded>
-__global__ __launch_bounds__(kDenseWaves* kWave, sizeof(T) == 8 && !kBanded ? 1 : 2) void nuts_dense_kernel(DevTarget<T> tg, DevSample sa, RowLds rl)
+// kTurns: as in nuts_elem.h.
+template <typename T, bool kBanded, bool kTurns>
+__global__ __launch_bounds__(kDenseWaves* kWave, sizeof(T) == 8 && !kBanded ? 1 : 2) void nuts_dense_kernel(DevTarget<T> tg, DevSample sa, RowLds rl, unsigned* turns)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     T* mat = reinterpret_cast<T*>(smem);  // dense: d rows of kDensePitch; banded: nothing
@@ -120,10 +121,10 @@ __global__ __launch_bounds__(kDenseWaves* kWave, sizeof(T) == 8 && !kBanded ? 1 
     __syncthreads();
     const size_t slot = (size_t)blockIdx.x * kDenseWaves + wave;
     T* tree = mat + dense_base_elems(mat_rows) + (size_t)wave * (rl.n_first + rl.n_pool) * 2 * kDensePitch;
-    RowChain<T, 1, true, true> ch(sa, tg.d, lane, reinterpret_cast<T*>(sa.workspace + slot * sa.slot_bytes), tree, rl);
+    RowChain<T, 1, true, true, false, kTurns> ch(sa, tg.d, lane, reinterpret_cast<T*>(sa.workspace + slot * sa.slot_bytes), tree, rl, turns);
     const DenseGradient<T, kBanded> grad(tg, lane, mat, bcast);
-    while (ch.fetch()) {
-        ch.start_chain(grad(ch.th, ch.g));
+    while (const int taken = ch.take()) {
+        if (taken == kTakeFresh) ch.start_chain(grad(ch.th, ch.g));
         do {
             ch.iter_begin();
             do {

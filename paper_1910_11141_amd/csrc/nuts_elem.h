@@ -15,7 +15,7 @@
 // Against the kernel before it (weights as logarithms through a table, 53 KB of LDS for that table, the random numbers
 // of a doubling drawn one by one, first leaves and both ends in memory), the same outputs bit for bit: d = 2 binary64, 4
 // chains, 100 iterations 1170 -> 670 us; d = 500 binary32 standard normal, 16384 chains, 20 iterations 10.0 -> 4.3 ms; d = 1000 binary32
-// diagonal, 16384 chains, 8 iterations 95 -> 52 ms.
+// diagonal, 16384 chains, 8 iterations 95 -> 52 ms (now 42.9: sums in one pass, chains that take turns, nuts_row.h).
 #pragma once
 #include "nuts_row.h"
 
@@ -26,8 +26,10 @@ template <typename T, int kC>
 constexpr int elem_lane_bytes() { return 2 * kC * (int)sizeof(T); }
 
 // Workgroups are four waves; LDS: 1 / sigma^2 (unless it is held in registers), then the slots' tree storage.
-template <typename T, int kC>
-__global__ __launch_bounds__(256, (elem_lane_bytes<T, kC>() <= 64 ? 2 : 1)) void nuts_elem_kernel(DevTarget<T> tg, DevSample sa, RowLds rl)
+// kTurns: the call's last chains take turns.  An instance of its own: with the code for turns a step takes 1.02 to 1.03 times
+// as long where its latency counts (d = 2 and 100, one wave per SIMD or less).
+template <typename T, int kC, bool kTurns>
+__global__ __launch_bounds__(256, (elem_lane_bytes<T, kC>() <= 64 ? 2 : 1)) void nuts_elem_kernel(DevTarget<T> tg, DevSample sa, RowLds rl, unsigned* turns)
 {
     typedef typename RowVec<T>::type Vec;
     constexpr int kVpl = 2 * kC;
@@ -37,7 +39,7 @@ __global__ __launch_bounds__(256, (elem_lane_bytes<T, kC>() <= 64 ? 2 : 1)) void
     const int lane = threadIdx.x & (kWave - 1), wave = uni((int)(threadIdx.x / kWave));
     const size_t slot = (size_t)blockIdx.x * 4 + wave;
     T* const tree = s_w + (kHeld ? 0 : 128 * kC) + (size_t)wave * (rl.n_first + rl.n_pool) * 2 * 128 * kC;
-    RowChain<T, kC, kHeld, false> ch(sa, tg.d, lane, reinterpret_cast<T*>(sa.workspace + slot * sa.slot_bytes), tree, rl);
+    RowChain<T, kC, kHeld, false, false, kTurns> ch(sa, tg.d, lane, reinterpret_cast<T*>(sa.workspace + slot * sa.slot_bytes), tree, rl, turns);
     // 1 / sigma^2, zero beyond d
     auto weight = [&](int i) -> T { return i < tg.d ? (tg.kind == kGaussDiag ? tg.inv_var[i] : T(1)) : T(0); };
     T w_reg[kHeld ? kVpl : 1];
@@ -80,19 +82,21 @@ __global__ __launch_bounds__(256, (elem_lane_bytes<T, kC>() <= 64 ? 2 : 1)) void
         }
         return lp;
     };
-    while (ch.fetch()) {
+    while (const int taken = ch.take()) {
         double lp = 0.0;
+        if (taken == kTakeFresh) {
 #pragma unroll
-        for (int q = 0; q < kC; ++q) {
-            T w[2];
-            pair_weight(q, w);
+            for (int q = 0; q < kC; ++q) {
+                T w[2];
+                pair_weight(q, w);
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const T g = -(ch.th[2 * q + e] * w[e]);
-                lp = fma((double)ch.th[2 * q + e], (double)g, lp);
+                for (int e = 0; e < 2; ++e) {
+                    const T g = -(ch.th[2 * q + e] * w[e]);
+                    lp = fma((double)ch.th[2 * q + e], (double)g, lp);
+                }
             }
+            ch.start_chain(lp);
         }
-        ch.start_chain(lp);
         do {
             ch.iter_begin();
             do {
@@ -116,7 +120,7 @@ __global__ __launch_bounds__(256, (elem_lane_bytes<T, kC>() <= 64 ? 2 : 1)) void
 }
 
 // The instance with the compiler flags of nuts_gauss.hip; with them d = 1000 takes 1.03 (binary32) to 1.06 times as long.
-#define NUTS_ELEM_INSTANCE(T, kC) template __global__ void nuts_elem_kernel<T, kC>(DevTarget<T>, DevSample, RowLds);
-extern NUTS_ELEM_INSTANCE(double, 16)
+#define NUTS_ELEM_INSTANCE(T, kC, kTurns) template __global__ void nuts_elem_kernel<T, kC, kTurns>(DevTarget<T>, DevSample, RowLds, unsigned*);
+extern NUTS_ELEM_INSTANCE(double, 16, false)
 
 }  // namespace nuts

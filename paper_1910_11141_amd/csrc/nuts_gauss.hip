@@ -29,6 +29,6 @@ template hipError_t block_launch<float>(const BlockData&, const DevSample&, cons
 template hipError_t block_launch<double>(const BlockData&, const DevSample&, const BlockPlan&, hipStream_t);
 
 NUTS_BAND_INSTANCES()
-NUTS_ELEM_INSTANCE(double, 16)
+NUTS_ELEM_INSTANCE(double, 16, false)
 
 }  // namespace nuts

@@ -1643,6 +1643,34 @@ def test_chains_have_the_same_bits_in_either_lock_step_form_where_rounding_decid
         assert differ.sum() == 0, f"{differ.sum()} of {differ.size} values differ"
 
 
+# More chains than slots, iterations and steps enough for several turns: element-wise, dense and banded kernels, with vectors held in registers
+# and in memory, ragged dimensions, chains that all take turns (up to eight per slot) and chains of which only the last do.
+@pytest.mark.parametrize("kind,dim,dtype,chains,iters,eps,more", [
+    (W.STD_NORMAL, 2, np.float64, 5001, 30, 0.05, {}), (W.GAUSS_DIAG, 7, np.float32, 30011, 8, 0.02, {}), (W.GAUSS_DIAG, 130, np.float64, 3100, 9, 0.02, {}),
+    (W.STD_NORMAL, 500, np.float64, 2203, 12, 0.05, {}), (W.GAUSS_DIAG, 1000, np.float32, 2049, 6, 0.02, {"sampler": 1}), (W.GAUSS_DIAG, 1999, np.float32, 1027, 6, 0.02, {}),
+    ("ar1", 33, np.float32, 2051, 12, 0.02, {}), ("ar1", 128, np.float64, 2050, 9, 0.05, {"leaf_steps": 4}), ("ar1", 200, np.float64, 2057, 7, 0.05, {}),
+    ("ar1", 1500, np.float32, 1029, 6, 0.05, {}), ("ar1", 777, np.float64, 1029, 6, 0.05, {}), ("spd", 100, np.float64, 1031, 10, 0.05, {"variant": "NUTS_VARIANT_DENSE"})])
+def test_chains_that_take_turns_have_the_bits_of_chains_that_keep_their_slot(kind, dim, dtype, chains, iters, eps, more):
+    rng = np.random.default_rng(dim)
+    w = W.Workload("turns", W.GAUSS_DENSE if kind in ("ar1", "spd") else kind, dim, np.dtype(dtype), chains, iters, eps, 8, seed=19)
+    if kind in ("ar1", "spd"):
+        w.precision = W.ar1_precision(dim, 0.8) if kind == "ar1" else W.random_spd_precision(dim, 3)
+    elif kind == W.GAUSS_DIAG:
+        w.scales = 10.0 ** (-1.0 + 2.0 * rng.random(dim))
+    more = {k: getattr(N(), x) if k == "variant" else x for k, x in more.items()}
+    tgt = gpu_target(w)
+    turns = gpu_run(w, tgt=tgt, **more)
+    assert turns[3]["grid_blocks"] * 4 < chains, "every chain has a slot: nothing takes turns"
+    assert turns[2].sum(0).mean() > 2 * 256, "too few steps for turns"
+    kept = gpu_run(w, tgt=tgt, schedule=1, **more)                # a launch per iteration: no turns
+    for k in range(3):
+        assert np.array_equal(turns[k], kept[k])
+    assert turns[3]["leaf_slots_useful"] == turns[2].sum() and turns[3]["extra_grad_evals"] == chains
+    again = gpu_run(w, tgt=tgt, n_chains=9, **more)               # a slot each
+    for k in range(3):
+        assert np.array_equal(again[k], turns[k][:, :9])
+
+
 # rows at the edges of a tile of 16, of the eight sums and of the pairs of tiles (the last of a wave's tiles alone, ragged, or with a
 # ragged one beside it), on either side of 64 tiles per sum; features at the edges of the feature tiles, with and without a
 # constant column, where operands are asked for a tile and half a tile ahead
