@@ -39,44 +39,32 @@ struct DenseGradient {
         }
     }
 
-    // Banded: components 2*lane - 4 .. 2*lane + 5 (the buffer has kBandHalf zeros on either side), and the gradient from them.
-    __device__ __forceinline__ void neighbours(const T (&th)[2], T (&x)[2 * kBandHalf + 2]) const
-    {
-        *reinterpret_cast<Vec*>(bcast + 2 * lane) = Vec{th[0], th[1]};
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int u = 0; u < kBandHalf + 1; ++u) {
-            const Vec p = *reinterpret_cast<const Vec*>(bcast + 2 * lane - kBandHalf + 2 * u);
-            x[2 * u] = p.x;
-            x[2 * u + 1] = p.y;
-        }
-        __builtin_amdgcn_wave_barrier();
-    }
-    __device__ __forceinline__ double banded(const T (&th)[2], const T (&x)[2 * kBandHalf + 2], T (&g)[2]) const
-    {
-        double acc0 = 0.0, acc1 = 0.0;
-#pragma unroll
-        for (int k = 0; k < 2 * kBandHalf + 1; ++k) {
-            acc0 = fma((double)band0[k], (double)x[k], acc0);
-            acc1 = fma((double)band1[k], (double)x[k + 1], acc1);
-        }
-        g[0] = (T)(-acc0);
-        g[1] = (T)(-acc1);
-        return fma((double)th[0], -acc0, (double)th[1] * -acc1);
-    }
-
     // g = -P theta; returns the partial sum of theta_i g_i of this lane (logp is half the wave's total).  Columns are
     // taken in ascending order with a binary64 accumulator.
     __device__ __forceinline__ double operator()(const T (&th)[2], T (&g)[2]) const
     {
-        if (kBanded) {
-            T x[2 * kBandHalf + 2];
-            neighbours(th, x);
-            return banded(th, x, g);
-        }
         *reinterpret_cast<Vec*>(bcast + 2 * lane) = Vec{th[0], th[1]};
         __builtin_amdgcn_wave_barrier();
         double acc0 = 0.0, acc1 = 0.0;
+        if (kBanded) {
+            // components 2*lane - 4 .. 2*lane + 5 (the buffer has kBandHalf zeros on either side)
+            T x[2 * kBandHalf + 2];
+#pragma unroll
+            for (int u = 0; u < kBandHalf + 1; ++u) {
+                const Vec p = *reinterpret_cast<const Vec*>(bcast + 2 * lane - kBandHalf + 2 * u);
+                x[2 * u] = p.x;
+                x[2 * u + 1] = p.y;
+            }
+#pragma unroll
+            for (int k = 0; k < 2 * kBandHalf + 1; ++k) {
+                acc0 = fma((double)band0[k], (double)x[k], acc0);
+                acc1 = fma((double)band1[k], (double)x[k + 1], acc1);
+            }
+            __builtin_amdgcn_wave_barrier();
+            g[0] = (T)(-acc0);
+            g[1] = (T)(-acc1);
+            return fma((double)th[0], -acc0, (double)th[1] * -acc1);
+        }
         const T* row = mat + 2 * lane;
         // columns in batches of 20 so that the LDS reads of a batch are all in flight together
         constexpr int kBatch = 20;
@@ -141,56 +129,15 @@ __global__ __launch_bounds__(kDenseWaves* kWave, sizeof(T) == 8 && !kBanded ? 1 
             ch.iter_begin();
             do {
                 ch.double_begin();
-                if constexpr (kBanded) {
-                    // The first leapfrog step of the next leaf is taken while this leaf is being judged (it is lost at a doubling's end): its
-                    // LDS reads under the sums over the wave, its products between the steps of the exponential.  d = 100, 1024
-                    // chains, 100 iterations 9.10 -> 8.98 ms (without the asm below the compiler moves the products to where they are
-                    // used, after the merges: 9.23); what is left of a step, two thirds, are the merges, of which there is one a leaf.
-                    ch.kick_drift();
-                    double lp = grad(ch.th, ch.g);
-                    ch.kick();
-                    for (;;) {
-                        for (int step = 1; step < sa.leaf_steps; ++step) {
-                            ch.kick_drift();
-                            lp = grad(ch.th, ch.g);
-                            ch.kick();
-                        }
-                        const T half = (T)(0.5 * (ch.v * sa.eps)), full = (T)(ch.v * sa.eps);
-                        T th[2], r[2], g[2], x[2 * kBandHalf + 2];
-                        double lp_next;
-                        const bool more = ch.finish_leaf(
-                            lp,
-                            [&]() __attribute__((always_inline)) {
-#pragma unroll
-                                for (int i = 0; i < 2; ++i) {
-                                    r[i] = ch.r[i] + half * ch.g[i];
-                                    th[i] = ch.th[i] + full * r[i];
-                                }
-                                grad.neighbours(th, x);
-                            },
-                            [&]() __attribute__((always_inline)) {
-                                lp_next = grad.banded(th, x, g);
-#pragma unroll
-                                for (int i = 0; i < 2; ++i) r[i] = r[i] + half * g[i];
-                                asm volatile("" : "+v"(lp_next), "+v"(r[0]), "+v"(r[1]), "+v"(g[0]), "+v"(g[1]));  // (here, not where they are used)
-                            });
-                        if (!more) break;
-                        ch.copy(ch.th, th);
-                        ch.copy(ch.r, r);
-                        ch.copy(ch.g, g);
-                        lp = lp_next;
+                double lp;
+                do {
+                    for (int step = 0;;) {
+                        ch.kick_drift();
+                        lp = grad(ch.th, ch.g);
+                        ch.kick();
+                        if (++step >= sa.leaf_steps) break;
                     }
-                } else {
-                    double lp;
-                    do {
-                        for (int step = 0;;) {
-                            ch.kick_drift();
-                            lp = grad(ch.th, ch.g);
-                            ch.kick();
-                            if (++step >= sa.leaf_steps) break;
-                        }
-                    } while (ch.finish_leaf(lp));
-                }
+                } while (ch.finish_leaf(lp));
             } while (ch.double_end());
         } while (ch.iter_end());
     }

@@ -129,8 +129,6 @@ struct RowChain {
     uint32_t dirbits = 0;
     int u_sub_leaf = 0, u_sub_base = 0;
     int cur_s = 0, cur_idx = kInEdge;
-    double leaf_delta = 0;   // of the leaf being finished: its energy error,
-    bool pair_ok = false;    // and whether its span with the leaf before it has not turned
     double frame_w = 0, pool_logp = 0;  // lane k: level k / pool buffer k
     int frame_idx = 0;
     unsigned long long n_leaf = 0, n_extra = 0;
@@ -519,7 +517,7 @@ struct RowChain {
     }
 
     // One subtree's halves become one: weights added, proposal selected, U-turn test over its span (of two leaves: pair_ok).
-    __device__ __forceinline__ void merge(int level)
+    __device__ __forceinline__ void merge(int level, bool pair_ok)
     {
         T xt[kVpl], xr[kVpl];
         if (level > 1) {
@@ -558,50 +556,15 @@ struct RowChain {
     // completes.  True if the doubling wants another leaf.
     __device__ __forceinline__ bool finish_leaf(double lp)
     {
-        finish_sums(lp, [] {});
-        if (sa.sampler == kSamplerSlice)
-            slice_weight();
-        else
-            multinomial_weight();
-        return finish_merges();
-    }
-    // The same with work that depends on none of it beside its two serial chains, the sums over the wave and the exponential, where
-    // a lone wave would wait for one instruction after the other: `ask` with the first, `answer` with the second.
-    template <typename A, typename B>
-    __device__ __forceinline__ bool finish_leaf(double lp, A&& ask, B&& answer)
-    {
-        finish_sums(lp, ask);
-        const double e = log_unit_w - leaf_delta;
-        double w = exp_bounded(e);
-        answer();
-        asm volatile("" : "+v"(w));  // (here, although the slice sampler has no use for it)
-        cur_w = w;
-        if (sa.sampler == kSamplerSlice) {
-            slice_weight();
-        } else {
-            if (agreed(e > 600.0)) {
-                new_unit(e);
-                cur_w = 1.0;
-            }
-            cur_s = agreed(leaf_delta <= kDeltaMax);
-        }
-        return finish_merges();
-    }
-
-    template <typename A>
-    __device__ __forceinline__ void finish_sums(double lp, A&& meanwhile)
-    {
         double kin = 0.0;
 #pragma unroll
         for (int i = 0; i < kVpl; ++i) kin = fma((double)r[i], (double)r[i], kin);
         m += 1;
         // An even leaf, if it is valid, is merged with the one before it: that span's two sums go with the leaf's own.
-        pair_ok = false;
+        bool pair_ok = false;
         if (m & 1) {
-            meanwhile();
             wave_sum2(lp, kin);
         } else {
-            meanwhile();
             double da, db;
             span_dots(pth, pr, da, db);
             const double x = wave_sum_rows(lp, kin, da, db);
@@ -611,34 +574,23 @@ struct RowChain {
         edge_logp = 0.5 * lp;
         nleap += sa.leaf_steps;
         n_leaf += sa.leaf_steps;
-        leaf_delta = (-edge_logp + 0.5 * kin) - H0;
-        if (!(fabs(leaf_delta) < INFINITY)) leaf_delta = INFINITY;
-    }
-    __device__ __forceinline__ void slice_weight()
-    {
-        cur_w = (log_slice <= -leaf_delta) ? 1.0 : 0.0;
-        cur_s = agreed(log_slice < kDeltaMax - leaf_delta);
-    }
-    // The energy has fallen far: this leaf becomes the unit (e: logarithm of its weight in the unit until now).
-    __device__ __forceinline__ void new_unit(double e)
-    {
-        const double shrink = exp_bounded(-e);
-        w_tree *= shrink;
-        frame_w *= shrink;
-        log_unit_w = leaf_delta;
-    }
-    __device__ __forceinline__ void multinomial_weight()
-    {
-        double e = log_unit_w - leaf_delta;  // logarithm of the leaf's weight in the current unit
-        if (agreed(e > 600.0)) {
-            new_unit(e);
-            e = 0.0;
+        double delta = (-edge_logp + 0.5 * kin) - H0;
+        if (!(fabs(delta) < INFINITY)) delta = INFINITY;
+        if (sa.sampler == kSamplerSlice) {
+            cur_w = (log_slice <= -delta) ? 1.0 : 0.0;
+            cur_s = agreed(log_slice < kDeltaMax - delta);
+        } else {
+            double e = log_unit_w - delta;  // logarithm of the leaf's weight in the current unit
+            if (agreed(e > 600.0)) {  // the energy has fallen far: this leaf becomes the unit
+                const double shrink = exp_bounded(-e);
+                w_tree *= shrink;
+                frame_w *= shrink;
+                log_unit_w = delta;
+                e = 0.0;
+            }
+            cur_w = exp_bounded(e);
+            cur_s = agreed(delta <= kDeltaMax);
         }
-        cur_w = exp_bounded(e);
-        cur_s = agreed(leaf_delta <= kDeltaMax);
-    }
-    __device__ __forceinline__ bool finish_merges()
-    {
         cur_idx = kInEdge;
         if (!cur_s) return false;
         const int n_done = __ffs(m) - 1;  // levels that this leaf completes
@@ -654,7 +606,7 @@ struct RowChain {
             if (s >= 2) first_store(s, th, r);
         } else {
             for (int level = 1; level <= n_done; ++level) {
-                merge(uni(level));
+                merge(uni(level), pair_ok);
                 if (!cur_s) return false;
             }
             if (n_done == j) return false;
