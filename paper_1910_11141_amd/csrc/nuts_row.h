@@ -111,6 +111,7 @@ struct RowChain {
     T th[kVpl], r[kVpl], g[kGrad ? kVpl : 1];     // the end of the trajectory that the current doubling extends
     T pth[kVpl], pr[kVpl], pg[kGrad ? kVpl : 1];  // the last odd leaf, until the leaf after it has been merged with it
     T rest[kHeld ? kRowRest : 1][kHeld ? kVpl : 1];
+    static constexpr uint32_t kNoSeveral = 1u << 31;  // (no iteration follows it)
     static constexpr int kInEdge = -1, kInPrev = -2;  // cur_idx / frame_idx: the proposal is th, or pth
 
     int j = 0, m = 0, v = 0, nleap = 0, iter = 0;  // v: direction of the end in th (0: both ends are the same point)
@@ -136,6 +137,8 @@ struct RowChain {
     double kin_next = 0, u_top_next = 0, log_slice_next = 0;
     uint32_t dirbits_next = 0;
     int ahead = -1;
+    T several[2] = {};             // momenta of the iterations from several_from on (draw_momentum)
+    uint32_t several_from = kNoSeveral;
     unsigned* const turns;   // NULL: no turns
     unsigned turn_from = 0;  // n_leaf when the slot took its chain
 
@@ -245,6 +248,32 @@ struct RowChain {
         }
     }
 
+    // Momenta.  Of up to 32 components one pass of the generator, and the logarithm, root, sine and cosine after it, serves 64 / n
+    // iterations, n the power of two from the number of pairs on: lane n k + p makes pair p of the k-th one.  d = 2, 4 chains, 100 iterations
+    // 584 -> 530 us.  (Kernels that hold a gradient have no scalar registers for it: d = 100 banded 1.02 times as long.)
+    __device__ __forceinline__ void draw_momentum(uint32_t iteration, T (&out)[kVpl])
+    {
+        if constexpr (kC > 1 || kGrad) {
+            draw_normals(kDrawMomentum, iteration, out);
+        } else {
+            const int pairs = (d + 1) >> 1, shift = pairs > 1 ? 32 - __builtin_clz(pairs - 1) : 0, per = kWave >> shift;
+            if (iteration - several_from >= (unsigned)per) {
+                const int p = lane & ((1 << shift) - 1);
+                double z0, z1;
+                normal_pair(draw(key(), (uint32_t)p, kDrawMomentum, 0, iteration + (uint32_t)(lane >> shift), gchain), z0, z1);
+                several[0] = p < pairs ? (T)z0 : T(0);
+                several[1] = 2 * p + 1 < d ? (T)z1 : T(0);
+                several_from = iteration;
+            }
+            const int from = lane < pairs ? ((int)(iteration - several_from) << shift) + lane : 0;
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const T x = __shfl(several[e], from, kWave);
+                out[e] = lane < pairs ? x : T(0);
+            }
+        }
+    }
+
     __device__ uint32_t all_bufs() const { return (1u << (D + 1)) - 1u; }
     // The current proposal gets a pool buffer, unless it has one.
     __device__ __forceinline__ void materialise_cur()
@@ -294,6 +323,7 @@ struct RowChain {
         gchain = (uint32_t)(sa.first_chain + chain);
         iter = sa.iter_begin;
         ahead = -1;
+        several_from = kNoSeveral;
         if (sa.init_states) {
             const T* src = (const T*)sa.init_states + (size_t)chain * d;
 #pragma unroll
@@ -399,6 +429,7 @@ struct RowChain {
         chain = turn_plan().first + (long)taken - 1;
         gchain = (uint32_t)(sa.first_chain + chain);
         ahead = -1;
+        several_from = kNoSeveral;
         const unsigned long long* row = turn_row();
         T x[kVpl];
         turn_got(row, x);
@@ -429,9 +460,9 @@ struct RowChain {
         n_extra += 1;
     }
 
-    __device__ __forceinline__ void draw_iteration(int it, T (&momentum)[kVpl], double& kin, double& tops, double& slice, uint32_t& dirs) const
+    __device__ __forceinline__ void draw_iteration(int it, T (&momentum)[kVpl], double& kin, double& tops, double& slice, uint32_t& dirs)
     {
-        draw_normals(kDrawMomentum, (uint32_t)it, momentum);
+        draw_momentum((uint32_t)it, momentum);
         kin = 0.0;
 #pragma unroll
         for (int i = 0; i < kVpl; ++i) kin = fma((double)momentum[i], (double)momentum[i], kin);

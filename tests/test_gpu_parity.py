@@ -1643,6 +1643,19 @@ def test_chains_have_the_same_bits_in_either_lock_step_form_where_rounding_decid
         assert differ.sum() == 0, f"{differ.sum()} of {differ.size} values differ"
 
 
+# One pass of the generator makes the momenta of 64 / n iterations (n: pairs of components, up to a power of two): dimensions at the edges of
+# n, iterations beyond one pass.
+@pytest.mark.parametrize("dim,dtype", [(1, np.float64), (2, np.float64), (3, np.float32), (4, np.float64), (5, np.float64), (9, np.float32), (17, np.float64),
+                                       (32, np.float64), (33, np.float64), (64, np.float32), (65, np.float64), (128, np.float64)])
+def test_momenta_made_for_several_iterations_at_once(dim, dtype):
+    sig = 10.0 ** np.linspace(-0.3, 0.3, dim)
+    w = W.Workload("several", W.GAUSS_DIAG, dim, np.dtype(dtype), 5, 131, 0.3, 4, seed=23, scales=sig)
+    g = gpu_run(w)
+    assert_parity(g, ref_run(w), F64_TOL if dtype == np.float64 else F32_TOL, exact_ints=dtype == np.float64, label=f"several {dim}")
+    for x, y in zip(gpu_run(w, schedule=1)[:3], g[:3]):           # a launch per iteration: a pass each
+        assert np.array_equal(x, y)
+
+
 # More chains than slots, iterations and steps enough for several turns: element-wise, dense and banded kernels, with vectors held in registers
 # and in memory, ragged dimensions, chains that all take turns (up to eight per slot) and chains of which only the last do.
 @pytest.mark.parametrize("kind,dim,dtype,chains,iters,eps,more", [
