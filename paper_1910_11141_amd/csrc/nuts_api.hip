@@ -115,7 +115,7 @@ struct nuts_target {
     unsigned* chip_state = nullptr;     // chip kernel: pinned, how the last run ended
     int chip_most = 0;                  // chip kernel: the most workgroups of the call's further launches, 0: no bound
     int chip_refuse = 0, chip_bound = 0;  // nuts_debug_chip_starts
-    bool wide_apart = false;              // nuts_debug_wide_apart
+    int wide_apart = 0;                   // nuts_debug_wide_apart
     int* halted_host = nullptr;         // grid kernels: pinned, two snapshots of the "halted" flags
     hipEvent_t ev_batch[2 * nuts::kGridMaxStreams] = {};  // [snapshot][stream]
     bool has_run = false;
@@ -437,7 +437,12 @@ __global__ void zero_counters_kernel(unsigned long long* c, int words)
 // busiest of them works, so that many slots x its gradient count were issued; the chain queue restarts.
 __global__ void close_launch_kernel(unsigned long long* c, unsigned long long slots, int words)
 {
-    for (int i = threadIdx.x; i < words; i += blockDim.x) reinterpret_cast<unsigned*>(c + nuts::kCtrCount)[i] = 0u;
+    for (int i = threadIdx.x; i < words; i += blockDim.x) {
+        unsigned* const word = reinterpret_cast<unsigned*>(c + nuts::kCtrCount) + i;
+        if ((*word & nuts::kMeetBoth) == nuts::kMeetBoth && !(*word & nuts::kMeetAlone)) atomicAdd(&c[nuts::kCtrPairsMet], 1ull);
+        if (*word & nuts::kMeetLost) atomicAdd(&c[nuts::kCtrPairsLost], 1ull);
+        *word = 0u;
+    }
     if (threadIdx.x == 0) {
         c[nuts::kCtrIssued] += slots * c[nuts::kCtrSlotMax];
         c[nuts::kCtrSlotMax] = 0ull;
@@ -1005,7 +1010,7 @@ int launch_wide(nuts_target* t, nuts::DevSample sa, int nc, int cus)
     sa.workspace = t->ws_cur;
     sa.slot_bytes = block;
     const nuts::WideArgs wa{nuts::tile_args(t->tile, 1.0 / (t->prior_scale * t->prior_scale)), t->tile.ks1, (int)pairs,
-                            reinterpret_cast<unsigned*>(t->counters_cur + nuts::kCtrCount), t->ws_cur + slots, t->wide_apart ? 1 : 0};
+                            reinterpret_cast<unsigned*>(t->counters_cur + nuts::kCtrCount), t->ws_cur + slots, t->wide_apart};
     (t->dtype == NUTS_F64 ? nuts::wide_launch_f64 : nuts::wide_launch_f32)(wa, sa, nc, (int)blocks, g_stream);
     HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
     t->last_variant = NUTS_VARIANT_TILE;
@@ -1150,11 +1155,24 @@ int nuts_debug_chip_starts(nuts_target* t, int refused, int most_blocks)
     return NUTS_OK;
 }
 
-// For tests: the wide kernel's pairs of workgroups do not meet; the first takes all rows.
+// For tests: 1: the wide kernel's pairs of workgroups do not meet, the first takes all rows; 2 or 3: the first or the second of them
+// sends nothing from its third round on, and the other waits 0.2 ms for it; 0: as ever.
 int nuts_debug_wide_apart(nuts_target* t, int apart)
 {
-    if (!t) return fail(NUTS_E_INVALID_ARG, "nuts_debug_wide_apart: bad argument");
-    t->wide_apart = apart != 0;
+    if (!t || apart < 0 || apart > 3) return fail(NUTS_E_INVALID_ARG, "nuts_debug_wide_apart: bad argument");
+    t->wide_apart = apart;
+    return NUTS_OK;
+}
+
+// For tests, of the last call on a target: pairs of the wide kernel's workgroups that met, and of these the ones of which one went on alone.
+int nuts_debug_counts(const nuts_target* t, unsigned long long* pairs_met, unsigned long long* pairs_lost)
+{
+    if (!t || !pairs_met || !pairs_lost || !t->has_run) return fail(NUTS_E_INVALID_ARG, "nuts_debug_counts: bad argument");
+    HIP_TRY(hipEventSynchronize(t->ev_stop), NUTS_E_DEVICE);
+    unsigned long long c[nuts::kCtrCount];
+    HIP_TRY(hipMemcpy(c, t->counters_cur, sizeof(c), hipMemcpyDeviceToHost), NUTS_E_DEVICE);
+    *pairs_met = c[nuts::kCtrPairsMet];
+    *pairs_lost = c[nuts::kCtrPairsLost];
     return NUTS_OK;
 }
 

@@ -69,7 +69,8 @@ enum : int {
     kCtrQueue = 0, kCtrIssued = 1, kCtrUseful = 2, kCtrExtra = 3, kCtrRounds = 4,
     kCtrCycControl = 5, kCtrCycGrad = 6, kCtrCycPost = 7,  // shader-clock ticks, summed over workgroups
     kCtrSlotMax = 8,  // wave and element-wise kernels: most gradient evaluations done by one slot in this launch
-    kCtrCount = 9
+    kCtrPairsMet = 9, kCtrPairsLost = 10,  // wide kernel, divided rows: groups whose workgroups met, and that one of them went on with alone
+    kCtrCount = 11
 };
 
 // Program points of one chain.  This is the NUTS recursion written in the

@@ -91,7 +91,7 @@ struct WideArgs {
     int n_pairs;
     unsigned* meet;
     char* exchange;
-    int apart;  // (for tests: the second of two workgroups behaves as if it had come too late)
+    int apart;  // (for tests) 1: the second of two workgroups behaves as if it had come too late; 2 + h: half h sends nothing after its third round
 };
 
 // Exchange between the two workgroups of a group of chains: [half][parity of the round][wave][vector][lane]{low, tag, high, tag}, a
@@ -99,12 +99,15 @@ struct WideArgs {
 __host__ __device__ constexpr int wide_exchange_half(int mt) { return 2 * (kTileWaves / 2) * (mt + 1) * kWave * 16; }  // bytes
 constexpr int kWideAgent = 16;                       // cache policy of a buffer instruction: agent scope (sc1)
 constexpr long long kWideMeetLimit = 20000;          // 0.2 ms (100 MHz)
+constexpr int kWideLost = 256;
 constexpr long long kWideLostLimit = 6000000000ll;   // 60 s
-enum : unsigned { kMeetAlone = 4u };                 // beside bit h: half h has come
+enum : unsigned { kMeetBoth = 3u, kMeetAlone = 4u, kMeetLost = 8u };  // bit h: half h has come
 
 // A workgroup that waits for its partner must have it resident: each announces itself before anything is done, and one whose
 // partner has not come within 0.2 ms (a device or a mask of compute units without room for both) takes the whole group's rows, part
-// after part; the partner, when it starts, finds that and returns.  Two that have met are both running and stay so.
+// after part; the partner, when it starts, finds that and returns.  Two that have met are both running and stay so.  Should one wait
+// for the other's sums beyond kWideLostLimit all the same, the first half begins again and takes all rows, and the second ends: no wait is
+// without an end, and the call returns the same bits.
 //
 // The other half of the group: true if it has come, and both go on together; false if this one goes on alone (`late`: not at
 // all, the other one has gone on alone).
@@ -176,7 +179,7 @@ __global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) voi
     __shared__ double sLL[kTileWaves][NC];
     __shared__ double sHalfCol[S::kResidual ? 1 : 16 * MT];  // column sums of X~, halved
     __shared__ __align__(16) double sSpread[kSplit ? S::kWaves : 1][S::kTilesAtOnce][kSplit ? kWave : 1];
-    __shared__ int sHalted, sMeet, sLost;
+    __shared__ int sHalted, sMeet;  // sHalted: chains that have halted; from kWideLost on: sums were missing
     __shared__ __align__(16) double sFtab[S::kTab];
     const double* const log_tab = sFtab + S::kTab - kLogTabDoubles;
     __shared__ T sPool[NC][kLP > 0 ? kLP : 1][2][kLP > 0 ? kVec : 1];
@@ -245,7 +248,7 @@ __global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) voi
     for (int i = tid; i < S::kTab; i += kThreads) sFtab[i] = ta.ftab[kFtabDoubles + kLogTabDoubles - S::kTab + i];
     for (int i = tid; i < NC * S::kPitch; i += kThreads) (&sTheta[0][0])[i] = 0.0;
     for (int i = tid; i < (S::kResidual ? 0 : 16 * MT); i += kThreads) sHalfCol[i] = 0.5 * ta.colsum[i];
-    if (tid == 0) sHalted = 0, sLost = 0;
+    if (tid == 0) sHalted = 0;
     constexpr int kHalfBytes = wide_exchange_half(MT);
     const __amdgpu_buffer_rsrc_t other_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         wa.exchange + (size_t)(2 * pair + (1 - half_id)) * kHalfBytes, 0, kSplit ? kHalfBytes : 0, 0x00020000);
@@ -260,8 +263,8 @@ __global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) voi
         __syncthreads();
         if (tid == 0) {
             bool late = false;
-            const bool both = !wa.apart && wide_meet(wa.meet + pair, half_id, late);
-            sMeet = (wa.apart ? half_id == 1 : late) ? 2 : both ? 1 : 0;
+            const bool apart = wa.apart == 1, both = !apart && wide_meet(wa.meet + pair, half_id, late);
+            sMeet = (apart ? half_id == 1 : late) ? 2 : both ? 1 : 0;
         }
         __syncthreads();
         const int met = uni(sMeet);
@@ -271,8 +274,8 @@ __global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) voi
         __syncthreads();
     }
     const bool lead = !kSplit || alone || half_id == 0;  // writes what the call returns
-    const int first_part = alone ? 0 : half_id, last_part = kSplit && alone ? 1 : first_part;
     unsigned round = 0;
+    const unsigned last_sent = wa.apart == 2 + half_id ? 3u : ~0u;  // (rounds beyond it are sent with its number)
 
     // where component i goes in the first GEMM's contraction (see feat1 in tile_pack_operands)
     auto slot_of = [&](int i) __attribute__((always_inline)) -> int {
@@ -607,6 +610,7 @@ __global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) voi
             a1[p] = load_at(offset_of(t) + (pairs1 + p) * 1024);
             if (kTwo) b1_[kTwo ? p : 0] = load_at(offset_of(t + kTileWaves) + (pairs1 + p) * 1024);
         };
+        const int first_part = alone ? 0 : half_id, last_part = kSplit && alone ? 1 : first_part;
         if (kSplit) {
             ask_first(first_part * S::kWaves + wave);
             ask_second(first_part * S::kWaves + wave);
@@ -621,8 +625,27 @@ __global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) voi
             }
         }
         tile_lds_barrier();
-        if (*const_cast<volatile int*>(&sHalted) == NC) break;  // every chain of the workgroup has halted
-        if (kSplit && *const_cast<volatile int*>(&sLost)) break;
+        // (scalar branches: what follows a vector one in the loop over rounds is taken to differ from lane to lane, and every load of operands then
+        // becomes a loop over its addresses, 1.35 to 1.57 times the time)
+        const int halted = kSplit ? uni(*const_cast<volatile int*>(&sHalted)) : *const_cast<volatile int*>(&sHalted);
+        if (kSplit && __builtin_expect(halted >= kWideLost, 0)) {  // (before anything else: the last round's sums were not all there)
+            tile_lds_barrier();
+            if (half_id == 1) break;
+            if (tid == 0) {
+                sHalted = 0;
+                atomicOr(wa.meet + pair, (unsigned)kMeetLost);
+            }
+            tile_lds_barrier();
+            alone = true;
+            if (owns) c.pc = kPcFetch;  // (what a chain that is fetched does not set itself)
+            c.ret = 0;
+            c.sub = 0;
+            taken = false;
+            n_leaf = n_rounds = 0;
+            n_extra = 0;
+            continue;
+        }
+        if (kSplit ? __builtin_expect(halted == NC, 0) : halted == NC) break;  // every chain of the workgroup has halted
         n_rounds += 1;
         round += 1;
         const long long t1 = clock64();
@@ -882,8 +905,9 @@ __global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) voi
                 // than a round ahead of the other.
                 if (!alone) {
                     const int at = (((int)(round & 1) * S::kWaves + wave) * (MT + 1)) * kWave * 16;
+                    const unsigned tag = min(round, last_sent);
                     auto send = [&](double v, int i) __attribute__((always_inline)) {
-                        const v4u w{(unsigned)__double2loint(v), round, (unsigned)__double2hiint(v), round};
+                        const v4u w{(unsigned)__double2loint(v), tag, (unsigned)__double2hiint(v), tag};
                         __builtin_amdgcn_raw_buffer_store_b128(w, own_rsrc, lane * 16, at + i * kWave * 16, kWideAgent);
                     };
 #pragma unroll
@@ -900,11 +924,11 @@ __global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) voi
 #pragma unroll
                         for (int i = 0; i <= MT; ++i) there = there && in[i][1] == round && in[i][3] == round;
                         if (__all(there)) break;
-                        if ((looks & 255) == 0) {  // (no wait is without an end)
+                        if (__builtin_expect((looks & 255) == 0, 0)) {
                             const long long now = wall_clock64();
                             if (t0 == 0) t0 = now;
-                            if (now - t0 > kWideLostLimit) {
-                                sLost = 1;
+                            if (now - t0 > (wa.apart >= 2 ? kWideMeetLimit : kWideLostLimit)) {
+                                atomicOr(&sHalted, kWideLost);
                                 break;
                             }
                         }
@@ -1001,8 +1025,6 @@ __global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) voi
         cyc_post += clock64() - t2;
     }
 
-    if (kSplit && sLost && lead && owns && k == 0 && c.pc != kPcHalt && sa.out_depths)  // (it shows: no tree has this depth)
-        sa.out_depths[(size_t)c.iter * (size_t)sa.n_chains + (size_t)(c.gchain - (uint32_t)sa.first_chain)] = -1;
     if (!lead) return;
     if (owns && k == 0) {
         atomicAdd(&sa.counters[kCtrUseful], n_leaf);

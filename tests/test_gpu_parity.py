@@ -1713,6 +1713,25 @@ def test_rows_divided_between_two_workgroups_give_the_same_bits(n_data, dim, dty
     assert_parity(pairs, ref_run(w), F64_TOL if dtype == np.float64 else F32_TOL, exact_ints=dtype == np.float64, label="rows divided")
 
 
+@pytest.mark.parametrize("silent", [2, 3])                        # the first half stops sending, the second half
+@pytest.mark.parametrize("n_data,dim,dtype", [(1000, 25, np.float64), (1137, 9, np.float32), (1263, 65, np.float64)])
+def test_a_workgroup_whose_partner_falls_silent_goes_on_alone(n_data, dim, dtype, silent):
+    import ctypes as C
+    w = W.small_logreg(n_data, dim, seed=dim, dtype=dtype)
+    w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = 11, 4, 0.7 / np.sqrt(n_data), 5
+    tgt, B = gpu_target(w), N()
+    pairs = gpu_run(w, tgt=tgt)
+    met, lost = C.c_uint64(), C.c_uint64()
+    B._check(B.lib().nuts_debug_counts(tgt.handle, C.byref(met), C.byref(lost)))
+    assert met.value == 3 and lost.value == 0
+    B._check(B.lib().nuts_debug_wide_apart(tgt.handle, C.c_int(silent)))
+    alone = gpu_run(w, tgt=tgt)
+    B._check(B.lib().nuts_debug_counts(tgt.handle, C.byref(met), C.byref(lost)))
+    assert met.value == 3 and lost.value == 3
+    for x, y in zip(alone[:3], pairs[:3]):
+        assert np.array_equal(x, y)
+
+
 @pytest.mark.parametrize("n_data,dim", [(37, 33), (300, 100), (2000, 60), (5000, 40)])
 def test_wide_kernel_gradients_are_as_exact_as_the_general_kernels(n_data, dim):
     """One leaf of 64 leapfrog steps from points near the posterior, against the same steps in extended precision (64-bit
