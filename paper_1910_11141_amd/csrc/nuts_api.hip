@@ -102,6 +102,9 @@ struct nuts_target {
     // per-call scratch, grown on demand and kept
     char* workspace = nullptr;
     size_t workspace_bytes = 0;
+    size_t workspace_refused = SIZE_MAX;  // least size that a call did without because it could not be allocated
+    size_t workspace_most = SIZE_MAX;     // nuts_debug_workspace
+    int workspace_refusals = 0;           // (how often an allocation was asked for in vain)
     unsigned long long* counters = nullptr;
     // where the call in progress keeps its workspace and counters: the target's own allocations, or the
     // device's static scratch array (nuts_sample_static)
@@ -382,6 +385,13 @@ int ensure_device(nuts_target* t)
     return NUTS_OK;
 }
 
+hipError_t workspace_alloc(nuts_target* t, char** p, size_t bytes)
+{
+    const hipError_t e = bytes > t->workspace_most ? hipErrorOutOfMemory : hipMalloc((void**)p, bytes);
+    if (e != hipSuccess) t->workspace_refusals += 1;
+    return e;
+}
+
 int ensure_workspace(nuts_target* t, size_t bytes)
 {
     if (t->static_call) {  // no allocation: the workspace is the device's static array, or the call is refused
@@ -399,10 +409,52 @@ int ensure_workspace(nuts_target* t, size_t bytes)
         t->workspace = nullptr;
         t->workspace_bytes = 0;
     }
-    HIP_TRY(hipMalloc((void**)&t->workspace, bytes), NUTS_E_ALLOC);
+    HIP_TRY(workspace_alloc(t, &t->workspace, bytes), NUTS_E_ALLOC);
     t->workspace_bytes = bytes;
+    t->workspace_refused = SIZE_MAX;
     t->ws_cur = t->workspace;
     return NUTS_OK;
+}
+
+// Nothing can be allocated while a graph is captured (nor where that cannot be found out: another stream of the process is capturing).
+bool stream_captures()
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(g_stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+// For runs that are faster with a workspace of `most` bytes and do with `least`: *has says which of them there is.  An allocation that was
+// refused is not tried again before the workspace has grown, and costs the workspace that is there only if that would not do either.
+int ensure_workspace_or(nuts_target* t, size_t least, size_t most, bool* has)
+{
+    *has = !t->static_call && most <= t->workspace_bytes;
+    if (!*has && !t->static_call && most < t->workspace_refused && !stream_captures()) {
+        if (least <= t->workspace_bytes) {
+            char* larger = nullptr;
+            if (workspace_alloc(t, &larger, most) == hipSuccess) {
+                if (hipDeviceSynchronize() != hipSuccess) {
+                    (void)hipFree(larger);
+                    return fail(NUTS_E_DEVICE, "hipDeviceSynchronize failed");
+                }
+                (void)hipFree(t->workspace);
+                t->workspace = larger;
+                t->workspace_bytes = most;
+                t->workspace_refused = SIZE_MAX;
+                *has = true;
+            }
+        } else {
+            const int rc = ensure_workspace(t, most);
+            if (rc != NUTS_OK && rc != NUTS_E_ALLOC) return rc;
+            *has = rc == NUTS_OK;
+        }
+        if (!*has) {
+            (void)hipGetLastError();
+            t->workspace_refused = most;
+        }
+    }
+    return ensure_workspace(t, *has ? most : least);
 }
 
 // The logistic table of the grid kernels' weight merges.  Built when the target is created; never by nuts_sample_static.
@@ -994,19 +1046,20 @@ int launch_wide(nuts_target* t, nuts::DevSample sa, int nc, int cus)
     const size_t block = nuts::wide_block_bytes((int)t->dim, t->dtype == NUTS_F64 ? 8 : 4, nc, sa.max_depth);
     long blocks = (sa.n_chains + nc - 1) / nc;
     if (blocks > cus) blocks = cus;  // one workgroup per compute unit; further chains wait in the queue
-    // (nuts_sample_static has no words for pairs to meet at)
-    const bool split = !t->static_call && nc == 4 && blocks <= nuts::kWideMaxPairs && nuts::wide_split_pays(sa.n_chains, cus, t->n);
-    const long pairs = split ? blocks : 0;
-    if (split) blocks *= 2;
     if (t->static_call) {
         int rc = tile_eligible(t, sa.max_depth) ? NUTS_OK : static_check(t, sa);
         if (rc) return rc;
         const long fit = (long)(((size_t)NUTS_STATIC_SCRATCH_BYTES - kStaticHeader) / block);
         if (fit >= 1 && blocks > fit) blocks = fit;
     }
-    const size_t slots = (block * (size_t)blocks + 255) & ~(size_t)255;
-    int rc = ensure_workspace(t, slots + (size_t)pairs * 2 * nuts::wide_exchange_half(t->tile.mt));
+    // Divided rows, if the workspace for twice as many workgroups can be had.  (nuts_sample_static has no words for pairs to meet at.)
+    bool split = !t->static_call && nc == 4 && blocks <= nuts::kWideMaxPairs && nuts::wide_split_pays(sa.n_chains, cus, t->n);
+    const size_t slots = (block * (size_t)blocks * (split ? 2 : 1) + 255) & ~(size_t)255;
+    int rc = split ? ensure_workspace_or(t, block * (size_t)blocks, slots + (size_t)blocks * 2 * nuts::wide_exchange_half(t->tile.mt), &split)
+                   : ensure_workspace(t, slots);
     if (rc) return rc;
+    const long pairs = split ? blocks : 0;
+    if (split) blocks *= 2;
     sa.workspace = t->ws_cur;
     sa.slot_bytes = block;
     const nuts::WideArgs wa{nuts::tile_args(t->tile, 1.0 / (t->prior_scale * t->prior_scale)), t->tile.ks1, (int)pairs,
@@ -1161,6 +1214,17 @@ int nuts_debug_wide_apart(nuts_target* t, int apart)
 {
     if (!t || apart < 0 || apart > 3) return fail(NUTS_E_INVALID_ARG, "nuts_debug_wide_apart: bad argument");
     t->wide_apart = apart;
+    return NUTS_OK;
+}
+
+// For tests: allocations of more than `most` bytes of workspace are refused from now on (0: only those that the device refuses).
+// *bytes: the workspace that there is; *refusals: how many have been refused.
+int nuts_debug_workspace(nuts_target* t, unsigned long long most, unsigned long long* bytes, int* refusals)
+{
+    if (!t || !bytes || !refusals) return fail(NUTS_E_INVALID_ARG, "nuts_debug_workspace: bad argument");
+    t->workspace_most = most == 0 ? SIZE_MAX : (size_t)most;
+    *bytes = t->workspace_bytes;
+    *refusals = t->workspace_refusals;
     return NUTS_OK;
 }
 

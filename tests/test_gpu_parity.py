@@ -1713,6 +1713,71 @@ def test_rows_divided_between_two_workgroups_give_the_same_bits(n_data, dim, dty
     assert_parity(pairs, ref_run(w), F64_TOL if dtype == np.float64 else F32_TOL, exact_ints=dtype == np.float64, label="rows divided")
 
 
+def workspace_of(tgt, most=0):
+    """Bytes of workspace and refused allocations so far; from now on those of more than `most` bytes are refused (0: none)."""
+    import ctypes as C
+    size, refusals = C.c_uint64(), C.c_int()
+    N()._check(N().lib().nuts_debug_workspace(tgt.handle, C.c_uint64(most), C.byref(size), C.byref(refusals)))
+    return size.value, refusals.value
+
+
+def captured_run(w, tgt, n_chains, n_iters, between, replays=3):
+    """The same call captured in a graph; outputs of every replay, with `between` run after each."""
+    import torch
+    B, stream = N(), torch.cuda.Stream()
+    tdt = torch.float64 if w.dtype == np.float64 else torch.float32
+    out = (torch.empty((n_iters, n_chains, w.dim), dtype=tdt, device="cuda"), torch.empty((n_iters, n_chains), dtype=torch.int32, device="cuda"),
+           torch.empty((n_iters, n_chains), dtype=torch.int32, device="cuda"))
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    try:
+        with torch.cuda.stream(stream):
+            graph.capture_begin()
+            try:
+                B.nuts_set_stream(stream)
+                B.nuts_sample(tgt, n_chains, n_iters, w.step_size, w.max_tree_depth, w.seed, out=out)
+            finally:
+                graph.capture_end()
+        runs = []
+        for _ in range(replays):
+            for t in out:
+                t.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            runs.append([t.cpu().numpy() for t in out])
+            B.nuts_set_stream(None)
+            between()
+            torch.cuda.synchronize()
+    finally:
+        B.nuts_set_stream(None)
+    return runs
+
+
+def test_rows_stay_whole_where_the_workspace_for_two_workgroups_cannot_be_had():
+    w = W.small_logreg(1000, 20, seed=3)
+    w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = 512, 2, 0.02, 5
+    want = gpu_run(w)
+    assert want[3]["grid_blocks"] == 256                          # two workgroups for every four chains
+    tgt = gpu_target(w)
+    more = gpu_run(w, tgt=tgt, n_chains=1000)                     # (undivided, as there is no room for 500 workgroups)
+    size = workspace_of(tgt, 1)[0]                                # no allocation from here on
+    for calls in (1, 2):
+        got = gpu_run(w, tgt=tgt)
+        assert got[3]["grid_blocks"] == 128
+        assert workspace_of(tgt, 1) == (size, 1)                  # asked for once only, and what is there stays
+        for x, y in zip(got[:3], want[:3]):
+            assert np.array_equal(x, y)
+    workspace_of(tgt, 0)
+    again = lambda: np.testing.assert_array_equal(gpu_run(w, tgt=tgt, n_chains=1000)[0], more[0])
+    for got in captured_run(w, tgt, 512, 2, again):
+        for x, y in zip(got, want[:3]):
+            assert np.array_equal(x, y)
+    fresh = gpu_target(w)                                         # a refusal where there is no workspace yet
+    workspace_of(fresh, size)
+    assert gpu_run(w, tgt=fresh)[3]["grid_blocks"] == 128 and workspace_of(fresh)[1] == 1
+
+
 @pytest.mark.parametrize("silent", [2, 3])                        # the first half stops sending, the second half
 @pytest.mark.parametrize("n_data,dim,dtype", [(1000, 25, np.float64), (1137, 9, np.float32), (1263, 65, np.float64)])
 def test_a_workgroup_whose_partner_falls_silent_goes_on_alone(n_data, dim, dtype, silent):
