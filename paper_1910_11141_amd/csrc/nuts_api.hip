@@ -411,7 +411,7 @@ int ensure_workspace(nuts_target* t, size_t bytes)
     }
     HIP_TRY(workspace_alloc(t, &t->workspace, bytes), NUTS_E_ALLOC);
     t->workspace_bytes = bytes;
-    t->workspace_refused = SIZE_MAX;
+    if (bytes >= t->workspace_refused) t->workspace_refused = SIZE_MAX;
     t->ws_cur = t->workspace;
     return NUTS_OK;
 }
@@ -426,7 +426,7 @@ bool stream_captures()
 }
 
 // For runs that are faster with a workspace of `most` bytes and do with `least`: *has says which of them there is.  An allocation that was
-// refused is not tried again before the workspace has grown, and costs the workspace that is there only if that would not do either.
+// refused is not tried again before one of that size was to be had, and costs the workspace that is there only if that would not do either.
 int ensure_workspace_or(nuts_target* t, size_t least, size_t most, bool* has)
 {
     *has = !t->static_call && most <= t->workspace_bytes;
@@ -441,7 +441,6 @@ int ensure_workspace_or(nuts_target* t, size_t least, size_t most, bool* has)
                 (void)hipFree(t->workspace);
                 t->workspace = larger;
                 t->workspace_bytes = most;
-                t->workspace_refused = SIZE_MAX;
                 *has = true;
             }
         } else {
@@ -632,20 +631,12 @@ int row_workspace(nuts_target* t, nuts::DevSample& sa, size_t slot, long slots, 
         words = ((nuts::kTurnRing + (size_t)ring) * sizeof(unsigned) + 255) & ~(size_t)255;
         rows = (size_t)plan.row_bytes * (size_t)n;
     }
-    if (words && base + words + rows > t->workspace_bytes && base <= t->workspace_bytes) {
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;  // nothing can be allocated while a graph is captured
-        if (hipStreamIsCapturing(g_stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) words = rows = 0;
-    }
-    int rc = ensure_workspace(t, base + words + rows);
-    if (rc == NUTS_E_ALLOC && words) {
-        (void)hipGetLastError();
-        rc = ensure_workspace(t, base);
-        words = 0;
-    }
+    bool has = false;
+    int rc = words ? ensure_workspace_or(t, base, base + words + rows, &has) : ensure_workspace(t, base);
     if (rc) return rc;
     sa.workspace = t->ws_cur;
     sa.slot_bytes = slot;
-    if (words && take) {
+    if (has && take) {
         *turns = reinterpret_cast<unsigned*>(t->ws_cur + base);
         plan.rows = t->ws_cur + base + words;
         hipLaunchKernelGGL(begin_turns_kernel, dim3(1), dim3(1024), 0, g_stream, *turns, plan);

@@ -1656,6 +1656,14 @@ def test_momenta_made_for_several_iterations_at_once(dim, dtype):
         assert np.array_equal(x, y)
 
 
+def workspace_of(tgt, most=0):
+    """Bytes of workspace and refused allocations so far; from now on those of more than `most` bytes are refused (0: none)."""
+    import ctypes as C
+    size, refusals = C.c_uint64(), C.c_int()
+    N()._check(N().lib().nuts_debug_workspace(tgt.handle, C.c_uint64(most), C.byref(size), C.byref(refusals)))
+    return size.value, refusals.value
+
+
 # More chains than slots, iterations and steps enough for several turns: element-wise, dense and banded kernels, with vectors held in registers
 # and in memory, ragged dimensions, chains that all take turns (up to eight per slot) and chains of which only the last do.
 @pytest.mark.parametrize("kind,dim,dtype,chains,iters,eps,more", [
@@ -1682,6 +1690,22 @@ def test_chains_that_take_turns_have_the_bits_of_chains_that_keep_their_slot(kin
     again = gpu_run(w, tgt=tgt, n_chains=9, **more)               # a slot each
     for k in range(3):
         assert np.array_equal(again[k], turns[k][:, :9])
+
+
+def test_chains_keep_their_slots_where_the_workspace_for_turns_cannot_be_had():
+    w = W.Workload("turns", W.STD_NORMAL, 500, np.dtype(np.float64), 2203, 12, 0.05, 8, seed=19)
+    tgt = gpu_target(w)
+    want = gpu_run(w, tgt=tgt)
+    assert want[3]["grid_blocks"] * 4 < w.n_chains
+    full = workspace_of(tgt)[0]
+    short = gpu_target(w)
+    workspace_of(short, full - 1)
+    for calls in (1, 2):
+        got = gpu_run(w, tgt=short)
+        size, refusals = workspace_of(short, 1)                   # (no allocation at all in the second call: what is there stays)
+        assert size < full and refusals == 1                      # asked for once only
+        for x, y in zip(got[:3], want[:3]):
+            assert np.array_equal(x, y)
 
 
 # rows at the edges of a tile of 16, of the eight sums and of the pairs of tiles (the last of a wave's tiles alone, ragged, or with a
@@ -1711,14 +1735,6 @@ def test_rows_divided_between_two_workgroups_give_the_same_bits(n_data, dim, dty
         for r in runs:
             assert np.array_equal(r[k], pairs[k])
     assert_parity(pairs, ref_run(w), F64_TOL if dtype == np.float64 else F32_TOL, exact_ints=dtype == np.float64, label="rows divided")
-
-
-def workspace_of(tgt, most=0):
-    """Bytes of workspace and refused allocations so far; from now on those of more than `most` bytes are refused (0: none)."""
-    import ctypes as C
-    size, refusals = C.c_uint64(), C.c_int()
-    N()._check(N().lib().nuts_debug_workspace(tgt.handle, C.c_uint64(most), C.byref(size), C.byref(refusals)))
-    return size.value, refusals.value
 
 
 def captured_run(w, tgt, n_chains, n_iters, between, replays=3):
