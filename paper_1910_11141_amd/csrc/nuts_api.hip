@@ -613,15 +613,17 @@ nuts::RowLds row_lds(long blocks, int cus, size_t base, int kc, size_t elem, int
 }
 
 // Where chains wait for slots the call's last ones take turns (nuts_row.h).  The memory does not depend on the number of iterations, so that a
-// call of one iteration prepares for one of many (which may then be captured); it is at most about a third of what the slots take,
-// and a call that cannot have it does without.  nuts_sample_static does without too: its memory is fixed.
+// call of one iteration prepares for one of many (which may then be captured); eight vectors a slot (with a gradient sixteen) are added to
+// the 4 max_depth + 9 that it has, and a call that cannot have them does without.  So does one whose iterations are awaited by all
+// chains (a launch each: nothing could turn), and nuts_sample_static: its memory is fixed.
 int row_workspace(nuts_target* t, nuts::DevSample& sa, size_t slot, long slots, int kc, size_t elem, bool grad, bool take, unsigned** turns)
 {
     nuts::RowTurns plan{};
     *turns = nullptr;
     const size_t base = slot * (size_t)slots;
     size_t words = 0, rows = 0;
-    if (!t->static_call && sa.n_chains > slots && 2 * kc * elem <= (size_t)nuts::kTurnLaneBytes) {
+    const bool awaited = sa.iter_end - sa.iter_begin < sa.n_iters;
+    if (!t->static_call && !awaited && sa.n_chains > slots && 2 * kc * elem <= (size_t)nuts::kTurnLaneBytes) {
         const long n = std::min(sa.n_chains, nuts::kTurnChains * slots);
         unsigned ring = 1;
         while ((long)ring < n) ring *= 2;

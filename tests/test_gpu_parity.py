@@ -1708,6 +1708,15 @@ def test_chains_keep_their_slots_where_the_workspace_for_turns_cannot_be_had():
             assert np.array_equal(x, y)
 
 
+def test_awaited_iterations_need_no_workspace_for_turns():
+    w = W.Workload("turns", W.STD_NORMAL, 500, np.dtype(np.float64), 2203, 3, 0.05, 8, seed=19)
+    free, awaited = gpu_target(w), gpu_target(w)
+    want, got = gpu_run(w, tgt=free), gpu_run(w, tgt=awaited, schedule=1)
+    assert workspace_of(awaited)[0] == want[3]["grid_blocks"] * 4 * (4 * (w.max_tree_depth + 1) + 5) * 512 * 8 < workspace_of(free)[0]
+    for x, y in zip(got[:3], want[:3]):
+        assert np.array_equal(x, y)
+
+
 # rows at the edges of a tile of 16, of the eight sums and of the pairs of tiles (the last of a wave's tiles alone, ragged, or with a
 # ragged one beside it), on either side of 64 tiles per sum; features at the edges of the feature tiles, with and without a
 # constant column, where operands are asked for a tile and half a tile ahead
