@@ -105,6 +105,8 @@ struct nuts_target {
     size_t workspace_refused = SIZE_MAX;  // least size that a call did without because it could not be allocated
     size_t workspace_most = SIZE_MAX;     // nuts_debug_workspace
     int workspace_refusals = 0;           // (how often an allocation was asked for in vain)
+    long turn_steps = -1;                 // nuts_debug_turns
+    unsigned* turns_cur = nullptr;        // the queue of chains in turns of the launch in progress
     unsigned long long* counters = nullptr;
     // where the call in progress keeps its workspace and counters: the target's own allocations, or the
     // device's static scratch array (nuts_sample_static)
@@ -486,7 +488,7 @@ __global__ void zero_counters_kernel(unsigned long long* c, int words)
 
 // After every launch: the wave and element-wise kernels hold `slots` chain slots for as long as the
 // busiest of them works, so that many slots x its gradient count were issued; the chain queue restarts.
-__global__ void close_launch_kernel(unsigned long long* c, unsigned long long slots, int words)
+__global__ void close_launch_kernel(unsigned long long* c, unsigned long long slots, int words, const unsigned* turns)
 {
     for (int i = threadIdx.x; i < words; i += blockDim.x) {
         unsigned* const word = reinterpret_cast<unsigned*>(c + nuts::kCtrCount) + i;
@@ -498,6 +500,7 @@ __global__ void close_launch_kernel(unsigned long long* c, unsigned long long sl
         c[nuts::kCtrIssued] += slots * c[nuts::kCtrSlotMax];
         c[nuts::kCtrSlotMax] = 0ull;
         c[nuts::kCtrQueue] = 0ull;
+        if (turns) c[nuts::kCtrTurns] += turns[nuts::kTurnTail];
     }
 }
 
@@ -612,42 +615,57 @@ nuts::RowLds row_lds(long blocks, int cus, size_t base, int kc, size_t elem, int
     return nuts::row_lds_split(budget > base ? (budget - base) / 4 : 0, kc, elem, max_depth, grad);
 }
 
-// Where chains wait for slots the call's last ones take turns (nuts_row.h).  The memory does not depend on the number of iterations, so that a
-// call of one iteration prepares for one of many (which may then be captured); eight vectors a slot (with a gradient sixteen) are added to
-// the 4 max_depth + 9 that it has, and a call that cannot have them does without.  So does one whose iterations are awaited by all
-// chains (a launch each: nothing could turn), and nuts_sample_static: its memory is fixed.
+// Whether a call's last chains take turns (nuts_row.h), `steps` steps at least: where chains wait for slots, where there are iterations
+// enough to turn between, and where a chain can take that many steps before its last one.  Time without turns over time with:
+//   diagonal, 2000 to 16384 chains, 8 to 40 iterations of 200 to 760 steps: d = 2 1.10, d = 60 1.13, d = 130 1.11 and 1.24 (binary32, 64), d = 300 1.18,
+//   d = 400 1.22, d = 700 1.11, d = 1000 1.07, d = 1500 1.11; four iterations of 75 steps 0.99; equal scales, d = 100 to 1000, 0.98 to 1.10
+//   banded up to d = 128, 2100 to 4096 chains, 10 to 40 iterations of 30 to 90 steps: d = 10 1.03, d = 50 1.12, d = 100 1.11 and 1.30, d = 120 1.17; in a
+//   call of 0.4 ms 0.97, of 0.8 ms 0.98
+//   full matrix up to d = 128, 1300 to 4096 chains, 30 to 40 iterations of 31 steps: binary64 1.18 and 1.35, binary32 1.00 to 1.07; 10 iterations 0.99
+// Not the standard normal, whose chains take about as many steps each (0.94 to 1.02), nor two or three iterations (0.98), nor banded matrices
+// beyond d = 128 (nuts_band.h, 0.97 to 1.02: the code for turns takes registers that the state needs), nor nuts_sample_static, whose memory is fixed.
+bool takes_turns(const nuts_target* t, const nuts::DevSample& sa, long slots, unsigned steps)
+{
+    const long iters = sa.iter_end - sa.iter_begin;
+    return !t->static_call && sa.n_chains > slots && t->kind != NUTS_TARGET_STD_NORMAL && iters >= 4 &&
+           (iters - 1) * sa.leaf_steps * ((1l << sa.max_depth) - 1) >= (long)steps;
+}
+
+// Workspace of the row kernels.  That of chains in turns adds eight vectors a slot (with a gradient sixteen) to the 4 max_depth + 9 that it has;
+// a call that cannot have it does without turns.
 int row_workspace(nuts_target* t, nuts::DevSample& sa, size_t slot, long slots, int kc, size_t elem, bool grad, bool take, unsigned** turns)
 {
-    nuts::RowTurns plan{};
     *turns = nullptr;
     const size_t base = slot * (size_t)slots;
-    size_t words = 0, rows = 0;
-    const bool awaited = sa.iter_end - sa.iter_begin < sa.n_iters;
-    if (!t->static_call && !awaited && sa.n_chains > slots && 2 * kc * elem <= (size_t)nuts::kTurnLaneBytes) {
+    nuts::RowTurns plan{};
+    size_t words = 0;
+    bool has = false;
+    int rc;
+    if (take) {
         const long n = std::min(sa.n_chains, nuts::kTurnChains * slots);
         unsigned ring = 1;
         while ((long)ring < n) ring *= 2;
         plan.mask = ring - 1;
         plan.row_bytes = (unsigned)nuts::row_turn_bytes(kc, elem, grad);
+        plan.steps = t->turn_steps >= 0 ? (unsigned)t->turn_steps : grad ? nuts::kTurnStepsDense : nuts::kTurnSteps;
         plan.first = sa.n_chains - n;
         words = ((nuts::kTurnRing + (size_t)ring) * sizeof(unsigned) + 255) & ~(size_t)255;
-        rows = (size_t)plan.row_bytes * (size_t)n;
+        rc = ensure_workspace_or(t, base, base + words + (size_t)plan.row_bytes * (size_t)n, &has);
+    } else {
+        rc = ensure_workspace(t, base);
     }
-    bool has = false;
-    int rc = words ? ensure_workspace_or(t, base, base + words + rows, &has) : ensure_workspace(t, base);
     if (rc) return rc;
     sa.workspace = t->ws_cur;
     sa.slot_bytes = slot;
-    if (has && take) {
+    if (has) {
         *turns = reinterpret_cast<unsigned*>(t->ws_cur + base);
         plan.rows = t->ws_cur + base + words;
         hipLaunchKernelGGL(begin_turns_kernel, dim3(1), dim3(1024), 0, g_stream, *turns, plan);
         HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
+        t->turns_cur = *turns;
     }
     return NUTS_OK;
 }
-
-bool takes_turns(const nuts_target* t, const nuts::DevSample& sa, long slots) { return !t->static_call && sa.n_chains > slots && sa.iter_end - sa.iter_begin > 1; }
 
 template <typename T, int kC, bool kTurns = false>
 int launch_elem_inst(nuts_target* t, nuts::DevSample sa, int variant)
@@ -663,7 +681,7 @@ int launch_elem_inst(nuts_target* t, nuts::DevSample sa, int variant)
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device), NUTS_E_DEVICE);
     if (per_cu < 1) per_cu = 1;
     if constexpr (!kTurns && nuts::row_takes_turns<T, kC>())
-        if (takes_turns(t, sa, 4L * per_cu * cus)) return launch_elem_inst<T, kC, true>(t, sa, variant);
+        if (takes_turns(t, sa, 4L * per_cu * cus, nuts::kTurnSteps)) return launch_elem_inst<T, kC, true>(t, sa, variant);
     long blocks = (sa.n_chains + 3) / 4;
     if (blocks > (long)per_cu * cus) blocks = (long)per_cu * cus;
     if (t->static_call) {
@@ -728,7 +746,7 @@ int launch_dense_inst(nuts_target* t, nuts::DevSample sa)
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device), NUTS_E_DEVICE);
     if (per_cu < 1) per_cu = 1;
     if constexpr (!kTurns)
-        if (takes_turns(t, sa, (long)kDenseWaves * per_cu * cus)) return launch_dense_inst<T, kBanded, true>(t, sa);
+        if (takes_turns(t, sa, (long)kDenseWaves * per_cu * cus, kTurnStepsDense)) return launch_dense_inst<T, kBanded, true>(t, sa);
     long blocks = (sa.n_chains + kDenseWaves - 1) / kDenseWaves;
     const long resident = (long)per_cu * cus;
     if (blocks > resident) blocks = resident;
@@ -751,21 +769,19 @@ int launch_dense(nuts_target* t, const nuts::DevSample& sa)
     return t->dBand ? launch_dense_inst<T, true>(t, sa) : launch_dense_inst<T, false>(t, sa);
 }
 
-template <typename T, int kC, bool kTurns = false>
+template <typename T, int kC>
 int launch_band_inst(nuts_target* t, nuts::DevSample sa)
 {
     const nuts::DevTarget<T> tg = dev_target<T>(t);
     size_t slot = (size_t)nuts::row_num_vectors(sa.max_depth) * 128 * kC * sizeof(T);
     slot = (slot + 255) & ~(size_t)255;
-    const void* fn = reinterpret_cast<const void*>(nuts::nuts_band_kernel<T, kC, kTurns>);
+    const void* fn = reinterpret_cast<const void*>(nuts::nuts_band_kernel<T, kC>);
     HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes), NUTS_E_DEVICE);
     size_t lds_bytes = (size_t)4 * nuts::band_bcast(kC) * sizeof(T);
     int per_cu = 0, cus = 0;
-    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (nuts::nuts_band_kernel<T, kC, kTurns>), 256, lds_bytes), NUTS_E_DEVICE);
+    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (nuts::nuts_band_kernel<T, kC>), 256, lds_bytes), NUTS_E_DEVICE);
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device), NUTS_E_DEVICE);
     if (per_cu < 1) per_cu = 1;
-    if constexpr (!kTurns && nuts::row_takes_turns<T, kC>())
-        if (takes_turns(t, sa, 4L * per_cu * cus)) return launch_band_inst<T, kC, true>(t, sa);
     long blocks = (sa.n_chains + 3) / 4;
     if (blocks > (long)per_cu * cus) blocks = (long)per_cu * cus;
     if (t->static_call) {
@@ -776,11 +792,12 @@ int launch_band_inst(nuts_target* t, nuts::DevSample sa)
     }
     const nuts::RowLds rl = row_lds(blocks, cus, lds_bytes, kC, sizeof(T), sa.max_depth, true);
     lds_bytes += (size_t)4 * (rl.n_first + rl.n_pool) * nuts::row_entry_bytes(kC, sizeof(T));
-    unsigned* turns;
-    int rc = row_workspace(t, sa, slot, blocks * 4, kC, sizeof(T), true, kTurns, &turns);
+    int rc = ensure_workspace(t, slot * (size_t)blocks * 4);
     if (rc) return rc;
-    hipLaunchKernelGGL((nuts::nuts_band_kernel<T, kC, kTurns>), dim3((unsigned)blocks), dim3(256), lds_bytes, g_stream, tg,
-                       static_cast<const T*>(t->dDiag), t->diag_present, sa, rl, turns);
+    sa.workspace = t->ws_cur;
+    sa.slot_bytes = slot;
+    hipLaunchKernelGGL((nuts::nuts_band_kernel<T, kC>), dim3((unsigned)blocks), dim3(256), lds_bytes, g_stream, tg,
+                       static_cast<const T*>(t->dDiag), t->diag_present, sa, rl);
     HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
     t->last_variant = NUTS_VARIANT_WAVE;
     t->last_grid = (int)blocks;
@@ -1210,6 +1227,14 @@ int nuts_debug_wide_apart(nuts_target* t, int apart)
     return NUTS_OK;
 }
 
+// For tests: how many steps a slot of the row kernels takes with a chain while others wait (less than 0: as ever).
+int nuts_debug_turns(nuts_target* t, int steps)
+{
+    if (!t) return fail(NUTS_E_INVALID_ARG, "nuts_debug_turns: bad argument");
+    t->turn_steps = steps;
+    return NUTS_OK;
+}
+
 // For tests: allocations of more than `most` bytes of workspace are refused from now on (0: only those that the device refuses).
 // *bytes: the workspace that there is; *refusals: how many have been refused.
 int nuts_debug_workspace(nuts_target* t, unsigned long long most, unsigned long long* bytes, int* refusals)
@@ -1221,15 +1246,17 @@ int nuts_debug_workspace(nuts_target* t, unsigned long long most, unsigned long 
     return NUTS_OK;
 }
 
-// For tests, of the last call on a target: pairs of the wide kernel's workgroups that met, and of these the ones of which one went on alone.
-int nuts_debug_counts(const nuts_target* t, unsigned long long* pairs_met, unsigned long long* pairs_lost)
+// For tests, of the last call on a target: pairs of the wide kernel's workgroups that met, of these the ones of which one went on alone, and chains
+// of the row kernels that were handed over.
+int nuts_debug_counts(const nuts_target* t, unsigned long long* pairs_met, unsigned long long* pairs_lost, unsigned long long* turns)
 {
-    if (!t || !pairs_met || !pairs_lost || !t->has_run) return fail(NUTS_E_INVALID_ARG, "nuts_debug_counts: bad argument");
+    if (!t || !pairs_met || !pairs_lost || !turns || !t->has_run) return fail(NUTS_E_INVALID_ARG, "nuts_debug_counts: bad argument");
     HIP_TRY(hipEventSynchronize(t->ev_stop), NUTS_E_DEVICE);
     unsigned long long c[nuts::kCtrCount];
     HIP_TRY(hipMemcpy(c, t->counters_cur, sizeof(c), hipMemcpyDeviceToHost), NUTS_E_DEVICE);
     *pairs_met = c[nuts::kCtrPairsMet];
     *pairs_lost = c[nuts::kCtrPairsLost];
+    *turns = c[nuts::kCtrTurns];
     return NUTS_OK;
 }
 
@@ -1432,6 +1459,7 @@ int sample_impl(const nuts_target* target, int64_t n_chains, int64_t n_iters, do
 
     auto launch = [&](const nuts::DevSample& s) -> int {
         int r;
+        t->turns_cur = nullptr;
         if (use_quad)
             r = launch_quad(t, s);
         else if (use_dense)
@@ -1449,7 +1477,7 @@ int sample_impl(const nuts_target* target, int64_t n_chains, int64_t n_iters, do
         else
             r = t->dtype == NUTS_F64 ? launch_wave<double>(t, s) : launch_wave<float>(t, s);
         if (r) return r;
-        hipLaunchKernelGGL(close_launch_kernel, dim3(1), dim3(64), 0, g_stream, t->counters_cur, (unsigned long long)t->last_slots, pair_words);
+        hipLaunchKernelGGL(close_launch_kernel, dim3(1), dim3(64), 0, g_stream, t->counters_cur, (unsigned long long)t->last_slots, pair_words, t->turns_cur);
         HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
         return NUTS_OK;
     };

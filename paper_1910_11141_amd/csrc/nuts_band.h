@@ -25,9 +25,9 @@ constexpr int band_lane_bytes() { return 2 * kC * (int)sizeof(T); }  // register
 __host__ __device__ constexpr int band_bcast(int kc) { return 128 * kc + 2 * kBandHalf; }
 
 // diag: [2 kBandHalf + 1][128 kC], element (k, i) = P[i][i + k - kBandHalf]; bit k of `present`: diagonal k is not all zero
-template <typename T, int kC, bool kTurns>
+template <typename T, int kC>
 __global__ __launch_bounds__(256, (band_lane_bytes<T, kC>() <= 32 ? 2 : 1)) void nuts_band_kernel(DevTarget<T> tg, const T* diag, int present,
-                                                                                       DevSample sa, RowLds rl, unsigned* turns)
+                                                                                       DevSample sa, RowLds rl)
 {
     typedef typename RowVec<T>::type Vec;
     constexpr int kN = 2 * kBandHalf + 1;
@@ -39,8 +39,8 @@ __global__ __launch_bounds__(256, (band_lane_bytes<T, kC>() <= 32 ? 2 : 1)) void
     T* const bcast = base + (size_t)wave * band_bcast(kC) + kBandHalf;
     T* const tree = base + 4 * (size_t)band_bcast(kC) + (size_t)wave * (rl.n_first + rl.n_pool) * 2 * 128 * kC;
     const size_t slot = (size_t)blockIdx.x * 4 + wave;
-    RowChain<T, kC, (band_lane_bytes<T, kC>() <= 16), true, false, kTurns> ch(
-        sa, tg.d, lane, reinterpret_cast<T*>(sa.workspace + slot * sa.slot_bytes), tree, rl, turns);
+    RowChain<T, kC, (band_lane_bytes<T, kC>() <= 16), true> ch(sa, tg.d, lane, reinterpret_cast<T*>(sa.workspace + slot * sa.slot_bytes),
+                                                               tree, rl);
     // g = -P theta; returns this lane's share of theta . g
     auto grad = [&]() __attribute__((always_inline)) -> double {
 #pragma unroll
@@ -72,8 +72,8 @@ __global__ __launch_bounds__(256, (band_lane_bytes<T, kC>() <= 32 ? 2 : 1)) void
         __builtin_amdgcn_wave_barrier();
         return lp;
     };
-    while (const int taken = ch.take()) {
-        if (taken == kTakeFresh) ch.start_chain(grad());
+    while (ch.fetch()) {
+        ch.start_chain(grad());
         do {
             ch.iter_begin();
             do {
@@ -102,9 +102,8 @@ __global__ __launch_bounds__(256, (band_lane_bytes<T, kC>() <= 32 ? 2 : 1)) void
 // Instances with the compiler flags of nuts_gauss.hip: those whose state does not fit the registers beside hoisted constants.  The
 // others are 3 to 6 % faster without (kC = 4 in binary64 only up to four chains per compute unit: beyond, the flags would give it
 // a second wave per SIMD and 1.4 to 1.5 times the speed).
-#define NUTS_BAND_INSTANCE(T, kC, kTurns) template __global__ void nuts_band_kernel<T, kC, kTurns>(DevTarget<T>, const T*, int, DevSample, RowLds, unsigned*);
-#define NUTS_BAND_INSTANCES(pre) pre NUTS_BAND_INSTANCE(float, 16, false) pre NUTS_BAND_INSTANCE(double, 8, false) pre NUTS_BAND_INSTANCE(double, 16, false) \
-                                 pre NUTS_BAND_INSTANCE(float, 16, true) pre NUTS_BAND_INSTANCE(double, 8, true)
+#define NUTS_BAND_INSTANCE(T, kC) template __global__ void nuts_band_kernel<T, kC>(DevTarget<T>, const T*, int, DevSample, RowLds);
+#define NUTS_BAND_INSTANCES(pre) pre NUTS_BAND_INSTANCE(float, 16) pre NUTS_BAND_INSTANCE(double, 8) pre NUTS_BAND_INSTANCE(double, 16)
 NUTS_BAND_INSTANCES(extern)
 
 }  // namespace nuts

@@ -70,7 +70,8 @@ enum : int {
     kCtrCycControl = 5, kCtrCycGrad = 6, kCtrCycPost = 7,  // shader-clock ticks, summed over workgroups
     kCtrSlotMax = 8,  // wave and element-wise kernels: most gradient evaluations done by one slot in this launch
     kCtrPairsMet = 9, kCtrPairsLost = 10,  // wide kernel, divided rows: groups whose workgroups met, and that one of them went on with alone
-    kCtrCount = 11
+    kCtrTurns = 11,  // row kernels: chains handed over
+    kCtrCount = 12
 };
 
 // Program points of one chain.  This is the NUTS recursion written in the

@@ -1664,6 +1664,57 @@ def workspace_of(tgt, most=0):
     return size.value, refusals.value
 
 
+def counts_of(tgt):
+    """Of the last call: pairs of workgroups that met, pairs of which one went on alone, chains handed over to another slot."""
+    import ctypes as C
+    c = [C.c_uint64() for _ in range(3)]
+    N()._check(N().lib().nuts_debug_counts(tgt.handle, *[C.byref(x) for x in c]))
+    return tuple(x.value for x in c)
+
+
+# Every instance that takes turns (components of a lane: the edges of each), a turn after every iteration that leaves another chain waiting;
+# chains that all take turns and (more than eight for a slot) chains of which only the last do.
+@pytest.mark.parametrize("kind,dim,dtype,chains,iters", [
+    (W.GAUSS_DIAG, 3, np.float64, 8001, 9), (W.GAUSS_DIAG, 128, np.float32, 30011, 5), (W.GAUSS_DIAG, 129, np.float64, 3001, 6), (W.GAUSS_DIAG, 256, np.float32, 4099, 6),
+    (W.GAUSS_DIAG, 257, np.float32, 3001, 6), (W.GAUSS_DIAG, 500, np.float64, 2203, 6), (W.GAUSS_DIAG, 777, np.float64, 1031, 5), (W.GAUSS_DIAG, 1000, np.float32, 2051, 5),
+    (W.GAUSS_DIAG, 1025, np.float32, 1031, 5), ("ar1", 100, np.float64, 2051, 7), ("ar1", 7, np.float64, 20011, 5), ("ar1", 127, np.float32, 2051, 7), ("spd", 64, np.float64, 1301, 7), ("spd", 101, np.float32, 2051, 7)])
+def test_chains_are_handed_over_and_keep_their_bits(kind, dim, dtype, chains, iters):
+    import ctypes as C
+    w = W.Workload("turns", kind if kind == W.GAUSS_DIAG else W.GAUSS_DENSE, dim, np.dtype(dtype), chains, iters, 0.05, 9, seed=29)
+    if kind != W.GAUSS_DIAG:
+        w.precision = W.ar1_precision(dim, 0.8) if kind == "ar1" else W.random_spd_precision(dim, 3)
+    else:
+        w.scales = 10.0 ** (-1.0 + 2.0 * np.random.default_rng(dim).random(dim))
+    tgt = gpu_target(w)
+    N()._check(N().lib().nuts_debug_turns(tgt.handle, C.c_int(0)))
+    turns = gpu_run(w, tgt=tgt)
+    slots = turns[3]["grid_blocks"] * 4
+    assert slots < chains and counts_of(tgt)[2] > slots
+    kept = gpu_run(w, tgt=tgt, schedule=1)                        # a launch per iteration
+    assert counts_of(tgt)[2] == 0
+    for k in range(3):
+        assert np.array_equal(turns[k], kept[k])
+    assert turns[3]["leaf_slots_useful"] == turns[2].sum() and turns[3]["extra_grad_evals"] == chains
+
+
+def test_which_calls_take_turns():
+    import ctypes as C
+    diag = dict(scales=np.ones(600))
+    ar1, spd = dict(precision=W.ar1_precision(100, 0.5)), dict(precision=W.random_spd_precision(100, 3))
+    for kind, dim, chains, iters, depth, want, more in [
+            (W.GAUSS_DIAG, 600, 2203, 4, 9, True, diag), (W.GAUSS_DIAG, 600, 2203, 3, 10, False, diag), (W.GAUSS_DIAG, 600, 2203, 5, 8, False, diag),
+            (W.GAUSS_DIAG, 600, 900, 4, 9, False, diag), (W.STD_NORMAL, 600, 2203, 4, 9, False, {}),
+            (W.GAUSS_DENSE, 100, 2203, 4, 8, True, ar1), (W.GAUSS_DENSE, 100, 2203, 4, 7, False, ar1), (W.GAUSS_DENSE, 100, 2203, 4, 8, True, spd),
+            (W.GAUSS_DENSE, 300, 2203, 4, 9, False, dict(precision=W.ar1_precision(300, 0.5)))]:
+        w = W.Workload("which", kind, dim, np.dtype(np.float32), chains, iters, 0.1, depth, seed=31)
+        for name, x in more.items():
+            setattr(w, name, x)
+        tgt = gpu_target(w)
+        N()._check(N().lib().nuts_debug_turns(tgt.handle, C.c_int(0)))
+        gpu_run(w, tgt=tgt)
+        assert (counts_of(tgt)[2] > 0) == want, (kind, dim, chains, iters, depth)
+
+
 # More chains than slots, iterations and steps enough for several turns: element-wise, dense and banded kernels, with vectors held in registers
 # and in memory, ragged dimensions, chains that all take turns (up to eight per slot) and chains of which only the last do.
 @pytest.mark.parametrize("kind,dim,dtype,chains,iters,eps,more", [
@@ -1693,7 +1744,7 @@ def test_chains_that_take_turns_have_the_bits_of_chains_that_keep_their_slot(kin
 
 
 def test_chains_keep_their_slots_where_the_workspace_for_turns_cannot_be_had():
-    w = W.Workload("turns", W.STD_NORMAL, 500, np.dtype(np.float64), 2203, 12, 0.05, 8, seed=19)
+    w = W.Workload("turns", W.GAUSS_DIAG, 500, np.dtype(np.float64), 2203, 12, 0.05, 8, seed=19, scales=10.0 ** np.linspace(-1, 1, 500))
     tgt = gpu_target(w)
     want = gpu_run(w, tgt=tgt)
     assert want[3]["grid_blocks"] * 4 < w.n_chains
@@ -1709,7 +1760,7 @@ def test_chains_keep_their_slots_where_the_workspace_for_turns_cannot_be_had():
 
 
 def test_awaited_iterations_need_no_workspace_for_turns():
-    w = W.Workload("turns", W.STD_NORMAL, 500, np.dtype(np.float64), 2203, 3, 0.05, 8, seed=19)
+    w = W.Workload("turns", W.GAUSS_DIAG, 500, np.dtype(np.float64), 2203, 6, 0.05, 8, seed=19, scales=10.0 ** np.linspace(-1, 1, 500))
     free, awaited = gpu_target(w), gpu_target(w)
     want, got = gpu_run(w, tgt=free), gpu_run(w, tgt=awaited, schedule=1)
     assert workspace_of(awaited)[0] == want[3]["grid_blocks"] * 4 * (4 * (w.max_tree_depth + 1) + 5) * 512 * 8 < workspace_of(free)[0]
@@ -1811,13 +1862,10 @@ def test_a_workgroup_whose_partner_falls_silent_goes_on_alone(n_data, dim, dtype
     w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = 11, 4, 0.7 / np.sqrt(n_data), 5
     tgt, B = gpu_target(w), N()
     pairs = gpu_run(w, tgt=tgt)
-    met, lost = C.c_uint64(), C.c_uint64()
-    B._check(B.lib().nuts_debug_counts(tgt.handle, C.byref(met), C.byref(lost)))
-    assert met.value == 3 and lost.value == 0
+    assert counts_of(tgt)[:2] == (3, 0)                           # pairs that met, and that were left
     B._check(B.lib().nuts_debug_wide_apart(tgt.handle, C.c_int(silent)))
     alone = gpu_run(w, tgt=tgt)
-    B._check(B.lib().nuts_debug_counts(tgt.handle, C.byref(met), C.byref(lost)))
-    assert met.value == 3 and lost.value == 3
+    assert counts_of(tgt)[:2] == (3, 3)
     for x, y in zip(alone[:3], pairs[:3]):
         assert np.array_equal(x, y)
 
