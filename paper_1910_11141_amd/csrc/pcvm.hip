@@ -414,14 +414,15 @@ __host__ __device__ inline size_t small_wave_bytes(int n_stacks, int ring)
 // registers that the compiler does not know of: only by its number can a register be the base of an access in the register
 // index mode.  The limit of 64 registers that eight waves per SIMD stand for keeps the compiler below them (with four to spare,
 // for the registers in which it parks scalars come on top of its limit), and the clobber of the last one makes the kernel own
-// them: four waves per SIMD.  `w` picks the variable with its low eight bits.
+// them: four waves per SIMD.  `w` picks the variable with its low eight bits (the index mode keeps them in M0).
 __device__ __forceinline__ void file_own() { asm volatile("" ::: "v127"); }
 __device__ __forceinline__ unsigned long long file_read(unsigned w, unsigned& c)
 {
     unsigned l, h;
     asm volatile("s_set_gpr_idx_on %3, gpr_idx(SRC0)\n\tv_mov_b32 %0, v68\n\tv_mov_b32 %1, v84\n\tv_mov_b32 %2, v100\n\ts_set_gpr_idx_off"
                  : "=&v"(l), "=&v"(h), "=&v"(c)
-                 : "s"(w));
+                 : "s"(w)
+                 : "m0");
     return (unsigned long long)l | (unsigned long long)h << 32;
 }
 __device__ __forceinline__ unsigned long long file_read(unsigned w)
@@ -432,7 +433,8 @@ __device__ __forceinline__ unsigned long long file_read(unsigned w)
 __device__ __forceinline__ void file_write(unsigned w, unsigned long long x, unsigned c)
 {
     asm volatile("s_set_gpr_idx_on %3, gpr_idx(DST)\n\tv_mov_b32 v68, %0\n\tv_mov_b32 v84, %1\n\tv_mov_b32 v100, %2\n\ts_set_gpr_idx_off" ::"v"((unsigned)x),
-                 "v"((unsigned)(x >> 32)), "v"(c), "s"(w));
+                 "v"((unsigned)(x >> 32)), "v"(c), "s"(w)
+                 : "m0");
 }
 
 // ---- the step loop ----
@@ -652,7 +654,7 @@ __global__ __launch_bounds__(kWave* kWavesPerBlock) __attribute__((amdgpu_waves_
       [hi2] "v"(r_hi2), [row2] "v"(r_row2), [record] "v"(r_record), [base] "v"(base),                                       \
       [held_max] "v"(held_max), [mask] "s"(W - 1), [full] "s"(full), [lowest] "s"(lowest), [resume] "s"(resume),            \
       [f_down] "s"(sm.frame_bits), [f_up] "s"(32 - sm.frame_bits), [f_mask] "s"((1 << sm.frame_bits) - 1)                   \
-    : "memory", "vcc", "scc", "s40", "s41", "s42", "s43", "s44", "s45", "s46", "s47", "s48", "s49", "s50", "s51", "s52",    \
+    : "memory", "m0", "vcc", "scc", "s40", "s41", "s42", "s43", "s44", "s45", "s46", "s47", "s48", "s49", "s50", "s51", "s52",    \
       "s53", "s54", "s55", "s56", "s57", "s58", "s59", "s60", "s61", "s62", "s63", "s68", "s69"
 #define VM_RUN(choose, none)                                                                                                \
     if constexpr (kWide)                                                                                                    \

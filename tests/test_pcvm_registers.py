@@ -30,3 +30,13 @@ def test_the_compiler_stays_below_the_register_files(tmp_path):
             name = None
     assert len(kernels) == 6 and min(kernels.values()) > 0
     assert max(kernels.values()) < FIRST_OF_THE_FILES, kernels
+
+
+def test_the_register_index_mode_is_declared(tmp_path):
+    """s_set_gpr_idx_on writes M0: every piece of assembly that has it says so to the compiler."""
+    src, out = os.path.join(build.CSRC, "pcvm.hip"), str(tmp_path / "pcvm.ll")
+    subprocess.run([build.HIPCC] + build.flags_of(src) + ["--offload-device-only", "-S", "-emit-llvm", src, "-o", out], check=True,
+                   stderr=subprocess.DEVNULL)
+    pieces = [line for line in open(out) if "call" in line and "s_set_gpr_idx_on" in line]
+    assert len(pieces) >= 6
+    assert all("~{m0}" in line for line in pieces)
