@@ -87,7 +87,9 @@ struct RowTurns {
 enum : int { kTurnHead = 0, kTurnTail = 32, kTurnCount = 64, kTurnPlan = 96, kTurnRing = 128 };
 __host__ __device__ inline size_t row_turn_bytes(int kc, size_t elem, bool grad) { return ((size_t)(grad ? 2 : 1) * 128 * kc * elem + 16 + 127) & ~(size_t)127; }
 
-// Chains whose vectors take up more of a lane than this keep their slot: their kernels have no register left for more code.
+// Chains whose vectors take up more of a lane than this keep their slot: their kernels have no register left for more code.  (The element-wise one
+// with the code for turns spills to accumulation registers and to scratch memory at once, and the compiler then lost a register of a
+// reload: faults_in_assembly in build.py.  The code for turns had no part in the wrong values that this gave.)
 constexpr int kTurnLaneBytes = 128;
 template <typename T, int kC>
 constexpr bool row_takes_turns() { return 2 * kC * (int)sizeof(T) <= kTurnLaneBytes; }
