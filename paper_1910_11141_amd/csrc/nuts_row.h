@@ -257,7 +257,7 @@ struct RowChain {
         }
     }
 
-    // Momenta.  Of up to 32 components one pass of the generator, and the logarithm, root, sine and cosine after it, serves 64 / n
+    // Momenta.  Of up to 64 components one pass of the generator, and the logarithm, root, sine and cosine after it, serves 64 / n
     // iterations, n the power of two from the number of pairs on: lane n k + p makes pair p of the k-th one.  d = 2, 4 chains, 100 iterations
     // 584 -> 530 us.  (Kernels that hold a gradient have no scalar registers for it: d = 100 banded 1.02 times as long.)
     __device__ __forceinline__ void draw_momentum(uint32_t iteration, T (&out)[kVpl])

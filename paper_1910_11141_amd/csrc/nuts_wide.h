@@ -99,7 +99,6 @@ struct WideArgs {
 __host__ __device__ constexpr int wide_exchange_half(int mt) { return 2 * (kTileWaves / 2) * (mt + 1) * kWave * 16; }  // bytes
 constexpr int kWideAgent = 16;                       // cache policy of a buffer instruction: agent scope (sc1)
 constexpr long long kWideMeetLimit = 20000;          // 0.2 ms (100 MHz)
-constexpr int kWideLost = 256;
 constexpr long long kWideLostLimit = 6000000000ll;   // 60 s
 enum : unsigned { kMeetBoth = 3u, kMeetAlone = 4u, kMeetLost = 8u };  // bit h: half h has come
 
@@ -179,7 +178,7 @@ __global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) voi
     __shared__ double sLL[kTileWaves][NC];
     __shared__ double sHalfCol[S::kResidual ? 1 : 16 * MT];  // column sums of X~, halved
     __shared__ __align__(16) double sSpread[kSplit ? S::kWaves : 1][S::kTilesAtOnce][kSplit ? kWave : 1];
-    __shared__ int sHalted, sMeet;  // sHalted: chains that have halted; from kWideLost on: sums were missing
+    __shared__ int sHalted, sMeet, sLost;
     __shared__ __align__(16) double sFtab[S::kTab];
     const double* const log_tab = sFtab + S::kTab - kLogTabDoubles;
     __shared__ T sPool[NC][kLP > 0 ? kLP : 1][2][kLP > 0 ? kVec : 1];
@@ -248,7 +247,7 @@ __global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) voi
     for (int i = tid; i < S::kTab; i += kThreads) sFtab[i] = ta.ftab[kFtabDoubles + kLogTabDoubles - S::kTab + i];
     for (int i = tid; i < NC * S::kPitch; i += kThreads) (&sTheta[0][0])[i] = 0.0;
     for (int i = tid; i < (S::kResidual ? 0 : 16 * MT); i += kThreads) sHalfCol[i] = 0.5 * ta.colsum[i];
-    if (tid == 0) sHalted = 0;
+    if (tid == 0) sHalted = 0, sLost = 0;
     constexpr int kHalfBytes = wide_exchange_half(MT);
     const __amdgpu_buffer_rsrc_t other_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         wa.exchange + (size_t)(2 * pair + (1 - half_id)) * kHalfBytes, 0, kSplit ? kHalfBytes : 0, 0x00020000);
@@ -625,14 +624,13 @@ __global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) voi
             }
         }
         tile_lds_barrier();
-        // (scalar branches: what follows a vector one in the loop over rounds is taken to differ from lane to lane, and every load of operands then
-        // becomes a loop over its addresses, 1.35 to 1.57 times the time)
-        const int halted = kSplit ? uni(*const_cast<volatile int*>(&sHalted)) : *const_cast<volatile int*>(&sHalted);
-        if (kSplit && __builtin_expect(halted >= kWideLost, 0)) {  // (before anything else: the last round's sums were not all there)
+        // (a vote: begun again behind a vector branch, the loop over rounds is taken to differ from lane to lane, and every load of operands becomes a
+        // loop over its addresses, 1.35 to 1.57 times the time; with one word for sHalted and sLost, and scalar branches on it, up to 1.04 times)
+        if (kSplit && __builtin_expect(__any(*const_cast<volatile int*>(&sLost) != 0), 0)) {  // (before anything else: the last round's sums were not all there)
             tile_lds_barrier();
             if (half_id == 1) break;
             if (tid == 0) {
-                sHalted = 0;
+                sHalted = sLost = 0;
                 atomicOr(wa.meet + pair, (unsigned)kMeetLost);
             }
             tile_lds_barrier();
@@ -645,7 +643,7 @@ __global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) voi
             n_extra = 0;
             continue;
         }
-        if (kSplit ? __builtin_expect(halted == NC, 0) : halted == NC) break;  // every chain of the workgroup has halted
+        if (*const_cast<volatile int*>(&sHalted) == NC) break;  // every chain of the workgroup has halted
         n_rounds += 1;
         round += 1;
         const long long t1 = clock64();
@@ -928,7 +926,7 @@ __global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) voi
                             const long long now = wall_clock64();
                             if (t0 == 0) t0 = now;
                             if (now - t0 > (wa.apart >= 2 ? kWideMeetLimit : kWideLostLimit)) {
-                                atomicOr(&sHalted, kWideLost);
+                                sLost = 1;
                                 break;
                             }
                         }

@@ -1715,8 +1715,8 @@ def test_which_calls_take_turns():
         assert (counts_of(tgt)[2] > 0) == want, (kind, dim, chains, iters, depth)
 
 
-# More chains than slots, iterations and steps enough for several turns: element-wise, dense and banded kernels, with vectors held in registers
-# and in memory, ragged dimensions, chains that all take turns (up to eight per slot) and chains of which only the last do.
+# More chains than slots, several iterations, the steps between turns as they are: element-wise, dense and banded kernels, with vectors held in registers
+# and in memory, ragged dimensions, up to eight chains per slot and more.  (That chains are handed over: the tests above.)
 @pytest.mark.parametrize("kind,dim,dtype,chains,iters,eps,more", [
     (W.STD_NORMAL, 2, np.float64, 5001, 30, 0.05, {}), (W.GAUSS_DIAG, 7, np.float32, 30011, 8, 0.02, {}), (W.GAUSS_DIAG, 130, np.float64, 3100, 9, 0.02, {}),
     (W.STD_NORMAL, 500, np.float64, 2203, 12, 0.05, {}), (W.GAUSS_DIAG, 1000, np.float32, 2049, 6, 0.02, {"sampler": 1}), (W.GAUSS_DIAG, 1999, np.float32, 1027, 6, 0.02, {}),
@@ -1783,6 +1783,7 @@ def test_rows_divided_between_two_workgroups_give_the_same_bits(n_data, dim, dty
     tgt = gpu_target(w)
     pairs = gpu_run(w, tgt=tgt)
     assert pairs[3]["variant"] == N().NUTS_VARIANT_TILE and pairs[3]["grid_blocks"] == 6
+    assert counts_of(tgt)[:2] == (3, 0), "pairs that did not meet have exchanged nothing"
     assert pairs[3]["leaf_slots_useful"] == pairs[2].sum() and pairs[3]["extra_grad_evals"] == w.n_chains
     whole = gpu_run(w, tgt=tgt, n_chains=1000)                    # too many chains for two workgroups of every four
     assert whole[3]["grid_blocks"] <= 250
