@@ -1063,7 +1063,7 @@ int launch_wide(nuts_target* t, nuts::DevSample sa, int nc, int cus)
         if (fit >= 1 && blocks > fit) blocks = fit;
     }
     // Divided rows, if the workspace for twice as many workgroups can be had.  (nuts_sample_static has no words for pairs to meet at.)
-    bool split = !t->static_call && nc == 4 && blocks <= nuts::kWideMaxPairs && nuts::wide_split_pays(sa.n_chains, cus, t->n);
+    bool split = !t->static_call && nc == 4 && blocks <= nuts::kWideMaxPairs && nuts::wide_split_pays(sa.n_chains, cus, sa.iter_end - sa.iter_begin, t->n, t->tile.residual);
     const size_t slots = (block * (size_t)blocks * (split ? 2 : 1) + 255) & ~(size_t)255;
     int rc = split ? ensure_workspace_or(t, block * (size_t)blocks, slots + (size_t)blocks * 2 * nuts::wide_exchange_half(t->tile.mt), &split)
                    : ensure_workspace(t, slots);

@@ -1071,8 +1071,18 @@ inline int wide_chains_per_block(long n_chains, int cus, long iters, long n, int
 //   90            1.10 1.02      1.25 1.13      1.41 1.21      1.65 1.45
 //   128           1.15 1.06      1.33 1.18      1.42 1.27      1.73 1.49
 // (100 rows: 0.6 to 0.8.)
+// In a launch of one iteration (awaited iterations) the two meet for that alone, 10 us.  8 and 512 chains:
+//   features               1000 rows      1500           2000           3000           5000
+//   5, binary64            0.96 0.92      1.02 0.98      1.05 1.02      1.13 1.11      1.18 1.06
+//   9                      0.97 0.93      1.05 1.04      1.07 1.05      1.12 1.10      1.19 1.20
+//   25                     1.03 0.98      1.12 1.08      1.16 1.13      1.22 1.17      1.31 1.26
+//   60 (residuals)         1.20 1.11      1.31 1.27      1.34 1.30      1.49 1.46      1.67 1.69
+//   9, binary32 (same)     1.05 1.03      1.20 1.18
 constexpr int kWideMaxPairs = 256;
-inline bool wide_split_pays(long n_chains, int cus, long n) { return n >= 1000 && (n_chains + 3) / 4 * 2 <= cus; }
+inline bool wide_split_pays(long n_chains, int cus, long iters, long n, bool residual)
+{
+    return n >= (residual || iters > 1 ? 1000 : 1500) && (n_chains + 3) / 4 * 2 <= cus;
+}
 
 inline size_t wide_block_bytes(int d, int dtype_bytes, int nc, int max_depth)
 {

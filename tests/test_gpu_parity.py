@@ -1798,6 +1798,15 @@ def test_rows_divided_between_two_workgroups_give_the_same_bits(n_data, dim, dty
     assert_parity(pairs, ref_run(w), F64_TOL if dtype == np.float64 else F32_TOL, exact_ints=dtype == np.float64, label="rows divided")
 
 
+@pytest.mark.parametrize("n_data,dim,dtype,schedule,iters,blocks", [
+    (1000, 32, np.float64, 0, 2, 6), (999, 32, np.float64, 0, 2, 3), (1000, 32, np.float64, 0, 1, 3), (1499, 5, np.float64, 1, 3, 3), (1500, 5, np.float64, 1, 3, 6),
+    (1000, 33, np.float64, 1, 3, 6), (999, 33, np.float64, 0, 3, 3), (1000, 9, np.float32, 1, 3, 6)])
+def test_which_calls_divide_their_rows(n_data, dim, dtype, schedule, iters, blocks):
+    w = W.small_logreg(n_data, dim, seed=dim, dtype=dtype)
+    w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = 11, iters, 0.02, 4
+    assert gpu_run(w, schedule=schedule)[3]["grid_blocks"] == blocks
+
+
 def captured_run(w, tgt, n_chains, n_iters, between, replays=3):
     """The same call captured in a graph; outputs of every replay, with `between` run after each."""
     import torch
