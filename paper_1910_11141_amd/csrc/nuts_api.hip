@@ -102,6 +102,8 @@ struct nuts_target {
     // per-call scratch, grown on demand and kept
     char* workspace = nullptr;
     size_t workspace_bytes = 0;
+    bool workspace_captured = false;      // a captured call uses it
+    std::vector<char*> workspaces_kept;   // those that captured calls use and later calls do not
     size_t workspace_refused = SIZE_MAX;  // least size that a call did without because it could not be allocated
     size_t workspace_most = SIZE_MAX;     // nuts_debug_workspace
     int workspace_refusals = 0;           // (how often an allocation was asked for in vain)
@@ -351,6 +353,7 @@ void release(nuts_target* t)
         (void)hipFree(t->tile.ftab);
         (void)hipFree(t->tile.colsum);
         (void)hipFree(t->workspace);
+        for (char* w : t->workspaces_kept) (void)hipFree(w);
         (void)hipFree(t->carry);
         (void)hipFree(t->counters);
         if (t->ev_start) (void)hipEventDestroy(t->ev_start);
@@ -394,6 +397,35 @@ hipError_t workspace_alloc(nuts_target* t, char** p, size_t bytes)
     return e;
 }
 
+// Nothing can be allocated while a graph is captured (nor where that cannot be found out: another stream of the process is capturing).
+bool stream_captures()
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(g_stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+// The workspace makes way for another one.  A graph of a captured call may be replayed at any time, so what such a call uses stays as long as the target.
+int leave_workspace(nuts_target* t)
+{
+    if (!t->workspace) return NUTS_OK;
+    if (t->workspace_captured) {
+        try {
+            t->workspaces_kept.push_back(t->workspace);
+        } catch (const std::bad_alloc&) {
+            return fail(NUTS_E_ALLOC, "out of host memory");
+        }
+    } else {
+        HIP_TRY(hipDeviceSynchronize(), NUTS_E_DEVICE);
+        (void)hipFree(t->workspace);
+    }
+    t->workspace = nullptr;
+    t->workspace_bytes = 0;
+    t->workspace_captured = false;
+    return NUTS_OK;
+}
+
 int ensure_workspace(nuts_target* t, size_t bytes)
 {
     if (t->static_call) {  // no allocation: the workspace is the device's static array, or the call is refused
@@ -403,28 +435,16 @@ int ensure_workspace(nuts_target* t, size_t bytes)
         t->ws_cur = reinterpret_cast<char*>(g_scratch_ptr[t->device]) + kStaticHeader;
         return NUTS_OK;
     }
-    t->ws_cur = t->workspace;
-    if (bytes <= t->workspace_bytes) return NUTS_OK;
-    if (t->workspace) {
-        HIP_TRY(hipDeviceSynchronize(), NUTS_E_DEVICE);
-        (void)hipFree(t->workspace);
-        t->workspace = nullptr;
-        t->workspace_bytes = 0;
+    if (bytes > t->workspace_bytes) {
+        const int rc = leave_workspace(t);
+        if (rc) return rc;
+        HIP_TRY(workspace_alloc(t, &t->workspace, bytes), NUTS_E_ALLOC);
+        t->workspace_bytes = bytes;
+        if (bytes >= t->workspace_refused) t->workspace_refused = SIZE_MAX;
     }
-    HIP_TRY(workspace_alloc(t, &t->workspace, bytes), NUTS_E_ALLOC);
-    t->workspace_bytes = bytes;
-    if (bytes >= t->workspace_refused) t->workspace_refused = SIZE_MAX;
+    t->workspace_captured = t->workspace_captured || stream_captures();
     t->ws_cur = t->workspace;
     return NUTS_OK;
-}
-
-// Nothing can be allocated while a graph is captured (nor where that cannot be found out: another stream of the process is capturing).
-bool stream_captures()
-{
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(g_stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    return true;
 }
 
 // For runs that are faster with a workspace of `most` bytes and do with `least`: *has says which of them there is.  An allocation that was
@@ -436,11 +456,11 @@ int ensure_workspace_or(nuts_target* t, size_t least, size_t most, bool* has)
         if (least <= t->workspace_bytes) {
             char* larger = nullptr;
             if (workspace_alloc(t, &larger, most) == hipSuccess) {
-                if (hipDeviceSynchronize() != hipSuccess) {
+                const int rc = leave_workspace(t);
+                if (rc) {
                     (void)hipFree(larger);
-                    return fail(NUTS_E_DEVICE, "hipDeviceSynchronize failed");
+                    return rc;
                 }
-                (void)hipFree(t->workspace);
                 t->workspace = larger;
                 t->workspace_bytes = most;
                 *has = true;

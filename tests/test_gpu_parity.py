@@ -1864,6 +1864,32 @@ def test_rows_stay_whole_where_the_workspace_for_two_workgroups_cannot_be_had():
     assert gpu_run(w, tgt=fresh)[3]["grid_blocks"] == 128 and workspace_of(fresh)[1] == 1
 
 
+# A call that does without the larger workspace is captured; the same call outside a capture then has the target grow it.
+@pytest.mark.parametrize("rows", [True, False])                   # divided rows, turns
+def test_a_captured_call_keeps_the_workspace_it_was_captured_with(rows):
+    if rows:
+        w = W.small_logreg(1000, 20, seed=3)
+        w.n_chains, w.n_iters, w.step_size, w.max_tree_depth = 512, 2, 0.02, 5
+        prepare = dict(n_chains=1000)
+    else:
+        w = W.Workload("turns", W.GAUSS_DIAG, 500, np.dtype(np.float64), 2203, 4, 0.05, 9, seed=19, scales=10.0 ** np.linspace(-1, 1, 500))
+        prepare = dict(schedule=1)
+    want = gpu_run(w)
+    tgt = gpu_target(w)
+    gpu_run(w, tgt=tgt, **prepare)
+    sizes = [workspace_of(tgt)[0]]
+
+    def between():
+        for x, y in zip(gpu_run(w, tgt=tgt)[:3], want[:3]):
+            assert np.array_equal(x, y)
+        sizes.append(workspace_of(tgt)[0])
+
+    for got in captured_run(w, tgt, w.n_chains, w.n_iters, between):
+        for x, y in zip(got, want[:3]):
+            assert np.array_equal(x, y)
+    assert sizes[0] < sizes[1] == sizes[-1]                       # (it did grow, and not while a graph was captured)
+
+
 @pytest.mark.parametrize("silent", [2, 3])                        # the first half stops sending, the second half
 @pytest.mark.parametrize("n_data,dim,dtype", [(1000, 25, np.float64), (1137, 9, np.float32), (1263, 65, np.float64)])
 def test_a_workgroup_whose_partner_falls_silent_goes_on_alone(n_data, dim, dtype, silent):
