@@ -647,6 +647,7 @@ __global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) voi
         n_rounds += 1;
         round += 1;
         const long long t1 = clock64();
+        bool lost = false;  // (divided rows) the other half's sums did not come
         // (divided rows, alone: the other half's four sums, too)
         for (int part = first_part; part <= last_part; ++part) {
             const int turn = kSplit ? part * S::kWaves + wave : wave;  // which of the eight sums
@@ -926,7 +927,7 @@ __global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) voi
                             const long long now = wall_clock64();
                             if (t0 == 0) t0 = now;
                             if (now - t0 > (wa.apart >= 2 ? kWideMeetLimit : kWideLostLimit)) {
-                                sLost = 1;
+                                lost = true;
                                 break;
                             }
                         }
@@ -939,6 +940,7 @@ __global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) voi
             }
         }
         tile_lds_barrier();
+        if (kSplit && __builtin_expect(lost, 0)) sLost = 1;  // (behind the barrier: before it, a wave might not have looked at this round's)
         const long long t2 = clock64();
 
         // ---- 3. every chain collects its gradient and finishes its step ----
