@@ -903,8 +903,11 @@ __global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) voi
                 // half a value, so a value that is there needs no flag and no fence; two buffers in turn, as neither half is more
                 // than a round ahead of the other.
                 if (!alone) {
-                    const int at = (((int)(round & 1) * S::kWaves + wave) * (MT + 1)) * kWave * 16;
-                    const unsigned tag = min(round, last_sent);
+                    // (the same for all lanes, which the compiler does not see behind the way to begin again: it would take the place for one that
+                    // differs from lane to lane, and make a loop of every load and store)
+                    const unsigned now_round = (unsigned)uni((int)round);
+                    const int at = (((int)(now_round & 1) * S::kWaves + wave) * (MT + 1)) * kWave * 16;
+                    const unsigned tag = min(now_round, last_sent);
                     auto send = [&](double v, int i) __attribute__((always_inline)) {
                         const v4u w{(unsigned)__double2loint(v), tag, (unsigned)__double2hiint(v), tag};
                         __builtin_amdgcn_raw_buffer_store_b128(w, own_rsrc, lane * 16, at + i * kWave * 16, kWideAgent);
@@ -921,7 +924,7 @@ __global__ __launch_bounds__((WideShape<T, MT, NC, kSplit>::kWaves * kWave)) voi
                         for (int i = 0; i <= MT; ++i)
                             in[i] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(other_rsrc, lane * 16, at + i * kWave * 16, kWideAgent));
 #pragma unroll
-                        for (int i = 0; i <= MT; ++i) there = there && in[i][1] == round && in[i][3] == round;
+                        for (int i = 0; i <= MT; ++i) there = there && in[i][1] == now_round && in[i][3] == now_round;
                         if (__all(there)) break;
                         if (__builtin_expect((looks & 255) == 0, 0)) {
                             const long long now = wall_clock64();
