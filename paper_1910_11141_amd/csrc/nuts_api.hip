@@ -635,25 +635,38 @@ nuts::RowLds row_lds(long blocks, int cus, size_t base, int kc, size_t elem, int
     return nuts::row_lds_split(budget > base ? (budget - base) / 4 : 0, kc, elem, max_depth, grad);
 }
 
-// Whether a call's last chains take turns (nuts_row.h), `steps` steps at least: where chains wait for slots, where there are iterations
-// enough to turn between, and where a chain can take that many steps before its last one.  Time without turns over time with:
+// How many steps a slot takes with one of a call's last chains before it turns to another (nuts_row.h; 0: it keeps its chain): where chains wait for
+// slots, where there are iterations enough to turn between, and where a chain can take that many steps before its last one.  Time without turns over time with:
 //   diagonal, 2000 to 16384 chains, 8 to 40 iterations of 200 to 760 steps: d = 2 1.10, d = 60 1.13, d = 130 1.11 and 1.24 (binary32, 64), d = 300 1.18,
 //   d = 400 1.22, d = 700 1.11, d = 1000 1.07, d = 1500 1.11; four iterations of 75 steps 0.99; equal scales, d = 100 to 1000, 0.98 to 1.10
 //   banded up to d = 128, 2100 to 4096 chains, 10 to 40 iterations of 30 to 90 steps: d = 10 1.03, d = 50 1.12, d = 100 1.11 and 1.30, d = 120 1.17; in a
 //   call of 0.4 ms 0.97, of 0.8 ms 0.98
 //   full matrix up to d = 128, 1300 to 4096 chains, 30 to 40 iterations of 31 steps: binary64 1.18 and 1.35, binary32 1.00 to 1.07; 10 iterations 0.99
-// Not the standard normal, whose chains take about as many steps each (0.94 to 1.02), nor two or three iterations (0.98), nor banded matrices
-// beyond d = 128 (nuts_band.h, 0.97 to 1.02: the code for turns takes registers that the state needs), nor nuts_sample_static, whose memory is fixed.
-bool takes_turns(const nuts_target* t, const nuts::DevSample& sa, long slots, unsigned steps)
+// Not two or three iterations (0.98), nor banded matrices beyond d = 128 (nuts_band.h, 0.97 to 1.02: the code for turns takes registers that the
+// state needs), nor nuts_sample_static, whose memory is fixed.
+// Chains of the standard normal take about as many steps each, some 4.5 / eps an iteration.  So slots would turn all at once, and idle only in the last of the
+// rounds in which they take the chains, if those do not fill it.  After 256 and 1024 steps, 1.1, 1.35, 1.48 and 3.3 times as many chains as slots:
+//   one wave a SIMD (d = 649 and 1000 in binary64, 1100 and 2000 in binary32): 360 steps 1.04 to 1.12 and 0.97 to 1.04, 600 1.00 to 1.30 and 0.98 to 1.09,
+//   1500 1.15 to 1.65 and 1.16 to 1.49; 280 steps 0.93 to 1.02; 1.6 and 3.8 times as many chains, 600 steps 0.95 to 1.00
+//   two (d = 600 and 1000 in binary32), 1.1 times as many: 360 steps 1.00 and 1.03, 600 1.10 to 1.20 and 1.02, 1500 1.24 to 1.33 and 1.31 to 1.38; more chains, 600
+//   steps 0.86 to 1.03 and 0.99 to 1.08, 1500 0.97 to 1.13 and 1.00 to 1.13 (1.9 times as many, d = 700: after 256 1.10 times as fast as after 1024)
+//   three (d = 60 in binary64, 140 in binary32), 600 steps: 0.70 to 0.84 and 1.00 to 1.02
+unsigned turn_steps(const nuts_target* t, const nuts::DevSample& sa, long slots, int cus, unsigned steps)
 {
     const long iters = sa.iter_end - sa.iter_begin;
-    return !t->static_call && sa.n_chains > slots && t->kind != NUTS_TARGET_STD_NORMAL && iters >= 4 &&
-           (iters - 1) * sa.leaf_steps * ((1l << sa.max_depth) - 1) >= (long)steps;
+    if (t->static_call || sa.n_chains <= slots || iters < 4) return 0;
+    if (t->kind == NUTS_TARGET_STD_NORMAL) {
+        const long rest = sa.n_chains % slots, waves = slots / (4L * cus);  // (of a SIMD)
+        if (waves <= 2) steps = nuts::kTurnStepsEven;
+        const bool few = waves <= 2 && rest <= (waves == 2 ? slots / 8 : slots / 2);
+        if (rest == 0 || 4.5 * (double)iters < (few ? steps : nuts::kTurnSteps) * sa.eps) return 0;
+    }
+    return (iters - 1) * sa.leaf_steps * ((1l << sa.max_depth) - 1) >= (long)steps ? steps : 0;
 }
 
 // Workspace of the row kernels.  That of chains in turns adds eight vectors a slot (with a gradient sixteen) to the 4 max_depth + 9 that it has;
 // a call that cannot have it does without turns.
-int row_workspace(nuts_target* t, nuts::DevSample& sa, size_t slot, long slots, int kc, size_t elem, bool grad, bool take, unsigned** turns)
+int row_workspace(nuts_target* t, nuts::DevSample& sa, size_t slot, long slots, int kc, size_t elem, bool grad, unsigned steps, unsigned** turns)
 {
     *turns = nullptr;
     const size_t base = slot * (size_t)slots;
@@ -661,13 +674,13 @@ int row_workspace(nuts_target* t, nuts::DevSample& sa, size_t slot, long slots, 
     size_t words = 0;
     bool has = false;
     int rc;
-    if (take) {
+    if (steps) {
         const long n = std::min(sa.n_chains, nuts::kTurnChains * slots);
         unsigned ring = 1;
         while ((long)ring < n) ring *= 2;
         plan.mask = ring - 1;
         plan.row_bytes = (unsigned)nuts::row_turn_bytes(kc, elem, grad);
-        plan.steps = t->turn_steps >= 0 ? (unsigned)t->turn_steps : grad ? nuts::kTurnStepsDense : nuts::kTurnSteps;
+        plan.steps = t->turn_steps >= 0 ? (unsigned)t->turn_steps : steps;
         plan.first = sa.n_chains - n;
         words = ((nuts::kTurnRing + (size_t)ring) * sizeof(unsigned) + 255) & ~(size_t)255;
         rc = ensure_workspace_or(t, base, base + words + (size_t)plan.row_bytes * (size_t)n, &has);
@@ -688,7 +701,7 @@ int row_workspace(nuts_target* t, nuts::DevSample& sa, size_t slot, long slots, 
 }
 
 template <typename T, int kC, bool kTurns = false>
-int launch_elem_inst(nuts_target* t, nuts::DevSample sa, int variant)
+int launch_elem_inst(nuts_target* t, nuts::DevSample sa, int variant, unsigned steps = 0)  // (steps: of turn_steps)
 {
     const nuts::DevTarget<T> tg = dev_target<T>(t);
     size_t slot = (size_t)nuts::row_num_vectors(sa.max_depth) * 128 * kC * sizeof(T);
@@ -701,7 +714,7 @@ int launch_elem_inst(nuts_target* t, nuts::DevSample sa, int variant)
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device), NUTS_E_DEVICE);
     if (per_cu < 1) per_cu = 1;
     if constexpr (!kTurns && nuts::row_takes_turns<T, kC>())
-        if (takes_turns(t, sa, 4L * per_cu * cus, nuts::kTurnSteps)) return launch_elem_inst<T, kC, true>(t, sa, variant);
+        if (const unsigned n = turn_steps(t, sa, 4L * per_cu * cus, cus, nuts::kTurnSteps)) return launch_elem_inst<T, kC, true>(t, sa, variant, n);
     long blocks = (sa.n_chains + 3) / 4;
     if (blocks > (long)per_cu * cus) blocks = (long)per_cu * cus;
     if (t->static_call) {
@@ -722,7 +735,7 @@ int launch_elem_inst(nuts_target* t, nuts::DevSample sa, int variant)
     const nuts::RowLds rl = row_lds(blocks, cus, lds_bytes, kC, sizeof(T), sa.max_depth, false);
     lds_bytes += (size_t)4 * (rl.n_first + rl.n_pool) * nuts::row_entry_bytes(kC, sizeof(T));
     unsigned* turns;
-    int rc = row_workspace(t, sa, slot, blocks * 4, kC, sizeof(T), false, kTurns, &turns);
+    int rc = row_workspace(t, sa, slot, blocks * 4, kC, sizeof(T), false, steps, &turns);
     if (rc) return rc;
     hipLaunchKernelGGL((nuts::nuts_elem_kernel<T, kC, kTurns>), dim3((unsigned)blocks), dim3(256), lds_bytes, g_stream, tg, sa, rl, turns);
     HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);
@@ -750,7 +763,7 @@ bool dense_eligible(const nuts_target* t)
 }
 
 template <typename T, bool kBanded, bool kTurns = false>
-int launch_dense_inst(nuts_target* t, nuts::DevSample sa)
+int launch_dense_inst(nuts_target* t, nuts::DevSample sa, unsigned steps = 0)
 {
     using namespace nuts;
     DevTarget<T> tg = dev_target<T>(t);
@@ -766,14 +779,14 @@ int launch_dense_inst(nuts_target* t, nuts::DevSample sa)
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, t->device), NUTS_E_DEVICE);
     if (per_cu < 1) per_cu = 1;
     if constexpr (!kTurns)
-        if (takes_turns(t, sa, (long)kDenseWaves * per_cu * cus, kTurnStepsDense)) return launch_dense_inst<T, kBanded, true>(t, sa);
+        if (const unsigned n = turn_steps(t, sa, (long)kDenseWaves * per_cu * cus, cus, kTurnStepsDense)) return launch_dense_inst<T, kBanded, true>(t, sa, n);
     long blocks = (sa.n_chains + kDenseWaves - 1) / kDenseWaves;
     const long resident = (long)per_cu * cus;
     if (blocks > resident) blocks = resident;
     const RowLds rl = row_lds(blocks, cus, lds_bytes, 1, sizeof(T), sa.max_depth, true);
     lds_bytes += (size_t)kDenseWaves * (rl.n_first + rl.n_pool) * row_entry_bytes(1, sizeof(T));
     unsigned* turns;
-    int rc = row_workspace(t, sa, slot, blocks * kDenseWaves, 1, sizeof(T), true, kTurns, &turns);
+    int rc = row_workspace(t, sa, slot, blocks * kDenseWaves, 1, sizeof(T), true, steps, &turns);
     if (rc) return rc;
     hipLaunchKernelGGL((nuts_dense_kernel<T, kBanded, kTurns>), dim3((unsigned)blocks), dim3(threads), lds_bytes, g_stream, tg, sa, rl, turns);
     HIP_TRY(hipGetLastError(), NUTS_E_DEVICE);

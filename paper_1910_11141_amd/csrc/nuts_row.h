@@ -62,7 +62,7 @@ inline RowLds row_lds_split(size_t bytes, int kc, size_t elem, int max_depth, bo
 
 // Chains that take turns.  A slot that keeps a chain to its end leaves the chip half idle while the last chains finish.  So the last chains of
 // a call are handed over between two iterations, when little more than the position belongs to a chain: a slot that has
-// taken kTurnSteps steps with one of them puts it at the end of a queue and takes the one that has waited longest, unless none
+// taken so many steps (kTurnSteps) with one of them puts it at the end of a queue and takes the one that has waited longest, unless none
 // waits.  Every chain that is neither waiting nor finished has a slot, so a slot that finds the queue empty has nothing to wait
 // for: it goes on with its chain, or ends.
 // A turn costs some 10 us, and 70 where 2048 slots turn at once, as they do while all chains take about as many steps: hence so many steps
@@ -70,10 +70,10 @@ inline RowLds row_lds_split(size_t bytes, int kc, size_t elem, int max_depth, bo
 // 400) and 1024 (512) steps: diagonal, d = 130 binary64, 3000 chains, 1.25 1.24 1.24; d = 1000 binary32, 16384 chains, 1.05 1.06 1.07; equal scales, d = 100
 // binary32, 16384 chains, 0.76 0.88 0.98, d = 200 binary64, 4096 chains, 0.81 0.94 1.00; banded, d = 100, 4096 chains, 1.12 1.11 1.12, d = 120 with four
 // steps a leaf, 0.4 ms, 0.78 0.97 0.98; full, d = 60 binary64, 1500 chains, 1.27 1.18 1.10.  (A time between turns, in place of steps, fills
-// itself with turns where many slots turn at once: 0.15 ms 0.43 to 1.1.)  Which calls take turns: takes_turns in nuts_api.hip.
+// itself with turns where many slots turn at once: 0.15 ms 0.43 to 1.1.)  Which calls take turns, and kTurnStepsEven: turn_steps in nuts_api.hip.
 // More chains than kTurnChains per slot would not shorten the end.
 constexpr int kTurnChains = 8;
-constexpr unsigned kTurnSteps = 1024, kTurnStepsDense = 400;
+constexpr unsigned kTurnSteps = 1024, kTurnStepsDense = 400, kTurnStepsEven = 256;
 // What a slot needs for that is read from memory where a turn ends: in scalar registers throughout it would cost every step
 // (d = 2, 4 chains 1.02 times as long).
 struct RowTurns {

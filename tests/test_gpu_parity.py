@@ -1705,7 +1705,10 @@ def test_which_calls_take_turns():
             (W.GAUSS_DIAG, 600, 2203, 4, 9, True, diag), (W.GAUSS_DIAG, 600, 2203, 3, 10, False, diag), (W.GAUSS_DIAG, 600, 2203, 5, 8, False, diag),
             (W.GAUSS_DIAG, 600, 900, 4, 9, False, diag), (W.STD_NORMAL, 600, 2203, 4, 9, False, {}),
             (W.GAUSS_DENSE, 100, 2203, 4, 8, True, ar1), (W.GAUSS_DENSE, 100, 2203, 4, 7, False, ar1), (W.GAUSS_DENSE, 100, 2203, 4, 8, True, spd),
-            (W.GAUSS_DENSE, 300, 2203, 4, 9, False, dict(precision=W.ar1_precision(300, 0.5)))]:
+            (W.GAUSS_DENSE, 300, 2203, 4, 9, False, dict(precision=W.ar1_precision(300, 0.5))),
+            (W.STD_NORMAL, 600, 2203, 6, 9, True, {}), (W.STD_NORMAL, 600, 2203, 5, 9, False, {}), (W.STD_NORMAL, 600, 2305, 6, 9, False, {}),
+            (W.STD_NORMAL, 600, 2305, 23, 9, True, {}), (W.STD_NORMAL, 1100, 2560, 6, 9, True, {}), (W.STD_NORMAL, 1100, 2561, 6, 9, False, {}),
+            (W.STD_NORMAL, 1100, 2048, 40, 9, False, {}), (W.STD_NORMAL, 60, 3200, 22, 9, False, {}), (W.STD_NORMAL, 60, 3200, 23, 9, True, {})]:
         w = W.Workload("which", kind, dim, np.dtype(np.float32), chains, iters, 0.1, depth, seed=31)
         for name, x in more.items():
             setattr(w, name, x)
