@@ -1891,6 +1891,10 @@ def test_a_captured_call_keeps_the_workspace_it_was_captured_with(rows):
         for x, y in zip(got, want[:3]):
             assert np.array_equal(x, y)
     assert sizes[0] < sizes[1] == sizes[-1]                       # (it did grow, and not while a graph was captured)
+    for got in captured_run(w, tgt, w.n_chains, w.n_iters, between):  # with the larger one: divided rows and turns in a graph
+        for x, y in zip(got, want[:3]):
+            assert np.array_equal(x, y)
+    assert counts_of(tgt)[0 if rows else 2] > 0 and sizes[-1] == sizes[1]
 
 
 @pytest.mark.parametrize("silent", [2, 3])                        # the first half stops sending, the second half
