@@ -28,7 +28,7 @@
 // the instructions would take 11 k) and, with few features, the instructions of two waves that share a SIMD: a tile of 1000 x 25 takes
 // a wave 1310 ticks, and its transposition through LDS in place of half the stream made that 1620.  Divided, a wave issues alone:
 // 770 ticks a tile of 25 features, two tiles interleaved, and 1340 of 60 (2450); the exchange takes 2.5 k ticks a round (3.0 k with
-// more than 32 features).  5000 x 60, 512 chains: a round 101 k -> 63 k ticks; 20 000 x 25, 64 chains, 8.5 -> 4.4 ms.  Measured against the wave kernel, which read X twice per chain and gradient with the
+// more than 32 features).  5000 x 60, 512 chains: a round 101 k -> 63 k ticks; 20 000 x 25, 64 chains, 9.6 -> 5.0 ms, 3000 x 80, 128 chains 4.0 -> 2.7.  Measured against the wave kernel, which read X twice per chain and gradient with the
 // vector ALUs: binary64, 512 chains, 5000 x 60: 1.1e5 -> 5.5e6 gradient evaluations per second; binary32, 250 chains, 700 x 17,
 // slice sampler, four steps a leaf: 3.6e6 -> 5.0e7.  What the residuals cost against the tile kernel's functions: 700 x 17 in
 // binary32, 4096 chains, 10 iterations 2.0 -> 2.5 ms; 1000 x 60, 4096 chains, 4 iterations 2.39 -> 2.55; 1000 x 120 3.74 -> 3.85;
