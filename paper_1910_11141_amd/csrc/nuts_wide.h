@@ -1079,7 +1079,7 @@ inline int wide_chains_per_block(long n_chains, int cus, long iters, long n, int
 //   60            1.00 0.96      1.18 1.12      1.39 1.28      1.64 1.59      1.80 1.87
 //   90            1.10 1.02      1.25 1.13      1.41 1.21      1.65 1.45
 //   128           1.15 1.06      1.33 1.18      1.42 1.27      1.73 1.49
-// (100 rows: 0.6 to 0.8.)
+// (100 rows: 0.6 to 0.8.  One line for all numbers of features: what 700 rows of 90 and more would gain is left.)
 // In a launch of one iteration (awaited iterations) the two meet for that alone, 10 us.  8 and 512 chains:
 //   features               1000 rows      1500           2000           3000           5000
 //   5, binary64            0.96 0.92      1.02 0.98      1.05 1.02      1.13 1.11      1.18 1.06
